@@ -564,7 +564,7 @@ static int build_graph(dsp_block* b)
             continue;
         }
         if (L.d.op != DSP_OP_CONV) continue;
-        L.sum_tiles = nx.sum_tiles = conv_forward_row_tiles(b->dtype, L.cs);
+        L.sum_tiles = nx.sum_tiles = conv_forward_row_tiles(b->dtype, L.cs, d.m_k > 0);
         const size_t e = (size_t)L.sum_tiles * L.d.cout;
         if (e > partial_elems) partial_elems = e;
     }
@@ -646,7 +646,7 @@ static int run_forward(dsp_block* b, const ForwardPass& P, const ForwardPass* tw
             if (twin) tw = ConvForwardTwin{conv_src(*twin), act_of(*twin, i), L.sum_tiles > 0 ? bn_buffers(*twin).partial : nullptr};
             DSP_TRY(launch_conv_forward(b->dtype, L.cs, conv_src(P), L.cin_pad ? weights_for_dgrad(b, L) : weights_for_forward(b, L),
                                         act_of(P, i), st, L.sum_tiles > 0 ? bn_buffers(P).partial : nullptr,
-                                        twin ? &tw : nullptr));
+                                        twin ? &tw : nullptr, b->desc.m_k > 0));
             break;
         }
         case DSP_OP_BN: {

@@ -161,14 +161,16 @@ inline ConvShape make_conv_shape(int N, int H, int W, int Cin, int Cout, int R, 
 // twin != nullptr: the same launch also computes twin->y = conv(twin->x, w) (and twin->column_sums if
 // column_sums is given): the forward pass of the current mini-batch and the recompute of a stale one
 // share their parameters, so one launch per layer serves both.
+// pair: most launches of this layer carry two instances; the tile is chosen for that many, with and without a twin (so
+// that both give the same bits), and conv_forward_row_tiles has to be asked with the same flag.
 struct ConvForwardTwin {
     const void* x;
     void* y;
     double* column_sums;
 };
 int launch_conv_forward(int dtype, const ConvShape& c, const void* x, const void* w, void* y, hipStream_t st,
-                        double* column_sums = nullptr, const ConvForwardTwin* twin = nullptr);
-int conv_forward_row_tiles(int dtype, const ConvShape& c);
+                        double* column_sums = nullptr, const ConvForwardTwin* twin = nullptr, bool pair = false);
+int conv_forward_row_tiles(int dtype, const ConvShape& c, bool pair);
 // dx (+)= conv^T(dy, w);  wt in [Cin][R-1-r][S-1-s][Cout] for stride 1.  For stride 2 the copy is stored class by
 // class (dgrad_classes): class (hi % 2, wi % 2) of the input pixels uses the taps r' = r0 + 2 j, s' = s0 + 2 l of the
 // flipped filter, kept as [Cin][j][l][Cout] at element offset wt_off; the classes follow each other.

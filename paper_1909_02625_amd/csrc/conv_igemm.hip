@@ -212,6 +212,8 @@ struct GatherGeom {
     uint32_t wo_mul, wo_sh, ho_mul, ho_sh;  // m / Wo and (m / Wo) / Ho by multiplication (fast_div)
     int accum;     // add to `out` instead of overwriting it
     int out_vec;  // `out` rows can be written as whole 16-byte runs
+    int pair;     // the layer's launches usually carry two instances (tile choice only)
+    int n_major;  // direct-to-LDS kernel: consecutive tiles walk the rows (set by its launcher)
     // Output row of tile row m = (n, ho, wo): pixel (n, ho * oh_mul + oh_off, wo * ow_mul + ow_off) of an N x OH x OW
     // map; oh_mul = 0 means the rows are simply consecutive (the usual case).  Backward-data of a stride-2
     // convolution runs as four dense problems, one per parity class of the input pixel, each writing its own pixels.
@@ -571,37 +573,54 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::MI
 }
 
 // ---- bf16 gather-GEMM fed by direct global -> LDS loads ---------------------------------------------
-// For bf16 layers whose gathered channel count is a multiple of 64 (every 64-element k tile then lies inside one
-// filter tap) the operands need no detour through registers: `buffer_load ... lds` moves 16 bytes per lane from
-// memory straight into LDS.  A load instruction of one wave fills 1 KB of LDS contiguously (lane l -> bytes
-// 16 l .. 16 l + 15), i.e. 8 tile rows of 128 bytes, so rows cannot be padded; instead the 16-byte chunk c of row R
-// is kept at position c ^ ((R >> 1) & 7) of its row -- the lane that owns position p of row R simply fetches chunk
-// p ^ ((R >> 1) & 7) -- which spreads the 16 rows a group of 16 lanes reads over all 64 banks.  Three LDS stages:
-// while k tile t is multiplied, tile t+1 has landed or is landing and the loads of tile t+2 are issued, so a
-// gather has two multiply phases to arrive and no vector register or LDS-write instruction is spent on it.
-// A 256-thread workgroup owns BM x BN outputs (256 x 128: each of the 2 x 2 waves a 128 x 64 sub-tile = 4 x 2
-// MFMA tiles of 32 x 32, 6 LDS operand reads per 8 MFMAs).  Per k tile the tap and the channel offset are uniform,
-// so a lane's address is (row base + uniform tap offset) or "out of range" (padding tap / row past M: the buffer
-// load then writes zeros).
-template <int BM_, int BN_, int WGM_, int WGN_, int BKB_, int STAGES_, int WAVES_ = 1>
+// For bf16 layers whose gathered channel count (of one group) is a multiple of a k tile (64 or 32 elements, so that a k
+// tile lies inside one filter tap) the operands need no detour through registers: `buffer_load ... lds` moves 16 bytes
+// per lane from memory straight into LDS.  A load instruction of one wave fills 1 KB of LDS contiguously (lane l ->
+// bytes 16 l .. 16 l + 15), i.e. 8 tile rows of 128 bytes, so rows cannot be padded; instead the 16-byte chunk c of row
+// R is kept at position c ^ swz(R) of its row -- the lane that owns position p of row R simply fetches chunk
+// p ^ swz(R) -- which spreads the 16 rows a group of 16 lanes reads over all 64 banks.  Several LDS stages: while k tile
+// t is multiplied, tiles t + 1 .. t + STAGES - 2 have landed or are landing, so a gather has at least one whole
+// multiply phase to arrive and no vector register or LDS-write instruction is spent on it.
+// Per k tile the tap and the channel offset are uniform, so a lane's address is (row base + uniform tap offset) or "out
+// of range" (padding tap / row past M: the buffer load then writes zeros).
+// Eight waves per 256-row tile (two per SIMD, wave tiles of 128 x 64 or 64 x 64): a direct load costs its wave some sixty
+// cycles of issue, which the other wave of the SIMD fills with MFMAs -- with four waves of 128 x 128 the same tile ran at
+// 750 instead of 1040 TFLOP/s (256 x 14x14, 256 -> 256 3x3).
+template <int BM_, int BN_, int WGM_, int WGN_, int BKB_, int STAGES_, int WAVES_, int KG_ = 1, bool GEN_ = false>
 struct DmaTile {
-    static constexpr int WAVES = WAVES_;  // waves per SIMD the register allocation aims for (workgroups per compute unit)
+    static constexpr int WAVES = WAVES_;  // waves per SIMD the register allocation aims for
     static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, STAGES = STAGES_;
-    static_assert(WGM * WGN == 4, "four waves per workgroup");
+    // KG groups of WGM x WGN waves share the contraction: each owns a contiguous part of the k tiles, a ring of LDS
+    // stages and a full set of accumulators; the groups' tiles are summed through LDS at the end (in group order)
+    static constexpr int KG = KG_;
+    // GEN: any channel count that is a multiple of 8 (a 16-byte chunk then lies inside one filter tap, a k tile need not):
+    // every lane keeps the tap and channel of its own chunk
+    static constexpr bool GEN = GEN_;
+    static_assert(!GEN || BKB_ == 64, "the chunk a lane loads is the same in all its rows");
+    static constexpr int NW = WGM * WGN, THREADS = 64 * NW * KG;
+    static_assert(NW * KG == 2 || NW * KG == 4 || NW * KG == 8 || NW * KG == 16, "four, eight or sixteen waves per workgroup");
     static constexpr int TM = BM / (WGM * 32), TN = BN / (WGN * 32);
+    static_assert(TM * WGM * 32 == BM && TN * WGN * 32 == BN, "whole MFMA tiles per wave");
     static constexpr int ROWB = BKB_;                      // bytes of k per row: 64 or 32 bf16
     static constexpr int BK = ROWB / 2;
     static constexpr int CPR = ROWB / 16;                  // 16-byte chunks per row
     static constexpr int RPG = 1024 / ROWB;                // rows per 1 KB load instruction
     static constexpr int NKS = ROWB / 32;                  // MFMA k steps (16 elements) per tile
-    static constexpr int A_G = BM / RPG / 4, B_G = BN / RPG / 4;  // load instructions per wave and tile
+    // the BM + BN rows of a k tile are (BM + BN) / RPG load instructions, dealt out to the waves in order
+    static constexpr int A_INST = BM / RPG, LOADS = (BM + BN) / RPG / NW;
+    static_assert(BM % RPG == 0 && BN % RPG == 0 && LOADS * RPG * NW == BM + BN, "whole load instructions per wave");
+    static constexpr bool ONE_SIDED = A_INST % LOADS == 0;  // a wave loads input rows only or filter rows only
     static constexpr int STAGE_BYTES = (BM + BN) * ROWB;
+    static constexpr int RING_BYTES = STAGES * STAGE_BYTES;
+    static constexpr int SUM_BYTES = (KG - 1) * BM * BN * 4;
     static constexpr int EPI_ROWB = BN * 2 + 16;
     static constexpr int EPI_BYTES = BM * EPI_ROWB;
-    static constexpr int STATS_BYTES = kThreads * 2 * (int)sizeof(double);
-    static constexpr int LDS_BYTES = cmax(STAGES * STAGE_BYTES, EPI_BYTES + STATS_BYTES);
-    static_assert((ROWB == 128 || ROWB == 64) && BM % (4 * RPG) == 0 && BN % (4 * RPG) == 0 && kThreads % BN == 0 &&
-                      STAGES >= 3 && LDS_BYTES <= 160 * 1024, "tile shape");
+    // column sums: a thread owns a run of 4 columns and every SG-th row; the groups' sums meet behind the staged tile
+    static constexpr int SG = THREADS / (BN / 4);
+    static constexpr int STATS_BYTES = SG * BN * 2 * (int)sizeof(float);
+    static constexpr int LDS_BYTES = cmax(KG * RING_BYTES, cmax(SUM_BYTES, EPI_BYTES + STATS_BYTES));
+    static_assert((ROWB == 128 || ROWB == 64) && THREADS % (BN / 4) == 0 && THREADS >= BN && STAGES >= 3 &&
+                      EPI_BYTES % 16 == 0 && LDS_BYTES <= 160 * 1024, "tile shape");
     // chunk c of row R sits at position c ^ swz(R) of its row: the 16 rows a group of 16 lanes reads (same c) then
     // fall on 16 different 16-byte bank groups of the 64 banks
     __device__ static inline int swz(int R) { return ROWB == 128 ? (R >> 1) & 7 : (R >> 2) & 3; }
@@ -615,7 +634,7 @@ __device__ inline void dma16(__amdgpu_buffer_rsrc_t r, char* lds_wave_base, uint
 }
 
 template <typename TL>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::WAVES, TL::WAVES))) void conv_dma_gemm_kernel(
+__global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL::WAVES, TL::WAVES))) void conv_dma_gemm_kernel(
     const bf16_t* __restrict__ in_, const bf16_t* __restrict__ wgt, bf16_t* __restrict__ out_, GatherGeom g)
 {
     typedef bf16_t T;
@@ -625,61 +644,114 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::WA
     T* __restrict__ out = blockIdx.y ? (T*)g.out1 : out_;
     double* stats = blockIdx.y ? g.stats1 : g.stats;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, lane = tid & 63, wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = TL::KG == 1 ? wave_id : wave_id % TL::NW, kgrp = TL::KG == 1 ? 0 : wave_id / TL::NW;
     const int wave_m = wave / TL::WGN, wave_n = wave % TL::WGN;
     const int tiles_n = (g.Co + BN - 1) / BN;
     const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
+    // consecutive tiles (which meet in one XCD's L2) sweep the output channels of the same input rows, or, where the
+    // filters are the larger operand, the rows of the same output channels
+    const unsigned tiles_m = gridDim.x / tiles_n;
+    const unsigned tile_m = g.n_major ? tile % tiles_m : tile / tiles_n, tile_n = g.n_major ? tile / tiles_m : tile % tiles_n;
+    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    char* const ring = smem + kgrp * TL::RING_BYTES;
+    const int in_c0 = blockIdx.z * g.Ci, out_c0 = blockIdx.z * g.Co;  // grouped convolution: as in the kernel above
 
-    // loader state: this lane owns position (lane % CPR) of row (lane / CPR) of each 1 KB row group of its wave
+    // loader state: this lane owns position (lane % CPR) of row (lane / CPR) of each 1 KB row group its wave loads.  Row
+    // group i of the wave is instruction wave * LOADS + i of the k tile: input rows first, then filter rows.
+    //   l_base = byte offset of the row's first tap (may lie before the tensor) or of its filters
+    //   l_mask = bit (r*S + s) set iff tap (r, s) falls inside the image; filter rows: all bits, none past Co
     const int lrow = lane / TL::CPR, lpos = lane % TL::CPR;
-    uint32_t a_base[TL::A_G], a_mask[TL::A_G], b_base[TL::B_G];
+    uint32_t l_base[TL::LOADS], l_mask[TL::LOADS];
 #pragma unroll
-    for (int i = 0; i < TL::A_G; ++i) {
-        const int row = (wave * TL::A_G + i) * TL::RPG + lrow, m = m0 + row;
-        const uint32_t chunk = (uint32_t)(lpos ^ TL::swz(row));
-        a_base[i] = 0;
-        a_mask[i] = 0;
-        if (m < g.M) {
-            const int t = (int)fast_div((uint32_t)m, g.wo_mul, g.wo_sh), wo = m - t * g.Wo;
-            const int n = (int)fast_div((uint32_t)t, g.ho_mul, g.ho_sh), ho = t - n * g.Ho;
-            const int th0 = ho * g.ostride - g.pad_h, tw0 = wo * g.ostride - g.pad_w;
-            const int s_lo = tw0 < 0 ? -tw0 : 0, s_hi = g.Wi - tw0 < g.S ? g.Wi - tw0 : g.S;
-            const uint32_t cols = s_hi > s_lo ? ((1u << s_hi) - 1) & ~((1u << s_lo) - 1) : 0u;
-            uint32_t mask = 0;
-            for (int r = 0; r < g.R; ++r)
-                if (th0 + r >= 0 && th0 + r < g.Hi) mask |= cols << (r * g.S);
-            a_mask[i] = mask;
-            a_base[i] = (uint32_t)n * g.Hi * g.Wi * g.Ci * 2u + (uint32_t)((th0 * g.Wi + tw0) * g.Ci) * 2u + chunk * 16u;
+    for (int i = 0; i < TL::LOADS; ++i) {
+        const int inst = wave * TL::LOADS + i;
+        l_base[i] = 0;
+        l_mask[i] = 0;
+        if (inst < TL::A_INST) {
+            const int row = inst * TL::RPG + lrow, m = m0 + row;
+            if (m < g.M) {
+                const int t = (int)fast_div((uint32_t)m, g.wo_mul, g.wo_sh), wo = m - t * g.Wo;
+                const int n = (int)fast_div((uint32_t)t, g.ho_mul, g.ho_sh), ho = t - n * g.Ho;
+                const int th0 = ho * g.ostride - g.pad_h, tw0 = wo * g.ostride - g.pad_w;
+                const int s_lo = tw0 < 0 ? -tw0 : 0, s_hi = g.Wi - tw0 < g.S ? g.Wi - tw0 : g.S;
+                const uint32_t cols = s_hi > s_lo ? ((1u << s_hi) - 1) & ~((1u << s_lo) - 1) : 0u;
+                uint32_t mask = 0;
+                for (int r = 0; r < g.R; ++r)
+                    if (th0 + r >= 0 && th0 + r < g.Hi) mask |= cols << (r * g.S);
+                l_mask[i] = mask;
+                l_base[i] = ((uint32_t)n * g.Hi * g.Wi * g.Cis + in_c0) * 2u + (uint32_t)((th0 * g.Wi + tw0) * g.Cis) * 2u;
+            }
+            if (!TL::GEN) l_base[i] += (uint32_t)(lpos ^ TL::swz(row)) * 16u;
+        } else {
+            const int row = (inst - TL::A_INST) * TL::RPG + lrow, co = n0 + row;
+            if (co < g.Co) {
+                l_mask[i] = 0xffffffffu;
+                l_base[i] = (uint32_t)((out_c0 + co) * g.Kdim) * 2u;
+            }
+            if (!TL::GEN) l_base[i] += (uint32_t)(lpos ^ TL::swz(row)) * 16u;
         }
     }
-#pragma unroll
-    for (int i = 0; i < TL::B_G; ++i) {
-        const int row = (wave * TL::B_G + i) * TL::RPG + lrow, co = n0 + row;
-        const uint32_t chunk = (uint32_t)(lpos ^ TL::swz(row));
-        b_base[i] = co < g.Co ? (uint32_t)(co * g.Kdim) * 2u + chunk * 16u : kOutOfRange;
-    }
-    const __amdgpu_buffer_rsrc_t rin = make_rsrc(in, (uint32_t)g.N * g.Hi * g.Wi * g.Ci * 2u);
-    const __amdgpu_buffer_rsrc_t rw = make_rsrc(wgt, (uint32_t)g.Co * g.Kdim * 2u);
+    const uint32_t in_bytes = (uint32_t)g.N * g.Hi * g.Wi * g.Cis * 2u, w_bytes = (uint32_t)gridDim.z * g.Co * g.Kdim * 2u;
+    const bool wave_in = wave * TL::LOADS < TL::A_INST;
+    const __amdgpu_buffer_rsrc_t rwave = make_rsrc(wave_in ? (const void*)in : (const void*)wgt, wave_in ? in_bytes : w_bytes);
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(wgt, w_bytes);
 
-    const int nk = g.Kdim / TL::BK;
-    const int tiles_per_tap = g.Ci / TL::BK;
+    const int nk_all = TL::GEN ? (g.Kdim + TL::BK - 1) / TL::BK : g.Kdim / TL::BK;
+    const int tiles_per_tap = TL::GEN ? 1 : g.Ci / TL::BK;
+    // k tiles [k_first, k_end) are this group's; every group runs nk iterations (its loads past k_end read zeros)
+    const int nk = (nk_all + TL::KG - 1) / TL::KG, k_first = kgrp * nk;
+    const int k_end = TL::KG == 1 ? nk : (k_first + nk < nk_all ? k_first + nk : nk_all);
     // position of the k tile whose loads are issued next (all uniform)
-    int l_kt = 0, l_tap = 0, l_r = 0, l_s = 0, l_c = 0;
-    auto issue_loads = [&](int stage) {
-        char* sA = smem + stage * TL::STAGE_BYTES + wave * (TL::A_G * 1024);
-        char* sB = smem + stage * TL::STAGE_BYTES + BM * TL::ROWB + wave * (TL::B_G * 1024);
-        const bool live = l_kt < nk;
-        const uint32_t tap_off = (uint32_t)((l_r * g.Wi + l_s) * g.Ci + l_c * TL::BK) * 2u;
-        const uint32_t tap_bit = live ? (1u << l_tap) : 0u;
+    int l_kt = k_first, l_tap = TL::KG == 1 ? 0 : k_first / tiles_per_tap, l_c = k_first - l_tap * tiles_per_tap;
+    int l_r = TL::KG == 1 ? 0 : l_tap / g.S, l_s = l_tap - l_r * g.S;
+    // GEN: element l_k of the contraction = channel l_ch of tap l_t is where this lane's chunk starts
+    int l_k = 0, l_t = 0, l_ch = 0, ch_steps = 0;
+    if constexpr (TL::GEN) {
+        l_k = k_first * TL::BK + (lpos ^ TL::swz(lrow)) * 8;
+        l_t = l_k / g.Ci;
+        l_ch = l_k - l_t * g.Ci;
+        ch_steps = (TL::BK + g.Ci - 1) / g.Ci;
+    }
+    // loads [first, last) of the wave's loads of that tile
+    auto issue_loads = [&](int stage, int first, int last) {
+        char* dst = ring + stage * TL::STAGE_BYTES + wave * (TL::LOADS * 1024);
+        const bool live = l_kt < k_end;
+        uint32_t tap_off, tap_bit, kb;
+        if constexpr (TL::GEN) {
+            const int r = (l_t * g.s_inv) >> 16, c = l_t - r * g.S;
+            tap_off = (uint32_t)((r * g.Wi + c) * g.Cis + l_ch) * 2u;
+            tap_bit = live && l_k < g.Kdim ? (1u << l_t) : 0u;
+            kb = (uint32_t)l_k * 2u;
+        } else {
+            tap_off = (uint32_t)((l_r * g.Wi + l_s) * g.Cis + l_c * TL::BK) * 2u;
+            tap_bit = live ? (1u << l_tap) : 0u;
+            kb = (uint32_t)l_kt * (uint32_t)TL::ROWB;
+        }
 #pragma unroll
-        for (int i = 0; i < TL::A_G; ++i)
-            dma16(rin, sA + i * 1024, (a_mask[i] & tap_bit) ? a_base[i] + tap_off : kOutOfRange);
-        const uint32_t kb = (uint32_t)l_kt * (uint32_t)TL::ROWB;
-#pragma unroll
-        for (int i = 0; i < TL::B_G; ++i)
-            dma16(rw, sB + i * 1024, (live && b_base[i] != kOutOfRange) ? b_base[i] + kb : kOutOfRange);
+        for (int i = 0; i < TL::LOADS; ++i) {
+            if (i < first || i >= last) continue;
+            if (TL::ONE_SIDED) {
+                dma16(rwave, dst + i * 1024, (l_mask[i] & tap_bit) ? l_base[i] + (wave_in ? tap_off : kb) : kOutOfRange);
+            } else if (wave * TL::LOADS + i < TL::A_INST) {
+                dma16(rwave, dst + i * 1024, (l_mask[i] & tap_bit) ? l_base[i] + tap_off : kOutOfRange);
+            } else {
+                dma16(rw, dst + i * 1024, (l_mask[i] & tap_bit) ? l_base[i] + kb : kOutOfRange);
+            }
+        }
+    };
+    auto next_tile = [&]() {
         ++l_kt;
+        if constexpr (TL::GEN) {
+            l_k += TL::BK;
+            l_ch += TL::BK;
+            for (int q = 0; q < ch_steps; ++q)
+                if (l_ch >= g.Ci) {
+                    l_ch -= g.Ci;
+                    ++l_t;
+                }
+            return;
+        }
         if (++l_c == tiles_per_tap) {
             l_c = 0;
             ++l_tap;
@@ -713,10 +785,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::WA
     };
     auto mfmas = [&](const u32x4 (&a)[TM], const u32x4 (&b)[TN]) {
         __builtin_amdgcn_sched_barrier(0);  // the reads of the next step are issued before this step's MFMAs, not among them
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) Mma<T, 32>::run(b[j], a[i], acc[i][j]);
+        __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
     };
 
@@ -724,21 +798,26 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::WA
     // barrier).  ST stages: tiles kt .. kt + ST - 2 are in LDS or on their way, tile kt + ST - 1 is issued during
     // tile kt.  One barrier per k tile, in the MIDDLE of the tile's k steps: by then the loads of tile kt + 1 have
     // landed -- each wave waits until only its loads of the later tiles are outstanding, the barrier makes them
-    // visible to all -- and every wave has finished reading tile kt - 1, whose stage the loads issued right after
-    // the barrier overwrite.  The operands of a tile's first k step are read during the last k step of the tile
-    // before, so no wave meets the barrier and a burst of LDS reads at the same moment.
-    constexpr int LOADS = TL::A_G + TL::B_G;      // loads one wave issues per k tile
+    // visible to all -- and every wave has finished reading tile kt - 1, whose stage the loads issued after the
+    // barrier overwrite.  The operands of a tile's first k step are read during the last k step of the tile before,
+    // so no wave meets the barrier and a burst of LDS reads at the same moment.  A load costs its wave some sixty
+    // cycles of issue, so the loads of a tile are dealt out between the k steps that follow the barrier.
+    constexpr int LOADS = TL::LOADS;              // loads one wave issues per k tile
     constexpr int AHEAD = (ST - 3) * LOADS;       // loads that may stay outstanding at the barrier
+    constexpr int SLOTS = NKS / 2 + 1;            // k steps of a tile behind the barrier, the one in front of it included
 #pragma unroll
-    for (int t = 0; t < ST - 1; ++t) issue_loads(t);
+    for (int t = 0; t < ST - 1; ++t) {
+        issue_loads(t, 0, LOADS);
+        next_tile();
+    }
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((ST - 2) * LOADS) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     u32x4 fa[2][TM], fb[2][TN];
-    read_frags(smem, 0, fa[0], fb[0]);
+    read_frags(ring, 0, fa[0], fb[0]);
     int st = 0;
     for (int kt = 0; kt < nk; ++kt) {
-        const char* s = smem + st * TL::STAGE_BYTES;
+        const char* s = ring + st * TL::STAGE_BYTES;
         int st1 = st + 1;
         if (st1 == ST) st1 = 0;
         int stl = st - 1;        // the stage of tile kt - 1 = the stage of tile kt + ST - 1
@@ -748,85 +827,123 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::WA
             if (ks + 1 < NKS)
                 read_frags(s, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
             else
-                read_frags(smem + st1 * TL::STAGE_BYTES, 0, fa[0], fb[0]);
+                read_frags(ring + st1 * TL::STAGE_BYTES, 0, fa[0], fb[0]);
             mfmas(fa[ks & 1], fb[ks & 1]);
             if (ks == NKS / 2 - 1) {
                 asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");
-                __builtin_amdgcn_s_barrier();
+                if (TL::NW > 1) __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                issue_loads(stl);   // tile kt + ST - 1 (zeros past the end) replaces tile kt - 1
+            }
+            if (ks >= NKS / 2 - 1) {  // tile kt + ST - 1 (zeros past the end) replaces tile kt - 1
+                const int slot = ks - (NKS / 2 - 1);
+                issue_loads(stl, LOADS * slot / SLOTS, LOADS * (slot + 1) / SLOTS);
+                if (slot == SLOTS - 1) next_tile();
             }
         }
         st = st1;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the zero loads past the end must not land in the staged output tile
     __syncthreads();
+    if constexpr (TL::KG > 1) {
+        f32x4* part = (f32x4*)smem;  // [group - 1][wave][run of 4 accumulators][lane]
+        constexpr int RUNS = TM * TN * 4;
+        if (kgrp > 0) {
+#pragma unroll
+            for (int r = 0; r < RUNS; ++r)
+                part[(((kgrp - 1) * TL::NW + wave) * RUNS + r) * 64 + lane] =
+                    f32x4{acc[r / 4 / TN][r / 4 % TN][r % 4 * 4], acc[r / 4 / TN][r / 4 % TN][r % 4 * 4 + 1],
+                          acc[r / 4 / TN][r / 4 % TN][r % 4 * 4 + 2], acc[r / 4 / TN][r / 4 % TN][r % 4 * 4 + 3]};
+        }
+        __syncthreads();
+        if (kgrp == 0) {
+#pragma unroll
+            for (int q = 0; q < TL::KG - 1; ++q)
+#pragma unroll
+                for (int r = 0; r < RUNS; ++r) {
+                    const f32x4 v = part[((q * TL::NW + wave) * RUNS + r) * 64 + lane];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[r / 4 / TN][r / 4 % TN][r % 4 * 4 + e] += v[e];
+                }
+        }
+        __syncthreads();
+    }
 
     // ---- epilogue: the accumulators hold the transposed tile (a lane has, for output row lane % 32 of its block,
-    // runs of 4 consecutive output channels); stage it in LDS, then store 16-byte runs ----
+    // runs of 4 consecutive output channels); stage it in LDS, then store 16-byte runs.  An accumulating launch first
+    // fetches all old runs of one block row (a buffer load returns zeros for rows past M and columns past Co) ----
     typedef typename Run4<T>::V RunV;
+    const __amdgpu_buffer_rsrc_t rout = make_rsrc(out, 0x80000000u);
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM && kgrp == 0; ++i) {
+        const int lr = (wave_m * TM + i) * 32 + (lane & 31);
+        const int m = m0 + lr;
+        RunV old[TN * 4];
+        if (g.accum) {
+            const uint32_t row_off = m < g.M ? (uint32_t)((int)out_row(g, m) * g.Cos + out_c0) * 2u : kOutOfRange;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int lr = (wave_m * TM + i) * 32 + (lane & 31);
-            const int m = m0 + lr;
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int col = n0 + (wave_n * TN + j) * 32 + acc_row<32>(lane, 4 * q);
+                    const uint32_t off = (m < g.M && col < g.Co) ? row_off + (uint32_t)col * 2u : kOutOfRange;
+                    old[j * 4 + q] = __builtin_bit_cast(RunV, __builtin_amdgcn_raw_buffer_load_b64(rout, (int)off, 0, 0));
+                }
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float o[4];
+                    Run4<T>::unpack(old[j * 4 + q], o);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += o[e];
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int lcol = (wave_n * TN + j) * 32 + acc_row<32>(lane, 4 * q);
-                const int col = n0 + lcol;
-                if (g.accum && m < g.M) {
-                    if (g.out_vec && col + 4 <= g.Co) {
-                        float o[4];
-                        Run4<T>::unpack(*(const RunV*)(out + (int64_t)m * g.Co + col), o);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += o[e];
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (col + e < g.Co) acc[i][j][4 * q + e] += to_float<T>(out[(int64_t)m * g.Co + col + e]);
-                    }
-                }
                 *(RunV*)(smem + lr * TL::EPI_ROWB + lcol * 2) =
                     Run4<T>::pack(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
             }
-        }
+    }
     __syncthreads();
     constexpr int OCPR = BN / 8;  // 16-byte runs per tile row
-    for (int c = tid; c < BM * OCPR; c += kThreads) {
+#pragma unroll 4
+    for (int c = tid; c < BM * OCPR; c += TL::THREADS) {
         const int lr = c / OCPR, cc = (c % OCPR) * 8;
         const int m = m0 + lr, col = n0 + cc;
         if (m >= g.M || col >= g.Co) continue;
-        const char* src = smem + lr * TL::EPI_ROWB + cc * 2;
-        T* dst = out + (int64_t)m * g.Co + col;
-        if (g.out_vec && col + 8 <= g.Co) {
-            *(u32x4*)dst = *(const u32x4*)src;
-        } else {
-            for (int e = 0; e < 8 && col + e < g.Co; ++e) dst[e] = ((const T*)src)[e];
-        }
+        *(u32x4*)(out + out_row(g, m) * g.Cos + out_c0 + col) = *(const u32x4*)(smem + lr * TL::EPI_ROWB + cc * 2);
     }
     if (stats) {
-        // column sums of the staged tile (rows past M hold zeros): thread = (row group, column)
-        constexpr int G = kThreads / BN;
-        const int c = tid % BN, rg = tid / BN;
-        float s0 = 0.f, s1 = 0.f;
-        for (int r = rg; r < BM; r += G) {
-            const float v = to_float<T>(*(const T*)(smem + r * TL::EPI_ROWB + c * 2));
-            s0 += v;
-            s1 += v * v;
+        // column sums of the staged tile (rows past M hold zeros): thread = (row group, run of 4 columns), at most 32 rows
+        // per float sum, the groups' sums in double
+        constexpr int CG = BN / 4, SG = TL::SG;
+        const int cg = tid % CG, rg = tid / CG;
+        float s0[4] = {}, s1[4] = {};
+#pragma unroll 8
+        for (int r = rg; r < BM; r += SG) {
+            float v[4];
+            Run4<T>::unpack(*(const RunV*)(smem + r * TL::EPI_ROWB + cg * 8), v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                s0[e] += v[e];
+                s1[e] += v[e] * v[e];
+            }
         }
-        double* sred = (double*)(smem + TL::EPI_BYTES);
-        sred[(rg * BN + c) * 2] = (double)s0;
-        sred[(rg * BN + c) * 2 + 1] = (double)s1;
+        float* sred = (float*)(smem + TL::EPI_BYTES);  // [sum | sum of squares][row group][column]
+        *(f32x4*)(sred + rg * BN + cg * 4) = f32x4{s0[0], s0[1], s0[2], s0[3]};
+        *(f32x4*)(sred + (SG + rg) * BN + cg * 4) = f32x4{s1[0], s1[1], s1[2], s1[3]};
         __syncthreads();
-        if (rg == 0 && n0 + c < g.Co) {
+        if (tid < BN && n0 + tid < g.Co) {
             double a = 0.0, b = 0.0;
 #pragma unroll
-            for (int k = 0; k < G; ++k) {
-                a += sred[(k * BN + c) * 2];
-                b += sred[(k * BN + c) * 2 + 1];
+            for (int k = 0; k < SG; ++k) {
+                a += (double)sred[k * BN + tid];
+                b += (double)sred[(SG + k) * BN + tid];
             }
-            double* dst = stats + ((int64_t)(tile / tiles_n) * g.Co + n0 + c) * 2;
+            double* dst = stats + ((int64_t)tile_m * g.Cos + out_c0 + n0 + tid) * 2;
             dst[0] = a;
             dst[1] = b;
         }
@@ -2532,21 +2649,70 @@ inline int direct_grid(const GatherGeom& g)
 // CIFAR-sized layers) small tiles with long k steps: there the kernel is bound by the latency of the
 // gathers, and what helps is many workgroups with many bytes in flight each.
 // Returns the tile id used by dispatch_gather and the tile's row count.
-// The direct-to-LDS kernel: bf16, gathered channels a multiple of 64 (a k tile never straddles two taps), at most 32
-// taps (one mask word per row), no dilation, whole 128-wide column tiles, enough 256-row tiles for the chip, and a
-// long contraction (K >= 2304: with one workgroup per compute unit nothing overlaps a tile's prologue and epilogue,
-// which only long k loops amortise; measured: 3x3 layers of 256 / 512 channels gain 5-10 %, 128-channel ones lose 20 %).
-template <typename T>
-bool dma_wide(const GatherGeom& g)  // 256 x 256 tiles (half the LDS operand reads per MFMA) where enough of them exist
+// ---- tiles of the direct-to-LDS kernel ----
+// Expected microseconds of a launch with k64 = Kdim / 64: the tiles run in rounds of per_cu tiles on each of the 256
+// compute units, a tile costs t0 + k64 * t where per_cu of them share the compute unit and t0_one + k64 * t_one where the
+// last round leaves it alone there, and a launch costs t_launch.  The constants are fits to measured durations (one
+// MI355X; 227 layers for CI64, their input just written by another kernel, and 150 for GEN: 1x1 and 3x3, stride 1 and 2,
+// M = 200 .. 670 k rows, Co = 16 .. 1024, K = 16 .. 9216), 7-12 % rms; the tile the table picks is 0.9 % (CI64) and 1.2 %
+// (GEN) slower than the best one, geometric mean.  Durations against the register-staged tiles: 1.39x (CI64) and, for
+// K >= 512, 1.35x (GEN) faster over random layers; 256 x 14x14, 256 -> 256 3x3: 79 -> 57 us (1.04 PFLOP/s); 64 x 14x14,
+// 256 -> 256 3x3: 31 -> 20 us; 128 x 4x4, 512 -> 512 3x3: 35 -> 17 us; 19 x 16x16, 1024 -> 256 1x1: 13.4 -> 9.2 us.
+// What bounds them: the direct loads deliver 23-58 bytes per clock and compute unit (58 where all data sits in the L1),
+// and a launch of one tile per compute unit alternates between loading, multiplying and storing.
+struct DmaCost {
+    int bm, bn, per_cu;
+    float t, t_one, t0, t0_one, t_launch;
+};
+inline float dma_time(const DmaCost& d, const GatherGeom& g)
 {
-    return g.Co % 256 == 0 && tile_count(g, 256, 256) >= 192;
+    const int64_t tiles = (int64_t)ceil_div(g.M, d.bm) * ceil_div(g.Co, d.bn) * g.groups * (g.pair ? 2 : 1);
+    const int64_t full = tiles / (256 * d.per_cu), rest = tiles - full * 256 * d.per_cu;
+    const float k64 = (float)g.Kdim / 64.f, shared = d.t0 + k64 * d.t;
+    float us = d.t_launch + (float)(full * d.per_cu) * shared;
+    if (rest > 256) us += 2.f * shared;
+    else if (rest > 0) us += d.t0_one + k64 * d.t_one;
+    return us;
 }
+// Gathered channels (of a group) a multiple of 64.
+constexpr DmaCost kDmaCi64[] = {
+    {256, 256, 1, 1.143f, 1.143f, 8.6f, 8.6f, 0.4f}, {256, 128, 1, 0.698f, 0.698f, 6.1f, 6.1f, 1.7f},
+    {256, 128, 2, 0.911f, 1.065f, 3.1f, 5.0f, 3.8f}, {128, 128, 2, 0.531f, 0.522f, 1.8f, 2.4f, 3.1f},
+    {128, 128, 1, 0.418f, 0.418f, 3.6f, 3.6f, 2.5f}, {128, 64, 2, 0.314f, 0.514f, 1.5f, 2.2f, 3.4f},
+    {128, 64, 2, 0.363f, 0.487f, 0.9f, 0.7f, 4.3f},  {256, 64, 2, 0.641f, 0.686f, 2.0f, 3.4f, 3.8f},
+    {64, 64, 2, 0.181f, 0.259f, 1.2f, 1.4f, 3.6f},   {64, 64, 1, 0.174f, 0.174f, 3.2f, 3.2f, 2.9f},
+    {32, 32, 1, 0.105f, 0.105f, 2.8f, 2.8f, 3.0f}};
+// Any multiple of 8.
+constexpr DmaCost kDmaGen[] = {
+    {256, 256, 1, 1.255f, 1.255f, 6.6f, 6.6f, 0.8f}, {256, 128, 2, 0.842f, 1.124f, 3.1f, 4.0f, 3.2f},
+    {128, 128, 2, 0.495f, 0.646f, 2.0f, 1.5f, 3.0f}, {64, 64, 2, 0.262f, 0.513f, 0.6f, 0.5f, 3.4f},
+    {64, 64, 2, 0.329f, 0.307f, 2.8f, 2.6f, 1.7f},   {32, 32, 1, 0.094f, 0.094f, 3.2f, 3.2f, 1.6f},
+    {128, 32, 2, 0.256f, 0.351f, 1.8f, 2.8f, 2.2f},  {64, 32, 2, 0.189f, 0.276f, 1.3f, 2.2f, 2.0f}};
+constexpr int kDmaId = 32, kDmaGenId = 48;  // tile ids of the first entries of the two tables
+
+// bf16, whole 16-byte runs of channels on both sides, at most 32 taps (one mask word per row), no dilation; shorter
+// contractions over channel counts that are no multiple of 64 are as fast or faster on the register-staged tiles
+// (K = 144, 16 -> 16 channels, M = 129600: 7.4 us there, 8.1 us here; K = 3240, 360 -> 32: 21.0 and 18.6 us).
 template <typename T>
-bool dma_eligible(const GatherGeom& g)
+int select_dma_tile(const GatherGeom& g)
 {
-    return sizeof(T) == 2 && g.groups == 1 && g.Ci % 64 == 0 && g.R * g.S <= 32 && g.idil == 1 && g.oh_mul == 0 && g.Co % 128 == 0 && g.Kdim >= 2304 &&
-           (tile_count(g, 256, 128) >= 192 || dma_wide<T>(g));
+    if (sizeof(T) != 2 || g.Ci % 8 != 0 || g.Co % 8 != 0 || g.R * g.S > 32 || g.idil != 1) return -1;
+    const bool gen = g.Ci % 64 != 0;
+    if (gen && g.Kdim < 512) return -1;
+    const DmaCost* table = gen ? kDmaGen : kDmaCi64;
+    const int n = gen ? (int)(sizeof(kDmaGen) / sizeof(DmaCost)) : (int)(sizeof(kDmaCi64) / sizeof(DmaCost));
+    int best = 0;
+    float best_us = dma_time(table[0], g);
+    for (int i = 1; i < n; ++i) {
+        const float us = dma_time(table[i], g);
+        if (us < best_us) {
+            best_us = us;
+            best = i;
+        }
+    }
+    return (gen ? kDmaGenId : kDmaId) + best;
 }
+inline int dma_rows(int id) { return id >= kDmaGenId ? kDmaGen[id - kDmaGenId].bm : kDmaCi64[id - kDmaId].bm; }
 
 // The register-resident-filter kernel: bf16, 3x3 / stride 1 / pad 1, 64 channels on both sides, no groups, rows wide
 // enough to fill the chip, and image rows of 51 .. 62 pixels (the input rows of a 256-pixel tile are kept as 8 x 64 pixels).
@@ -2585,7 +2751,7 @@ int select_gather_tile(const GatherGeom& g, int* bm)
 {
     if (c64_eligible<T>(g)) { *bm = 256; return 21; }
     if (c16_eligible<T>(g)) { *bm = 128; return 22; }
-    if (dma_eligible<T>(g)) { *bm = 256; return 20; }
+    if (const int id = select_dma_tile<T>(g); id >= 0) { *bm = dma_rows(id); return id; }
     if (g.Co <= 16) {
         // (bf16 always takes the 64-row tile: measured in the four-stream resnet56 pipeline)
         if (sizeof(T) == 4 && tile_count(g, 256, 16) >= kEnoughTiles) { *bm = 256; return 0; }
@@ -2607,10 +2773,11 @@ int select_gather_tile(const GatherGeom& g, int* bm)
 }
 
 template <typename TL>
-int run_dma(const GatherGeom& g, const void* in, const void* w, void* out, hipStream_t st, double flops)
+int run_dma(GatherGeom g, const void* in, const void* w, void* out, hipStream_t st, double flops)
 {
     const int64_t tiles = (int64_t)ceil_div(g.M, TL::BM) * ceil_div(g.Co, TL::BN);
     DSP_REQUIRE(tiles > 0 && tiles < (1ll << 31), DSP_EINVAL, "conv: bad tile count");
+    g.n_major = (int64_t)g.Co * g.Kdim > (int64_t)g.N * g.Hi * g.Wi * g.Ci;
     auto kern = conv_dma_gemm_kernel<TL>;
     static std::atomic<bool> attr_done{false};
     if (!attr_done) {
@@ -2619,16 +2786,42 @@ int run_dma(const GatherGeom& g, const void* in, const void* w, void* out, hipSt
     }
     static const KernelName name = [] {
         KernelName k;
-        snprintf(k.text, sizeof(k.text), "conv_dma_gemm<bf16,mfma32,BM%d,BN%d,BK%d>", TL::BM, TL::BN, TL::BK);
+        snprintf(k.text, sizeof(k.text), "conv_dma_gemm<bf16,BM%d,BN%d,BK%d,%dx%d waves%s>", TL::BM, TL::BN, TL::BK, TL::NW, TL::KG,
+                 TL::GEN ? ",any Ci" : "");
         return k;
     }();
     {
         ProfScope ps(name.text, flops, 0);
-        DSP_LAUNCH(ps, kern, dim3((unsigned)tiles, g.in1 ? 2 : 1), dim3(kThreads), TL::LDS_BYTES, st, (const bf16_t*)in,
-                   (const bf16_t*)w, (bf16_t*)out, g);
+        DSP_LAUNCH(ps, kern, dim3((unsigned)tiles, g.in1 ? 2 : 1, (unsigned)g.groups), dim3(TL::THREADS), TL::LDS_BYTES, st,
+                   (const bf16_t*)in, (const bf16_t*)w, (bf16_t*)out, g);
     }
     DSP_HIP(hipGetLastError());
     return DSP_OK;
+}
+
+int dispatch_dma(int id, const GatherGeom& g, const void* in, const void* w, void* out, hipStream_t st, double flops)
+{
+    switch (id) {
+    case kDmaId + 0: return run_dma<DmaTile<256, 256, 2, 4, 64, 4, 2>>(g, in, w, out, st, flops);
+    case kDmaId + 1: return run_dma<DmaTile<256, 128, 4, 2, 128, 3, 2>>(g, in, w, out, st, flops);
+    case kDmaId + 2: return run_dma<DmaTile<256, 128, 2, 2, 64, 3, 2>>(g, in, w, out, st, flops);
+    case kDmaId + 3: return run_dma<DmaTile<128, 128, 2, 4, 64, 4, 4>>(g, in, w, out, st, flops);
+    case kDmaId + 4: return run_dma<DmaTile<128, 128, 2, 4, 128, 4, 2>>(g, in, w, out, st, flops);
+    case kDmaId + 5: return run_dma<DmaTile<128, 64, 2, 2, 128, 3, 2>>(g, in, w, out, st, flops);
+    case kDmaId + 6: return run_dma<DmaTile<128, 64, 4, 1, 64, 4, 3>>(g, in, w, out, st, flops);
+    case kDmaId + 7: return run_dma<DmaTile<256, 64, 4, 1, 64, 4, 2>>(g, in, w, out, st, flops);
+    case kDmaId + 8: return run_dma<DmaTile<64, 64, 2, 2, 128, 4, 2>>(g, in, w, out, st, flops);
+    case kDmaId + 9: return run_dma<DmaTile<64, 64, 2, 2, 128, 4, 2, 2>>(g, in, w, out, st, flops);
+    case kDmaId + 10: return run_dma<DmaTile<32, 32, 1, 1, 64, 4, 2, 8>>(g, in, w, out, st, flops);
+    case kDmaGenId + 0: return run_dma<DmaTile<256, 256, 2, 4, 64, 4, 2, 1, true>>(g, in, w, out, st, flops);
+    case kDmaGenId + 1: return run_dma<DmaTile<256, 128, 2, 2, 64, 3, 2, 1, true>>(g, in, w, out, st, flops);
+    case kDmaGenId + 2: return run_dma<DmaTile<128, 128, 2, 4, 64, 4, 4, 1, true>>(g, in, w, out, st, flops);
+    case kDmaGenId + 3: return run_dma<DmaTile<64, 64, 2, 2, 64, 4, 4, 1, true>>(g, in, w, out, st, flops);
+    case kDmaGenId + 4: return run_dma<DmaTile<64, 64, 2, 2, 64, 4, 2, 2, true>>(g, in, w, out, st, flops);
+    case kDmaGenId + 5: return run_dma<DmaTile<32, 32, 1, 1, 64, 4, 2, 8, true>>(g, in, w, out, st, flops);
+    case kDmaGenId + 6: return run_dma<DmaTile<128, 32, 2, 1, 64, 4, 2, 2, true>>(g, in, w, out, st, flops);
+    default: return run_dma<DmaTile<64, 32, 2, 1, 64, 4, 2, 2, true>>(g, in, w, out, st, flops);
+    }
 }
 
 int run_c64(const GatherGeom& g, const void* in, const void* w, void* out, hipStream_t st, double flops)
@@ -2714,12 +2907,8 @@ int dispatch_gather(GatherGeom g, bool accum, const void* in, const void* w, voi
         DSP_REQUIRE(g.stats == nullptr, DSP_EINVAL, "conv forward with column sums: x, w and y must be 16-byte aligned");
         id = 10;
     }
-    if (id == 20) {
-        const bool aligned = vec && ((uintptr_t)g.in1 % 16) == 0 && ((uintptr_t)g.out1 % 16) == 0;
-        if (aligned && g.out_vec) {
-            if (dma_wide<T>(g)) return run_dma<DmaTile<256, 256, 2, 2, 64, 4>>(g, in, w, out, st, flops);
-            return run_dma<DmaTile<256, 128, 2, 2, 128, 3>>(g, in, w, out, st, flops);
-        }
+    if (id >= kDmaId) {
+        if (vec && g.out_vec && ((uintptr_t)g.in1 % 16) == 0 && ((uintptr_t)g.out1 % 16) == 0) return dispatch_dma(id, g, in, w, out, st, flops);
         // unaligned tensors (single-layer calls only) take the register-staged tiles; their row tiles differ
         DSP_REQUIRE(g.stats == nullptr, DSP_EINVAL, "conv forward with column sums: x, w and y must be 16-byte aligned");
         id = -1;
@@ -3064,17 +3253,18 @@ static void set_groups(GatherGeom& g, int groups, int in_channels, int out_chann
     g.Cos = out_channels;
 }
 
-static GatherGeom forward_geom(const ConvShape& c)
+static GatherGeom forward_geom(const ConvShape& c, bool pair)
 {
     const int G = conv_groups(c);
     GatherGeom g = make_geom(c.N, c.H, c.W, c.Cin / G, c.Ho, c.Wo, c.Cout / G, c.R, c.S, c.pad, c.pad, c.stride, 1);
     set_groups(g, G, c.Cin, c.Cout);
+    g.pair = pair ? 1 : 0;
     return g;
 }
 
-int conv_forward_row_tiles(int dtype, const ConvShape& c)
+int conv_forward_row_tiles(int dtype, const ConvShape& c, bool pair)
 {
-    const GatherGeom g = forward_geom(c);
+    const GatherGeom g = forward_geom(c, pair);
     if (dtype == DSP_FP32 && direct_eligible<float>(g, nullptr, nullptr)) return direct_grid(g);
     int bm;
     if (dtype == DSP_BF16) {
@@ -3088,10 +3278,10 @@ int conv_forward_row_tiles(int dtype, const ConvShape& c)
 }
 
 int launch_conv_forward(int dtype, const ConvShape& c, const void* x, const void* w, void* y, hipStream_t st,
-                        double* column_sums, const ConvForwardTwin* twin)
+                        double* column_sums, const ConvForwardTwin* twin, bool pair)
 {
     DSP_TRY(check_shape(c));
-    GatherGeom g = forward_geom(c);
+    GatherGeom g = forward_geom(c, pair);
     g.stats = column_sums;
     if (twin) {
         DSP_REQUIRE(twin->x && twin->y && (twin->column_sums != nullptr) == (column_sums != nullptr), DSP_EINVAL,

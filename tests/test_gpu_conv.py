@@ -90,6 +90,30 @@ def test_conv_forward_dgrad_wgrad(shape, dtype):
     assert torch.equal(d_dw, d_dw2)
 
 
+# The direct-to-LDS tiles where they can go wrong: rows and output channels that fill no tile, fewer k tiles than a tile
+# has LDS stages or groups of waves (K = 64 for eight groups), taps cut by every border, and channel counts that are no
+# multiple of a k tile (chunks of one k tile in different taps, a ragged k tail), both strides.
+DIRECT_TO_LDS = [
+    (5, 9, 9, 64, 72, 3, 3, 1, 1),
+    (1, 5, 5, 64, 32, 1, 1, 1, 0),
+    (2, 4, 4, 128, 8, 3, 3, 1, 1),
+    (3, 13, 11, 192, 136, 3, 3, 2, 1),
+    (9, 17, 15, 256, 200, 1, 1, 1, 0),
+    (16, 24, 24, 64, 128, 3, 3, 1, 1),
+    (40, 16, 16, 128, 256, 3, 3, 1, 1),
+    (2, 9, 9, 72, 40, 3, 3, 1, 1),
+    (3, 11, 10, 104, 264, 3, 3, 2, 1),
+    (1, 6, 6, 520, 24, 1, 1, 1, 0),
+    (12, 20, 20, 88, 96, 3, 3, 1, 1),
+    (2, 7, 7, 24, 32, 5, 5, 1, 2),
+]
+
+
+@pytest.mark.parametrize("shape", DIRECT_TO_LDS, ids=lambda s: "x".join(map(str, s)))
+def test_direct_to_lds_tiles(shape):
+    test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
+
+
 # (N, H, W, Cin, Cout, R, S, stride, pad, groups)
 GROUPED = [
     (3, 9, 9, 32, 48, 3, 3, 1, 1, 4),       # 8 -> 12 channels per group: bf16 rows of the output are no whole 16-byte runs
