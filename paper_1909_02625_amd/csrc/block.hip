@@ -155,7 +155,9 @@ struct dsp_block {
     void* wf16 = nullptr;  // bf16 copy of x in the same layout (bf16 blocks only)
     void* wt = nullptr;    // backward-data filter copies [cin][R-1-r][S-1-s][cout] in the storage type
     size_t wt_elems = 0;
-    std::vector<int32_t> perm;  // library index -> layer-order index
+    ParamSegment* segs = nullptr;   // where the library's order of the parameters differs from layer order (device copy)
+    int n_segs = 0;
+    float* staging = nullptr;       // nP floats in layer order, between the device arrays and the caller's host array
 
     int ring_entries = 1;
     char* ring = nullptr;
@@ -404,7 +406,13 @@ static int build_graph(dsp_block* b)
     }
 
     // parameter index maps and the update kernel's task list
-    b->perm.resize(b->nP);
+    std::vector<ParamSegment> segs;
+    auto segment = [&](size_t p0, size_t n, int ci, int rs) {
+        if (n == 0) return;
+        if (ci == 1) rs = 1;
+        if (rs == 1 && !segs.empty() && segs.back().rs == 1) segs.back().n += (uint32_t)n;
+        else segs.push_back(ParamSegment{(uint32_t)p0, (uint32_t)n, ci, rs});
+    };
     std::vector<int32_t> tmap(b->nP, -1);
     std::vector<UpdateTask> tasks;
     std::vector<int32_t> tap_tab;
@@ -425,17 +433,17 @@ static int build_graph(dsp_block* b)
             const int G = conv_groups(L.cs), Cog = L.d.cout / G;
             const int Co = L.d.cout, Ci = L.d.cin / G, R = L.d.r, S = L.d.s;  // Ci: input channels of one group
             const size_t n = (size_t)Co * R * S * Ci;
-            for (int co = 0; co < Co; ++co)
+            segment(L.p0, n, Ci, R * S);
+            for (int co = 0; co < (L.cin_pad ? Co : 0); ++co)
                 for (int r = 0; r < R; ++r)
                     for (int s = 0; s < S; ++s)
                         for (int ci = 0; ci < Ci; ++ci) {
                             const size_t lib = L.p0 + (((size_t)co * R + r) * S + s) * Ci + ci;
-                            b->perm[lib] = (int32_t)(L.p0 + (((size_t)co * Ci + ci) * R + r) * S + s);
                             if (L.s2d) {
                                 const int ur = r - 3, us = s - 3;  // offsets from the centre tap; >> and & floor towards -inf
                                 const int ta = (ur >> 1) + 2, tb = (us >> 1) + 2, cell = (ur & 1) * 2 + (us & 1);
                                 tmap[lib] = (int32_t)(L.wt_off + (((size_t)co * 4 + ta) * 4 + tb) * L.cin_pad + cell * Ci + ci);
-                            } else if (L.cin_pad)
+                            } else
                                 tmap[lib] = (int32_t)(L.wt_off + (((size_t)co * R + r) * S + s) * L.cin_pad + ci);
                         }
             if (L.cin_pad) {
@@ -469,11 +477,11 @@ static int build_graph(dsp_block* b)
                 flat_task(L.p0, n, true);
             }
         } else if (L.d.op == DSP_OP_BN) {
-            for (size_t j = 0; j < 2 * (size_t)L.d.cin; ++j) b->perm[L.p0 + j] = (int32_t)(L.p0 + j);
+            segment(L.p0, 2 * (size_t)L.d.cin, 1, 1);
             flat_task(L.p0, 2 * (size_t)L.d.cin, false);
         } else if (L.d.op == DSP_OP_LINEAR) {
             const size_t nw = (size_t)L.d.cin * L.d.cout;
-            for (size_t j = 0; j < nw + L.d.cout; ++j) b->perm[L.p0 + j] = (int32_t)(L.p0 + j);
+            segment(L.p0, nw + L.d.cout, 1, 1);
             flat_task(L.p0, nw, true);
             flat_task(L.p0 + nw, (size_t)L.d.cout, false);
         }
@@ -490,6 +498,10 @@ static int build_graph(dsp_block* b)
     DSP_TRY(dev_alloc(b, (void**)&b->upd_tasks, tasks.size() * sizeof(UpdateTask), &b->param_bytes));
     if (!tasks.empty())
         DSP_HIP(hipMemcpy(b->upd_tasks, tasks.data(), tasks.size() * sizeof(UpdateTask), hipMemcpyHostToDevice));
+    b->n_segs = (int)segs.size();
+    DSP_TRY(dev_alloc(b, (void**)&b->segs, segs.size() * sizeof(ParamSegment), &b->param_bytes));
+    if (!segs.empty()) DSP_HIP(hipMemcpy(b->segs, segs.data(), segs.size() * sizeof(ParamSegment), hipMemcpyHostToDevice));
+    DSP_TRY(dev_alloc(b, (void**)&b->staging, b->nP * 4, &b->param_bytes));
     DSP_TRY(dev_alloc(b, (void**)&b->tap_tab, tap_tab.size() * sizeof(int32_t), &b->param_bytes));
     if (!tap_tab.empty())
         DSP_HIP(hipMemcpy(b->tap_tab, tap_tab.data(), tap_tab.size() * sizeof(int32_t), hipMemcpyHostToDevice));
@@ -584,18 +596,19 @@ static int build_graph(dsp_block* b)
 
 static int upload_params(dsp_block* b, const float* h, float* dst)
 {
-    std::vector<float> lib(b->nP);
-    for (size_t i = 0; i < b->nP; ++i) lib[i] = h[b->perm[i]];
-    if (b->nP) DSP_HIP(hipMemcpy(dst, lib.data(), b->nP * 4, hipMemcpyHostToDevice));
+    if (b->nP == 0) return DSP_OK;
+    DSP_HIP(hipMemcpy(b->staging, h, b->nP * 4, hipMemcpyHostToDevice));
+    DSP_TRY(launch_layer_order(b->staging, dst, b->segs, b->n_segs, b->nP, false, nullptr));
+    DSP_HIP(hipStreamSynchronize(nullptr));
     return DSP_OK;
 }
 
 static int download_params(dsp_block* b, const float* src, float* h)
 {
-    std::vector<float> lib(b->nP);
     DSP_HIP(hipDeviceSynchronize());
-    if (b->nP) DSP_HIP(hipMemcpy(lib.data(), src, b->nP * 4, hipMemcpyDeviceToHost));
-    for (size_t i = 0; i < b->nP; ++i) h[b->perm[i]] = lib[i];
+    if (b->nP == 0) return DSP_OK;
+    DSP_TRY(launch_layer_order(src, b->staging, b->segs, b->n_segs, b->nP, true, nullptr));
+    DSP_HIP(hipMemcpy(h, b->staging, b->nP * 4, hipMemcpyDeviceToHost));
     return DSP_OK;
 }
 

@@ -322,6 +322,14 @@ int launch_grad_pass(int dtype, const void* dy, void* dx0, bool acc0, void* dx1,
 int launch_pad_channels(int dtype, const void* src, void* dst, int64_t pixels, int C, int Cp, hipStream_t st);
 // dst[i] = src[idx[i] - base]: a filter gradient formed in a padded / transformed layout back into the layer's own.
 int launch_gather_f32(const float* src, const int32_t* idx, int32_t base, float* dst, int64_t n, hipStream_t st);
+// The parameters of a block between the library's order (filters w[co][r][s][ci]) and layer order (w[co][ci][r][s]):
+// segment by segment of the flat array, in order and without gaps; rs = 1: the two orders agree.
+struct ParamSegment {
+    uint32_t p0, n;
+    int32_t ci, rs;
+};
+int launch_layer_order(const float* src, float* dst, const ParamSegment* segs, int n_segs, size_t n, bool to_layer_order,
+                       hipStream_t st);
 // Space-to-depth by 2 with channel padding: dst[n][h][w][(dh * 2 + dw) * C + c] = src[n][2h + dh][2w + dw][c], channels
 // 4C .. Cp-1 zero; H and W even, Cp * sizeof(T) a multiple of 16.
 int launch_space_to_depth2(int dtype, const void* src, void* dst, int N, int H, int W, int C, int Cp, hipStream_t st);
