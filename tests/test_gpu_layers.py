@@ -407,3 +407,22 @@ def test_single_layer_entry_points_check_their_arguments():
         D.dsp_add_forward(7, x, x, x, 16)                                                        # unknown storage type
     with pytest.raises(D.DSPError):
         D.dsp_softmax_ce(x, None, x, x, x, 4, 4)                                                 # no labels
+
+
+@pytest.mark.parametrize("N,cin,cout", [(1, 1, 1), (17, 15, 16), (16, 64, 17), (33, 99, 34), (8, 516, 3), (19, 2052, 36)])
+def test_linear_tiles(N, cin, cout):
+    """The linear layer's three products where its 16 x 16 tiles and steps of 16 run out: single rows and columns, one more
+    and one less than a tile, channel counts with and without whole 16-byte runs, more steps than one trip holds.
+    Bound: fp32 sums of K terms, sqrt(K) * 2^-24 < 3e-6 for K <= 2052."""
+    rng = np.random.default_rng(N + cin + cout)
+    x, w = rng.standard_normal((N, cin)).astype(np.float32), rng.standard_normal((cout, cin)).astype(np.float32)
+    bias, dz = rng.standard_normal(cout).astype(np.float32), rng.standard_normal((N, cout)).astype(np.float32)
+    d_x, d_w, d_dz = _dev_f32(x), _dev_f32(w), _dev_f32(dz)
+    nan = lambda n: torch.full((n,), float("nan"), device="cuda")  # noqa: E731
+    z, dx, dw, db = nan(N * cout), nan(N * cin), nan(cout * cin), nan(cout)
+    D.dsp_linear_forward(d_x, d_w, _dev_f32(bias), z, N, cin, cout)
+    D.dsp_linear_backward(d_x, d_w, d_dz, dx, dw, db, N, cin, cout)
+    torch.cuda.synchronize()
+    x64, w64, dz64 = x.astype(np.float64), w.astype(np.float64), dz.astype(np.float64)
+    for got, ref in ((z, x64 @ w64.T + bias), (dx, dz64 @ w64), (dw, dz64.T @ x64), (db, dz64.sum(0))):
+        assert rel_err(got.cpu().numpy().reshape(ref.shape), ref) < 3e-6
