@@ -1859,23 +1859,15 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_kernel(const typename TL:
         }
 }
 
-// bf16 backward-weight for the 64- and 128-wide tiles without any register transpose.  Both operands go
-// into LDS exactly as they lie in memory (rows = m, 16-byte channel runs); the MFMA operand layout
+// bf16 backward-weight, fed by direct global -> LDS loads (see conv_dma_gemm_kernel) and without any register transpose.
+// Both operands go into LDS exactly as they lie in memory (rows = m, 16-byte channel runs); the MFMA operand layout
 // (lane = channel, 8 consecutive m per lane) is produced by the LDS transpose read: in each group of 16
 // lanes, lane i receives as element f the element (i % 4) of the 8 bytes that lane 4 f + i / 4 addressed.
 // So the 16 lanes address rows m0 .. m0+3 (lane / 4), 4 channels each (lane % 4), and come away with
 // 4 consecutive m of 16 channels; two such reads make one 8-element operand.  LDS rows are not padded:
-// within every 256-byte line the 16-byte chunk index is XORed with 4 * (line % 4), which spreads the
-// four rows of a read over all banks.
+// the 16-byte chunk index is XORed with a multiple of 4 that depends on the row (wgrad_swz), so that the 64 bytes of
+// four rows that half a wave reads fall on all 64 banks once.
 typedef short short4v __attribute__((ext_vector_type(4)));
-
-// Byte offset of 16-byte chunk `chunk` of row `row` in an unpadded tile whose rows are `row_bytes` long.
-__device__ inline int swizzled_chunk(int row, int chunk, int row_bytes)
-{
-    const int lin = row * row_bytes + chunk * 16;
-    const int line = lin >> 8, cl = (lin >> 4) & 15;
-    return (line << 8) + ((cl ^ ((line & 3) << 2)) << 4);
-}
 
 __device__ inline u32x2 lds_read_tr16(const char* p)
 {
@@ -1883,23 +1875,67 @@ __device__ inline u32x2 lds_read_tr16(const char* p)
         u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(p)));
 }
 
-template <typename TL>
-__global__ __launch_bounds__(kThreads) void conv_wgrad_tr_kernel(const bf16_t* __restrict__ x,
-                                                                 const bf16_t* __restrict__ dy,
-                                                                 float* __restrict__ part, WgradGeom g)
+// The direct load as an asm block: behind the builtin the compiler makes every transpose read wait for ALL outstanding
+// direct loads (it takes the read to alias their LDS writes), which leaves no load in flight across a k step.  The block
+// has no output; the waits for what it puts in LDS are written out in the kernel.  The s_nop covers the wait states that
+// M0 and a descriptor register fresh from a vector instruction need before a load reads them.
+__device__ inline void dma16_untracked(u32x4 rsrc, uint32_t lds_wave_base, uint32_t byte_off)
 {
-    typedef bf16_t T;
-    constexpr int BM = TL::BM, BN = TL::BN, BKm = TL::BK;
-    static_assert(sizeof(typename TL::T) == 2 && TL::MT == 32 && BKm == 64, "bf16, 32x32x16 MFMA, 64 rows of m per LDS tile");
-    static_assert((BM == 64 || BM == 128) && (BN == 64 || BN == 128), "tile widths the swizzle is laid out for");
-    constexpr int RA = BM * 2, RB = BN * 2;         // LDS row bytes of the two operands
-    constexpr int A_BYTES = BKm * RA, STAGE = BKm * (RA + RB);
-    constexpr int CA = BM / 8, CB = BN / 8;         // 16-byte chunks per row
-    constexpr int PA = BKm * CA / kThreads, PB = BKm * CB / kThreads;
-    constexpr int RSA = kThreads / CA, RSB = kThreads / CB;  // row step between a thread's chunks
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds_wave_base), "v"(byte_off), "s"(rsrc)
+                 : "memory");
+}
+__device__ inline u32x4 rsrc_words(const void* p, uint32_t bytes)
+{
+    const uint64_t a = (uint64_t)p;
+    return u32x4{(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
+}
+
+// Byte offset of 16-byte chunk `chunk` of row `row` in an unpadded tile whose rows are `row_bytes` long, where a 256-byte
+// line takes its turn of the banks (the kernels that stage rows of at most 256 bytes through registers).
+__device__ inline int swizzled_chunk(int row, int chunk, int row_bytes)
+{
+    const int lin = row * row_bytes + chunk * 16;
+    const int line = lin >> 8, cl = (lin >> 4) & 15;
+    return (line << 8) + ((cl ^ ((line & 3) << 2)) << 4);
+}
+// The same for direct loads, which need a chunk to stay in its row: four rows of 64 bytes are one turn of the banks as
+// they lie, of 128 bytes two, and longer rows all start at the same bank.
+__device__ constexpr int wgrad_swz(int row, int row_bytes)
+{
+    return row_bytes >= 256 ? (row & 3) << 2 : row_bytes == 128 ? (row & 2) << 1 : 0;
+}
+
+// BM output channels x BN columns per workgroup, WGM x WGN waves, LDS stages of BK rows of m.
+template <int BM_, int BN_, int WGM_, int WGN_, int BK_, int STAGES_, int WAVES_>
+struct WgradTile {
+    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, BK = BK_, STAGES = STAGES_;
+    static constexpr int WAVES = WAVES_;  // waves per SIMD the register allocation aims for
+    static constexpr int NW = WGM * WGN, THREADS = 64 * NW;
+    static constexpr int TM = BM / (WGM * 32), TN = BN / (WGN * 32), NKS = BK / 16;
+    static constexpr int RA = BM * 2, RB = BN * 2;             // LDS row bytes of the two operands
+    static constexpr int CA = RA / 16, CB = RB / 16;           // 16-byte chunks per row
+    static constexpr int RPA = 1024 / RA, RPB = 1024 / RB;     // rows per 1 KB load instruction
+    static constexpr int LA = BK / RPA / NW, LB = BK / RPB / NW, LOADS = LA + LB;  // load instructions per wave and stage
+    static constexpr int A_BYTES = BK * RA, STAGE_BYTES = BK * (RA + RB), LDS_BYTES = STAGES * STAGE_BYTES;
+    static_assert(TM * WGM * 32 == BM && TN * WGN * 32 == BN && NKS % 2 == 0, "whole MFMA tiles per wave");
+    static_assert(LA >= 1 && LB >= 1 && LA * RPA * NW == BK && LB * RPB * NW == BK, "whole load instructions per wave");
+    // the load instructions of a stage are dealt out to the waves in turn, so the rows of a lane are a multiple of 4 apart
+    // and its chunk is the same in all of them
+    static_assert(NW * RPA % 4 == 0 && NW * RPB % 4 == 0, "one chunk per lane");
+    static_assert(RA <= 512 && RB <= 512 && RA >= 64 && RB >= 64 && STAGES >= 3 && LDS_BYTES <= 160 * 1024, "tile shape");
+};
+
+template <typename TL>
+__global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL::WAVES, TL::WAVES))) void conv_wgrad_dma_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy, float* __restrict__ part, WgradGeom g)
+{
+    constexpr int BM = TL::BM, BN = TL::BN, BK = TL::BK, TM = TL::TM, TN = TL::TN, NKS = TL::NKS, ST = TL::STAGES;
+    constexpr int RA = TL::RA, RB = TL::RB, NW = TL::NW;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_m = wave / TL::WGN, wave_n = wave % TL::WGN;
     const int tiles_n = (g.Kdim + BN - 1) / BN;
     const unsigned lin = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
@@ -1908,106 +1944,169 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_tr_kernel(const bf16_t* _
     const int j0 = (tile % tiles_n) * BN;
     const int m_begin = slice * g.m_per_split;
     const int m_end = min(g.M, m_begin + g.m_per_split);
-    const int nk = (m_end - m_begin + BKm - 1) / BKm;
+    const int nk = (m_end - m_begin + BK - 1) / BK;
     // grouped convolution (blockIdx.z = group): dy columns dy_c0 .. of rows Cos wide, x channels x_c0 .. of pixels Cis wide
     const int dy_c0 = blockIdx.z * g.Co, x_c0 = blockIdx.z * g.Ci;
 
-    typename Mma<T, 32>::Acc acc[TL::TM][TL::TN];
-    zero_acc<TL>(acc);
+    // loader: load instruction i of this wave fills rows (i * NW + wave) * RP + lane / C of the stage, this lane position
+    // lane % C of its row, whose chunk is the same for every i
+    const int a_row = wave * TL::RPA + lane / TL::CA, b_row = wave * TL::RPB + lane / TL::CB;
+    const int ca = c0 + ((lane % TL::CA) ^ wgrad_swz(a_row, RA)) * 8;
+    const int jb = j0 + ((lane % TL::CB) ^ wgrad_swz(b_row, RB)) * 8;
+    const int tap = jb / g.Ci, tap_r = tap / g.S, tap_s = tap - tap_r * g.S;
+    // a chunk past the last channel or column never loads: its rows end before they begin
+    const int a_end = ca < g.Co ? m_end : m_begin, b_end = jb < g.Kdim ? m_end : m_begin;
+    const u32x4 rdy = rsrc_words(dy, (uint32_t)g.M * g.Cos * 2u);
+    const u32x4 rx = rsrc_words(x, (uint32_t)g.N * g.H * g.W * g.Cis * 2u);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
+    // Every row of a lane moves on by BK output pixels per stage = d_n images + d_ho rows + d_wo columns with a carry each;
+    // position and byte offset of its x pixel follow by additions (two divisions and five 32-bit multiplications a row
+    // cost more cycles than the MFMAs of a 64x64 tile).
+    const int d_t = (int)fast_div((uint32_t)BK, g.wo_mul, g.wo_sh), d_wo = BK - d_t * g.Wo;
+    const int d_n = (int)fast_div((uint32_t)d_t, g.ho_mul, g.ho_sh), d_ho = d_t - d_n * g.Ho;
+    const int d_wi = d_wo * g.stride, d_hi = d_ho * g.stride, row_w = g.Wo * g.stride, img_h = g.Ho * g.stride;
+    const uint32_t px = (uint32_t)g.Cis * 2u;
+    const uint32_t d_off = (uint32_t)((d_n * g.H + d_hi) * g.W + d_wi) * px;
+    const uint32_t d_row = (uint32_t)(g.stride * g.W - row_w) * px, d_img = (uint32_t)((g.H - img_h) * g.W) * px;
+    const int wi_end = row_w - g.pad + tap_s, hi_end = img_h - g.pad + tap_r;
+    uint32_t a_off[TL::LA], b_off[TL::LB];
+    int b_hi[TL::LB], b_wi[TL::LB];
+#pragma unroll
+    for (int i = 0; i < TL::LA; ++i)
+        a_off[i] = (uint32_t)(m_begin + a_row + i * NW * TL::RPA) * (uint32_t)(g.Cos * 2) + (uint32_t)(dy_c0 + ca) * 2u;
+#pragma unroll
+    for (int i = 0; i < TL::LB; ++i) {
+        const int m = m_begin + b_row + i * NW * TL::RPB;
+        const int t = (int)fast_div((uint32_t)m, g.wo_mul, g.wo_sh), n = (int)fast_div((uint32_t)t, g.ho_mul, g.ho_sh);
+        b_wi[i] = (m - t * g.Wo) * g.stride - g.pad + tap_s;
+        b_hi[i] = (t - n * g.Ho) * g.stride - g.pad + tap_r;
+        b_off[i] = (uint32_t)((n * g.H + b_hi[i]) * g.W + b_wi[i]) * px + (uint32_t)(x_c0 + jb - tap * g.Ci) * 2u;
+    }
+    const uint32_t d_a = (uint32_t)BK * (uint32_t)(g.Cos * 2);
+    int l_m = m_begin;  // first row of the stage whose loads are issued next
+    // loads [first, last) of the wave's loads of that stage; each moves its row on to the stage after it
+    auto issue_loads = [&](int stage, int first, int last) {
+        const uint32_t dst = lds0 + stage * TL::STAGE_BYTES + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < TL::LOADS; ++i) {
+            if (i < first || i >= last) continue;
+            if (i < TL::LA) {
+                dma16_untracked(rdy, dst + i * NW * 1024, l_m + a_row + i * NW * TL::RPA < a_end ? a_off[i] : kOutOfRange);
+                a_off[i] += d_a;
+            } else {
+                const int j = i - TL::LA;
+                const bool ok = (l_m + b_row + j * NW * TL::RPB < b_end) & ((unsigned)b_hi[j] < (unsigned)g.H) &
+                                ((unsigned)b_wi[j] < (unsigned)g.W);
+                dma16_untracked(rx, dst + TL::A_BYTES + j * NW * 1024, ok ? b_off[j] : kOutOfRange);
+                const int wi = b_wi[j] + d_wi;
+                const bool next_row = wi >= wi_end;
+                b_wi[j] = next_row ? wi - row_w : wi;
+                const int hi = b_hi[j] + d_hi + (next_row ? g.stride : 0);
+                const bool next_img = hi >= hi_end;
+                b_hi[j] = next_img ? hi - img_h : hi;
+                b_off[j] += d_off + (next_row ? d_row : 0u) + (next_img ? d_img : 0u);
+            }
+        }
+    };
 
-    // loader: this thread's chunk column is fixed, its rows are row0 + i * RS
-    const int a_chunk = tid % CA, a_row0 = tid / CA;
-    const int b_chunk = tid % CB, b_row0 = tid / CB;
-    const bool a_ok = c0 + a_chunk * 8 < g.Co;
-    const int jb = j0 + b_chunk * 8;
-    const bool b_ok = jb < g.Kdim;
-    const int tap = b_ok ? jb / g.Ci : 0, b_ci = b_ok ? jb % g.Ci : 0;
-    const int tap_r = tap / g.S, tap_s = tap % g.S;
-    const __amdgpu_buffer_rsrc_t rdy = make_rsrc(dy, (uint32_t)g.M * g.Cos * 2u);
-    const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, (uint32_t)g.N * g.H * g.W * g.Cis * 2u);
-    u32x4 ra[PA], rb[PB];
-    auto load_tiles = [&](int mb) {
+    typename Mma<bf16_t, 32>::Acc acc[TM][TN];
 #pragma unroll
-        for (int i = 0; i < PA; ++i) {
-            const int m = mb + a_row0 + i * RSA;
-            ra[i] = load16(rdy, (a_ok && m < m_end) ? (uint32_t)(m * g.Cos + dy_c0 + c0 + a_chunk * 8) * 2u : kOutOfRange);
-        }
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int i = 0; i < PB; ++i) {
-            const int m = mb + b_row0 + i * RSB;
-            const uint32_t tq = fast_div((uint32_t)m, g.wo_mul, g.wo_sh);
-            const int wo = m - (int)tq * g.Wo;
-            const int n = (int)fast_div(tq, g.ho_mul, g.ho_sh);
-            const int ho = (int)tq - n * g.Ho;
-            const int hi = ho * g.stride - g.pad + tap_r, wi = wo * g.stride - g.pad + tap_s;
-            const bool ok = b_ok && m < m_end && (unsigned)hi < (unsigned)g.H && (unsigned)wi < (unsigned)g.W;
-            rb[i] = load16(rx, ok ? (uint32_t)(((n * g.H + hi) * g.W + wi) * g.Cis + x_c0 + b_ci) * 2u : kOutOfRange);
-        }
-    };
-    auto store_tiles = [&](int buf) {
-        char* sA = smem + buf * STAGE;
-        char* sB = sA + A_BYTES;
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int i = 0; i < PA; ++i) *(u32x4*)(sA + swizzled_chunk(a_row0 + i * RSA, a_chunk, RA)) = ra[i];
-#pragma unroll
-        for (int i = 0; i < PB; ++i) *(u32x4*)(sB + swizzled_chunk(b_row0 + i * RSB, b_chunk, RB)) = rb[i];
-    };
-    // operand reads: 16-lane group = (channel half cs, m half kg); lane j of it addresses row j / 4, channels 4 (j % 4)
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+    // operand reads: 16-lane group = (channel half cs, m half kg); lane j of it addresses row j / 4, channels 4 (j % 4).
+    // Rows 4 apart share a swizzle, so a lane's chunk offset is the same for every k step.
     const int j16 = lane & 15, cs = (lane >> 4) & 1, kg = lane >> 5;
     const int frag_row = 8 * kg + (j16 >> 2);            // + 16 * ks + 4 * h
     const int frag_chunk = cs * 2 + ((j16 & 3) >> 1);    // + 4 * (32-wide tile index)
-    const int frag_half = (j16 & 1) * 8;
-    auto mma = [&](const char* sA, const char* sB) {
+    int a_addr[TM], b_addr[TN];
 #pragma unroll
-        for (int ks = 0; ks < BKm / 16; ++ks) {
-            u32x4 a[TL::TM], b[TL::TN];
+    for (int i = 0; i < TM; ++i)
+        a_addr[i] = frag_row * RA + ((((wave_m * TM + i) * 4 + frag_chunk) ^ wgrad_swz(frag_row, RA)) << 4) + (j16 & 1) * 8;
 #pragma unroll
-            for (int i = 0; i < TL::TM; ++i) {
-                const int ch = (wave_m * TL::TM + i) * 4 + frag_chunk;
-                const u32x2 lo = lds_read_tr16(sA + swizzled_chunk(16 * ks + frag_row, ch, RA) + frag_half);
-                const u32x2 hi = lds_read_tr16(sA + swizzled_chunk(16 * ks + 4 + frag_row, ch, RA) + frag_half);
-                a[i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-            }
+    for (int j = 0; j < TN; ++j)
+        b_addr[j] = TL::A_BYTES + frag_row * RB + ((((wave_n * TN + j) * 4 + frag_chunk) ^ wgrad_swz(frag_row, RB)) << 4) +
+                    (j16 & 1) * 8;
+    auto read_frags = [&](const char* s, int ks, u32x4 (&a)[TM], u32x4 (&b)[TN]) {
 #pragma unroll
-            for (int jn = 0; jn < TL::TN; ++jn) {
-                const int ch = (wave_n * TL::TN + jn) * 4 + frag_chunk;
-                const u32x2 lo = lds_read_tr16(sB + swizzled_chunk(16 * ks + frag_row, ch, RB) + frag_half);
-                const u32x2 hi = lds_read_tr16(sB + swizzled_chunk(16 * ks + 4 + frag_row, ch, RB) + frag_half);
-                b[jn] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-            }
+        for (int i = 0; i < TM; ++i) {
+            const u32x2 lo = lds_read_tr16(s + a_addr[i] + 16 * ks * RA), hi = lds_read_tr16(s + a_addr[i] + (16 * ks + 4) * RA);
+            a[i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        }
 #pragma unroll
-            for (int i = 0; i < TL::TM; ++i)
-#pragma unroll
-                for (int jn = 0; jn < TL::TN; ++jn) Mma<T, 32>::run(a[i], b[jn], acc[i][jn]);
+        for (int j = 0; j < TN; ++j) {
+            const u32x2 lo = lds_read_tr16(s + b_addr[j] + 16 * ks * RB), hi = lds_read_tr16(s + b_addr[j] + (16 * ks + 4) * RB);
+            b[j] = u32x4{lo[0], lo[1], hi[0], hi[1]};
         }
     };
-    // rows at or past m_end load as zeros, so the loop may fetch (and store into the idle stage) one tile
-    // past the slice: a single loop body with one back edge keeps the accumulators in place
-    load_tiles(m_begin);
-    store_tiles(0);
-    __syncthreads();
-    int kt = 0;
-    for (; kt + 1 < nk; kt += 2) {
-        load_tiles(m_begin + (kt + 1) * BKm);
-        mma(smem, smem + A_BYTES);
-        store_tiles(1);
-        __syncthreads();
-        load_tiles(m_begin + (kt + 2) * BKm);
-        mma(smem + STAGE, smem + STAGE + A_BYTES);
-        store_tiles(0);
-        __syncthreads();
+    auto mfmas = [&](const u32x4 (&a)[TM], const u32x4 (&b)[TN]) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) Mma<bf16_t, 32>::run(a[i], b[j], acc[i][j]);
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // Pipeline and synchronisation as in conv_dma_gemm_kernel: stages kt .. kt + ST - 2 are in LDS or on their way; one
+    // barrier per stage, in the middle of its k steps.
+    constexpr int LOADS = TL::LOADS;
+    constexpr int AHEAD = (ST - 3) * LOADS;
+    constexpr int SLOTS = NKS / 2 + 1;
+#pragma unroll
+    for (int t = 0; t < ST - 1; ++t) {
+        issue_loads(t, 0, LOADS);
+        l_m += BK;
     }
-    if (kt < nk) mma(smem, smem + A_BYTES);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((ST - 2) * LOADS) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): no scalar load is pending when the counted waits of the loop begin
+    u32x4 fa[2][TM], fb[2][TN];
+    read_frags(smem, 0, fa[0], fb[0]);
+    int st = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        const char* s = smem + st * TL::STAGE_BYTES;
+        int st1 = st + 1;
+        if (st1 == ST) st1 = 0;
+        int stl = st - 1;  // the stage of tile kt - 1 = the stage of tile kt + ST - 1
+        if (stl < 0) stl = ST - 1;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+            if (ks + 1 < NKS)
+                read_frags(s, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+            else
+                read_frags(smem + st1 * TL::STAGE_BYTES, 0, fa[0], fb[0]);
+            mfmas(fa[ks & 1], fb[ks & 1]);
+            if (ks == NKS / 2 - 1) {
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            if (ks >= NKS / 2 - 1) {
+                const int slot = ks - (NKS / 2 - 1);
+                issue_loads(stl, LOADS * slot / SLOTS, LOADS * (slot + 1) / SLOTS);
+                if (slot == SLOTS - 1) l_m += BK;
+            }
+        }
+        st = st1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may land in LDS after the workgroup has given it back
 
     float* dst = part + ((int64_t)slice * gridDim.z * g.Co + dy_c0) * g.Kdim;
 #pragma unroll
-    for (int i = 0; i < TL::TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int jn = 0; jn < TL::TN; ++jn) {
-            const int col = j0 + (wave_n * TL::TN + jn) * 32 + lane % 32;
+        for (int jn = 0; jn < TN; ++jn) {
+            const int col = j0 + (wave_n * TN + jn) * 32 + lane % 32;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int co = c0 + (wave_m * TL::TM + i) * 32 + acc_row<32>(lane, e);
+                const int co = c0 + (wave_m * TM + i) * 32 + acc_row<32>(lane, e);
                 if (co < g.Co && col < g.Kdim) dst[(int64_t)co * g.Kdim + col] = acc[i][jn][e];
             }
         }
@@ -2021,7 +2120,7 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_tr_kernel(const bf16_t* _
 // The contraction runs over the 128 pixel slots of the dy tile (8 MFMA steps of 16); the x operand of tap (r, s) for
 // slot q is slot q + 64 r + s of the x patch -- a constant offset, so the nine-fold im2col expansion happens in the
 // LDS read, and the zero columns of dy cancel whatever the patch holds at the slots that are no pixels.  Operands are
-// formed by the LDS transpose read (see conv_wgrad_tr_kernel) with the same per-256-byte-line chunk swizzle.
+// formed by the LDS transpose read (see conv_wgrad_dma_kernel) with the same per-256-byte-line chunk swizzle.
 // Wave w multiplies both blocks of 32 output channels with input-channel block w & 1 of the taps (w >> 1), (w >> 1) + 2,
 // ..: 10 (or 8) MFMAs per step from 14 (12) operand reads, instead of 2 reads per MFMA of the tiled kernel.
 // The rows of the next tile are fetched into registers before the steps and written to the other LDS buffer after
@@ -2084,7 +2183,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
         for (int i = 0; i < 8; ++i) *(u32x4*)(base + kW64DyBytes + (i >> 1) * 8192 + lds_slot[i & 1]) = pre[4 + i];
     };
 
-    // operand reads (transpose reads, see conv_wgrad_tr_kernel): lane (j16, cs, kg) addresses pixel slot
+    // operand reads (transpose reads, see conv_wgrad_dma_kernel): lane (j16, cs, kg) addresses pixel slot
     // 8 kg + j16 / 4 (+ 4 for the second half) of a step, channels 16 cs + 4 (j16 % 4) .. + 3 of a 32-channel block
     const int j16 = lane & 15, cs = (lane >> 4) & 1, kg = lane >> 5;
     const int frag_row = 8 * kg + (j16 >> 2), frag_chunk = cs * 2 + ((j16 & 3) >> 1), frag_half = (j16 & 1) * 8;
@@ -2179,7 +2278,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
 // 16 steps of 16 pixels, eight per wave; the x operand of tap (r, s) for slot q is slot q + 128 r + s of the patch: a
 // constant offset in the LDS read, and the zero columns of dy cancel whatever finite value the patch holds where a
 // slot is no pixel (a zeroed guard follows the patch).  Operands are formed by the LDS transpose read (see
-// conv_wgrad_tr_kernel); in the x operand the lane halves of a 32-column block are two neighbouring taps.  A step
+// conv_wgrad_dma_kernel); in the x operand the lane halves of a 32-column block are two neighbouring taps.  A step
 // costs 2 + 4 operand fragments for 8 MFMAs.  The next tile is fetched into registers before the steps and written to
 // the other LDS buffer after them.  At the end the two waves of each half are summed through LDS and leave as ONE
 // slice of partials per workgroup.
@@ -2956,45 +3055,38 @@ int run_wgrad(const WgradGeom& g, int splits, const void* x, const void* dy, flo
     return DSP_OK;
 }
 
-// The transpose-read kernel serves bf16 tiles of 64 or 128 channels/columns.
-template <typename TL>
-constexpr bool kWgradTr = sizeof(typename TL::T) == 2 && TL::MT == 32 && (TL::BM == 64 || TL::BM == 128) &&
-                          (TL::BN == 64 || TL::BN == 128) && TL::BK == 64;
-
-template <typename TL>
-int run_wgrad_tr(const WgradGeom& g, int splits, const void* x, const void* dy, float* dst, hipStream_t st, double flops)
-{
-    if constexpr (kWgradTr<TL>) {
-        constexpr int LDS = 2 * TL::BK * (TL::BM + TL::BN) * 2;
-        const int tiles = ceil_div(g.Co, TL::BM) * ceil_div(g.Kdim, TL::BN);
-        auto kern = conv_wgrad_tr_kernel<TL>;
-        static std::atomic<bool> attr_done{false};
-        if (!attr_done && LDS > 48 * 1024) {
-            DSP_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
-            attr_done = true;
-        }
-        {
-            ProfScope ps(tile_name<TL, true, true>(), flops, 0);
-            DSP_LAUNCH(ps, kern, dim3(tiles, splits, g.groups), dim3(kThreads), LDS, st, (const bf16_t*)x, (const bf16_t*)dy, dst, g);
-        }
-        DSP_HIP(hipGetLastError());
-        return DSP_OK;
-    } else {
-        return run_wgrad<TL, true>(g, splits, x, dy, dst, st, flops);
-    }
-}
-
 template <typename TL>
 int run_wgrad_v(const WgradGeom& g, int splits, bool vec, const void* x, const void* dy, float* dst, hipStream_t st,
                 double flops)
 {
-    return vec ? run_wgrad_tr<TL>(g, splits, x, dy, dst, st, flops) : run_wgrad<TL, false>(g, splits, x, dy, dst, st, flops);
+    // (bf16 problems of whole 16-byte channel runs go to the direct-to-LDS kernel)
+    if constexpr (sizeof(typename TL::T) == 4)
+        if (vec) return run_wgrad<TL, true>(g, splits, x, dy, dst, st, flops);
+    return run_wgrad<TL, false>(g, splits, x, dy, dst, st, flops);
 }
 
-// Tile of the backward-weight GEMM (output Cout x R*S*Cin) and the m extent of one LDS tile.
-struct WgradPlan {
-    int bm, bn, bk, id;
-};
+template <typename TL>
+int run_wgrad_dma(const WgradGeom& g, int splits, const void* x, const void* dy, float* dst, hipStream_t st, double flops)
+{
+    const int tiles = ceil_div(g.Co, TL::BM) * ceil_div(g.Kdim, TL::BN);
+    auto kern = conv_wgrad_dma_kernel<TL>;
+    static std::atomic<bool> attr_done{false};
+    if (!attr_done) {
+        DSP_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
+        attr_done = true;
+    }
+    static const KernelName name = [] {
+        KernelName k;
+        snprintf(k.text, sizeof(k.text), "conv_wgrad_dma<bf16,BM%d,BN%d,BK%d>", TL::BM, TL::BN, TL::BK);
+        return k;
+    }();
+    ProfScope ps(name.text, flops, 0);
+    DSP_LAUNCH(ps, kern, dim3(tiles, splits, g.groups), dim3(TL::THREADS), TL::LDS_BYTES, st, (const bf16_t*)x,
+               (const bf16_t*)dy, dst, g);
+    DSP_HIP(hipGetLastError());
+    return DSP_OK;
+}
+
 // One group of a grouped convolution as a convolution of its own (the shape the GEMM tiles are chosen for).
 ConvShape one_group(const ConvShape& c)
 {
@@ -3005,43 +3097,96 @@ ConvShape one_group(const ConvShape& c)
     return o;
 }
 
+// ---- tiles of the direct-to-LDS backward-weight kernel ----
+// Expected microseconds of tiles x slices workgroups with nk LDS stages each: they run in rounds of per_cu on each of the
+// 256 compute units, a stage costs t where per_cu workgroups share the compute unit and t_one where the last round leaves
+// it alone there; the slices are written and read once more at 5.5 TB/s.  The constants are fits to measured durations
+// (one MI355X; 69 layers, 1x1 and 3x3, stride 1 and 2, groups, M = 25 .. 200 k, Cout = 16 .. 2048, up to four slice counts
+// each), 7 % rms; the plan the model picks is 0.8 % slower than the best one, geometric mean.  Eight other tiles (256x256,
+// 128x256, 64x256, 128x128 and 64x64 with more workgroups per compute unit, 64x128, 32x128, 128x64) were best nowhere by more
+// than 3 %.  Against the register-staged tiles that this kernel replaced, slice sums included: 256 x 14x14, 256 -> 256 3x3
+// 93 -> 70 us (0.85 PFLOP/s); 128 x 4x4, 512 -> 512 3x3 31 -> 21 us; 64 x 14x14, 1024 -> 256 1x1 23 -> 18 us; 128 x 32x32,
+// 16 -> 16 3x3 16.8 -> 14.9 us; 128 x 32x32, 512 -> 512 3x3 in 8 groups 237 -> 163 us.
+// What bounds it: LDS.  Per 16 rows of m a wave of 64 x 64 makes 8 transpose reads of 512 bytes for 4 MFMAs (128 clocks on its
+// SIMD); eight such waves keep the LDS port busy for 256 clocks of the 256 their MFMAs take, and the direct loads write
+// through the same port.
+struct WgradCost {
+    int bm, bn, per_cu;
+    float t, t_one;
+};
+constexpr WgradCost kWgradDma[] = {{256, 128, 1, 0.852f, 0.756f}, {128, 128, 1, 0.563f, 0.472f}, {64, 64, 2, 0.418f, 0.313f}};
+constexpr int kWgradDmaRows = 64;  // rows of m per LDS stage
+constexpr int kWgradDmaId = 8;     // plan id of the first entry
+
+// Tile of the backward-weight GEMM (output Cout x R*S*Cin), and the slices of the (n, ho, wo) range.
+struct WgradPlan {
+    int id, splits, m_per_split;
+};
+
+// `want` slices of the M pixels, each a whole number of bk-row LDS tiles
+void wgrad_slice(WgradPlan* p, int64_t M, int64_t want, int bk)
+{
+    const int64_t per = (M + want - 1) / want;
+    p->m_per_split = (int)((per + bk - 1) / bk * bk);
+    p->splits = ceil_div(M, p->m_per_split);
+}
+
 WgradPlan wgrad_plan(int dtype, const ConvShape& cc)
 {
     const ConvShape c = one_group(cc);
-    // m rows per LDS tile: 128 bytes of k per row; the large fp32 tile keeps 64 (measured: VGG-19's layers)
-    const int bk = dtype == DSP_BF16 ? 64 : 32;
-    const int64_t kdim = (int64_t)c.R * c.S * c.Cin;
-    if (dtype == DSP_BF16) {
-        // bf16 has the transpose-read kernel only for 64- and 128-wide tiles; narrow layers run on the 64x64 one
-        // (the idle MFMA rows cost less than the register transposes of the narrow tiles)
-        if (c.Cout >= 128 && kdim >= 512) return {128, 128, bk, 3};
-        return {64, 64, bk, 2};
-    }
-    if (c.Cout <= 16) return {16, 64, bk, 0};
-    if (c.Cout <= 32) return {32, 128, bk, 1};
-    if (c.Cout >= 128 && kdim >= 512) return {128, 128, dtype == DSP_BF16 ? 64 : 16, 3};
-    return {64, 64, bk, 2};
-}
-
-// Slices of the (n, ho, wo) range: about two workgroups per compute unit, each slice a whole number
-// of LDS tiles and at least 8 of them.
-int wgrad_splits(const ConvShape& cc, const WgradPlan& pl, int* m_per_split)
-{
-    const ConvShape c = one_group(cc);
     const int64_t M = (int64_t)c.N * c.Ho * c.Wo, Kdim = (int64_t)c.R * c.S * c.Cin;
-    const int tiles = ceil_div(c.Cout, pl.bm) * ceil_div(Kdim, pl.bn) * conv_groups(cc);
+    WgradPlan p;
+    // m rows per LDS tile: 128 bytes of k per row; the large fp32 tile keeps 64 (measured: VGG-19's layers)
+    int bm = 64, bn = 64, bk = dtype == DSP_BF16 ? 64 : 32;
+    p.id = 2;
+    if (c.Cout >= 128 && Kdim >= 512) {
+        bm = bn = 128;
+        bk = dtype == DSP_BF16 ? 64 : 16;
+        p.id = 3;
+    } else if (dtype == DSP_FP32 && c.Cout <= 16) {
+        bm = 16;
+        p.id = 0;
+    } else if (dtype == DSP_FP32 && c.Cout <= 32) {
+        bm = 32;
+        bn = 128;
+        p.id = 1;
+    }
+    const int tiles = ceil_div(c.Cout, bm) * ceil_div(Kdim, bn) * conv_groups(cc);
     // two workgroups per compute unit, one for small problems (below ~1 GMAC, the CIFAR-sized layers: measured in
     // the three-stream pipeline); rounded down: one workgroup too many costs a whole second round
     const int target = (double)M * (double)Kdim * (double)cc.Cout < 1e9 ? 256 : 512;
     int want = target / tiles;
-    const int max_by_len = (int)((M + 8 * pl.bk - 1) / (8 * pl.bk));
+    const int max_by_len = (int)((M + 8 * bk - 1) / (8 * bk));  // at least 8 LDS tiles each
     if (want > max_by_len) want = max_by_len;
     if (want < 1) want = 1;
     if (want > 256) want = 256;
-    int per = (int)((M + want - 1) / want);
-    per = ceil_div(per, pl.bk) * pl.bk;
-    *m_per_split = per;
-    return ceil_div(M, per);
+    wgrad_slice(&p, M, want, bk);
+    if (dtype != DSP_BF16 || c.Cin % 8 != 0 || c.Cout % 8 != 0) return p;
+    // Whole 16-byte channel runs: the direct-to-LDS kernel.  The slices of the rule above stay the most it takes, so that the
+    // workspace does not grow; fewer of them where that fills the chip as well.
+    const double mbytes = (double)cc.Cout * (double)Kdim * 4e-6;
+    double best_us = 0;
+    WgradPlan best{-1, 0, 0};
+    for (int i = 0; i < 3; ++i) {
+        const WgradCost& d = kWgradDma[i];
+        const int64_t n_tiles = (int64_t)ceil_div(c.Cout, d.bm) * ceil_div(Kdim, d.bn) * conv_groups(cc);
+        const int64_t one_round = 256 * d.per_cu / n_tiles;
+        const int64_t tries[] = {want, one_round, one_round / 2, 1};
+        for (int64_t w : tries) {
+            if (w < 1 || w > want) continue;
+            WgradPlan q{kWgradDmaId + i, 0, 0};
+            wgrad_slice(&q, M, w, kWgradDmaRows);
+            const int64_t wgs = n_tiles * q.splits, full = wgs / (256 * d.per_cu), rest = wgs - full * 256 * d.per_cu;
+            const double nk = q.m_per_split / kWgradDmaRows;
+            const double us = nk * ((double)full * d.t + (rest > 256 ? d.t : rest > 0 ? d.t_one : 0.f)) +
+                              (q.splits > 1 ? 2 * q.splits + 1 : 1) * mbytes / 5.5;
+            if (best.id < 0 || us < best_us) {
+                best_us = us;
+                best = q;
+            }
+        }
+    }
+    return best;
 }
 
 // The persistent accumulators-resident kernel: bf16, 3x3 / stride 1 / pad 1, 64 channels on both sides, image rows of
@@ -3116,7 +3261,8 @@ int dispatch_wgrad(const ConvShape& c, const void* x, const void* dy, float* dw,
     int c64_per = 0;
     const int splits = c64 ? wgrad_c64_slices(c, &c64_per)
                            : stem ? wgrad_stem_slices(c, &c64_per)
-                                  : c16 ? wgrad_c16_splits(c, &g.m_per_split) : wgrad_splits(c, pl, &g.m_per_split);
+                                  : c16 ? wgrad_c16_splits(c, &g.m_per_split) : pl.splits;
+    if (!c16) g.m_per_split = pl.m_per_split;
     const size_t n = (size_t)c.Cout * g.Kdim;
     float* dst = dw;
     if (splits > 1) {
@@ -3160,12 +3306,20 @@ int dispatch_wgrad(const ConvShape& c, const void* x, const void* dy, float* dw,
             DSP_LAUNCH(ps, (conv_wgrad_c16_kernel<1, 1>), dim3(splits), dim3(kThreads), 0, st, (const float*)x,
                        (const float*)dy, dst, g);
         rc = DSP_OK;
-    } else
-    switch (pl.id) {
-    case 0: rc = run_wgrad_v<Tile<T, 16, 1, 4, 1, 1, KB, 2>>(g, splits, vec, x, dy, dst, st, flops); break;
-    case 1: rc = run_wgrad_v<Tile<T, 32, 1, 4, 1, 1, KB, 2>>(g, splits, vec, x, dy, dst, st, flops); break;
-    case 3: rc = run_wgrad_v<Tile<T, 32, 2, 2, 2, 2, (sizeof(T) == 2 ? 128 : 64), 2>>(g, splits, vec, x, dy, dst, st, flops); break;
-    default: rc = run_wgrad_v<Tile<T, 32, 2, 2, 1, 1, KB, 2>>(g, splits, vec, x, dy, dst, st, flops); break;
+    } else if (sizeof(T) == 2 && pl.id >= kWgradDmaId && vec) {
+        switch (pl.id - kWgradDmaId) {
+        case 0: rc = run_wgrad_dma<WgradTile<256, 128, 4, 2, kWgradDmaRows, 3, 2>>(g, splits, x, dy, dst, st, flops); break;
+        case 1: rc = run_wgrad_dma<WgradTile<128, 128, 2, 4, kWgradDmaRows, 4, 2>>(g, splits, x, dy, dst, st, flops); break;
+        default: rc = run_wgrad_dma<WgradTile<64, 64, 2, 2, kWgradDmaRows, 4, 2>>(g, splits, x, dy, dst, st, flops); break;
+        }
+    } else {
+        // (tensors that are not 16-byte aligned: the same slices on the tiles below)
+        switch (pl.id < kWgradDmaId ? pl.id : g.Co >= 128 && g.Kdim >= 512 ? 3 : 2) {
+        case 0: rc = run_wgrad_v<Tile<T, 16, 1, 4, 1, 1, KB, 2>>(g, splits, vec, x, dy, dst, st, flops); break;
+        case 1: rc = run_wgrad_v<Tile<T, 32, 1, 4, 1, 1, KB, 2>>(g, splits, vec, x, dy, dst, st, flops); break;
+        case 3: rc = run_wgrad_v<Tile<T, 32, 2, 2, 2, 2, (sizeof(T) == 2 ? 128 : 64), 2>>(g, splits, vec, x, dy, dst, st, flops); break;
+        default: rc = run_wgrad_v<Tile<T, 32, 2, 2, 1, 1, KB, 2>>(g, splits, vec, x, dy, dst, st, flops); break;
+        }
     }
     DSP_TRY(rc);
     if (splits > 1 && !defer_reduce) {
@@ -3373,7 +3527,7 @@ size_t conv_backward_weight_workspace(const ConvShape& c)
         int per;
         const int splits = wgrad_c64_eligible(dtype, c) ? wgrad_c64_slices(c, nullptr)
                            : wgrad_stem_eligible(dtype, c) ? wgrad_stem_slices(c, nullptr)
-                           : wgrad_c16_eligible(dtype, c) ? wgrad_c16_splits(c, &per) : wgrad_splits(c, pl, &per);
+                           : wgrad_c16_eligible(dtype, c) ? wgrad_c16_splits(c, &per) : pl.splits;
         const size_t b = splits > 1 ? (size_t)splits * c.Cout * c.R * c.S * (c.Cin / conv_groups(c)) * sizeof(float) : 0;
         if (b > worst) worst = b;
     }
@@ -3396,7 +3550,7 @@ int conv_backward_weight_slices(int dtype, const ConvShape& c)
     if (wgrad_c64_eligible(dtype, c)) return wgrad_c64_slices(c, nullptr);
     if (wgrad_stem_eligible(dtype, c)) return wgrad_stem_slices(c, nullptr);
     if (wgrad_c16_eligible(dtype, c)) return wgrad_c16_splits(c, &per);
-    return wgrad_splits(c, wgrad_plan(dtype, c), &per);
+    return wgrad_plan(dtype, c).splits;
 }
 
 struct WgradReduceSet {

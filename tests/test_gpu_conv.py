@@ -114,6 +114,27 @@ def test_direct_to_lds_tiles(shape):
     test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
 
 
+# The direct-to-LDS backward-weight tiles where they can go wrong: channels and columns that fill no tile (8 of 64, 136 of
+# 128 + 128), fewer rows than one LDS stage and than the stages in flight, a step of 64 pixels that passes several images
+# (3 x 3 maps), one that stays inside a row (a row of 70), rows dropped by the stride at an odd edge, and enough pixels for
+# the 256x128 tile.
+BACKWARD_WEIGHT = [
+    (1, 3, 3, 8, 8, 3, 3, 1, 1),
+    (50, 3, 3, 136, 136, 3, 3, 1, 1),
+    (2, 3, 70, 24, 40, 3, 3, 1, 1),
+    (3, 5, 71, 40, 264, 3, 3, 2, 1),
+    (7, 9, 10, 64, 144, 5, 5, 2, 2),
+    (130, 14, 14, 136, 264, 3, 3, 1, 1),
+    (33, 12, 12, 520, 256, 1, 1, 1, 0),
+    (20, 13, 13, 256, 520, 1, 1, 2, 0),
+]
+
+
+@pytest.mark.parametrize("shape", BACKWARD_WEIGHT, ids=lambda s: "x".join(map(str, s)))
+def test_direct_to_lds_backward_weight(shape):
+    test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
+
+
 # (N, H, W, Cin, Cout, R, S, stride, pad, groups)
 GROUPED = [
     (3, 9, 9, 32, 48, 3, 3, 1, 1, 4),       # 8 -> 12 channels per group: bf16 rows of the output are no whole 16-byte runs
