@@ -313,7 +313,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::MI
             if (masked) {
                 // taps s in [s_lo, s_hi) of a filter row fall inside the image; the same bits for every valid row r
                 const int s_lo = tw0 < 0 ? -tw0 : 0, s_hi = g.Wi - tw0 < g.S ? g.Wi - tw0 : g.S;
-                const uint64_t cols = s_hi > s_lo ? ((1ull << s_hi) - 1) & ~((1ull << s_lo) - 1) : 0ull;
+                const uint64_t cols = s_hi > s_lo ? (~0ull >> (64 - s_hi)) & (~0ull << s_lo) : 0ull;  // s_hi may be 64
                 uint64_t mask = 0;
                 for (int r = 0; r < g.R; ++r)
                     if (th0 + r >= 0 && th0 + r < g.Hi) mask |= cols << (r * g.S);
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
                 const int n = (int)fast_div((uint32_t)t, g.ho_mul, g.ho_sh), ho = t - n * g.Ho;
                 const int th0 = ho * g.ostride - g.pad_h, tw0 = wo * g.ostride - g.pad_w;
                 const int s_lo = tw0 < 0 ? -tw0 : 0, s_hi = g.Wi - tw0 < g.S ? g.Wi - tw0 : g.S;
-                const uint32_t cols = s_hi > s_lo ? ((1u << s_hi) - 1) & ~((1u << s_lo) - 1) : 0u;
+                const uint32_t cols = s_hi > s_lo ? (~0u >> (32 - s_hi)) & (~0u << s_lo) : 0u;  // s_hi may be 32
                 uint32_t mask = 0;
                 for (int r = 0; r < g.R; ++r)
                     if (th0 + r >= 0 && th0 + r < g.Hi) mask |= cols << (r * g.S);

@@ -135,6 +135,20 @@ def test_direct_to_lds_backward_weight(shape):
     test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
 
 
+# Filters as wide as a row's mask of taps has bits: 32 taps in one word (direct-to-LDS tiles), 64 in two (register-staged).
+WHOLE_MASK_ROWS = [
+    (2, 3, 40, 64, 64, 1, 32, 1, 0),
+    (2, 3, 37, 40, 16, 1, 32, 1, 0),
+    (1, 2, 70, 8, 16, 1, 64, 1, 0),
+]
+
+
+@pytest.mark.parametrize("dtype", [D.DSP_FP32, D.DSP_BF16], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("shape", WHOLE_MASK_ROWS, ids=lambda s: "x".join(map(str, s)))
+def test_filter_row_that_fills_the_tap_mask(shape, dtype):
+    test_conv_forward_dgrad_wgrad(shape, dtype)
+
+
 # (N, H, W, Cin, Cout, R, S, stride, pad, groups)
 GROUPED = [
     (3, 9, 9, 32, 48, 3, 3, 1, 1, 4),       # 8 -> 12 channels per group: bf16 rows of the output are no whole 16-byte runs
