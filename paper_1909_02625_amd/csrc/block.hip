@@ -79,6 +79,7 @@ struct Layer {
     dsp_layer_desc d;
     ConvShape cs;
     size_t p0 = 0, p1 = 0;  // offsets of (w | gamma | W) and (beta | bias) in the parameter arrays
+    size_t w16_off = 0;     // bf16 blocks: offset of the layer's parameters in the bf16 copy
     size_t wt_off = 0;      // offset of the backward-data filter copy
     float* mean = nullptr;
     float* invstd = nullptr;
@@ -152,7 +153,10 @@ struct dsp_block {
     UpdateTask* upd_tasks = nullptr;  // how the update kernel walks the flat arrays (device copy)
     int32_t* tap_tab = nullptr;       // per conv layer and tap: where that tap's filters sit in the backward-data copy
     int upd_n_tasks = 0, upd_blocks = 0;
-    void* wf16 = nullptr;  // bf16 copy of x in the same layout (bf16 blocks only)
+    // bf16 copy of x (bf16 blocks only), layer by layer in the order of x.  A layer begins at a multiple of 8 elements here and
+    // in wt, whatever the parameter counts in front of it: kernels that load filters as 16-byte runs are chosen by shape alone
+    void* wf16 = nullptr;
+    size_t w16_elems = 0;
     void* wt = nullptr;    // backward-data filter copies [cin][R-1-r][S-1-s][cout] in the storage type
     size_t wt_elems = 0;
     ParamSegment* segs = nullptr;   // where the library's order of the parameters differs from layer order (device copy)
@@ -205,7 +209,7 @@ static int dev_alloc(dsp_block* b, void** p, size_t bytes, size_t* counter)
 
 static const void* weights_for_forward(const dsp_block* b, const Layer& L)
 {
-    return b->dtype == DSP_BF16 ? (const void*)((const bf16_t*)b->wf16 + L.p0) : (const void*)(b->x + L.p0);
+    return b->dtype == DSP_BF16 ? (const void*)((const bf16_t*)b->wf16 + L.w16_off) : (const void*)(b->x + L.p0);
 }
 static const void* weights_for_dgrad(const dsp_block* b, const Layer& L)
 {
@@ -226,9 +230,10 @@ static int build_graph(dsp_block* b)
     b->input.elems = (size_t)d.N * d.C * d.H * d.W;
     b->layers.resize(d.n_layers);
     b->T.resize(d.n_layers);
-    size_t poff = 0, wtoff = 0;
+    size_t poff = 0, w16off = 0, wtoff = 0;
     for (int i = 0; i < d.n_layers; ++i) {
         Layer& L = b->layers[i];
+        const size_t p_begin = poff;
         L.d = d.layers[i];
         DSP_REQUIRE(L.d.in0 >= -1 && L.d.in0 < i, DSP_EINVAL, "layer %d: in0 must name an earlier tensor", i);
         const Tensor& s = L.d.in0 < 0 ? b->input : b->T[L.d.in0];
@@ -268,7 +273,7 @@ static int build_graph(dsp_block* b)
             L.p0 = poff;
             poff += (size_t)L.d.cout * (L.d.cin / G) * L.d.r * L.d.s;
             L.wt_off = wtoff;
-            wtoff += (size_t)L.d.cout * (cin / G) * L.cs.R * L.cs.S;
+            wtoff += ((size_t)L.d.cout * (cin / G) * L.cs.R * L.cs.S + 7) / 8 * 8;
             break;
         }
         case DSP_OP_BN:
@@ -317,11 +322,14 @@ static int build_graph(dsp_block* b)
         default:
             DSP_REQUIRE(false, DSP_EINVAL, "layer %d: unknown op %d", i, L.d.op);
         }
+        L.w16_off = w16off;
+        w16off += (poff - p_begin + 7) / 8 * 8;
         t.elems = (size_t)t.N * t.C * t.H * t.W;
     }
     b->out_idx = b->loss_idx >= 0 ? b->layers[b->loss_idx].d.in0 : d.n_layers - 1;
     DSP_REQUIRE(b->out_idx >= 0, DSP_EINVAL, "block: the loss needs a producing layer");
     b->nP = poff;
+    b->w16_elems = w16off;
     b->wt_elems = wtoff;
 
     // every tensor must be consumed (or be the block output); decide overwrite vs accumulate for
@@ -416,19 +424,21 @@ static int build_graph(dsp_block* b)
     std::vector<int32_t> tmap(b->nP, -1);
     std::vector<UpdateTask> tasks;
     std::vector<int32_t> tap_tab;
+    int32_t w16_shift = 0;  // of the layer at hand
     auto flat_task = [&](size_t p0, size_t n, bool decay) {
         if (n == 0) return;
         if (!tasks.empty() && tasks.back().kind == 0 && tasks.back().decay == (decay ? 1 : 0) &&
-            (size_t)tasks.back().p0 + tasks.back().n == p0) {
+            tasks.back().w16_shift == w16_shift && (size_t)tasks.back().p0 + tasks.back().n == p0) {
             tasks.back().n += (uint32_t)n;
             return;
         }
         UpdateTask t{};
-        t.kind = 0; t.decay = decay ? 1 : 0; t.p0 = (uint32_t)p0; t.n = (uint32_t)n;
+        t.kind = 0; t.decay = decay ? 1 : 0; t.p0 = (uint32_t)p0; t.n = (uint32_t)n; t.w16_shift = w16_shift;
         tasks.push_back(t);
     };
     for (int i = 0; i < d.n_layers; ++i) {
         const Layer& L = b->layers[i];
+        if (b->dtype == DSP_BF16) w16_shift = (int32_t)(L.w16_off - L.p0);
         if (L.d.op == DSP_OP_CONV) {
             const int G = conv_groups(L.cs), Cog = L.d.cout / G;
             const int Co = L.d.cout, Ci = L.d.cin / G, R = L.d.r, S = L.d.s;  // Ci: input channels of one group
@@ -448,11 +458,12 @@ static int build_graph(dsp_block* b)
                         }
             if (L.cin_pad) {
                 UpdateTask t{};
-                t.kind = 2; t.decay = 1; t.p0 = (uint32_t)L.p0; t.n = (uint32_t)n;
+                t.kind = 2; t.decay = 1; t.p0 = (uint32_t)L.p0; t.n = (uint32_t)n; t.w16_shift = w16_shift;
                 tasks.push_back(t);
             } else if (L.in0_grad) {
                 UpdateTask t{};
                 t.kind = 1; t.decay = 1; t.p0 = (uint32_t)L.p0; t.n = (uint32_t)n; t.wt_off = (uint32_t)L.wt_off;
+                t.w16_shift = w16_shift;
                 t.Co = Co; t.Ci = Ci; t.R = R; t.S = S; t.J = R * S * Ci; t.Cog = Cog;
                 t.tap_tab = (int)tap_tab.size();
                 DgradClass cls[4];
@@ -508,7 +519,7 @@ static int build_graph(dsp_block* b)
     DSP_TRY(dev_alloc(b, (void**)&b->tmap, b->nP * 4, &b->param_bytes));
     DSP_TRY(dev_alloc(b, &b->wt, b->wt_elems * esz, &b->param_bytes));
     DSP_HIP(hipMemset(b->wt, 0, b->wt_elems * esz ? b->wt_elems * esz : 16));  // the zero channels of padded filters stay zero
-    if (b->dtype == DSP_BF16) DSP_TRY(dev_alloc(b, &b->wf16, b->nP * 2, &b->param_bytes));
+    if (b->dtype == DSP_BF16) DSP_TRY(dev_alloc(b, &b->wf16, b->w16_elems * 2, &b->param_bytes));
     if (b->nP) {
         DSP_HIP(hipMemcpy(b->tmap, tmap.data(), b->nP * 4, hipMemcpyHostToDevice));
         DSP_HIP(hipMemset(b->v, 0, b->nP * 4));

@@ -292,13 +292,14 @@ int launch_softmax_ce(const float* z, const int32_t* labels, float* loss, float*
 constexpr int kDiffSumsqBlocks = 256;
 int launch_diff_sumsq(const float* a, const float* b, size_t n, double* partial, double* out, hipStream_t st);
 // v <- momentum*v + (g + wd*x*[decay]);  x <- x - lr*v (s = 0);  the copies the kernels read are refreshed in the
-// same pass: wf16[i] = bf16(x[i]) (bf16 blocks), and the backward-data filter copies in wt.  The parameters of a block
+// same pass: wf16[i + w16_shift] = bf16(x[i]) (bf16 blocks), and the backward-data filter copies in wt.  The parameters of a block
 // are described as a list of tasks over the flat arrays (built once at init, kept on the device):
 struct UpdateTask {
     int kind;          // 0: flat run, no copy in wt;  1: conv filters w[co][j] with the copy wt[ci][R-1-r][S-1-s][co];
                        // 2: one element per thread, copy position from the index table tmap (-1: none)
     int decay;         // weight decay applies (conv / linear weights)
     uint32_t p0, n;    // first element and length in the flat arrays
+    int32_t w16_shift; // bf16 blocks: distance of an element's bf16 copy from its own position
     uint32_t wt_off;   // kind 1: first element of the copy in wt
     int Co, J, Ci, R, S;  // kind 1: J = R * S * Ci (Ci: input channels of one group)
     int Cog;              // kind 1: output channels per group (= Co for an ordinary convolution); the copy of a

@@ -345,7 +345,7 @@ __global__ __launch_bounds__(kThreads) void sgd_update_kernel(float* __restrict_
             *(f32x4*)(v + i) = vv;
             *(f32x4*)(x + i) = xv;
         }
-        if (wf16) *(u32x2*)(wf16 + i) = u32x2{pack_bf16x2(xn[0], xn[1]), pack_bf16x2(xn[2], xn[3])};
+        if (wf16) *(u32x2*)(wf16 + i + t.w16_shift) = u32x2{pack_bf16x2(xn[0], xn[1]), pack_bf16x2(xn[2], xn[3])};
     };
     auto single = [&](size_t i) -> float {
         float vi = UPDATE ? v[i] : 0.f;
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kThreads) void sgd_update_kernel(float* __restrict_
             v[i] = vi;
             x[i] = xn;
         }
-        if (wf16) wf16[i] = float_to_bf16(xn);
+        if (wf16) wf16[i + t.w16_shift] = float_to_bf16(xn);
         return xn;
     };
 
@@ -629,9 +629,9 @@ int update_plan_finish(std::vector<UpdateTask>& tasks, int dtype, int* total_blo
             blocks += ceil_div(t.Co, kUpdTile) * t.tiles_j;
             const int E = dtype == DSP_BF16 ? 8 : 4;
             t.wt_aligned = (t.Cog % E == 0 && t.wt_off % E == 0) ? 1 : 0;  // every tap base and ci stride is a multiple of Cog
-            t.aligned = (t.p0 % 4 == 0 && t.J % 4 == 0) ? 1 : 0;
+            t.aligned = (t.p0 % 4 == 0 && t.w16_shift % 4 == 0 && t.J % 4 == 0) ? 1 : 0;
         }
-        if (t.kind == 0) t.aligned = (t.p0 % 4 == 0) ? 1 : 0;
+        if (t.kind == 0) t.aligned = (t.p0 % 4 == 0 && t.w16_shift % 4 == 0) ? 1 : 0;
     }
     *total_blocks = blocks;
     return DSP_OK;

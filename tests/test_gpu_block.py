@@ -244,6 +244,25 @@ def test_block_step_teacher_forced(name, dtype, ticks, kw):
     assert worst["steps"] > 0 and "out" in worst
 
 
+@pytest.mark.parametrize("dtype", [D.DSP_FP32, D.DSP_BF16], ids=["fp32", "bf16"])
+def test_filters_behind_a_ragged_parameter_count(dtype):
+    """Layers of 12 channels leave 7388 parameters in front of the 64 -> 64 convolution (not a whole number of 16-byte
+    runs) and a 1x1 layer of 5 filters an odd count in front of the last ones: every filter bank is found where the kernels
+    that load 16-byte runs expect it, in the first pass, after updates and with new parameters."""
+    conv = lambda src, cin, cout, k: dict(op="conv", cin=cin, cout=cout, r=k, s=k, stride=1, pad=k // 2, **{"in": src})  # noqa: E731
+    bn = lambda src, c: dict(op="bn", c=c, relu=True, res=None, **{"in": src})  # noqa: E731
+    widths = [(3, 12, 3), (12, 64, 3), (64, 64, 3), (64, 5, 1), (5, 64, 3), (64, 72, 3)]
+    layers = []
+    for cin, cout, k in widths:
+        layers.append(conv(len(layers) - 1, cin, cout, k))
+        layers.append(bn(len(layers) - 1, cout))
+    cfg = get_config("bn_probe")
+    cfg.update(blocks=[layers], input=(4, 3, 10, 10))
+    rng = np.random.default_rng(17)
+    worst = _teacher_forced(cfg, [perturb_affine(make_params(layers, rng), rng)], rng, dtype, 3)
+    assert worst["steps"] > 0 and "out" in worst
+
+
 def _free_running(cfg, params, rng, dtype, ticks, p=None, m=None, rtol=1e-3):
     K = cfg["K"]
     p = cfg["p"] if p is None else p
