@@ -1588,6 +1588,7 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_f32_kernel(const floa
 struct WgradGeom {
     int N, H, W, Ci, Ho, Wo, Co, R, S, pad, stride;
     int M, Kdim, m_per_split;
+    int m_chain;  // direct-to-LDS kernel: rows added up as one chain (a multiple of its LDS stage)
     // Grouped convolution: Ci and Co are the channels of ONE group (blockIdx.z); a pixel of x holds Cis = groups * Ci
     // channels and a row of dy Cos = groups * Co; the filter gradient has groups * Co rows of Kdim = R*S*Ci columns.
     int groups, Cis, Cos;
@@ -2009,13 +2010,27 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
         }
     };
 
-    typename Mma<bf16_t, 32>::Acc acc[TM][TN];
+    // A chain of additions is no longer than m_chain rows: `acc` is moved into `sum` behind every one of them.
+    typename Mma<bf16_t, 32>::Acc acc[TM][TN], sum[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = sum[i][j][e] = 0.f;
+    auto end_chain = [&]() {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    sum[i][j][e] += acc[i][j][e];
+                    acc[i][j][e] = 0.f;
+                }
+    };
+    const int chain = g.m_chain / BK;
+    int chain_end = chain;
 
     // operand reads: 16-lane group = (channel half cs, m half kg); lane j of it addresses row j / 4, channels 4 (j % 4).
     // Rows 4 apart share a swizzle, so a lane's chunk offset is the same for every k step.
@@ -2095,7 +2110,12 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
             }
         }
         st = st1;
+        if (kt + 1 == chain_end) {
+            end_chain();
+            chain_end += chain;
+        }
     }
+    end_chain();
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may land in LDS after the workgroup has given it back
 
     float* dst = part + ((int64_t)slice * gridDim.z * g.Co + dy_c0) * g.Kdim;
@@ -2107,7 +2127,7 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int co = c0 + (wave_m * TM + i) * 32 + acc_row<32>(lane, e);
-                if (co < g.Co && col < g.Kdim) dst[(int64_t)co * g.Kdim + col] = acc[i][jn][e];
+                if (co < g.Co && col < g.Kdim) dst[(int64_t)co * g.Kdim + col] = sum[i][jn][e];
             }
         }
 }
@@ -3105,8 +3125,9 @@ ConvShape one_group(const ConvShape& c)
 // each), 7 % rms; the plan the model picks is 0.8 % slower than the best one, geometric mean.  Eight other tiles (256x256,
 // 128x256, 64x256, 128x128 and 64x64 with more workgroups per compute unit, 64x128, 32x128, 128x64) were best nowhere by more
 // than 3 %.  Against the register-staged tiles that this kernel replaced, slice sums included: 256 x 14x14, 256 -> 256 3x3
-// 93 -> 70 us (0.85 PFLOP/s); 128 x 4x4, 512 -> 512 3x3 31 -> 21 us; 64 x 14x14, 1024 -> 256 1x1 23 -> 18 us; 128 x 32x32,
-// 16 -> 16 3x3 16.8 -> 14.9 us; 128 x 32x32, 512 -> 512 3x3 in 8 groups 237 -> 163 us.
+// 87 -> 69 us (0.86 PFLOP/s); 128 x 4x4, 512 -> 512 3x3 32 -> 23 us; 64 x 14x14, 1024 -> 256 1x1 23 -> 19 us; 256 x 28x28,
+// 128 -> 128 3x3 91 -> 79 us; 128 x 16x16, 32 -> 32 3x3 11.1 -> 10.5 us; 128 x 32x32, 512 -> 512 3x3 in 8 groups 233 -> 188 us.
+// (Ending a chain of additions every m_chain rows costs 0 to 5 % of that.)
 // What bounds it: LDS.  Per 16 rows of m a wave of 64 x 64 makes 8 transpose reads of 512 bytes for 4 MFMAs (128 clocks on its
 // SIMD); eight such waves keep the LDS port busy for 256 clocks of the 256 their MFMAs take, and the direct loads write
 // through the same port.
@@ -3121,6 +3142,9 @@ constexpr int kWgradDmaId = 8;     // plan id of the first entry
 // Tile of the backward-weight GEMM (output Cout x R*S*Cin), and the slices of the (n, ho, wo) range.
 struct WgradPlan {
     int id, splits, m_per_split;
+    // the register-staged tile and its slices (the same three where that is the kernel): tensors that are not 16-byte aligned
+    // take them, and no chain of additions of the direct-to-LDS tiles is longer than such a slice
+    int staged_id, staged_splits, staged_m_per_split;
 };
 
 // `want` slices of the M pixels, each a whole number of bk-row LDS tiles
@@ -3135,7 +3159,7 @@ WgradPlan wgrad_plan(int dtype, const ConvShape& cc)
 {
     const ConvShape c = one_group(cc);
     const int64_t M = (int64_t)c.N * c.Ho * c.Wo, Kdim = (int64_t)c.R * c.S * c.Cin;
-    WgradPlan p;
+    WgradPlan p{};
     // m rows per LDS tile: 128 bytes of k per row; the large fp32 tile keeps 64 (measured: VGG-19's layers)
     int bm = 64, bn = 64, bk = dtype == DSP_BF16 ? 64 : 32;
     p.id = 2;
@@ -3161,12 +3185,18 @@ WgradPlan wgrad_plan(int dtype, const ConvShape& cc)
     if (want < 1) want = 1;
     if (want > 256) want = 256;
     wgrad_slice(&p, M, want, bk);
+    p.staged_id = p.id;
+    p.staged_splits = p.splits;
+    p.staged_m_per_split = p.m_per_split;
     if (dtype != DSP_BF16 || c.Cin % 8 != 0 || c.Cout % 8 != 0) return p;
     // Whole 16-byte channel runs: the direct-to-LDS kernel.  The slices of the rule above stay the most it takes, so that the
-    // workspace does not grow; fewer of them where that fills the chip as well.
+    // workspace does not grow; fewer of them where that fills the chip as well.  The chains of fp32 additions stay as long as a
+    // slice of that rule: the rounding error grows with the square root of their length (128 x 4x4, 512 -> 512 3x3 in one slice:
+    // 1.8e-7 as one chain of 2048 rows, 1.0e-7 in runs of 704).
     const double mbytes = (double)cc.Cout * (double)Kdim * 4e-6;
     double best_us = 0;
-    WgradPlan best{-1, 0, 0};
+    WgradPlan best{};
+    best.id = -1;
     for (int i = 0; i < 3; ++i) {
         const WgradCost& d = kWgradDma[i];
         const int64_t n_tiles = (int64_t)ceil_div(c.Cout, d.bm) * ceil_div(Kdim, d.bn) * conv_groups(cc);
@@ -3174,7 +3204,8 @@ WgradPlan wgrad_plan(int dtype, const ConvShape& cc)
         const int64_t tries[] = {want, one_round, one_round / 2, 1};
         for (int64_t w : tries) {
             if (w < 1 || w > want) continue;
-            WgradPlan q{kWgradDmaId + i, 0, 0};
+            WgradPlan q = p;
+            q.id = kWgradDmaId + i;
             wgrad_slice(&q, M, w, kWgradDmaRows);
             const int64_t wgs = n_tiles * q.splits, full = wgs / (256 * d.per_cu), rest = wgs - full * 256 * d.per_cu;
             const double nk = q.m_per_split / kWgradDmaRows;
@@ -3258,11 +3289,15 @@ int dispatch_wgrad(const ConvShape& c, const void* x, const void* dy, float* dw,
     const bool c16 = wgrad_c16_eligible(dtype, c);
     const bool c64 = wgrad_c64_eligible(dtype, c);
     const bool stem = wgrad_stem_eligible(dtype, c);
+    const bool vec = (g.Ci % E) == 0 && (g.Co % E) == 0 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)dy % 16) == 0;
+    // (a caller that sums the slices later has been told how many there are)
+    const bool staged = !vec && !defer_reduce;
     int c64_per = 0;
     const int splits = c64 ? wgrad_c64_slices(c, &c64_per)
                            : stem ? wgrad_stem_slices(c, &c64_per)
-                                  : c16 ? wgrad_c16_splits(c, &g.m_per_split) : pl.splits;
-    if (!c16) g.m_per_split = pl.m_per_split;
+                                  : c16 ? wgrad_c16_splits(c, &g.m_per_split) : staged ? pl.staged_splits : pl.splits;
+    if (!c16) g.m_per_split = staged ? pl.staged_m_per_split : pl.m_per_split;
+    g.m_chain = pl.staged_m_per_split;
     const size_t n = (size_t)c.Cout * g.Kdim;
     float* dst = dw;
     if (splits > 1) {
@@ -3270,7 +3305,6 @@ int dispatch_wgrad(const ConvShape& c, const void* x, const void* dy, float* dw,
                     "conv backward-weight: workspace too small (%zu < %zu)", ws_bytes, n * splits * sizeof(float));
         dst = (float*)ws;
     }
-    const bool vec = (g.Ci % E) == 0 && (g.Co % E) == 0 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)dy % 16) == 0;
     int rc;
     if (c64) {
         // (the slice count is fixed by the shape; tensors that are not 16-byte aligned cannot use this kernel)
@@ -3313,8 +3347,7 @@ int dispatch_wgrad(const ConvShape& c, const void* x, const void* dy, float* dw,
         default: rc = run_wgrad_dma<WgradTile<64, 64, 2, 2, kWgradDmaRows, 4, 2>>(g, splits, x, dy, dst, st, flops); break;
         }
     } else {
-        // (tensors that are not 16-byte aligned: the same slices on the tiles below)
-        switch (pl.id < kWgradDmaId ? pl.id : g.Co >= 128 && g.Kdim >= 512 ? 3 : 2) {
+        switch (pl.staged_id) {
         case 0: rc = run_wgrad_v<Tile<T, 16, 1, 4, 1, 1, KB, 2>>(g, splits, vec, x, dy, dst, st, flops); break;
         case 1: rc = run_wgrad_v<Tile<T, 32, 1, 4, 1, 1, KB, 2>>(g, splits, vec, x, dy, dst, st, flops); break;
         case 3: rc = run_wgrad_v<Tile<T, 32, 2, 2, 2, 2, (sizeof(T) == 2 ? 128 : 64), 2>>(g, splits, vec, x, dy, dst, st, flops); break;
@@ -3527,7 +3560,7 @@ size_t conv_backward_weight_workspace(const ConvShape& c)
         int per;
         const int splits = wgrad_c64_eligible(dtype, c) ? wgrad_c64_slices(c, nullptr)
                            : wgrad_stem_eligible(dtype, c) ? wgrad_stem_slices(c, nullptr)
-                           : wgrad_c16_eligible(dtype, c) ? wgrad_c16_splits(c, &per) : pl.splits;
+                           : wgrad_c16_eligible(dtype, c) ? wgrad_c16_splits(c, &per) : pl.staged_splits;  // the most slices
         const size_t b = splits > 1 ? (size_t)splits * c.Cout * c.R * c.S * (c.Cin / conv_groups(c)) * sizeof(float) : 0;
         if (b > worst) worst = b;
     }

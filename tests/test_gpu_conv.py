@@ -135,6 +135,41 @@ def test_direct_to_lds_backward_weight(shape):
     test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
 
 
+# (shape, the longest run of pixels added up as one fp32 chain, slices): the slices of the register-staged rule, whatever
+# number of workgroups the direct-to-LDS tiles are dealt out to.
+CHAINS = [
+    ((128, 4, 4, 512, 512, 3, 3, 1, 1), 704, 3),
+    ((21, 12, 13, 144, 688, 3, 3, 1, 1), 512, 7),
+]
+
+
+@pytest.mark.parametrize("offset", [0, 4], ids=["aligned", "unaligned"])
+@pytest.mark.parametrize("shape, rows, slices", CHAINS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_backward_weight_rounds_as_short_chains(shape, rows, slices, offset):
+    """Rounding a sum to fp32 is off by 0.425 * 2^-24 of it (rms over the mantissas).  The partial sums of a chain of n matrix
+    instructions (16 independent products each) grow as sqrt(j / n), so the chain is off by 0.425 * 2^-24 * sqrt((n + 1) / 2) of
+    its result, and adding up s of them by sqrt((s + 1) / 2) of that unit more; 15 % on top for the roundings inside an
+    instruction.  One chain over all pixels is beyond it."""
+    N, H, W, Ci, Co, R, S, st, pd = shape
+    rng = np.random.default_rng(23)
+    x = round_like(rng.standard_normal((N, Ci, H, W)), D.DSP_BF16)
+    dy = round_like(rng.standard_normal((N, Co, H, W)), D.DSP_BF16)
+    xp = np.pad(x.transpose(0, 2, 3, 1).astype(np.float64), ((0, 0), (pd, pd), (pd, pd), (0, 0)))
+    dym = dy.transpose(0, 2, 3, 1).reshape(-1, Co).astype(np.float64)
+    ref = np.stack([dym.T @ xp[:, r:r + H, s:s + W].reshape(-1, Ci) for r in range(R) for s in range(S)], axis=1)
+    buf = torch.zeros(N * H * W * Ci + 8, device="cuda", dtype=torch.bfloat16)
+    d_x = buf[offset:offset + N * H * W * Ci]
+    d_x.copy_(to_dev(x, D.DSP_BF16).view(-1))
+    ws_bytes = D.dsp_conv_workspace_bytes(*shape)
+    ws = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device="cuda")
+    d_dw = torch.full((Co * R * S * Ci,), float("nan"), device="cuda", dtype=torch.float32)
+    D.dsp_conv_backward_weight(D.DSP_BF16, d_x, to_dev(dy, D.DSP_BF16), d_dw, *shape, ws, ws_bytes)
+    torch.cuda.synchronize()
+    bound = 1.15 * 0.425 * 2.0 ** -24 * np.sqrt((rows / 16 + 1) / 2 + (slices + 1) / 2)
+    err = rel_err(d_dw.cpu().numpy().reshape(ref.shape), ref)
+    assert err < bound
+
+
 # Filters as wide as a row's mask of taps has bits: 32 taps in one word (direct-to-LDS tiles), 64 in two (register-staged).
 WHOLE_MASK_ROWS = [
     (2, 3, 40, 64, 64, 1, 32, 1, 0),
