@@ -150,16 +150,19 @@ __global__ void gap_bwd_kernel(const float* __restrict__ dy, T* __restrict__ dx,
 // ---- linear head (fp32) ----------------------------------------------------------------------------
 // The three products are contractions of at most a few hundred MFLOP, bound by the latency of their loads, so they run on
 // the fp32 matrix instruction in 16 x 16 tiles of the result: a workgroup's eight waves deal out the contraction, a lane
-// loads four k of each operand per step (four steps in flight), and the eight partial tiles are summed through LDS
-// in wave order.  256 x 512 -> 1000: forward 49 -> 11 us, both gradients 76 -> 26 us in one launch; 128 x 1024 -> 10:
-// forward 17.5 -> 5.6 us; 128 x 64 -> 10: 4.2 us, gradients 8.2 -> 4.4 us.  (Before: eight outputs per wave and a shuffle tree,
-// one thread per element of dx.)
+// loads four k of each operand per step (four steps in flight), and the eight partial tiles are summed through LDS pairwise.
+// The forward product keeps sixteen partial sums per element, so that a chain of additions is K / 128 long and the rounding
+// error no larger than that of a sum dealt out to 64 lanes (5.3e-8 at 512 -> 1000, where one chain per wave gives 7.3e-8); the
+// gradients, whose plain sums were longer, keep one chain (2.1e-7 for dx there, 5.7e-7 as a loop over the outputs) and with it
+// the registers for two workgroups per compute unit.  256 x 512 -> 1000: forward 49 -> 11 us, both gradients 76 -> 26 us in one
+// launch; 128 x 1024 -> 10: forward 17.5 -> 5.6 us; 128 x 64 -> 10: 4.2 us, gradients 8.2 -> 4.4 us.  (Before: eight outputs
+// per wave and a shuffle tree, one thread per element of dx.)
 constexpr int kLinWaves = 8, kLinThreads = 64 * kLinWaves;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 // sum over k < K of a[i * ai + k * ak] * b[j * bj + k * bk] for the tile (i0 .., j0 ..) of an I x J result; a column j ==
 // ones_col takes b = 1.  AV / BV: the operand is contiguous along k (stride 1) and all its rows start 16-byte aligned.
 // Valid in wave 0: register r of a lane = row (lane >> 4) * 4 + r, column lane & 15.
-template <bool AV, bool BV>
+template <bool AV, bool BV, bool ONE_CHAIN>
 __device__ inline f32x4_t linear_tile(const float* __restrict__ a, int ai, int ak, int I, const float* __restrict__ b, int bj,
                                       int bk, int J, int ones_col, int K, int i0, int j0, f32x4_t (&red)[kLinWaves][64])
 {
@@ -176,7 +179,7 @@ __device__ inline f32x4_t linear_tile(const float* __restrict__ a, int ai, int a
         for (int e = 0; e < 4; ++e) v[e] = k + e < K ? p[(int64_t)(k + e) * stride] : 0.f;
         return v;
     };
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t part[ONE_CHAIN ? 1 : 4 * U] = {};
     for (int k0 = wave * 16; k0 < K; k0 += kLinWaves * 16 * U) {
         f32x4_t av[U], bv[U];
 #pragma unroll
@@ -188,17 +191,25 @@ __device__ inline f32x4_t linear_tile(const float* __restrict__ a, int ai, int a
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][e], bv[u][e], acc, 0, 0, 0);
+            for (int e = 0; e < 4; ++e) {
+                f32x4_t& p = part[ONE_CHAIN ? 0 : u * 4 + e];
+                p = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][e], bv[u][e], p, 0, 0, 0);
+            }
     }
+    auto add = [](const f32x4_t& p, const f32x4_t& q) -> f32x4_t { return {p[0] + q[0], p[1] + q[1], p[2] + q[2], p[3] + q[3]}; };
+#pragma unroll
+    for (int n = 2 * U; n > 0 && !ONE_CHAIN; n /= 2)
+#pragma unroll
+        for (int q = 0; q < n; ++q) part[q] = add(part[q], part[q + n]);
+    f32x4_t acc = part[0];
     red[wave][lane] = acc;
     __syncthreads();
-    if (wave == 0)
+    if (wave == 0) {
+        f32x4_t v[kLinWaves];
 #pragma unroll
-        for (int w = 1; w < kLinWaves; ++w) {
-            const f32x4_t v = red[w][lane];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] += v[r];
-        }
+        for (int w = 0; w < kLinWaves; ++w) v[w] = red[w][lane];
+        acc = add(add(add(v[0], v[1]), add(v[2], v[3])), add(add(v[4], v[5]), add(v[6], v[7])));
+    }
     return acc;
 }
 
@@ -210,7 +221,7 @@ __global__ __launch_bounds__(kLinThreads) void linear_fwd_kernel(const float* __
 {
     __shared__ f32x4_t red[kLinWaves][64];
     const int tiles_j = (Cout + 15) / 16, i0 = (int)(blockIdx.x / tiles_j) * 16, j0 = (int)(blockIdx.x % tiles_j) * 16;
-    const f32x4_t acc = linear_tile<VEC, VEC>(x, Cin, 1, N, w, Cin, 1, Cout, -1, Cin, i0, j0, red);
+    const f32x4_t acc = linear_tile<VEC, VEC, false>(x, Cin, 1, N, w, Cin, 1, Cout, -1, Cin, i0, j0, red);
     const int j = j0 + (int)(threadIdx.x & 15), n0 = i0 + (int)(threadIdx.x >> 4) * 4;
     if (threadIdx.x >= 64 || j >= Cout) return;
 #pragma unroll
@@ -231,8 +242,8 @@ __global__ __launch_bounds__(kLinThreads) void linear_bwd_kernel(const float* __
     const int blk = is_x ? (int)blockIdx.x : (int)blockIdx.x - x_blocks;
     const int rows = is_x ? N : Cout, cols = is_x ? Cin : Cin + 1;
     const int tiles_c = (cols + 15) / 16, i0 = blk / tiles_c * 16, j0 = blk % tiles_c * 16;
-    const f32x4_t acc = is_x ? linear_tile<VEC, false>(dz, Cout, 1, N, w, 1, Cin, Cin, -1, Cout, i0, j0, red)
-                             : linear_tile<false, false>(dz, 1, Cout, Cout, x, 1, Cin, Cin, Cin, N, i0, j0, red);
+    const f32x4_t acc = is_x ? linear_tile<VEC, false, true>(dz, Cout, 1, N, w, 1, Cin, Cin, -1, Cout, i0, j0, red)
+                             : linear_tile<false, false, true>(dz, 1, Cout, Cout, x, 1, Cin, Cin, Cin, N, i0, j0, red);
     const int c = j0 + (int)(threadIdx.x & 15), r0 = i0 + (int)(threadIdx.x >> 4) * 4;
     if (threadIdx.x >= 64 || c >= cols) return;
 #pragma unroll

@@ -345,6 +345,23 @@ def test_sum_of_two_maps_forward_and_backward(shape, dtype):
     assert np.mean(gotb != wantb) < 1e-5 and rel_err(gotb, wantb) < 1e-6
 
 
+@pytest.mark.parametrize("cin, cout", [(2048, 1000), (4096, 100), (2047, 33)])
+def test_linear_forward_rounds_as_short_chains(cin, cout):
+    """An output is the pairwise sum of 128 chains of cin / 128 products.  Rounding a sum to fp32 is off by 0.425 * 2^-24 of it
+    (rms over the mantissas), a chain of n products by sqrt((n + 1) / 2) of that unit, each of the seven levels of sums by one;
+    10 % on top for the sample.  One chain per wave is beyond it."""
+    n = 37
+    g = torch.Generator(device="cuda").manual_seed(31)
+    x = torch.randn((n, cin), generator=g, device="cuda").relu_()
+    w, b = torch.randn((cout, cin), generator=g, device="cuda"), torch.zeros(cout, device="cuda")
+    z = torch.full((n, cout), float("nan"), device="cuda")
+    D.dsp_linear_forward(x, w, b, z, n, cin, cout)
+    ref = x.double() @ w.double().t()
+    bound = 1.1 * 0.425 * 2.0 ** -24 * ((cin / 128 + 1) / 2 + 7) ** 0.5
+    err = float((z.double() - ref).norm() / ref.norm())
+    assert err < bound
+
+
 @pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
 @pytest.mark.parametrize("N,C,H,W,classes", [(5, 24, 3, 3, 10), (8, 64, 8, 8, 100), (256, 512, 7, 7, 1000), (3, 300, 1, 1, 7)])
 def test_head_pool_linear_softmax(N, C, H, W, classes, dtype):
