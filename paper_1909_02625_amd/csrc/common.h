@@ -326,7 +326,7 @@ int launch_gather_f32(const float* src, const int32_t* idx, int32_t base, float*
 // The parameters of a block between the library's order (filters w[co][r][s][ci]) and layer order (w[co][ci][r][s]):
 // segment by segment of the flat array, in order and without gaps; rs = 1: the two orders agree.
 struct ParamSegment {
-    uint32_t p0, n;
+    uint32_t p0;
     int32_t ci, rs;
 };
 int launch_layer_order(const float* src, float* dst, const ParamSegment* segs, int n_segs, size_t n, bool to_layer_order,

@@ -4,6 +4,8 @@ Per-step checks are teacher-forced: before each tick the library block gets the 
 parameters and momentum, is fed the oracle's block input and incoming error gradient, and its
 h_{k+1}, G_{h_k}, G_{x_k}, x_k, v_k are compared by ||a-b||_2 / ||b||_2.  The loss trajectory is
 compared free-running.  Tolerances: 1e-4 (fp32), 2e-2 (bf16 MFMA), 1e-3 on the loss trajectory."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -261,6 +263,39 @@ def test_filters_behind_a_ragged_parameter_count(dtype):
     rng = np.random.default_rng(17)
     worst = _teacher_forced(cfg, [perturb_affine(make_params(layers, rng), rng)], rng, dtype, 3)
     assert worst["steps"] > 0 and "out" in worst
+
+
+@pytest.mark.parametrize("width", [32, 512], ids=["short", "long"])
+def test_parameters_read_by_several_threads(width):
+    """Reads of one block from several threads at a time (parameters and momentum in turn) give what was written, for blocks
+    whose arrays are rearranged on the host and on the device; a block holds no memory for it beyond its own arrays."""
+    layers = [dict(op="conv", cin=16, cout=width, r=3, s=3, stride=1, pad=1, **{"in": -1}),
+              dict(op="bn", c=width, relu=True, res=None, **{"in": 0})]
+    n = width * 16 * 9 + 2 * width
+    rng = np.random.default_rng(3)
+    x, v = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
+    desc, keep = D.make_block_desc(layers, (1, 16, 4, 4), D.DSP_FP32, 0, 1, 0, needs_input_grad=False)
+    block = D.dsp_block_init(desc, x)
+    try:
+        D.dsp_block_set_momentum(block, v)
+        # x, v, g, the index table of the update and a filter copy: five arrays, and a few small tables
+        assert D.dsp_block_memory(block)["params"] < 4 * n * 5 + 16384
+        wrong = []
+
+        def read(first):
+            for i in range(40):
+                want, got = (x, D.dsp_block_get_params(block)) if (first + i) % 2 else (v, D.dsp_block_get_momentum(block))
+                if not np.array_equal(want, got):
+                    wrong.append((first, i))
+
+        threads = [threading.Thread(target=read, args=(k,)) for k in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not wrong
+    finally:
+        D.dsp_block_destroy(block)
 
 
 def _free_running(cfg, params, rng, dtype, ticks, p=None, m=None, rtol=1e-3):
