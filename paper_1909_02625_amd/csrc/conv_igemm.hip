@@ -1879,14 +1879,19 @@ __device__ inline u32x2 lds_read_tr16(const char* p)
 // The direct load as an asm block: behind the builtin the compiler makes every transpose read wait for ALL outstanding
 // direct loads (it takes the read to alias their LDS writes), which leaves no load in flight across a k step.  The block
 // has no output; the waits for what it puts in LDS are written out in the kernel.  The s_nop covers the wait states that
-// M0 and a descriptor register fresh from a vector instruction need before a load reads them.
+// M0 and a descriptor register fresh from a vector instruction need before a load reads them.  M0 is listed as overwritten, so
+// that the compiler keeps no value of its own there across the block (it warns that it does not save a reserved register
+// itself, which nothing here asks for).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ inline void dma16_untracked(u32x4 rsrc, uint32_t lds_wave_base, uint32_t byte_off)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :
                  : "s"(lds_wave_base), "v"(byte_off), "s"(rsrc)
-                 : "memory");
+                 : "m0", "memory");
 }
+#pragma clang diagnostic pop
 __device__ inline u32x4 rsrc_words(const void* p, uint32_t bytes)
 {
     const uint64_t a = (uint64_t)p;
