@@ -583,9 +583,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::MI
 // multiply phase to arrive and no vector register or LDS-write instruction is spent on it.
 // Per k tile the tap and the channel offset are uniform, so a lane's address is (row base + uniform tap offset) or "out
 // of range" (padding tap / row past M: the buffer load then writes zeros).
-// Eight waves per 256-row tile (two per SIMD, wave tiles of 128 x 64 or 64 x 64): a direct load costs its wave some sixty
-// cycles of issue, which the other wave of the SIMD fills with MFMAs -- with four waves of 128 x 128 the same tile ran at
-// 750 instead of 1040 TFLOP/s (256 x 14x14, 256 -> 256 3x3).
+// Two waves per SIMD: a direct load costs its wave some sixty cycles of issue, which the other wave fills with MFMAs.  A tile
+// that has a compute unit to itself (256x256, 256x128 of 64 k) has eight waves of 128 x 64 or 64 x 64 -- with four waves of
+// 128 x 128 the 256x256 tile ran at 750 instead of 1040 TFLOP/s (256 x 14x14, 256 -> 256 3x3); the smaller ones have four
+// or eight waves and as a rule two workgroups per compute unit.
 template <int BM_, int BN_, int WGM_, int WGN_, int BKB_, int STAGES_, int WAVES_, int KG_ = 1, bool GEN_ = false>
 struct DmaTile {
     static constexpr int WAVES = WAVES_;  // waves per SIMD the register allocation aims for
@@ -598,7 +599,7 @@ struct DmaTile {
     static constexpr bool GEN = GEN_;
     static_assert(!GEN || BKB_ == 64, "the chunk a lane loads is the same in all its rows");
     static constexpr int NW = WGM * WGN, THREADS = 64 * NW * KG;
-    static_assert(NW * KG == 2 || NW * KG == 4 || NW * KG == 8 || NW * KG == 16, "four, eight or sixteen waves per workgroup");
+    static_assert(NW * KG == 4 || NW * KG == 8, "four or eight waves per workgroup");
     static constexpr int TM = BM / (WGM * 32), TN = BN / (WGN * 32);
     static_assert(TM * WGM * 32 == BM && TN * WGN * 32 == BN, "whole MFMA tiles per wave");
     static constexpr int ROWB = BKB_;                      // bytes of k per row: 64 or 32 bf16

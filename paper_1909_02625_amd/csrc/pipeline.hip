@@ -292,9 +292,13 @@ static int pl_alloc(dsp_pipeline* pl, void** p, size_t bytes)
 // queue that the fewest streams of the process use, ties in a fixed order: two block streams that end up on one queue run
 // their chains one after the other.  Queues that are in unequal use when the pipeline is built (the null stream counts, and
 // so do streams of earlier pipelines) put K consecutive streams on fewer than min(K, 4) queues, so three idle streams first
-// bring them level -- from there on consecutive streams take the queues in turn -- and go once the K streams exist.
+// bring them level -- from there on consecutive streams take the queues in turn -- and go once the K streams exist.  Three are
+// enough where the queues are short of the fullest one by three streams in all, as behind the null stream or behind another
+// pipeline; a program whose own streams crowd one queue further may still see two blocks share a queue, which costs time
+// and changes no result.  (No call tells which queue a stream has: this rests on the times below.)
 // Measured, second and later pipelines of a process with 2 K interleaved streams -> this: resnet20 (K = 3) 19.5 -> 14.0 ms
-// for 16 ticks, resnet56 bf16 (K = 4) 30.4 -> 21.6 ms, resnet164 90.6 -> 73.4 ms for 8, resnet18 264 -> 254 ms for 32.
+// for 16 ticks, resnet56 bf16 (K = 4) 30.4 -> 21.6 ms, resnet164 90.6 -> 73.4 ms for 8, resnet18 264 -> 254 ms for 32.  The
+// first pipeline of a process had its streams on queues of their own before, too, and is as fast as it was.
 static int create_block_streams(int K, std::vector<hipStream_t>* streams)
 {
     constexpr int kLevelStreams = 3;

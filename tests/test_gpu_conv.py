@@ -36,7 +36,7 @@ SHAPES = [
     (21, 56, 56, 64, 64, 3, 3, 1, 1),
     (30, 52, 51, 64, 64, 3, 3, 1, 1),   # the shortest rows that kernel takes (a tile touches 8 input rows), H != W, odd W, M = 79560
     (20, 60, 62, 64, 64, 3, 3, 1, 1),   # the longest (patch rows of 64 pixels are full)
-    (65, 32, 32, 64, 64, 3, 3, 1, 1),   # rows too short for it: the register-staged 256x64 tile at a large M
+    (65, 32, 32, 64, 64, 3, 3, 1, 1),   # rows too short for it: in bf16 the direct-to-LDS 128x64 tile at a large M
 ]
 
 
@@ -91,8 +91,9 @@ def test_conv_forward_dgrad_wgrad(shape, dtype):
 
 
 # The direct-to-LDS tiles where they can go wrong: rows and output channels that fill no tile, fewer k tiles than a tile
-# has LDS stages or groups of waves (K = 64 for eight groups), taps cut by every border, and channel counts that are no
-# multiple of a k tile (chunks of one k tile in different taps, a ragged k tail), both strides.
+# has LDS stages (K = 64), eight groups of waves of which the last have no k tile (18 of them at K = 576), taps cut by every
+# border, and channel counts that are no multiple of a k tile (chunks of one k tile in different taps, a ragged k tail), both
+# strides.
 DIRECT_TO_LDS = [
     (5, 9, 9, 64, 72, 3, 3, 1, 1),
     (1, 5, 5, 64, 32, 1, 1, 1, 0),
@@ -116,8 +117,8 @@ def test_direct_to_lds_tiles(shape):
 
 # The direct-to-LDS backward-weight tiles where they can go wrong: channels and columns that fill no tile (8 of 64, 136 of
 # 128 + 128), fewer rows than one LDS stage and than the stages in flight, a step of 64 pixels that passes several images
-# (3 x 3 maps), one that stays inside a row (a row of 70), rows dropped by the stride at an odd edge, and enough pixels for
-# the 256x128 tile.
+# (3 x 3 maps), one that stays inside a row (a row of 70), rows dropped by the stride at an odd edge, and eight slices of the
+# 128x128 tile.
 BACKWARD_WEIGHT = [
     (1, 3, 3, 8, 8, 3, 3, 1, 1),
     (50, 3, 3, 136, 136, 3, 3, 1, 1),
@@ -133,6 +134,46 @@ BACKWARD_WEIGHT = [
 @pytest.mark.parametrize("shape", BACKWARD_WEIGHT, ids=lambda s: "x".join(map(str, s)))
 def test_direct_to_lds_backward_weight(shape):
     test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
+
+
+# One layer for every direct-to-LDS tile, forward ("conv_dma_gemm") and backward-weight ("conv_wgrad_dma"): the tile's name as
+# the library reports it, and a shape that fills it neither in rows nor in output channels (nor, in the backward-weight ones,
+# in columns).  The tiles are chosen by a model of their durations, so a change of that model may ask for other shapes here.
+EVERY_TILE = [
+    ("conv_dma_gemm<bf16,BM256,BN256,BK32,8x1 waves>", (90, 35, 14, 64, 144, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM256,BN128,BK64,8x1 waves>", (36, 37, 25, 256, 72, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM256,BN128,BK32,4x1 waves>", (108, 25, 37, 64, 80, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM128,BN128,BK32,8x1 waves>", (18, 34, 27, 64, 72, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM128,BN128,BK64,8x1 waves>", (27, 37, 17, 512, 72, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM128,BN64,BK64,4x1 waves>", (79, 30, 14, 384, 8, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM128,BN64,BK32,4x1 waves>", (107, 13, 12, 64, 8, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM256,BN64,BK32,4x1 waves>", (109, 23, 40, 64, 8, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM64,BN64,BK64,4x1 waves>", (1, 6, 33, 64, 8, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM64,BN64,BK64,4x2 waves>", (87, 3, 34, 1024, 8, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM32,BN32,BK32,1x8 waves>", (3, 8, 7, 64, 8, 3, 3, 1, 1)),
+    ("conv_dma_gemm<bf16,BM256,BN256,BK32,8x1 waves,any Ci>", (55, 30, 20, 528, 136, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM256,BN128,BK32,4x1 waves,any Ci>", (117, 24, 39, 528, 40, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM128,BN128,BK32,8x1 waves,any Ci>", (37, 12, 37, 520, 88, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM64,BN64,BK32,4x1 waves,any Ci>", (79, 11, 20, 560, 40, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM64,BN64,BK32,4x2 waves,any Ci>", (22, 12, 35, 24, 40, 5, 5, 1, 2)),
+    ("conv_dma_gemm<bf16,BM32,BN32,BK32,1x8 waves,any Ci>", (3, 3, 3, 200, 8, 3, 3, 1, 1)),
+    ("conv_dma_gemm<bf16,BM128,BN32,BK32,2x2 waves,any Ci>", (117, 19, 16, 568, 8, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM64,BN32,BK32,2x2 waves,any Ci>", (63, 6, 23, 600, 8, 1, 1, 1, 0)),
+    ("conv_wgrad_dma<bf16,BM256,BN128,BK64>", (1, 3, 3, 832, 864, 3, 3, 1, 1)),
+    ("conv_wgrad_dma<bf16,BM256,BN128,BK64>", (19, 11, 19, 408, 272, 3, 3, 1, 1)),  # four slices, two chains each
+    ("conv_wgrad_dma<bf16,BM128,BN128,BK64>", (1, 3, 4, 576, 192, 5, 5, 1, 2)),
+    ("conv_wgrad_dma<bf16,BM64,BN64,BK64>", (2, 12, 25, 8, 8, 1, 1, 1, 0)),
+]
+
+
+@pytest.mark.parametrize("tile, shape", EVERY_TILE, ids=lambda v: v if isinstance(v, str) else "x".join(map(str, v)))
+def test_every_direct_to_lds_tile(tile, shape):
+    D.dsp_profile_start(64)
+    try:
+        test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
+    finally:
+        launched = {k["name"] for k in D.dsp_profile_stop()}
+    assert tile in launched, launched
 
 
 # (shape, the longest run of pixels added up as one fp32 chain, slices): the slices of the register-staged rule, whatever
@@ -194,6 +235,11 @@ GROUPED = [
     (2, 10, 10, 512, 512, 3, 3, 1, 1, 8),   # ResNeXt-29 (8 x 64d) stage 1
     (1, 9, 9, 256, 256, 3, 3, 2, 1, 8),     # 32 -> 32 per group, stride 2, odd sides
     (5, 6, 6, 24, 64, 1, 1, 1, 0, 2),       # 12 -> 32 per group
+    # direct-to-LDS tiles whose k tiles straddle taps: 72 -> 40, 72 -> 40, 80 -> 32 and 112 -> 32 per group
+    (26, 9, 9, 144, 80, 3, 3, 1, 1, 2),
+    (21, 10, 10, 288, 160, 3, 3, 1, 1, 4),
+    (1, 4, 4, 160, 64, 3, 3, 1, 1, 2),
+    (21, 20, 20, 224, 64, 3, 3, 1, 1, 2),
 ]
 
 
@@ -262,12 +308,12 @@ FULL = [
     (D.DSP_BF16, 64, 14, 14, 256, 256, 3, 3, 1, 1),    # ResNet-50 conv4_x 3x3
     (D.DSP_BF16, 64, 14, 14, 256, 1024, 1, 1, 1, 0),   # its 1x1 expansion
     (D.DSP_BF16, 64, 14, 14, 1024, 256, 1, 1, 1, 0),   # and reduction
-    (D.DSP_BF16, 256, 28, 28, 128, 128, 3, 3, 1, 1),   # ResNet-18 stage 2 (128x128 tiles)
+    (D.DSP_BF16, 256, 28, 28, 128, 128, 3, 3, 1, 1),   # ResNet-18 stage 2 (direct-to-LDS 256x128 tiles)
     (D.DSP_BF16, 256, 56, 56, 64, 128, 3, 3, 2, 1),    # ResNet-18 stage transition
     (D.DSP_BF16, 256, 7, 7, 512, 512, 3, 3, 1, 1),     # ResNet-18 stage 4 (7x7 maps: pixel runs cross image rows; direct-to-LDS 256x128 tiles)
     (D.DSP_BF16, 256, 14, 14, 256, 256, 3, 3, 1, 1),   # ResNet-18 stage 3 (direct-to-LDS 256x256 tiles)
     (D.DSP_BF16, 250, 14, 14, 256, 256, 3, 3, 1, 1),   # the same with a ragged last row tile (M = 49000)
-    (D.DSP_BF16, 125, 14, 14, 256, 384, 3, 3, 1, 1),   # direct-to-LDS 256x128 tiles, three column tiles, ragged rows
+    (D.DSP_BF16, 125, 14, 14, 256, 384, 3, 3, 1, 1),   # direct-to-LDS 256x256 tiles, the second one half empty, ragged rows
     (D.DSP_BF16, 256, 56, 56, 64, 64, 3, 3, 1, 1),     # ResNet-18 stage 1 (filters in registers, 3136 tiles on 256 workgroups)
     (D.DSP_BF16, 128, 32, 32, 512, 512, 3, 3, 1, 1, 8),   # ResNeXt-29 (8 x 64d) stage 1: 8 groups of 64 -> 64
     (D.DSP_BF16, 128, 32, 32, 1024, 1024, 3, 3, 2, 1, 8), # stage 2 entry: 128 -> 128 per group, stride 2
