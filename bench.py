@@ -207,9 +207,9 @@ def hbm_traffic(workload, dtype_name, kernel):
     if not os.path.exists(path):
         return None
     for line in open(path):
-        f = line.split()
-        if len(f) == 4 and f[0] == "TRAFFIC" and f[1] == kernel:
-            return float(f[2]) + float(f[3])
+        f = line.rsplit(None, 2)  # (a kernel's name may hold spaces)
+        if len(f) == 3 and f[0] == "TRAFFIC " + kernel:
+            return float(f[1]) + float(f[2])
     return None
 
 

@@ -241,3 +241,16 @@ def test_schedule_waits_arguments():
         D.dsp_schedule_waits((1, 1, 0), (4, 2, 0), (1, 0, 0))    # block 0 has no queue below it
     with pytest.raises(D.DSPError):
         D.dsp_schedule_waits((1, 1, 0), (4, 2, 0), (0, 65, 0))
+
+
+def test_traffic_of_a_kernel_whose_name_holds_spaces(tmp_path, monkeypatch):
+    """The line of the benchmark's dominant kernel is found in the committed summary whatever its name is made of."""
+    import bench
+    names = ["conv_dma_gemm<bf16,BM256,BN128,BK64,8x1 waves>", "conv_dma_gemm<bf16,BM256,BN128,BK64,8x1 waves,any Ci>", "mean_kernel"]
+    (tmp_path / "profiles").mkdir()
+    (tmp_path / "profiles" / "rocprofv3_pmc_hbm_traffic_w_bf16_pipeline_tick.txt").write_text(
+        "kernel  launches\n" + "".join("TRAFFIC %s %d %d\n" % (n, 10 * i, i) for i, n in enumerate(names, 1)))
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert [bench.hbm_traffic("w", "bf16", n) for n in names] == [11.0, 22.0, 33.0]
+    assert bench.hbm_traffic("w", "bf16", "conv_dma_gemm<bf16,BM256,BN128,BK64,8x1") is None
+    assert bench.hbm_traffic("v", "bf16", "mean_kernel") is None
