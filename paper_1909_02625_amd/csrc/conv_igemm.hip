@@ -1934,7 +1934,9 @@ struct WgradTile {
     static_assert(RA <= 512 && RB <= 512 && RA >= 64 && RB >= 64 && STAGES >= 3 && LDS_BYTES <= 160 * 1024, "tile shape");
 };
 
-template <typename TL>
+// CHAINS: a slice is added up in chains of at most g.m_chain rows (a second set of accumulators; an instance of its own because
+// the registers are what kernels of other streams find free beside it: 192 instead of 127 for the 256x128 tile).
+template <typename TL, bool CHAINS>
 __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL::WAVES, TL::WAVES))) void conv_wgrad_dma_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy, float* __restrict__ part, WgradGeom g)
 {
@@ -2016,14 +2018,16 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
         }
     };
 
-    // A chain of additions is no longer than m_chain rows: `acc` is moved into `sum` behind every one of them.
-    typename Mma<bf16_t, 32>::Acc acc[TM][TN], sum[TM][TN];
+    typename Mma<bf16_t, 32>::Acc acc[TM][TN], sum[CHAINS ? TM : 1][CHAINS ? TN : 1];  // sum: of the chains before this one
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = sum[i][j][e] = 0.f;
+            for (int e = 0; e < 16; ++e) {
+                acc[i][j][e] = 0.f;
+                if constexpr (CHAINS) sum[i][j][e] = 0.f;
+            }
     auto end_chain = [&]() {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -2035,8 +2039,6 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
                     acc[i][j][e] = 0.f;
                 }
     };
-    const int chain = g.m_chain / BK;
-    int chain_end = chain;
 
     // operand reads: 16-lane group = (channel half cs, m half kg); lane j of it addresses row j / 4, channels 4 (j % 4).
     // Rows 4 apart share a swizzle, so a lane's chunk offset is the same for every k step.
@@ -2091,7 +2093,7 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
     u32x4 fa[2][TM], fb[2][TN];
     read_frags(smem, 0, fa[0], fb[0]);
     int st = 0;
-    for (int kt = 0; kt < nk; ++kt) {
+    auto stage = [&]() {
         const char* s = smem + st * TL::STAGE_BYTES;
         int st1 = st + 1;
         if (st1 == ST) st1 = 0;
@@ -2116,12 +2118,17 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
             }
         }
         st = st1;
-        if (kt + 1 == chain_end) {
+    };
+    if constexpr (CHAINS) {
+        const int chain = g.m_chain / BK;
+        for (int kt = 0; kt < nk; kt += chain) {
+            const int end = nk < kt + chain ? nk - kt : chain;
+            for (int q = 0; q < end; ++q) stage();
             end_chain();
-            chain_end += chain;
         }
+    } else {
+        for (int kt = 0; kt < nk; ++kt) stage();
     }
-    end_chain();
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may land in LDS after the workgroup has given it back
 
     float* dst = part + ((int64_t)slice * gridDim.z * g.Co + dy_c0) * g.Kdim;
@@ -2133,7 +2140,9 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int co = c0 + (wave_m * TM + i) * 32 + acc_row<32>(lane, e);
-                if (co < g.Co && col < g.Kdim) dst[(int64_t)co * g.Kdim + col] = sum[i][jn][e];
+                float v = acc[i][jn][e];
+                if constexpr (CHAINS) v = sum[i][jn][e];
+                if (co < g.Co && col < g.Kdim) dst[(int64_t)co * g.Kdim + col] = v;
             }
         }
 }
@@ -2770,21 +2779,21 @@ inline int direct_grid(const GatherGeom& g)
     return blocks < 256 ? blocks : 256;
 }
 
-// Largest tile of the channel class that still yields enough workgroups; for small problems (the
-// CIFAR-sized layers) small tiles with long k steps: there the kernel is bound by the latency of the
-// gathers, and what helps is many workgroups with many bytes in flight each.
-// Returns the tile id used by dispatch_gather and the tile's row count.
 // ---- tiles of the direct-to-LDS kernel ----
 // Expected microseconds of a launch with k64 = Kdim / 64: the tiles run in rounds of per_cu tiles on each of the 256
 // compute units, a tile costs t0 + k64 * t where per_cu of them share the compute unit and t0_one + k64 * t_one where the
-// last round leaves it alone there, and a launch costs t_launch.  The constants are fits to measured durations (one
-// MI355X; 227 layers for CI64, their input just written by another kernel, and 150 for GEN: 1x1 and 3x3, stride 1 and 2,
-// M = 200 .. 670 k rows, Co = 16 .. 1024, K = 16 .. 9216), 7-12 % rms; the tile the table picks is 0.9 % (CI64) and 1.2 %
-// (GEN) slower than the best one, geometric mean.  Durations against the register-staged tiles: 1.39x (CI64) and, for
-// K >= 512, 1.35x (GEN) faster over random layers; 256 x 14x14, 256 -> 256 3x3: 79 -> 57 us (1.04 PFLOP/s); 64 x 14x14,
-// 256 -> 256 3x3: 31 -> 20 us; 128 x 4x4, 512 -> 512 3x3: 35 -> 17 us; 19 x 16x16, 1024 -> 256 1x1: 13.4 -> 9.2 us.
-// What bounds them: the direct loads deliver 23-58 bytes per clock and compute unit (58 where all data sits in the L1),
-// and a launch of one tile per compute unit alternates between loading, multiplying and storing.
+// last round leaves it alone there, and a launch costs t_launch.  The constants are fits to measured durations (227 layers for
+// CI64, their input just written by another kernel, and 150 for GEN: 1x1 and 3x3, stride 1 and 2, M = 200 .. 670 k rows, Co =
+// 16 .. 1024, K = 16 .. 9216).  Over the 120 layers of profiles/direct_to_lds_tile_durations.txt, which holds every tile's
+// duration, the tile the table picks is 0.8 % (CI64) and 1.5 % (GEN) slower than the best one, geometric mean (worst 1.32x).
+// Durations against the register-staged tiles: 1.39x (CI64) and, for K >= 512, 1.35x (GEN) faster over random layers;
+// 256 x 14x14, 256 -> 256 3x3: 79 -> 57 us (1.04 PFLOP/s); 64 x 14x14, 256 -> 256 3x3: 31 -> 20 us; 128 x 4x4, 512 -> 512 3x3:
+// 35 -> 17 us; 19 x 16x16, 1024 -> 256 1x1: 13.4 -> 9.2 us.
+// What bounds them: no unit is full.  Over the layers of ResNet-18 (batch 256) the matrix pipes work 55 % (256x256) and 38 %
+// (256x128) of the time, LDS reads take 22-24 % of the cycles with 4-5 % of them in conflict, and the waves wait for memory 42
+// and 26 % of theirs; over those of a ResNet-50 stage at batch 64, one round of tiles or less, the pipes work 27-35 %: a
+// launch of one tile per compute unit loads, multiplies and stores one after the other.
+constexpr int kComputeUnits = 256;
 struct DmaCost {
     int bm, bn, per_cu;
     float t, t_one, t0, t0_one, t_launch;
@@ -2792,10 +2801,10 @@ struct DmaCost {
 inline float dma_time(const DmaCost& d, const GatherGeom& g)
 {
     const int64_t tiles = (int64_t)ceil_div(g.M, d.bm) * ceil_div(g.Co, d.bn) * g.groups * (g.pair ? 2 : 1);
-    const int64_t full = tiles / (256 * d.per_cu), rest = tiles - full * 256 * d.per_cu;
+    const int64_t round = kComputeUnits * d.per_cu, full = tiles / round, rest = tiles - full * round;
     const float k64 = (float)g.Kdim / 64.f, shared = d.t0 + k64 * d.t;
     float us = d.t_launch + (float)(full * d.per_cu) * shared;
-    if (rest > 256) us += 2.f * shared;
+    if (rest > kComputeUnits) us += 2.f * shared;
     else if (rest > 0) us += d.t0_one + k64 * d.t_one;
     return us;
 }
@@ -2871,6 +2880,10 @@ bool c16_eligible(const GatherGeom& g)
            g.pad_h == 2 && g.pad_w == 2 && g.Hi == g.Ho && g.Wi == g.Wo && g.oh_mul == 0 && g.M >= 256 * 256 &&
            g.Wi + 3 <= kC16Pitch && g.Wi >= 64 && !g.accum;  // a tile of 128 pixels then touches at most 3 rows
 }
+// The tile id used by dispatch_gather and the tile's row count: the kernels for one shape, the direct-to-LDS tiles, then the
+// largest register-staged tile of the channel class that still yields enough workgroups; for small problems (the CIFAR-sized
+// layers) small tiles with long k steps: there the kernel is bound by the latency of the gathers, and what helps is many
+// workgroups with many bytes in flight each.
 template <typename T>
 int select_gather_tile(const GatherGeom& g, int* bm)
 {
@@ -3091,11 +3104,11 @@ int run_wgrad_v(const WgradGeom& g, int splits, bool vec, const void* x, const v
     return run_wgrad<TL, false>(g, splits, x, dy, dst, st, flops);
 }
 
-template <typename TL>
-int run_wgrad_dma(const WgradGeom& g, int splits, const void* x, const void* dy, float* dst, hipStream_t st, double flops)
+template <typename TL, bool CHAINS>
+int run_wgrad_dma_as(const WgradGeom& g, int splits, const void* x, const void* dy, float* dst, hipStream_t st, double flops)
 {
     const int tiles = ceil_div(g.Co, TL::BM) * ceil_div(g.Kdim, TL::BN);
-    auto kern = conv_wgrad_dma_kernel<TL>;
+    auto kern = conv_wgrad_dma_kernel<TL, CHAINS>;
     static std::atomic<bool> attr_done{false};
     if (!attr_done) {
         DSP_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
@@ -3113,6 +3126,13 @@ int run_wgrad_dma(const WgradGeom& g, int splits, const void* x, const void* dy,
     return DSP_OK;
 }
 
+template <typename TL>
+int run_wgrad_dma(const WgradGeom& g, int splits, const void* x, const void* dy, float* dst, hipStream_t st, double flops)
+{
+    return g.m_per_split > g.m_chain ? run_wgrad_dma_as<TL, true>(g, splits, x, dy, dst, st, flops)
+                                     : run_wgrad_dma_as<TL, false>(g, splits, x, dy, dst, st, flops);
+}
+
 // One group of a grouped convolution as a convolution of its own (the shape the GEMM tiles are chosen for).
 ConvShape one_group(const ConvShape& c)
 {
@@ -3126,17 +3146,18 @@ ConvShape one_group(const ConvShape& c)
 // ---- tiles of the direct-to-LDS backward-weight kernel ----
 // Expected microseconds of tiles x slices workgroups with nk LDS stages each: they run in rounds of per_cu on each of the
 // 256 compute units, a stage costs t where per_cu workgroups share the compute unit and t_one where the last round leaves
-// it alone there; the slices are written and read once more at 5.5 TB/s.  The constants are fits to measured durations
-// (one MI355X; 69 layers, 1x1 and 3x3, stride 1 and 2, groups, M = 25 .. 200 k, Cout = 16 .. 2048, up to four slice counts
-// each), 7 % rms; the plan the model picks is 0.8 % slower than the best one, geometric mean.  Eight other tiles (256x256,
-// 128x256, 64x256, 128x128 and 64x64 with more workgroups per compute unit, 64x128, 32x128, 128x64) were best nowhere by more
-// than 3 %.  Against the register-staged tiles that this kernel replaced, slice sums included: 256 x 14x14, 256 -> 256 3x3
-// 87 -> 69 us (0.86 PFLOP/s); 128 x 4x4, 512 -> 512 3x3 32 -> 23 us; 64 x 14x14, 1024 -> 256 1x1 23 -> 19 us; 256 x 28x28,
-// 128 -> 128 3x3 91 -> 79 us; 128 x 16x16, 32 -> 32 3x3 11.1 -> 10.5 us; 128 x 32x32, 512 -> 512 3x3 in 8 groups 233 -> 188 us.
-// (Ending a chain of additions every m_chain rows costs 0 to 5 % of that.)
-// What bounds it: LDS.  Per 16 rows of m a wave of 64 x 64 makes 8 transpose reads of 512 bytes for 4 MFMAs (128 clocks on its
-// SIMD); eight such waves keep the LDS port busy for 256 clocks of the 256 their MFMAs take, and the direct loads write
-// through the same port.
+// it alone there; the slices are written and read once more at 5.5 TB/s.  Launch, first stages and stores, 5 to 8 us and much the
+// same for all tiles, are left out.  The constants are fits to measured durations (69 layers, 1x1 and 3x3, stride 1 and 2,
+// groups, M = 25 .. 200 k, Cout = 16 .. 2048, up to four slice counts each).  Over the 60 layers of
+// profiles/direct_to_lds_tile_durations.txt the plan the model picks is 0.3 % slower than the best one where one launch sums the
+// slices of all layers, as in a block, and 4.5 % where the layer has a launch of its own for it (geometric means).  Eight other
+// tiles (256x256, 128x256, 64x256, 128x128 and 64x64 with more workgroups per compute unit, 64x128, 32x128, 128x64) were best
+// nowhere by more than 3 %.  Against the register-staged tiles that this kernel replaced, slice sums included: 256 x 14x14,
+// 256 -> 256 3x3 87 -> 69 us (0.86 PFLOP/s); 128 x 4x4, 512 -> 512 3x3 32 -> 23 us; 64 x 14x14, 1024 -> 256 1x1 23 -> 19 us;
+// 256 x 28x28, 128 -> 128 3x3 91 -> 79 us; 128 x 16x16, 32 -> 32 3x3 11.1 -> 10.5 us; 128 x 32x32, 512 -> 512 3x3 in 8 groups
+// 233 -> 188 us.  (Ending a chain of additions every m_chain rows costs 0 to 3 % of that.)
+// What bounds it: no unit is full.  Over the layers of ResNet-18 (batch 256) the matrix pipes work 40-44 % of the time, the
+// transpose reads take 22-30 % of the LDS cycles without conflicts, and the waves wait for memory 25-27 % of theirs.
 struct WgradCost {
     int bm, bn, per_cu;
     float t, t_one;
@@ -3206,16 +3227,16 @@ WgradPlan wgrad_plan(int dtype, const ConvShape& cc)
     for (int i = 0; i < 3; ++i) {
         const WgradCost& d = kWgradDma[i];
         const int64_t n_tiles = (int64_t)ceil_div(c.Cout, d.bm) * ceil_div(Kdim, d.bn) * conv_groups(cc);
-        const int64_t one_round = 256 * d.per_cu / n_tiles;
+        const int64_t round = kComputeUnits * d.per_cu, one_round = round / n_tiles;
         const int64_t tries[] = {want, one_round, one_round / 2, 1};
         for (int64_t w : tries) {
             if (w < 1 || w > want) continue;
             WgradPlan q = p;
             q.id = kWgradDmaId + i;
             wgrad_slice(&q, M, w, kWgradDmaRows);
-            const int64_t wgs = n_tiles * q.splits, full = wgs / (256 * d.per_cu), rest = wgs - full * 256 * d.per_cu;
+            const int64_t wgs = n_tiles * q.splits, full = wgs / round, rest = wgs - full * round;
             const double nk = q.m_per_split / kWgradDmaRows;
-            const double us = nk * ((double)full * d.t + (rest > 256 ? d.t : rest > 0 ? d.t_one : 0.f)) +
+            const double us = nk * ((double)full * d.t + (rest > kComputeUnits ? d.t : rest > 0 ? d.t_one : 0.f)) +
                               (q.splits > 1 ? 2 * q.splits + 1 : 1) * mbytes / 5.5;
             if (best.id < 0 || us < best_us) {
                 best_us = us;
