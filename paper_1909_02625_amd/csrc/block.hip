@@ -605,10 +605,48 @@ static int build_graph(dsp_block* b)
 }
 
 // Parameters change their order on the way between the device and the caller's array.  The relayout runs on the device, in
-// a buffer that lives for the call alone: a block holds no memory for it, and calls on one block can run at the same time.
-// Short arrays are rearranged on the host, where the loop costs less than a device allocation (a read of 37 k parameters: 26
-// us, 32 us on the device; of 75 k: 40 and 37 us; of 4.7 M: 6.1 and 1.2 ms), and so are those the device has no room for.
+// a buffer that all blocks of a device share: one call at a time uses it, in runs of at most kRelayoutRun parameters, and it is
+// given back with the last block.  (A buffer per call cost 0.2 ms a call, one per block its share of memory for life.)
+// Short arrays are rearranged on the host, where the loop costs less than the launch (a read of 37 k parameters: 26 us, 32 us
+// on the device; of 75 k: 40 and 37 us; of 4.7 M: 6.1 and 1.2 ms), and so are those the device has no room for.
 constexpr size_t kHostRelayout = 65536;
+constexpr size_t kRelayoutRun = (size_t)8 << 20;  // 32 MB
+
+struct RelayoutBuffers {
+    std::mutex m;  // held while a buffer is in use
+    int blocks = 0;
+    float* of_device[64] = {};
+};
+static RelayoutBuffers g_relayout;
+
+static void relayout_block_made()
+{
+    std::lock_guard<std::mutex> lock(g_relayout.m);
+    ++g_relayout.blocks;
+}
+
+static void relayout_block_gone()
+{
+    std::lock_guard<std::mutex> lock(g_relayout.m);
+    if (--g_relayout.blocks > 0) return;
+    for (float*& p : g_relayout.of_device) {
+        if (p) (void)hipFree(p);
+        p = nullptr;
+    }
+}
+
+// The current device's buffer (nullptr: none to be had); g_relayout.m is held.
+static float* relayout_buffer()
+{
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+    float*& p = g_relayout.of_device[dev];
+    if (!p && hipMalloc((void**)&p, kRelayoutRun * 4) != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();
+    }
+    return p;
+}
 
 static void relayout_on_host(const dsp_block* b, const float* src, float* dst, bool to_layer_order)
 {
@@ -629,38 +667,25 @@ static void relayout_on_host(const dsp_block* b, const float* src, float* dst, b
     }
 }
 
-// The buffer of one call: on the device, or (`host`) in host memory.
-struct RelayoutBuffer {
-    float* device = nullptr;
-    std::unique_ptr<float[]> host;
-    int make(size_t n)
-    {
-        if (n > kHostRelayout && hipMalloc((void**)&device, n * 4) == hipSuccess) return DSP_OK;
-        device = nullptr;
-        (void)hipGetLastError();
-        host.reset(new (std::nothrow) float[n]);
-        DSP_REQUIRE(host, DSP_ENOMEM, "out of host memory for %zu parameters", n);
-        return DSP_OK;
-    }
-    ~RelayoutBuffer()
-    {
-        if (device) (void)hipFree(device);
-    }
-};
-
 static int upload_params(dsp_block* b, const float* h, float* dst)
 {
     if (b->nP == 0) return DSP_OK;
-    RelayoutBuffer buf;
-    DSP_TRY(buf.make(b->nP));
-    if (buf.host) {
-        relayout_on_host(b, h, buf.host.get(), false);
-        DSP_HIP(hipMemcpy(dst, buf.host.get(), b->nP * 4, hipMemcpyHostToDevice));
-        return DSP_OK;
+    if (b->nP > kHostRelayout) {
+        std::lock_guard<std::mutex> lock(g_relayout.m);
+        if (float* buf = relayout_buffer()) {
+            for (size_t i = 0; i < b->nP; i += kRelayoutRun) {
+                const size_t n = std::min(kRelayoutRun, b->nP - i);
+                DSP_HIP(hipMemcpy(buf, h + i, n * 4, hipMemcpyHostToDevice));
+                DSP_TRY(launch_layer_order(buf, dst, b->d_segs, (int)b->segs.size(), i, n, false, nullptr));
+            }
+            DSP_HIP(hipStreamSynchronize(nullptr));
+            return DSP_OK;
+        }
     }
-    DSP_HIP(hipMemcpy(buf.device, h, b->nP * 4, hipMemcpyHostToDevice));
-    DSP_TRY(launch_layer_order(buf.device, dst, b->d_segs, (int)b->segs.size(), b->nP, false, nullptr));
-    DSP_HIP(hipStreamSynchronize(nullptr));
+    std::unique_ptr<float[]> lib(new (std::nothrow) float[b->nP]);
+    DSP_REQUIRE(lib, DSP_ENOMEM, "out of host memory for %zu parameters", b->nP);
+    relayout_on_host(b, h, lib.get(), false);
+    DSP_HIP(hipMemcpy(dst, lib.get(), b->nP * 4, hipMemcpyHostToDevice));
     return DSP_OK;
 }
 
@@ -668,15 +693,21 @@ static int download_params(dsp_block* b, const float* src, float* h)
 {
     DSP_HIP(hipDeviceSynchronize());
     if (b->nP == 0) return DSP_OK;
-    RelayoutBuffer buf;
-    DSP_TRY(buf.make(b->nP));
-    if (buf.host) {
-        DSP_HIP(hipMemcpy(buf.host.get(), src, b->nP * 4, hipMemcpyDeviceToHost));
-        relayout_on_host(b, buf.host.get(), h, true);
-        return DSP_OK;
+    if (b->nP > kHostRelayout) {
+        std::lock_guard<std::mutex> lock(g_relayout.m);
+        if (float* buf = relayout_buffer()) {
+            for (size_t i = 0; i < b->nP; i += kRelayoutRun) {
+                const size_t n = std::min(kRelayoutRun, b->nP - i);
+                DSP_TRY(launch_layer_order(src, buf, b->d_segs, (int)b->segs.size(), i, n, true, nullptr));
+                DSP_HIP(hipMemcpy(h + i, buf, n * 4, hipMemcpyDeviceToHost));
+            }
+            return DSP_OK;
+        }
     }
-    DSP_TRY(launch_layer_order(src, buf.device, b->d_segs, (int)b->segs.size(), b->nP, true, nullptr));
-    DSP_HIP(hipMemcpy(h, buf.device, b->nP * 4, hipMemcpyDeviceToHost));
+    std::unique_ptr<float[]> lib(new (std::nothrow) float[b->nP]);
+    DSP_REQUIRE(lib, DSP_ENOMEM, "out of host memory for %zu parameters", b->nP);
+    DSP_HIP(hipMemcpy(lib.get(), src, b->nP * 4, hipMemcpyDeviceToHost));
+    relayout_on_host(b, lib.get(), h, true);
     return DSP_OK;
 }
 
@@ -909,6 +940,7 @@ int dsp_block_init(const dsp_block_desc* desc, const float* h_params, size_t n_p
     *out = nullptr;
     dsp_block* b = new (std::nothrow) dsp_block();
     DSP_REQUIRE(b, DSP_ENOMEM, "dsp_block_init: out of host memory");
+    relayout_block_made();
     b->desc = *desc;
     int rc = build_graph(b);
     if (rc == DSP_OK && n_params != b->nP) {
@@ -940,6 +972,7 @@ int dsp_block_destroy(dsp_block* b)
     (void)hipDeviceSynchronize();
     for (void* p : b->allocs) (void)hipFree(p);
     wgrad_reduce_set_destroy(b->wgrad_set);
+    relayout_block_gone();
     delete b->fwd_lane;
     delete b;
     return DSP_OK;

@@ -329,8 +329,10 @@ struct ParamSegment {
     uint32_t p0;
     int32_t ci, rs;
 };
-int launch_layer_order(const float* src, float* dst, const ParamSegment* segs, int n_segs, size_t n, bool to_layer_order,
-                       hipStream_t st);
+// Parameters first .. first + n - 1 in layer order <-> their places in the whole library-order array; the layer-order side is
+// the run alone.
+int launch_layer_order(const float* src, float* dst, const ParamSegment* segs, int n_segs, size_t first, size_t n,
+                       bool to_layer_order, hipStream_t st);
 // Space-to-depth by 2 with channel padding: dst[n][h][w][(dh * 2 + dw) * C + c] = src[n][2h + dh][2w + dw][c], channels
 // 4C .. Cp-1 zero; H and W even, Cp * sizeof(T) a multiple of 16.
 int launch_space_to_depth2(int dtype, const void* src, void* dst, int N, int H, int W, int C, int Cp, hipStream_t st);

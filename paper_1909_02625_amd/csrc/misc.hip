@@ -775,14 +775,15 @@ __global__ __launch_bounds__(kThreads) void gather_f32_kernel(const float* __res
         dst[i] = src[idx[i] - base];
 }
 
-// One thread per element of the layer-order array; its neighbours' elements of the library-order array lie ci apart,
+// One thread per element of a run of the layer-order array (parameters first .. first + n - 1); its neighbours' elements of the library-order array lie ci apart,
 // in rows that the same workgroup reads or writes whole.  (11.2 M parameters: 30 us; the copy to the host takes
 // milliseconds.)
 __global__ __launch_bounds__(kThreads) void layer_order_kernel(const float* __restrict__ src, float* __restrict__ dst,
-                                                               const ParamSegment* __restrict__ segs, int n_segs, uint32_t n,
-                                                               int to_layer_order)
+                                                               const ParamSegment* __restrict__ segs, int n_segs,
+                                                               uint32_t first, uint32_t n, int to_layer_order)
 {
-    for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) {
+    for (uint32_t q = blockIdx.x * kThreads + threadIdx.x; q < n; q += gridDim.x * kThreads) {
+        const uint32_t i = first + q;
         int lo = 0, hi = n_segs - 1;
         while (lo < hi) {  // the last segment that begins at or before i
             const int mid = (lo + hi + 1) / 2;
@@ -796,8 +797,8 @@ __global__ __launch_bounds__(kThreads) void layer_order_kernel(const float* __re
             const uint32_t ci = k / (uint32_t)s.rs, t = k - ci * (uint32_t)s.rs;
             lib = s.p0 + co * row + t * (uint32_t)s.ci + ci;
         }
-        if (to_layer_order) dst[i] = src[lib];
-        else dst[lib] = src[i];
+        if (to_layer_order) dst[q] = src[lib];
+        else dst[lib] = src[q];
     }
 }
 
@@ -913,14 +914,14 @@ int launch_gather_f32(const float* src, const int32_t* idx, int32_t base, float*
     return DSP_OK;
 }
 
-int launch_layer_order(const float* src, float* dst, const ParamSegment* segs, int n_segs, size_t n, bool to_layer_order,
-                       hipStream_t st)
+int launch_layer_order(const float* src, float* dst, const ParamSegment* segs, int n_segs, size_t first, size_t n,
+                       bool to_layer_order, hipStream_t st)
 {
     if (n == 0) return DSP_OK;
     DSP_REQUIRE(src && dst && segs && n_segs > 0, DSP_EINVAL, "layer order: bad argument");
     ProfScope ps("layer_order", (double)n * 8.0, 1);
-    DSP_LAUNCH(ps, layer_order_kernel, dim3(grid_for((int64_t)n)), dim3(kThreads), 0, st, src, dst, segs, n_segs, (uint32_t)n,
-               to_layer_order ? 1 : 0);
+    DSP_LAUNCH(ps, layer_order_kernel, dim3(grid_for((int64_t)n)), dim3(kThreads), 0, st, src, dst, segs, n_segs,
+               (uint32_t)first, (uint32_t)n, to_layer_order ? 1 : 0);
     DSP_HIP(hipGetLastError());
     return DSP_OK;
 }

@@ -265,16 +265,17 @@ def test_filters_behind_a_ragged_parameter_count(dtype):
     assert worst["steps"] > 0 and "out" in worst
 
 
-@pytest.mark.parametrize("width", [32, 512], ids=["short", "long"])
-def test_parameters_read_by_several_threads(width):
+@pytest.mark.parametrize("cin, width", [(16, 32), (16, 512), (1000, 1000)], ids=["short", "long", "two-runs"])
+def test_parameters_read_by_several_threads(cin, width):
     """Reads of one block from several threads at a time (parameters and momentum in turn) give what was written, for blocks
-    whose arrays are rearranged on the host and on the device; a block holds no memory for it beyond its own arrays."""
-    layers = [dict(op="conv", cin=16, cout=width, r=3, s=3, stride=1, pad=1, **{"in": -1}),
+    whose arrays are rearranged on the host, on the device in one run, and in two (9 M parameters, the second run beginning
+    inside a filter); a block holds no memory for it beyond its own arrays."""
+    layers = [dict(op="conv", cin=cin, cout=width, r=3, s=3, stride=1, pad=1, **{"in": -1}),
               dict(op="bn", c=width, relu=True, res=None, **{"in": 0})]
-    n = width * 16 * 9 + 2 * width
+    n = width * cin * 9 + 2 * width
     rng = np.random.default_rng(3)
     x, v = rng.standard_normal(n).astype(np.float32), rng.standard_normal(n).astype(np.float32)
-    desc, keep = D.make_block_desc(layers, (1, 16, 4, 4), D.DSP_FP32, 0, 1, 0, needs_input_grad=False)
+    desc, keep = D.make_block_desc(layers, (1, cin, 4, 4), D.DSP_FP32, 0, 1, 0, needs_input_grad=False)
     block = D.dsp_block_init(desc, x)
     try:
         D.dsp_block_set_momentum(block, v)
@@ -283,7 +284,7 @@ def test_parameters_read_by_several_threads(width):
         wrong = []
 
         def read(first):
-            for i in range(40):
+            for i in range(40 if n < 1 << 20 else 4):
                 want, got = (x, D.dsp_block_get_params(block)) if (first + i) % 2 else (v, D.dsp_block_get_momentum(block))
                 if not np.array_equal(want, got):
                     wrong.append((first, i))
