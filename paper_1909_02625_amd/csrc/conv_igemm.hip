@@ -2789,9 +2789,9 @@ inline int direct_grid(const GatherGeom& g)
 // Durations against the register-staged tiles: 1.39x (CI64) and, for K >= 512, 1.35x (GEN) faster over random layers;
 // 256 x 14x14, 256 -> 256 3x3: 79 -> 57 us (1.04 PFLOP/s); 64 x 14x14, 256 -> 256 3x3: 31 -> 20 us; 128 x 4x4, 512 -> 512 3x3:
 // 35 -> 17 us; 19 x 16x16, 1024 -> 256 1x1: 13.4 -> 9.2 us.
-// What bounds them: no unit is full.  Over the layers of ResNet-18 (batch 256) the matrix pipes work 55 % (256x256) and 38 %
-// (256x128) of the time, LDS reads take 22-24 % of the cycles with 4-5 % of them in conflict, and the waves wait for memory 42
-// and 26 % of theirs; over those of a ResNet-50 stage at batch 64, one round of tiles or less, the pipes work 27-35 %: a
+// What bounds them: no unit is full.  Over the layers of ResNet-18 (batch 256) the matrix pipes work 53 % (256x256) and 38 %
+// (256x128) of the time, LDS reads take 22-23 % of the cycles with 4-5 % of them in conflict, and the waves wait for memory 43
+// and 26 % of theirs; over those of a ResNet-50 stage at batch 64, one round of tiles or less, the pipes work 26-34 %: a
 // launch of one tile per compute unit loads, multiplies and stores one after the other.
 constexpr int kComputeUnits = 256;
 struct DmaCost {
@@ -3156,8 +3156,8 @@ ConvShape one_group(const ConvShape& c)
 // 256 -> 256 3x3 87 -> 69 us (0.86 PFLOP/s); 128 x 4x4, 512 -> 512 3x3 32 -> 23 us; 64 x 14x14, 1024 -> 256 1x1 23 -> 19 us;
 // 256 x 28x28, 128 -> 128 3x3 91 -> 79 us; 128 x 16x16, 32 -> 32 3x3 11.1 -> 10.5 us; 128 x 32x32, 512 -> 512 3x3 in 8 groups
 // 233 -> 188 us.  (Ending a chain of additions every m_chain rows costs 0 to 3 % of that.)
-// What bounds it: no unit is full.  Over the layers of ResNet-18 (batch 256) the matrix pipes work 40-44 % of the time, the
-// transpose reads take 22-30 % of the LDS cycles without conflicts, and the waves wait for memory 25-27 % of theirs.
+// What bounds it: no unit is full.  Over the layers of ResNet-18 (batch 256) the matrix pipes work 39-41 % of the time, the
+// transpose reads take 21-29 % of the LDS cycles without conflicts, and the waves wait for memory 25-26 % of theirs.
 struct WgradCost {
     int bm, bn, per_cu;
     float t, t_one;
