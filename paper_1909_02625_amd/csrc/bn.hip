@@ -226,6 +226,23 @@ struct BnStatOut {
     const double* part;
     float *mean, *invstd, *coef;
 };
+__device__ inline void bn_forward_coef(double a, double b, double inv_M, float eps, float gamma, float beta, const BnStatOut& o, int c,
+                                       int C, bool store, float* scale, float* shift)
+{
+    const double mu = a * inv_M;
+    double var = b * inv_M - mu * mu;
+    if (var < 0.0) var = 0.0;
+    const double is = 1.0 / sqrt(var + (double)eps);
+    const double sc = (double)gamma * is;
+    *scale = (float)sc;
+    *shift = (float)((double)beta - mu * sc);
+    if (store) {
+        o.mean[c] = (float)mu;
+        o.invstd[c] = (float)is;
+        o.coef[c] = *scale;
+        o.coef[C + c] = *shift;
+    }
+}
 __global__ __launch_bounds__(kMergeLanes * 4) void bn_fwd_finalize_kernel(BnStatOut o0, BnStatOut o1, int nblk, int C,
                                                                           double inv_M, float eps,
                                                                           const float* __restrict__ gamma,
@@ -236,41 +253,37 @@ __global__ __launch_bounds__(kMergeLanes * 4) void bn_fwd_finalize_kernel(BnStat
     double a, b;
     merge_partials(o.part, nblk, C, red, &a, &b);
     const int c = blockIdx.x * 4 + (threadIdx.x & 3);
-    if ((threadIdx.x >> 2) == 0 && c < C) {
-        const double mu = a * inv_M;
-        double var = b * inv_M - mu * mu;
-        if (var < 0.0) var = 0.0;
-        const double is = 1.0 / sqrt(var + (double)eps);
-        o.mean[c] = (float)mu;
-        o.invstd[c] = (float)is;
-        const double sc = (double)gamma[c] * is;
-        o.coef[c] = (float)sc;
-        o.coef[C + c] = (float)((double)beta[c] - mu * sc);
-    }
+    float scale, shift;
+    if ((threadIdx.x >> 2) == 0 && c < C) bn_forward_coef(a, b, inv_M, eps, gamma[c], beta[c], o, c, C, true, &scale, &shift);
 }
 
 // Backward: dgamma, dbeta and dx = c1*dz - c2*x + c0 with
 // c1 = gamma*invstd, c2 = c1*invstd*dgamma/M, c0 = c2*mean - c1*dbeta/M.
-__global__ __launch_bounds__(kMergeLanes * 4) void bn_bwd_finalize_kernel(const double* __restrict__ part, int nblk, int C,
-                                                                          double inv_M, const float* __restrict__ gamma,
-                                                                          const float* __restrict__ mean,
-                                                                          const float* __restrict__ invstd,
-                                                                          float* __restrict__ dgamma,
-                                                                          float* __restrict__ dbeta, float* __restrict__ coef)
+struct BnGradOut {
+    const double* part;
+    const float *gamma, *mean, *invstd;
+    float *dgamma, *dbeta, *coef;
+};
+__device__ inline void bn_backward_coef(double a, double b, double inv_M, const BnGradOut& o, int c, bool store, float* k1, float* k2,
+                                        float* k0)
+{
+    const double c1 = (double)o.gamma[c] * (double)o.invstd[c];
+    const double c2 = c1 * (double)o.invstd[c] * b * inv_M;
+    *k1 = (float)c1;
+    *k2 = (float)c2;
+    *k0 = (float)(c2 * (double)o.mean[c] - c1 * a * inv_M);
+    if (store) {
+        o.dbeta[c] = (float)a;
+        o.dgamma[c] = (float)b;
+    }
+}
+__global__ __launch_bounds__(kMergeLanes * 4) void bn_bwd_finalize_kernel(BnGradOut o, int nblk, int C, double inv_M)
 {
     __shared__ double red[kMergeLanes][4][2];
     double a, b;
-    merge_partials(part, nblk, C, red, &a, &b);
+    merge_partials(o.part, nblk, C, red, &a, &b);
     const int c = blockIdx.x * 4 + (threadIdx.x & 3);
-    if ((threadIdx.x >> 2) == 0 && c < C) {
-        dbeta[c] = (float)a;
-        dgamma[c] = (float)b;
-        const double c1 = (double)gamma[c] * (double)invstd[c];
-        const double c2 = c1 * (double)invstd[c] * b * inv_M;
-        coef[c] = (float)c1;
-        coef[C + c] = (float)c2;
-        coef[2 * C + c] = (float)(c2 * (double)mean[c] - c1 * a * inv_M);
-    }
+    if ((threadIdx.x >> 2) == 0 && c < C) bn_backward_coef(a, b, inv_M, o, c, true, o.coef + c, o.coef + C + c, o.coef + 2 * C + c);
 }
 
 // y = [relu](scale*x + shift [+ res]); blockIdx.y selects the instance of a twin launch
@@ -350,6 +363,236 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(const T* __restr
         }
         VecIO<T, VW>::store(dx + i * VW, ov);
         if (HAS_RES) VecIO<T, VW>::store(dres + i * VW, rv);
+    }
+}
+
+// ---- finalize inside the apply kernels --------------------------------------------------------------
+// On small tensors with few partial rows every apply workgroup merges the partials of its own channels instead of waiting for
+// a launch that does it once.  A workgroup owns a group of cg channels (a power of two, 128 bytes of a row where there are
+// that many), so that its share of the partials is short, over a run of rows; the first rows of its tensor are on their way
+// while it merges.  Its first row block also leaves the statistics.  Consecutive work items (the groups of one run of rows,
+// which share cache lines and partial rows) go to one XCD.  The sums are taken in merge_partials' order (64 row lanes, then a
+// tree), so which of the two forms a shape takes does not show in the results.
+// Bound by latency.  Forward and backward with their sums, six launches against four: 2664 x 72 fp32 27.8 -> 20.9 us, 2048 x 16
+// fp32 27.7 -> 21.1.  The line lies where the gain ends inside a network, where other streams' kernels fill the chip during
+// the extra launch anyway while every workgroup's merge reads L2: with merging up to 8192 partials (rows x channels of a group)
+// and 32 MB resnet20 was 8 % slower and conv4_x 4.5 %, up to 4096 and 2 MB resnet20 still 1 %, a 2048 x 512 bf16 layer 3 %.
+constexpr int kMergeEntries = 2048;  // partial rows x channels of a group
+constexpr int64_t kMergeTensorBytes = (int64_t)3 << 19;
+constexpr int kBnThreads = 512;
+struct BnLayout {
+    int cg, groups;              // channels per group, groups
+    int rows_per_wg, row_blocks;
+};
+__device__ inline int bn_work_item(const BnLayout& L, int* g0)
+{
+    const unsigned b = blockIdx.x, nb = gridDim.x, q = nb / 8, r = nb % 8, xcd = b % 8;
+    const unsigned item = xcd * q + (xcd < r ? xcd : r) + b / 8;
+    *g0 = (int)(item % (unsigned)L.groups) * L.cg;
+    return (int)(item / (unsigned)L.groups);
+}
+
+// Sums of channel g0 + tid % CG to the threads of row group 0 (tid < CG).  Thread = (channel, row group rg of RG): it holds the
+// row lanes rg, rg + RG, .. of the 64; the lanes 32, 16, .. RG apart meet in its registers, the others in LDS.
+template <int CG>
+__device__ inline void merge_group(const double* __restrict__ part, int nblk, int C, int g0, double (&red)[kBnThreads][2], double* sa,
+                                   double* sb)
+{
+    constexpr int RG = kBnThreads / CG, NL = kMergeLanes / RG;
+    const int tid = threadIdx.x, c = g0 + tid % CG, rg = tid / CG;
+    double a[NL], b[NL];
+#pragma unroll
+    for (int j = 0; j < NL; ++j) a[j] = b[j] = 0.0;
+    if (c < C)
+        for (int k0 = rg; k0 < nblk; k0 += kMergeLanes) {
+            f64x2 v[NL];
+#pragma unroll
+            for (int j = 0; j < NL; ++j) {
+                const int k = k0 + RG * j;
+                v[j] = k < nblk ? *(const f64x2*)(part + ((int64_t)k * C + c) * 2) : f64x2{0.0, 0.0};
+            }
+#pragma unroll
+            for (int j = 0; j < NL; ++j) {
+                a[j] += v[j][0];
+                b[j] += v[j][1];
+            }
+        }
+#pragma unroll
+    for (int w = NL / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int j = 0; j < w; ++j) {
+            a[j] += a[j + w];
+            b[j] += b[j + w];
+        }
+    red[tid][0] = a[0];
+    red[tid][1] = b[0];
+    __syncthreads();
+    for (int w = RG / 2; w > 0; w >>= 1) {
+        if (rg < w) {
+            red[tid][0] += red[tid + w * CG][0];
+            red[tid][1] += red[tid + w * CG][1];
+        }
+        __syncthreads();
+    }
+    *sa = red[tid][0];
+    *sb = red[tid][1];
+}
+__device__ inline void merge_channels(const BnLayout& L, const double* part, int nblk, int C, int g0, double (&red)[kBnThreads][2],
+                                      double* sa, double* sb)
+{
+    if (L.cg == 64) merge_group<64>(part, nblk, C, g0, red, sa, sb);
+    else if (L.cg == 32) merge_group<32>(part, nblk, C, g0, red, sa, sb);
+    else merge_group<16>(part, nblk, C, g0, red, sa, sb);
+}
+
+template <typename T, int VW, bool RELU, bool HAS_RES>
+__global__ __launch_bounds__(kBnThreads) void bn_fwd_merge_apply_kernel(BnApplyIo io0, BnApplyIo io1, BnStatOut o0, BnStatOut o1, BnLayout L,
+                                                                  int nblk, int64_t M, int C, double inv_M, float eps,
+                                                                  const float* __restrict__ gamma, const float* __restrict__ beta)
+{
+    typedef typename VecIO<T, VW>::Raw Raw;
+    __shared__ double red[kBnThreads][2];
+    __shared__ float coef[2][64];
+    const BnApplyIo io = blockIdx.y ? io1 : io0;
+    const BnStatOut o = blockIdx.y ? o1 : o0;
+    const T* __restrict__ x = (const T*)io.x;
+    const T* __restrict__ res = (const T*)io.res;
+    T* __restrict__ y = (T*)io.y;
+    int g0;
+    const int rb = bn_work_item(L, &g0);
+    const int tid = threadIdx.x, vpr = L.cg / VW, rpp = kBnThreads / vpr;
+    const int cl = (tid % vpr) * VW, c0 = g0 + cl;
+    const bool active = c0 < C;  // (channels come in whole vectors)
+    const int64_t r_end = (int64_t)(rb + 1) * L.rows_per_wg < M ? (int64_t)(rb + 1) * L.rows_per_wg : M;
+    constexpr int U = 4;
+    int64_t r = (int64_t)rb * L.rows_per_wg + tid / vpr;
+    Raw xr[U], rr[U];
+    auto load = [&]() {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t ru = r + (int64_t)u * rpp;
+            if (!active || ru >= r_end) continue;
+            xr[u] = VecIO<T, VW>::raw(x + ru * C + c0);
+            if (HAS_RES) rr[u] = VecIO<T, VW>::raw(res + ru * C + c0);
+        }
+    };
+    load();  // on their way while the partials are merged
+    double a, b;
+    merge_channels(L, o.part, nblk, C, g0, red, &a, &b);
+    if (tid < L.cg && g0 + tid < C)
+        bn_forward_coef(a, b, inv_M, eps, gamma[g0 + tid], beta[g0 + tid], o, g0 + tid, C, rb == 0, &coef[0][tid], &coef[1][tid]);
+    __syncthreads();
+    float sc[VW], sh[VW];
+#pragma unroll
+    for (int k = 0; k < VW; ++k) {
+        sc[k] = active ? coef[0][cl + k] : 0.f;
+        sh[k] = active ? coef[1][cl + k] : 0.f;
+    }
+    while (r < r_end) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t ru = r + (int64_t)u * rpp;
+            if (!active || ru >= r_end) continue;
+            float xv[VW], rv[VW], ov[VW];
+            VecIO<T, VW>::unpack(xr[u], xv);
+            if (HAS_RES) VecIO<T, VW>::unpack(rr[u], rv);
+#pragma unroll
+            for (int k = 0; k < VW; ++k) {
+                float v = __builtin_fmaf(xv[k], sc[k], sh[k]);
+                if (HAS_RES) v += rv[k];
+                if (RELU) v = v > 0.f ? v : 0.f;
+                ov[k] = v;
+            }
+            VecIO<T, VW>::store(y + ru * C + c0, ov);
+            if (RELU && VW > 1 && io.bits) {
+                uint32_t bits = 0u;
+#pragma unroll
+                for (int k = 0; k < VW; ++k) bits |= (to_float<T>(from_float<T>(ov[k])) > 0.f ? 1u : 0u) << k;
+                io.bits[ru * (C / VW) + c0 / VW] = (uint8_t)bits;
+            }
+        }
+        r += (int64_t)U * rpp;
+        if (r < r_end) load();
+    }
+}
+
+// dz = dy*[y>0] (y as stored, or formed again from x: RM as in bn_sums_kernel);  dx = [dx_prev +] c1*dz - c2*x + c0;  dres (+)= dz.  dx_prev is dx itself (accumulate in place)
+// or another tensor's gradient that reaches the same input (the shortcut of a pre-activation unit).
+template <typename T, int VW, int RM, bool HAS_RES, bool RES_ACC, bool DX_ACC>
+__global__ __launch_bounds__(kBnThreads) void bn_bwd_merge_apply_kernel(const T* __restrict__ dy, const T* __restrict__ x,
+                                                                  const T* __restrict__ y, T* dx, const T* dx_prev,
+                                                                  T* __restrict__ dres, BnGradOut o, BnLayout L, int nblk, int64_t M,
+                                                                  int C, double inv_M, const float* __restrict__ fcoef)
+{
+    typedef typename VecIO<T, VW>::Raw Raw;
+    __shared__ double red[kBnThreads][2];
+    __shared__ float coef[3][64];
+    int g0;
+    const int rb = bn_work_item(L, &g0);
+    const int tid = threadIdx.x, vpr = L.cg / VW, rpp = kBnThreads / vpr;
+    const int cl = (tid % vpr) * VW, c0 = g0 + cl;
+    const bool active = c0 < C;
+    const int64_t r_end = (int64_t)(rb + 1) * L.rows_per_wg < M ? (int64_t)(rb + 1) * L.rows_per_wg : M;
+    constexpr int U = 4;
+    int64_t r = (int64_t)rb * L.rows_per_wg + tid / vpr;
+    Raw gr[U], xr[U], yr[U], pr[U], rr[U];
+    uint32_t bits[U];
+    auto load = [&]() {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t ru = r + (int64_t)u * rpp;
+            if (!active || ru >= r_end) continue;
+            gr[u] = VecIO<T, VW>::raw(dy + ru * C + c0);
+            xr[u] = VecIO<T, VW>::raw(x + ru * C + c0);
+            if (RM == 1) yr[u] = VecIO<T, VW>::raw(y + ru * C + c0);
+            if (RM == 3) bits[u] = ((const uint8_t*)y)[ru * (C / VW) + c0 / VW];
+            if (DX_ACC) pr[u] = VecIO<T, VW>::raw(dx_prev + ru * C + c0);
+            if (HAS_RES && RES_ACC) rr[u] = VecIO<T, VW>::raw(dres + ru * C + c0);
+        }
+    };
+    load();
+    double a, b;
+    merge_channels(L, o.part, nblk, C, g0, red, &a, &b);
+    if (tid < L.cg && g0 + tid < C)
+        bn_backward_coef(a, b, inv_M, o, g0 + tid, rb == 0, &coef[0][tid], &coef[1][tid], &coef[2][tid]);
+    __syncthreads();
+    float c1[VW], c2[VW], c3[VW], fsc[VW], fsh[VW];
+#pragma unroll
+    for (int k = 0; k < VW; ++k) {
+        c1[k] = active ? coef[0][cl + k] : 0.f;
+        c2[k] = active ? coef[1][cl + k] : 0.f;
+        c3[k] = active ? coef[2][cl + k] : 0.f;
+        if (RM == 2) {
+            fsc[k] = active ? fcoef[c0 + k] : 0.f;
+            fsh[k] = active ? fcoef[C + c0 + k] : 0.f;
+        }
+    }
+    while (r < r_end) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t ru = r + (int64_t)u * rpp;
+            if (!active || ru >= r_end) continue;
+            float gv[VW], xv[VW], yv[VW], pv[VW], rv[VW], ov[VW];
+            VecIO<T, VW>::unpack(gr[u], gv);
+            VecIO<T, VW>::unpack(xr[u], xv);
+            if (RM == 1) VecIO<T, VW>::unpack(yr[u], yv);
+            if (DX_ACC) VecIO<T, VW>::unpack(pr[u], pv);
+            if (HAS_RES && RES_ACC) VecIO<T, VW>::unpack(rr[u], rv);
+#pragma unroll
+            for (int k = 0; k < VW; ++k) {
+                const bool on = RM == 0 ? true
+                                : RM == 1 ? yv[k] > 0.f
+                                : RM == 2 ? bn_value<T>(xv[k], fsc[k], fsh[k]) > 0.f : ((bits[u] >> k) & 1u) != 0;
+                const float dz = on ? gv[k] : 0.f;
+                const float d = c1[k] * dz - c2[k] * xv[k] + c3[k];
+                ov[k] = DX_ACC ? pv[k] + d : d;
+                if (HAS_RES) rv[k] = RES_ACC ? rv[k] + dz : dz;
+            }
+            VecIO<T, VW>::store(dx + ru * C + c0, ov);
+            if (HAS_RES) VecIO<T, VW>::store(dres + ru * C + c0, rv);
+        }
+        r += (int64_t)U * rpp;
+        if (r < r_end) load();
     }
 }
 
@@ -593,6 +836,40 @@ __global__ __launch_bounds__(kThreads) void bn_pool_bwd_apply_kernel(const bf16_
     }
 }
 
+// Channels per group: 128 bytes of a row (16 channels at least), smaller where that pads the channel count by less.
+int bn_channel_group(int C, int VW)
+{
+    int best = VW == 8 ? 64 : 32;
+    for (int cg = best / 2; cg >= 16; cg /= 2)
+        if (ceil_div(C, cg) * cg * 9 < ceil_div(C, best) * best * 8) best = cg;
+    return best;
+}
+BnLayout bn_layout(int64_t M, int C, int VW, int64_t blocks)
+{
+    BnLayout L;
+    L.cg = bn_channel_group(C, VW);
+    L.groups = ceil_div(C, L.cg);
+    const int rpp = kBnThreads / (L.cg / VW);
+    const int64_t trips = (M + blocks * rpp - 1) / (blocks * rpp);
+    L.rows_per_wg = (int)trips * rpp;
+    L.row_blocks = ceil_div(M, L.rows_per_wg);
+    return L;
+}
+// Up to 512 workgroups over all groups and instances, fewer where a thread would get less than two vectors.
+BnLayout merge_layout(int64_t M, int C, int VW, int instances)
+{
+    const int cg = bn_channel_group(C, VW), groups = ceil_div(C, cg);
+    const int64_t rpp = kBnThreads / (cg / VW);
+    int64_t blocks = (512 + groups * instances - 1) / (groups * instances);
+    const int64_t most = (M + 2 * rpp - 1) / (2 * rpp);
+    if (blocks > most) blocks = most;
+    return bn_layout(M, C, VW, blocks < 1 ? 1 : blocks);
+}
+inline bool merges(int64_t M, int C, int VW, int esz, int nblk)
+{
+    return M * C * esz <= kMergeTensorBytes && (int64_t)nblk * bn_channel_group(C, VW) <= kMergeEntries;
+}
+
 int plan_rows(int64_t M, const RowLayout& L, int* nblk)
 {
     // every thread should see >= 4 rows (one trip of the summing loop); at most kMaxPartialBlocks workgroups
@@ -633,9 +910,26 @@ int bn_forward_t(const void* x, const void* res, void* y, const float* gamma, co
                    (const T*)nullptr, (const float*)nullptr, (const float*)nullptr, buf.partial, M, C, L, rows,
                    (const T*)(tw ? tw->x : nullptr), tw ? tw->buf.partial : nullptr, AddOut<T>{}, (const float*)nullptr);
     }
+    const BnStatOut o0{buf.partial, buf.mean, buf.invstd, buf.coef};
+    const BnStatOut o1 = tw ? BnStatOut{tw->buf.partial, tw->buf.mean, tw->buf.invstd, tw->buf.coef} : o0;
+    const BnApplyIo io0{x, res, y, buf.coef, relu_bits};
+    const BnApplyIo io1 = tw ? BnApplyIo{tw->x, tw->res, tw->y, tw->buf.coef, tw->relu_bits} : io0;
+    if (!stats_only && merges(M, C, VW, sizeof(T), nblk)) {
+        const BnLayout ml = merge_layout(M, C, VW, (int)ni);
+        ProfScope ps(sizeof(T) == 2 ? "bn_merge_apply_relu<bf16>" : "bn_merge_apply_relu<fp32>", tensor_bytes * (res ? 3 : 2), 1);
+#define BN_APPLY(R, H)                                                                                                             \
+    DSP_LAUNCH(ps, (bn_fwd_merge_apply_kernel<T, VW, R, H>), dim3((unsigned)(ml.groups * ml.row_blocks), ni), dim3(kBnThreads), 0, st, \
+               io0, io1, o0, o1, ml, nblk, M, C, 1.0 / (double)M, eps, gamma, beta)
+        if (relu) {
+            if (res) BN_APPLY(true, true); else BN_APPLY(true, false);
+        } else {
+            if (res) BN_APPLY(false, true); else BN_APPLY(false, false);
+        }
+#undef BN_APPLY
+        DSP_HIP(hipGetLastError());
+        return DSP_OK;
+    }
     {
-        const BnStatOut o0{buf.partial, buf.mean, buf.invstd, buf.coef};
-        const BnStatOut o1 = tw ? BnStatOut{tw->buf.partial, tw->buf.mean, tw->buf.invstd, tw->buf.coef} : o0;
         ProfScope ps("bn_fwd_finalize", (double)nblk * C * 16.0 * ni, 1);
         DSP_LAUNCH(ps, bn_fwd_finalize_kernel, dim3(ceil_div(C, 4), ni), dim3(kMergeLanes * 4), 0, st, o0, o1, nblk, C,
                    1.0 / (double)M, eps, gamma, beta);
@@ -646,8 +940,6 @@ int bn_forward_t(const void* x, const void* res, void* y, const float* gamma, co
     }
     const int64_t nvec = M * (C / VW);
     const dim3 ag(apply_grid(nvec), ni);
-    const BnApplyIo io0{x, res, y, buf.coef, relu_bits};
-    const BnApplyIo io1 = tw ? BnApplyIo{tw->x, tw->res, tw->y, tw->buf.coef, tw->relu_bits} : io0;
     ProfScope ps(sizeof(T) == 2 ? "bn_apply_relu<bf16>" : "bn_apply_relu<fp32>", tensor_bytes * (res ? 3 : 2), 1);
 #define BN_APPLY(R, H) \
     DSP_LAUNCH(ps, (bn_fwd_apply_kernel<T, VW, R, H>), ag, dim3(kThreads), 0, st, io0, io1, nvec, C, L.cv)
@@ -677,18 +969,35 @@ int bn_backward_t(const void* dy, const void* x, const void* y, void* dx, void* 
                    (const T*)y, (const float*)buf.mean, (const float*)buf.invstd, buf.partial, M, C, L, rows,
                    (const T*)nullptr, (double*)nullptr, AddOut<T>{}, fcoef);
     }
+    const BnGradOut o{buf.partial, gamma, buf.mean, buf.invstd, dgamma, dbeta, buf.coef};
+    // reads dy, x (y too where the ReLU is decided from the stored output, and the old values where it accumulates);
+    // writes dx (and dres)
+    const double apply_bytes = tensor_bytes * (2 + (RM == 1 ? 1 : 0) + 1 + (xacc ? 1 : 0) + (dres ? 1 + (racc ? 1 : 0) : 0)) +
+                               (RM == 3 ? tensor_bytes / (VW * sizeof(T)) : 0.0);
+    if (merges(M, C, VW, sizeof(T), nblk)) {
+        const BnLayout ml = merge_layout(M, C, VW, 1);
+        ProfScope ps(sizeof(T) == 2 ? "bn_bwd_merge_apply<bf16>" : "bn_bwd_merge_apply<fp32>", apply_bytes, 1);
+#define BN_BAPPLY(H, RA, XA)                                                                                               \
+    DSP_LAUNCH(ps, (bn_bwd_merge_apply_kernel<T, VW, (H && RM == 2) ? 1 : RM, H, RA, XA>),                                 \
+               dim3((unsigned)(ml.groups * ml.row_blocks)), dim3(kBnThreads), 0, st, (const T*)dy, (const T*)x, (const T*)y, \
+               (T*)dx, (const T*)dx_prev, (T*)dres, o, ml, nblk, M, C, 1.0 / (double)M, fcoef)
+        if (dres) {
+            if (racc) { if (xacc) BN_BAPPLY(true, true, true); else BN_BAPPLY(true, true, false); }
+            else      { if (xacc) BN_BAPPLY(true, false, true); else BN_BAPPLY(true, false, false); }
+        } else {
+            if (xacc) BN_BAPPLY(false, false, true); else BN_BAPPLY(false, false, false);
+        }
+#undef BN_BAPPLY
+        DSP_HIP(hipGetLastError());
+        return DSP_OK;
+    }
     {
         ProfScope ps("bn_bwd_finalize", (double)nblk * C * 16.0, 1);
-        DSP_LAUNCH(ps, bn_bwd_finalize_kernel, dim3(ceil_div(C, 4)), dim3(kMergeLanes * 4), 0, st, (const double*)buf.partial, nblk, C,
-                   1.0 / (double)M, gamma, (const float*)buf.mean, (const float*)buf.invstd, dgamma, dbeta, buf.coef);
+        DSP_LAUNCH(ps, bn_bwd_finalize_kernel, dim3(ceil_div(C, 4)), dim3(kMergeLanes * 4), 0, st, o, nblk, C, 1.0 / (double)M);
     }
     const int64_t nvec = M * (C / VW);
     const dim3 ag(apply_grid(nvec));
-    // reads dy, x (y too where the ReLU is decided from the stored output, and the old values where it accumulates);
-    // writes dx (and dres)
-    ProfScope ps(sizeof(T) == 2 ? "bn_bwd_apply<bf16>" : "bn_bwd_apply<fp32>",
-                 tensor_bytes * (2 + (RM == 1 ? 1 : 0) + 1 + (xacc ? 1 : 0) + (dres ? 1 + (racc ? 1 : 0) : 0)) +
-                     (RM == 3 ? tensor_bytes / (VW * sizeof(T)) : 0.0), 1);
+    ProfScope ps(sizeof(T) == 2 ? "bn_bwd_apply<bf16>" : "bn_bwd_apply<fp32>", apply_bytes, 1);
 #define BN_BAPPLY(H, RA, XA)                                                                                   \
     DSP_LAUNCH(ps, (bn_bwd_apply_kernel<T, VW, (H && RM == 2) ? 1 : RM, H, RA, XA>), ag, dim3(kThreads), 0, st, \
                (const T*)dy, (const T*)x, (const T*)y, (T*)dx, (const T*)dx_prev, (T*)dres, (const float*)buf.coef,   \
@@ -850,8 +1159,8 @@ static int bn_pool_backward(const PoolGrad& pg, const void* x, void* dx, bool xa
     }
     {
         ProfScope ps("bn_bwd_finalize", (double)nblk * C * 16.0, 1);
-        DSP_LAUNCH(ps, bn_bwd_finalize_kernel, dim3(ceil_div(C, 4)), dim3(kMergeLanes * 4), 0, st, (const double*)buf.partial, nblk, C,
-                   1.0 / (double)M, gamma, (const float*)buf.mean, (const float*)buf.invstd, dgamma, dbeta, buf.coef);
+        const BnGradOut o{buf.partial, gamma, buf.mean, buf.invstd, dgamma, dbeta, buf.coef};
+        DSP_LAUNCH(ps, bn_bwd_finalize_kernel, dim3(ceil_div(C, 4)), dim3(kMergeLanes * 4), 0, st, o, nblk, C, 1.0 / (double)M);
     }
     const int64_t items = cells * L.cv;
     int64_t grid = (items + kThreads - 1) / kThreads;

@@ -340,28 +340,35 @@ int launch_space_to_depth2(int dtype, const void* src, void* dst, int N, int H, 
 int launch_record_loss(const float* loss, float* history, int32_t* counter, int64_t capacity, hipStream_t st);
 
 // ---- 16-byte (or single-element) loads and stores of VW consecutive elements as floats ------------
+// Raw: the elements as they lie in memory, for loads that wait in registers until they are used.
 template <typename T, int VW>
 struct VecIO;
 
 template <>
 struct VecIO<float, 4> {
-    __device__ static inline void load(const float* p, float (&v)[4])
+    typedef float4 Raw;
+    __device__ static inline Raw raw(const float* p) { return *(const float4*)p; }
+    __device__ static inline void unpack(const Raw& t, float (&v)[4])
     {
-        const float4 t = *(const float4*)p;
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     }
+    __device__ static inline void load(const float* p, float (&v)[4]) { unpack(raw(p), v); }
     __device__ static inline void store(float* p, const float (&v)[4]) { *(float4*)p = make_float4(v[0], v[1], v[2], v[3]); }
 };
 template <>
 struct VecIO<float, 1> {
+    typedef float Raw;
+    __device__ static inline Raw raw(const float* p) { return *p; }
+    __device__ static inline void unpack(const Raw& t, float (&v)[1]) { v[0] = t; }
     __device__ static inline void load(const float* p, float (&v)[1]) { v[0] = *p; }
     __device__ static inline void store(float* p, const float (&v)[1]) { *p = v[0]; }
 };
 template <>
 struct VecIO<bf16_t, 8> {
-    __device__ static inline void load(const bf16_t* p, float (&v)[8])
+    typedef uint4 Raw;
+    __device__ static inline Raw raw(const bf16_t* p) { return *(const uint4*)p; }
+    __device__ static inline void unpack(const Raw& t, float (&v)[8])
     {
-        const uint4 t = *(const uint4*)p;
         const uint32_t w[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -369,6 +376,7 @@ struct VecIO<bf16_t, 8> {
             v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
         }
     }
+    __device__ static inline void load(const bf16_t* p, float (&v)[8]) { unpack(raw(p), v); }
     __device__ static inline void store(bf16_t* p, const float (&v)[8])
     {
         uint32_t w[4];
@@ -380,6 +388,9 @@ struct VecIO<bf16_t, 8> {
 };
 template <>
 struct VecIO<bf16_t, 1> {
+    typedef bf16_t Raw;
+    __device__ static inline Raw raw(const bf16_t* p) { return *p; }
+    __device__ static inline void unpack(const Raw& t, float (&v)[1]) { v[0] = bf16_to_float(t); }
     __device__ static inline void load(const bf16_t* p, float (&v)[1]) { v[0] = bf16_to_float(*p); }
     __device__ static inline void store(bf16_t* p, const float (&v)[1]) { *p = float_to_bf16(v[0]); }
 };

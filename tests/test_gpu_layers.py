@@ -107,6 +107,33 @@ def test_batch_norm_forward_and_backward(shape, dtype, relu, res):
             assert rel_err(from_dev(d_dr2, shape), dr0 + g) < (1e-6 if dtype == D.DSP_FP32 else 4e-3)
 
 
+# (N, C, H, W), does the fp32 apply kernel merge the partial sums itself (up to 2048 partials, 1.5 MB)
+MERGE_SHAPES = [
+    ((1, 16, 1, 3), True),       # fewer rows than a workgroup holds
+    ((64, 4, 16, 16), True),     # a quarter of a channel group
+    ((7, 40, 9, 11), True),      # groups that do not divide the channels
+    ((2, 520, 6, 6), True),      # many groups, the last one short
+    ((3, 17, 20, 20), True),     # element-wise path
+    ((24, 16, 32, 32), True),    # 1.5 MB in fp32
+    ((1, 16, 157, 157), False),  # just above
+    ((16, 64, 256, 1), True),    # 64 partial rows of 32 channels
+    ((17, 64, 241, 1), False),   # 65
+]
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+@pytest.mark.parametrize("shape,merged", MERGE_SHAPES, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else "")
+def test_batch_norm_that_merges_its_partial_sums(shape, merged, dtype):
+    """The apply kernels that form the statistics of their own channels, at the edges of their range."""
+    D.dsp_profile_start(64)
+    for relu, res in ((True, False), (True, True), (False, False)):
+        test_batch_norm_forward_and_backward(shape, dtype, relu, res)
+    names = [k["name"] for k in D.dsp_profile_stop()]
+    if dtype == D.DSP_FP32:
+        assert ("bn_merge_apply_relu<fp32>" in names and "bn_bwd_merge_apply<fp32>" in names) == merged
+        assert ("bn_fwd_finalize" in names or "bn_bwd_finalize" in names) == (not merged)
+
+
 @pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
 @pytest.mark.parametrize("shape", [(3, 24, 7, 5), (4, 16, 32, 32), (2, 2048, 3, 3), (32, 64, 56, 56)], ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("res", [True, False], ids=["res", "nores"])
