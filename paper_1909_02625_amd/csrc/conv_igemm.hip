@@ -32,6 +32,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 
 constexpr int kThreads = 256;
 
@@ -237,6 +238,14 @@ constexpr uint32_t kOutOfRange = 0xfffffff0u;
 __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+// The same of a pointer and a size that are uniform but that the compiler may keep in vector registers: left there, it wraps
+// every access in a loop over the lanes.
+__device__ inline __amdgpu_buffer_rsrc_t uniform_rsrc(const void* p, uint32_t bytes)
+{
+    const uint64_t a = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return make_rsrc((const void*)(((uint64_t)hi << 32) | lo), __builtin_amdgcn_readfirstlane(bytes));
 }
 __device__ inline u32x4 load16(__amdgpu_buffer_rsrc_t r, uint32_t byte_off)
 {
@@ -634,6 +643,12 @@ __device__ inline void dma16(__amdgpu_buffer_rsrc_t r, char* lds_wave_base, uint
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)lds_wave_base, 16, (int)byte_off, 0, 0, 0);
 }
 
+// The same from byte_off + soff; soff is uniform (a lane's byte_off of kOutOfRange stays out of range)
+__device__ inline void dma16_at(__amdgpu_buffer_rsrc_t r, char* lds_wave_base, uint32_t byte_off, int soff)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)lds_wave_base, 16, (int)byte_off, soff, 0, 0);
+}
+
 template <typename TL>
 __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL::WAVES, TL::WAVES))) void conv_dma_gemm_kernel(
     const bf16_t* __restrict__ in_, const bf16_t* __restrict__ wgt, bf16_t* __restrict__ out_, GatherGeom g)
@@ -949,6 +964,343 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
             dst[1] = b;
         }
     }
+}
+
+// ---- the same contraction as one stream of k tiles over several output tiles (256 x 128 tile) -----------------------
+// A tile that has its compute unit to itself has nothing that covers the latency of its first loads and the burst of its
+// stores, 6 us of the 19 a 256 x 128 tile takes at K = 1152.  Here a workgroup walks several output tiles and the loads run on
+// across them: while the last k tiles of one are multiplied the first ones of the next are on their way, and the epilogue
+// needs neither LDS nor a barrier, so it delays nothing but its own wave.  The loader is ST k tiles ahead of the multiplication
+// and changes over to the next output tile by itself.
+// Epilogue in registers: a lane holds, for output row lane % 32 of a block, runs of four channels at 8 q + 4 (lane / 32); two
+// v_permlane32_swap per pair of runs leave each lane one run of eight, stored as 16 bytes.  The stores count in vmcnt, in
+// order, so the waits of the next ST - 2 k tiles leave them outstanding.  Column sums: the block rows in registers, 32 rows by
+// a tree of lane exchanges, the waves through LDS, in double, behind the next barrier.
+// 256 x 28x28, 128 -> 128 3x3 83 -> 75 us; 512 images 152 -> 144; 256 x 7x7, 512 -> 512 61 -> 59.6; where there is one round of
+// tiles about as before (128 x 14x14, 1024 -> 256 1x1 19.7 -> 20.1); conv4_x 80.8 -> 79.3 ms for 32 steps.  What bounds it, with
+// parts of the work left out (512 x 28x28): MFMAs alone 63 us, loads alone 100, both 112, with the LDS reads 129, with the
+// stores 148 -- the loads: a compute unit gets 50 to 60 bytes of them a nanosecond, rows of 64 bytes at most 64, rows of 128
+// at most 136 (loads alone, from L2).  The 256 x 256 tile (rows of 64 bytes in four stages, or of 128 in two) gained nothing
+// from it, tiles of 128 x 128 neither.
+template <typename TL>
+struct StreamLds {
+    static constexpr int SUMS = TL::WGM * TL::BN * 2 * (int)sizeof(float);
+    static constexpr int BYTES = TL::RING_BYTES + 2 * SUMS;
+    static_assert(TL::KG == 1 && !TL::GEN && BYTES <= 160 * 1024, "one contraction per workgroup");
+};
+struct StreamArgs {
+    int tiles, items;  // output tiles of one problem, of the launch (instances x groups x tiles)
+    int instances;
+};
+
+// Sum of COUNT values over the 32 lanes of equal lane / 32; lane l ends with the sum of value number `which`.
+template <int N, int MASK, int COUNT>
+__device__ inline void sum_lanes32(float (&a)[N], float (&b)[N], int lane, int& which)
+{
+    if constexpr (MASK < 32) {
+        const bool up = (lane & MASK) != 0;
+        constexpr int HALF = COUNT > 1 ? COUNT / 2 : 1, PATTERN = (MASK << 10) | 0x1f;
+#pragma unroll
+        for (int i = 0; i < HALF; ++i) {
+            const float ka = COUNT > 1 && up ? a[i + HALF] : a[i], sa = COUNT > 1 && !up ? a[(i + HALF) % N] : a[i];
+            const float kb = COUNT > 1 && up ? b[i + HALF] : b[i], sb = COUNT > 1 && !up ? b[(i + HALF) % N] : b[i];
+            a[i] = ka + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(sa), PATTERN));
+            b[i] = kb + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(sb), PATTERN));
+        }
+        if (COUNT > 1 && up) which += HALF;
+        sum_lanes32<N, MASK * 2, HALF>(a, b, lane, which);
+    }
+}
+
+template <typename TL>
+__global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL::WAVES, TL::WAVES))) void conv_dma_stream_kernel(
+    const bf16_t* __restrict__ in_, const bf16_t* __restrict__ wgt, bf16_t* __restrict__ out_, GatherGeom g, StreamArgs sa)
+{
+    typedef bf16_t T;
+    constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN, NKS = TL::NKS, ST = TL::STAGES, LOADS = TL::LOADS;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_m = wave / TL::WGN, wave_n = wave % TL::WGN;
+    const int tiles_n = (g.Co + BN - 1) / BN, tiles_m = sa.tiles / tiles_n;
+    // work items of this workgroup: in each round the workgroups of an XCD take consecutive ones
+    const int first = (int)xcd_tile(blockIdx.x, gridDim.x), stride = (int)gridDim.x;
+    struct Item {
+        int m0, n0, tile_m, inst, group;
+    };
+    auto item_at = [&](int it) __attribute__((always_inline)) {
+        Item r;
+        const int pass = it / sa.tiles, tile = it - pass * sa.tiles;
+        r.group = pass / sa.instances;
+        r.inst = pass - r.group * sa.instances;
+        r.tile_m = g.n_major ? tile % tiles_m : tile / tiles_n;
+        r.m0 = r.tile_m * BM;
+        r.n0 = (g.n_major ? tile / tiles_m : tile % tiles_n) * BN;
+        return r;
+    };
+
+    // Loader state of the output tile whose loads are issued: row groups as in the kernel above.  The instructions of a k tile
+    // that are no MFMA, LDS read or load are what bounds the loop, so the position in memory is kept in two parts: a lane's
+    // offset of the filter tap at hand (kOutOfRange where the tap is padding), formed anew when the tap changes, and the
+    // uniform offset within the tap's channels (within a row's filters), which the load instruction adds.
+    //   l_base, l_mask: as above; l_off: the offset to load from
+    const int lrow = lane / TL::CPR, lpos = lane % TL::CPR;
+    constexpr int A_LOADS = TL::A_INST / TL::NW;  // row group i of a wave is instruction i * NW + wave of the k tile: the first are input rows
+    static_assert(TL::A_INST % TL::NW == 0, "whole rounds of input rows");
+    uint32_t l_base[A_LOADS], l_mask[A_LOADS], l_off[LOADS];
+    const void* l_in = in_;
+    int l_item = first, l_kt = 0, l_tap = 0, l_c = 0, l_r = 0, l_s = 0;
+    const int nk = g.Kdim / TL::BK, tiles_per_tap = g.Ci / TL::BK;
+    auto set_tap = [&]() __attribute__((always_inline)) {
+        const uint32_t tap_off = (uint32_t)((l_r * g.Wi + l_s) * g.Cis) * 2u, tap_bit = 1u << l_tap;
+#pragma unroll
+        for (int i = 0; i < A_LOADS; ++i) l_off[i] = (l_mask[i] & tap_bit) ? l_base[i] + tap_off : kOutOfRange;
+    };
+    auto load_item = [&]() __attribute__((always_inline)) {
+        const bool live = l_item < sa.items && nk > 0;
+        const Item w = item_at(live ? l_item : first);
+        l_in = w.inst ? g.in1 : (const void*)in_;
+        const int in_c0 = w.group * g.Ci, out_c0 = w.group * g.Co;
+#pragma unroll
+        for (int i = 0; i < A_LOADS; ++i) {
+            const int row = (i * TL::NW + wave) * TL::RPG + lrow, m = w.m0 + row;
+            l_base[i] = 0;
+            l_mask[i] = 0;
+            if (live && m < g.M) {
+                const int t = (int)fast_div((uint32_t)m, g.wo_mul, g.wo_sh), wo = m - t * g.Wo;
+                const int n = (int)fast_div((uint32_t)t, g.ho_mul, g.ho_sh), ho = t - n * g.Ho;
+                const int th0 = ho * g.ostride - g.pad_h, tw0 = wo * g.ostride - g.pad_w;
+                const int s_lo = tw0 < 0 ? -tw0 : 0, s_hi = g.Wi - tw0 < g.S ? g.Wi - tw0 : g.S;
+                const uint32_t cols = s_hi > s_lo ? (~0u >> (32 - s_hi)) & (~0u << s_lo) : 0u;  // s_hi may be 32
+                uint32_t mask = 0;
+                for (int r = 0; r < g.R; ++r)
+                    if (th0 + r >= 0 && th0 + r < g.Hi) mask |= cols << (r * g.S);
+                l_mask[i] = mask;
+                l_base[i] = ((uint32_t)n * g.Hi * g.Wi * g.Cis + in_c0) * 2u + (uint32_t)((th0 * g.Wi + tw0) * g.Cis) * 2u;
+            }
+            l_base[i] += (uint32_t)(lpos ^ TL::swz(row)) * 16u;
+        }
+#pragma unroll
+        for (int i = A_LOADS; i < LOADS; ++i) {
+            const int row = (i * TL::NW + wave) * TL::RPG + lrow - BM, co = w.n0 + row;
+            l_off[i] = live && co < g.Co ? (uint32_t)((out_c0 + co) * g.Kdim) * 2u + (uint32_t)(lpos ^ TL::swz(row)) * 16u : kOutOfRange;
+        }
+        set_tap();
+    };
+    const uint32_t in_bytes = (uint32_t)g.N * g.Hi * g.Wi * g.Cis * 2u, w_bytes = (uint32_t)g.groups * g.Co * g.Kdim * 2u;
+    char* const l_lds = smem + wave * 1024;
+    // loads [from, to) of the wave's loads of the k tile at the loader's position (zeros behind the last item)
+    auto issue_loads = [&](int stage_off, int from, int to) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rin = uniform_rsrc(l_in, in_bytes), rw = uniform_rsrc(wgt, w_bytes);
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            if (i < from || i >= to) continue;
+            char* dst = l_lds + stage_off + i * (TL::NW * 1024);
+            if (i < A_LOADS) dma16_at(rin, dst, l_off[i], __builtin_amdgcn_readfirstlane(l_c * TL::ROWB));
+            else dma16_at(rw, dst, l_off[i], __builtin_amdgcn_readfirstlane(l_kt * TL::ROWB));
+        }
+    };
+    auto next_tile = [&]() __attribute__((always_inline)) {
+        // (readfirstlane: the compiler would keep these uniform counters in vector registers)
+        l_c = __builtin_amdgcn_readfirstlane(l_c + 1);
+        l_kt = __builtin_amdgcn_readfirstlane(l_kt + 1);
+        if (l_kt == nk) {
+            l_kt = l_tap = l_c = l_r = l_s = 0;
+            l_item = __builtin_amdgcn_readfirstlane(l_item + stride);
+            load_item();
+        } else if (l_c == tiles_per_tap) {
+            l_c = 0;
+            l_tap = __builtin_amdgcn_readfirstlane(l_tap + 1);
+            l_s = __builtin_amdgcn_readfirstlane(l_s + 1);
+            if (l_s == g.S) {
+                l_s = 0;
+                l_r = __builtin_amdgcn_readfirstlane(l_r + 1);
+            }
+            set_tap();
+        }
+    };
+
+    typename Mma<T, 32>::Acc acc[TM][TN];
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    };
+    clear();
+
+    const int frow = lane & 31, fg = lane >> 5, swl = TL::swz(frow);
+    int a_off[NKS], b_off[NKS];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+        a_off[ks] = (wave_m * TM * 32 + frow) * TL::ROWB + (((2 * ks + fg) ^ swl) << 4);
+        b_off[ks] = (BM + wave_n * TN * 32 + frow) * TL::ROWB + (((2 * ks + fg) ^ swl) << 4);
+    }
+    auto read_frags = [&](int stage_off, int ks, u32x4 (&a)[TM], u32x4 (&b)[TN]) __attribute__((always_inline)) {
+        const char* pa = smem + (stage_off + a_off[ks]);
+        const char* pb = smem + (stage_off + b_off[ks]);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) a[i] = *(const u32x4*)(pa + i * 32 * TL::ROWB);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) b[j] = *(const u32x4*)(pb + j * 32 * TL::ROWB);
+    };
+    auto mfmas = [&](const u32x4 (&a)[TM], const u32x4 (&b)[TN]) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) Mma<T, 32>::run(b[j], a[i], acc[i][j]);
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // column sums of the item before, left in LDS by its epilogue: the waves' parts added in double
+    int sums_tile = -1, sums_c0 = 0, sums_cols = 0, sums_half = 0;
+    double* sums_dst = nullptr;
+    auto flush_sums = [&]() __attribute__((always_inline)) {
+        if (sums_tile >= 0 && tid < 2 * BN && (tid >> 1) < sums_cols) {
+            const float* sred = (const float*)(smem + TL::RING_BYTES + sums_half * StreamLds<TL>::SUMS);
+            double a = 0.0;
+#pragma unroll
+            for (int w = 0; w < TL::WGM; ++w) a += (double)sred[w * 2 * BN + tid];
+            sums_dst[((int64_t)sums_tile * g.Cos + sums_c0) * 2 + tid] = a;
+        }
+        sums_tile = -1;
+    };
+    static_assert(TL::THREADS >= 2 * BN, "one thread per column sum");
+
+    constexpr int STORES = TM * TN * 2;           // stores of an epilogue, per wave
+    auto epilogue = [&](int it) __attribute__((always_inline)) {
+        const Item w = item_at(it);
+        T* out = w.inst ? (T*)g.out1 : out_;
+        double* stats = w.inst ? g.stats1 : g.stats;
+        const int out_c0 = w.group * g.Co;
+        const __amdgpu_buffer_rsrc_t rout = uniform_rsrc(out, 0x80000000u);
+        uint32_t row_off[TM];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int m = w.m0 + (wave_m * TM + i) * 32 + frow;
+            row_off[i] = m < g.M ? (uint32_t)((int)out_row(g, m) * g.Cos + out_c0) * 2u : kOutOfRange;
+        }
+        sums_half ^= 1;
+        float* sred = (float*)(smem + TL::RING_BYTES + sums_half * StreamLds<TL>::SUMS) + wave_m * 2 * BN;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int lcol = (wave_n * TN + j) * 32;
+            float s0[16], s1[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s0[e] = s1[e] = 0.f;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                if (g.accum) {
+                    u32x2 old[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int col = w.n0 + lcol + 8 * q + 4 * fg;
+                        const uint32_t off = (row_off[i] != kOutOfRange && col < g.Co) ? row_off[i] + (uint32_t)col * 2u : kOutOfRange;
+                        old[q] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rout, (int)off, 0, 0));
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            acc[i][j][4 * q + e] += __uint_as_float((e & 1) ? old[q][e >> 1] & 0xffff0000u : old[q][e >> 1] << 16);
+                }
+                uint32_t pk[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) pk[e] = pack_bf16x2(acc[i][j][2 * e], acc[i][j][2 * e + 1]);
+                if (stats)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const float v = __uint_as_float((e & 1) ? pk[e >> 1] & 0xffff0000u : pk[e >> 1] << 16);
+                        s0[e] += v;
+                        s1[e] += v * v;
+                    }
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    // runs 2p and 2p + 1: the lower half of the wave takes the first, the upper half the second
+                    const auto x = __builtin_amdgcn_permlane32_swap(pk[4 * p], pk[4 * p + 2], false, false);
+                    const auto y = __builtin_amdgcn_permlane32_swap(pk[4 * p + 1], pk[4 * p + 3], false, false);
+                    const u32x4 v = {x[0], y[0], x[1], y[1]};
+                    const int col = w.n0 + lcol + 16 * p + 8 * fg;
+                    const uint32_t off = (row_off[i] != kOutOfRange && col < g.Co) ? row_off[i] + (uint32_t)col * 2u : kOutOfRange;
+                    __builtin_amdgcn_raw_buffer_store_b128(v, rout, (int)off, 0, 0);
+                }
+            }
+            if (stats) {
+                // value number e of lane (row, fg) is column 8 (e / 4) + 4 fg + e % 4
+                int which = 0;
+                sum_lanes32<16, 1, 16>(s0, s1, lane, which);
+                const int col = lcol + 8 * (which >> 2) + 4 * fg + (which & 3);
+                if ((lane & 16) == 0) *(f32x2*)(sred + col * 2) = f32x2{s0[0], s1[0]};
+            }
+        }
+        if (stats) {
+            sums_tile = w.tile_m;
+            sums_c0 = out_c0 + w.n0;
+            sums_cols = g.Co - w.n0;
+            sums_dst = stats;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (the barriers below wait for no LDS write)
+        }
+        clear();
+    };
+
+    // Synchronisation by hand, over the k tiles of all items.  One barrier per k tile, in front of its last k step: by then every
+    // wave holds that step's operands, so the stage is free and takes the loads of tile kt + ST, and the loads of tile kt + 1
+    // have landed (each wave waits for its own), whose first operands are read behind the barrier while the last step is
+    // multiplied.  A load has ST - 1 k tiles to arrive.  The loads of a tile are dealt out over NKS k steps.
+    constexpr int AHEAD = (ST - 2) * LOADS;  // loads that may stay outstanding at the barrier
+    static_assert(AHEAD + STORES < 64 && AHEAD + LOADS < 64, "outstanding operations fit the counter");
+    load_item();
+#pragma unroll 1
+    for (int t = 0; t < ST - 1; ++t) {
+        issue_loads(t * TL::STAGE_BYTES, 0, LOADS);
+        next_tile();
+    }
+    issue_loads((ST - 1) * TL::STAGE_BYTES, 0, LOADS / NKS);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((ST - 2) * LOADS + LOADS / NKS) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    u32x4 fa[2][TM], fb[2][TN];
+    read_frags(0, 0, fa[0], fb[0]);
+    int st = 0, stl = (ST - 1) * TL::STAGE_BYTES;  // byte offsets of the stage multiplied and of the stage loaded into
+    int after = 0;  // k tiles whose loads were issued before the last epilogue's stores
+    for (int it = first; it < sa.items; it += stride) {
+        for (int kt = 0; kt < nk; ++kt) {
+            const int st1 = st == (ST - 1) * TL::STAGE_BYTES ? 0 : st + TL::STAGE_BYTES;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                if (ks + 1 < NKS) {
+                    read_frags(st, ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+                } else {
+                    if (after > 0) {
+                        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(AHEAD + STORES) : "memory");
+                        --after;
+                    } else {
+                        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(AHEAD) : "memory");
+                    }
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    read_frags(st1, 0, fa[0], fb[0]);
+                    stl = st;
+                }
+                mfmas(fa[ks & 1], fb[ks & 1]);
+                const int slot = (ks + 1) % NKS;
+                issue_loads(stl, LOADS * slot / NKS, LOADS * (slot + 1) / NKS);
+                if (slot == NKS - 1) next_tile();
+            }
+            st = st1;
+            if (kt == 0) flush_sums();
+        }
+        epilogue(it);
+        after = ST - 2;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the zero loads past the end
+    __syncthreads();
+    flush_sums();
 }
 
 // ---- bf16 3x3 / stride 1 / pad 1 convolutions with 64 channels on both sides, filters held in registers ----
@@ -2937,11 +3289,44 @@ int run_dma(GatherGeom g, const void* in, const void* w, void* out, hipStream_t 
     return DSP_OK;
 }
 
+// Workgroups: as many rounds as one workgroup per compute unit needs, the items spread evenly over them -- what is left of the
+// chip stays free for other streams' kernels.
+template <typename TL>
+int run_dma_stream(GatherGeom g, const void* in, const void* w, void* out, hipStream_t st, double flops)
+{
+    const int64_t tiles = (int64_t)ceil_div(g.M, TL::BM) * ceil_div(g.Co, TL::BN);
+    StreamArgs a;
+    a.instances = g.in1 ? 2 : 1;
+    DSP_REQUIRE(tiles > 0 && tiles * a.instances * g.groups < (1ll << 30), DSP_EINVAL, "conv: bad tile count");
+    a.tiles = (int)tiles;
+    a.items = (int)tiles * a.instances * g.groups;
+    g.n_major = (int64_t)g.Co * g.Kdim > (int64_t)g.N * g.Hi * g.Wi * g.Ci;
+    const int grid = ceil_div(a.items, ceil_div(a.items, kComputeUnits));
+    auto kern = conv_dma_stream_kernel<TL>;
+    static std::atomic<bool> attr_done{false};
+    if (!attr_done) {
+        DSP_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, StreamLds<TL>::BYTES));
+        attr_done = true;
+    }
+    static const KernelName name = [] {
+        KernelName k;
+        snprintf(k.text, sizeof(k.text), "conv_dma_gemm<bf16,BM%d,BN%d,BK%d,%dx%d waves>", TL::BM, TL::BN, TL::BK, TL::NW, TL::KG);
+        return k;
+    }();
+    {
+        ProfScope ps(name.text, flops, 0);
+        DSP_LAUNCH(ps, kern, dim3((unsigned)grid), dim3(TL::THREADS), StreamLds<TL>::BYTES, st, (const bf16_t*)in, (const bf16_t*)w,
+                   (bf16_t*)out, g, a);
+    }
+    DSP_HIP(hipGetLastError());
+    return DSP_OK;
+}
+
 int dispatch_dma(int id, const GatherGeom& g, const void* in, const void* w, void* out, hipStream_t st, double flops)
 {
     switch (id) {
     case kDmaId + 0: return run_dma<DmaTile<256, 256, 2, 4, 64, 4, 2>>(g, in, w, out, st, flops);
-    case kDmaId + 1: return run_dma<DmaTile<256, 128, 4, 2, 128, 3, 2>>(g, in, w, out, st, flops);
+    case kDmaId + 1: return run_dma_stream<DmaTile<256, 128, 4, 2, 128, 3, 2>>(g, in, w, out, st, flops);
     case kDmaId + 2: return run_dma<DmaTile<256, 128, 2, 2, 64, 3, 2>>(g, in, w, out, st, flops);
     case kDmaId + 3: return run_dma<DmaTile<128, 128, 2, 4, 64, 4, 4>>(g, in, w, out, st, flops);
     case kDmaId + 4: return run_dma<DmaTile<128, 128, 2, 4, 128, 4, 2>>(g, in, w, out, st, flops);

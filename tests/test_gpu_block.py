@@ -210,6 +210,7 @@ labels_by_batch = {}
     ("bn_probe", D.DSP_FP32, 3, {}),
     ("bn_probe", D.DSP_BF16, 3, {}),
     ("c64_probe", D.DSP_BF16, 3, {}),   # a ResNet-18 stage-1 block at a size that takes the filters-in-registers conv kernel
+    ("tiles_probe", D.DSP_BF16, 3, {}),  # convolution workgroups that walk several output tiles, of both instances of a twin launch
     ("stem_probe", D.DSP_BF16, 3, {}),  # the ImageNet stem at its real map size: its own conv kernel, batch norm folded into the pool
     ("stem_probe_wide", D.DSP_BF16, 3, {}),  # ... on a 65 x 125 map: widest row of that kernel, odd sizes, ragged last tile
     # VGG-19 with batch norm (2x2 max pools inside the blocks, 512-channel layers on 4x4 and 2x2 maps)

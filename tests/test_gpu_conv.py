@@ -115,6 +115,16 @@ def test_direct_to_lds_tiles(shape):
     test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
 
 
+def test_several_output_tiles_per_workgroup():
+    """389 tiles of 256 x 128 for 256 compute units, the last row tile and the channels ragged."""
+    D.dsp_profile_start(64)
+    try:
+        test_conv_forward_dgrad_wgrad((127, 28, 28, 128, 104, 3, 3, 1, 1), D.DSP_BF16)
+    finally:
+        launched = {k["name"] for k in D.dsp_profile_stop()}
+    assert "conv_dma_gemm<bf16,BM256,BN128,BK64,8x1 waves>" in launched, launched
+
+
 # The direct-to-LDS backward-weight tiles where they can go wrong: channels and columns that fill no tile (8 of 64, 136 of
 # 128 + 128), fewer rows than one LDS stage and than the stages in flight, a step of 64 pixels that passes several images
 # (3 x 3 maps), one that stays inside a row (a row of 70), rows dropped by the stride at an odd edge, and eight slices of the

@@ -260,6 +260,16 @@ def _c64_probe():
     return [b.layers]
 
 
+def _tiles_probe():
+    """One basic block of 128 channels (two 3x3 convolutions, identity shortcut)."""
+    b = _B()
+    a = b.conv(-1, 128, 128, 3)
+    a = b.bn(a, 128, relu=True)
+    a = b.conv(a, 128, 128, 3)
+    b.bn(a, 128, relu=True, res=-1)
+    return [b.layers]
+
+
 def _stem_probe():
     """The ImageNet stem alone (7x7 / stride-2 convolution of the 3-channel image, batch norm + ReLU, 3x3 / stride-2 max
     pool) at its real map size: large enough for the stem's own convolution kernel and for the pool kernels that fold
@@ -309,6 +319,10 @@ CONFIGS = {
     # one ragged; forward + recompute in one launch, fused batch-norm sums, accumulating backward-data)
     "c64_probe": dict(blocks=_c64_probe, input=(21, 64, 56, 56), classes=None, p=(0,), m=(1,), lr=0.01, beta=0.9,
                       wd=0.0, steps=3, seed=6, dtypes=("bf16",), grad_std=0.1, data_input=False),
+    # a batch whose twin launches have more 256-row tiles than the GPU has compute units (M = 49392 rows, 386 tiles of two
+    # instances, the last of each ragged): workgroups that walk several output tiles, with column sums and across instances
+    "tiles_probe": dict(blocks=_tiles_probe, input=(63, 128, 28, 28), classes=None, p=(0,), m=(1,), lr=0.01, beta=0.9,
+                        wd=0.0, steps=3, seed=9, dtypes=("bf16",), grad_std=0.1, data_input=False),
     # the ImageNet stem on 6 full-size images (M = 75264 output pixels of the convolution: 588 tiles of 128 for 512
     # workgroups; twin launches, fused sums, the pool with the batch norm folded in, forward and backward)
     "stem_probe": dict(blocks=_stem_probe, input=(6, 3, 224, 224), classes=None, p=(0,), m=(1,), lr=0.01, beta=0.9,
