@@ -107,6 +107,18 @@ def test_batch_norm_forward_and_backward(shape, dtype, relu, res):
             assert rel_err(from_dev(d_dr2, shape), dr0 + g) < (1e-6 if dtype == D.DSP_FP32 else 4e-3)
 
 
+# Channel vectors per row that divide a wave (1, 2, 4 .. 64 of 8, 4 or 1 channels) and the first count that does not; rows that
+# fill no trip of the summing loop.
+SUM_SHAPES = [(7, 1, 9, 9), (5, 2, 7, 7), (9, 8, 5, 5), (6, 32, 9, 11), (3, 128, 9, 13), (3, 256, 5, 7), (2, 512, 5, 9), (2, 1024, 3, 5)]
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+@pytest.mark.parametrize("shape", SUM_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_batch_norm_sums(shape, dtype):
+    for relu, res in ((True, False), (True, True), (False, False)):
+        test_batch_norm_forward_and_backward(shape, dtype, relu, res)
+
+
 # (N, C, H, W), does the fp32 apply kernel merge the partial sums itself (up to 2048 partials, 1.5 MB)
 MERGE_SHAPES = [
     ((1, 16, 1, 3), True),       # fewer rows than a workgroup holds
