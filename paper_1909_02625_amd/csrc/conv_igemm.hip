@@ -3113,12 +3113,12 @@ inline int64_t tile_count(const GatherGeom& g, int bm, int bn)
 }
 
 // The register-resident-filter kernel: fp32, 3x3, 16 gathered channels, 16 or 32 output channels, no
-// dilation, 16-byte aligned activations.  (The kernel also handles 32 gathered channels, but there
+// dilation, consecutive output rows, 16-byte aligned activations.  (The kernel also handles 32 gathered channels, but there
 // the per-wave filter load outweighs the saved LDS traffic and the tiled kernel is faster.)
 template <typename T>
 bool direct_eligible(const GatherGeom& g, const void* in, const void* out)
 {
-    return sizeof(T) == 4 && g.groups == 1 && g.R == 3 && g.S == 3 && g.idil == 1 && g.Ci == 16 && (g.Co == 16 || g.Co == 32) &&
+    return sizeof(T) == 4 && g.groups == 1 && g.R == 3 && g.S == 3 && g.idil == 1 && g.oh_mul == 0 && g.Ci == 16 && (g.Co == 16 || g.Co == 32) &&
            ((uintptr_t)in % 16) == 0 && ((uintptr_t)out % 16) == 0;
 }
 

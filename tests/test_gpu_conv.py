@@ -115,6 +115,14 @@ def test_direct_to_lds_tiles(shape):
     test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
 
 
+@pytest.mark.parametrize("dtype", [D.DSP_FP32, D.DSP_BF16], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("co", [16, 32])
+def test_backward_data_whose_parity_class_is_a_small_3x3(co, dtype):
+    """5x5 / stride 2: the class of even pixels is a 3x3 convolution of co -> 16 channels, the shape of the kernels that keep the
+    filters of such layers in registers, but its output rows lie two pixels apart."""
+    test_conv_forward_dgrad_wgrad((3, 13, 14, 16, co, 5, 5, 2, 2), dtype)
+
+
 def test_several_output_tiles_per_workgroup():
     """389 tiles of 256 x 128 for 256 compute units, the last row tile and the channels ragged."""
     D.dsp_profile_start(64)
