@@ -1930,6 +1930,142 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_f32_kernel(const floa
     }
 }
 
+// ---- bf16 3x3 convolutions with 16 or 32 channels on both sides ----------------------------------
+// The same scheme on the 16x16x32 bf16 MFMA: D[co][pixel] with the filters of all output channels (CO groups of 16) held in
+// registers and the pixels loaded straight into the operand layout -- lane (pixel p, quarter q) of a k step loads the 16 bytes
+// that are its eight k values: of 32 channels the eighth group q of one tap, of 16 channels half q % 2 of tap 2 t + q / 2, so that
+// a step takes two taps (nine make five steps; the tenth reads zeros).  No LDS, no barrier, no unpacking.  The result leaves each
+// lane with 4 consecutive output channels of one pixel: one 8-byte store.  A wave walks groups of 16 pixels with DEPTH - 1
+// groups of loads in flight.  The column sums for a following batch norm are taken of the values as stored, in double, one
+// partial row per workgroup -- the 64-row tiles left 2048 rows to merge at M = 131072.
+// Bound by the latency of its loads, with one wave per SIMD.  Against the register-staged tiles: 128 x 32x32, 16 -> 16 7.6 -> 6.2
+// us, 128 x 16x16, 32 -> 32 6.1 -> 5.1, 256 x 56x56, 32 -> 32 45.6 -> 41.0, 16 x 16x16, 32 -> 32 5.3 -> 4.7; resnet56 with
+// them 1.21 -> 1.13 ms a tick (four streams; 128 and 192 workgroups the same, 384 1.21, 512 1.23).
+template <int CI, int CO>
+__global__ __launch_bounds__(kThreads) void conv3x3_direct_bf16_kernel(const bf16_t* __restrict__ in_,
+                                                                       const bf16_t* __restrict__ wgt,
+                                                                       bf16_t* __restrict__ out_, GatherGeom g)
+{
+    constexpr int STEPS = CI == 16 ? 5 : 9, DEPTH = CI == 16 ? 4 : 2, WAVES = kThreads / 64;
+    const bf16_t* __restrict__ in = blockIdx.y ? (const bf16_t*)g.in1 : in_;
+    bf16_t* __restrict__ out = blockIdx.y ? (bf16_t*)g.out1 : out_;
+    double* stats = blockIdx.y ? g.stats1 : g.stats;
+    __shared__ double red[WAVES][CO * 16][2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, px = lane & 15, kq = lane >> 4;
+    const int groups = (g.M + 15) >> 4;
+    auto tap_of = [&](int t) { return CI == 16 ? 2 * t + (kq >> 1) : t; };
+    const int ch0 = CI == 16 ? (kq & 1) * 8 : kq * 8;
+
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(wgt, (uint32_t)(CO * 16 * 9 * CI) * 2u);
+    u32x4 wreg[STEPS][CO];
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t)
+#pragma unroll
+        for (int c = 0; c < CO; ++c)
+            wreg[t][c] = load16(rw, tap_of(t) < 9 ? (uint32_t)((c * 16 + px) * (9 * CI) + tap_of(t) * CI + ch0) * 2u : kOutOfRange);
+    const __amdgpu_buffer_rsrc_t rin = make_rsrc(in, (uint32_t)g.N * g.Hi * g.Wi * CI * 2u);
+    // this lane's tap of every step: row, column, distance from tap (0, 0)
+    int tr[STEPS], ts[STEPS];
+    uint32_t toff[STEPS];
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) {
+        tr[t] = tap_of(t) / 3;
+        ts[t] = tap_of(t) - 3 * tr[t];
+        toff[t] = (uint32_t)((tr[t] * g.Wi + ts[t]) * CI + ch0) * 2u;
+        if (tap_of(t) >= 9) tr[t] = 1 << 20;  // (never inside)
+    }
+    double s0[CO][4], s1[CO][4];
+#pragma unroll
+    for (int c = 0; c < CO; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s0[c][e] = s1[c][e] = 0.0;
+
+    // operands of pixel group grp; pixels past the end read zeros
+    auto gather = [&](u32x4 (&x)[STEPS], int grp) {
+        const int m = grp * 16 + px;
+        const bool live = m < g.M;
+        const int tq = (int)fast_div((uint32_t)m, g.wo_mul, g.wo_sh), wo = m - tq * g.Wo;
+        const int n = (int)fast_div((uint32_t)tq, g.ho_mul, g.ho_sh), ho = tq - n * g.Ho;
+        const int th0 = ho * g.ostride - g.pad_h, tw0 = wo * g.ostride - g.pad_w;
+        const uint32_t base = (uint32_t)(((n * g.Hi + th0) * g.Wi + tw0) * CI) * 2u;
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {
+            const bool ok = live && (unsigned)(th0 + tr[t]) < (unsigned)g.Hi && (unsigned)(tw0 + ts[t]) < (unsigned)g.Wi;
+            x[t] = load16(rin, ok ? base + toff[t] : kOutOfRange);
+        }
+    };
+    auto finish = [&](const u32x4 (&x)[STEPS], int grp) {
+        const int m = grp * 16 + px;
+#pragma unroll
+        for (int c = 0; c < CO; ++c) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < STEPS; ++t) Mma<bf16_t, 16>::run(wreg[t][c], x[t], acc);
+            bf16_t* dst = out + (size_t)m * (CO * 16) + c * 16 + 4 * kq;
+            if (m < g.M) {
+                if (g.accum) {
+                    float o[4];
+                    Run4<bf16_t>::unpack(*(const u32x2*)dst, o);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[e] += o[e];
+                }
+                const u32x2 v = Run4<bf16_t>::pack(acc[0], acc[1], acc[2], acc[3]);
+                *(u32x2*)dst = v;
+                if (stats) {
+                    float f[4];
+                    Run4<bf16_t>::unpack(v, f);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        s0[c][e] += (double)f[e];
+                        s1[c][e] += (double)f[e] * (double)f[e];
+                    }
+                }
+            }
+        }
+    };
+
+    const int stride_g = gridDim.x * WAVES;
+    const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
+    int grp = tile * WAVES + wave;
+    u32x4 xr[DEPTH][STEPS];
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+        if (grp + d * stride_g < groups) gather(xr[d], grp + d * stride_g);  // (wave-uniform conditions)
+    while (grp < groups) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            if (grp < groups) {
+                finish(xr[d], grp);
+                if (grp + DEPTH * stride_g < groups) gather(xr[d], grp + DEPTH * stride_g);
+            }
+            grp += stride_g;
+        }
+    }
+    if (stats) {
+#pragma unroll
+        for (int c = 0; c < CO; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                for (int off = 1; off < 16; off <<= 1) {
+                    s0[c][e] += __shfl_xor(s0[c][e], off, 64);
+                    s1[c][e] += __shfl_xor(s1[c][e], off, 64);
+                }
+                if (px == 0) {
+                    red[wave][c * 16 + 4 * kq + e][0] = s0[c][e];
+                    red[wave][c * 16 + 4 * kq + e][1] = s1[c][e];
+                }
+            }
+        __syncthreads();
+        if (tid < CO * 32) {
+            double a = 0.0;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) a += red[w][tid >> 1][tid & 1];
+            stats[(int64_t)tile * (CO * 32) + tid] = a;
+        }
+    }
+}
+
 // ---- backward-weight --------------------------------------------------------------------------
 // dw[co][j] = sum_m dy[m][co] * xcol[m][j].  Both operands are stored with m as the slow index while
 // the MFMA wants runs along m, so the loader moves E x E micro-tiles (E rows of m, one 16-byte
@@ -3112,21 +3248,23 @@ inline int64_t tile_count(const GatherGeom& g, int bm, int bn)
     return (int64_t)ceil_div(g.M, bm) * ceil_div(g.Co, bn) * g.groups;
 }
 
-// The register-resident-filter kernel: fp32, 3x3, 16 gathered channels, 16 or 32 output channels, no
-// dilation, consecutive output rows, 16-byte aligned activations.  (The kernel also handles 32 gathered channels, but there
-// the per-wave filter load outweighs the saved LDS traffic and the tiled kernel is faster.)
+// The register-resident-filter kernels: 3x3, no dilation, consecutive output rows, 16-byte aligned tensors; fp32 with 16
+// gathered channels and 16 or 32 output channels (the kernel also handles 32 gathered channels, but there the per-wave filter
+// load outweighs the saved LDS traffic and the tiled kernel is faster), bf16 with 16 or 32 on both sides.
 template <typename T>
-bool direct_eligible(const GatherGeom& g, const void* in, const void* out)
+bool direct_eligible(const GatherGeom& g, const void* in, const void* out, const void* w = nullptr)
 {
-    return sizeof(T) == 4 && g.groups == 1 && g.R == 3 && g.S == 3 && g.idil == 1 && g.oh_mul == 0 && g.Ci == 16 && (g.Co == 16 || g.Co == 32) &&
-           ((uintptr_t)in % 16) == 0 && ((uintptr_t)out % 16) == 0;
+    const bool ci = g.Ci == 16 || (sizeof(T) == 2 && g.Ci == 32);
+    return g.groups == 1 && g.R == 3 && g.S == 3 && g.idil == 1 && g.oh_mul == 0 && ci && (g.Co == 16 || g.Co == 32) &&
+           ((uintptr_t)in % 16) == 0 && ((uintptr_t)out % 16) == 0 && (sizeof(T) == 4 || ((uintptr_t)w % 16) == 0);
 }
 
-// Workgroups of the direct kernel: one per compute unit unless there are fewer pixel groups (measured in the
-// three-stream pipeline: 256 beats 128, 192, 384, 512 and 1024).
-inline int direct_grid(const GatherGeom& g)
+// Workgroups of the direct kernels: one per compute unit unless there are fewer pixel groups (measured in pipelines of three
+// and four streams: in fp32 256 beats 128, 192, 384, 512 and 1024, in bf16 384 and 512).
+template <typename T>
+int direct_grid(const GatherGeom& g)
 {
-    const int per_block = 4 / (g.Co / 16);
+    const int per_block = sizeof(T) == 2 ? 4 : 4 / (g.Co / 16);
     const int blocks = ceil_div(ceil_div(g.M, 16), per_block);
     return blocks < 256 ? blocks : 256;
 }
@@ -3394,19 +3532,25 @@ template <typename T>
 int dispatch_gather(GatherGeom g, bool accum, const void* in, const void* w, void* out, hipStream_t st, double flops)
 {
     constexpr int E = 16 / (int)sizeof(T);
-    if (direct_eligible<T>(g, in, out)) {
+    if (direct_eligible<T>(g, in, out, w)) {
         g.accum = accum ? 1 : 0;
-        const dim3 grid(direct_grid(g), g.in1 ? 2 : 1);
-        ProfScope ps(g.Ci == 16 ? "conv3x3_direct<fp32,ci16>" : "conv3x3_direct<fp32,ci32>", flops, 0);
-        if (g.Ci == 16)
+        const dim3 grid(direct_grid<T>(g), g.in1 ? 2 : 1);
+        if constexpr (sizeof(T) == 2) {
+            ProfScope ps(g.Ci == 16 ? "conv3x3_direct<bf16,ci16>" : "conv3x3_direct<bf16,ci32>", flops, 0);
+            auto kern = g.Ci == 16 ? (g.Co == 16 ? conv3x3_direct_bf16_kernel<16, 1> : conv3x3_direct_bf16_kernel<16, 2>)
+                                   : (g.Co == 16 ? conv3x3_direct_bf16_kernel<32, 1> : conv3x3_direct_bf16_kernel<32, 2>);
+            DSP_LAUNCH(ps, kern, grid, dim3(kThreads), 0, st, (const bf16_t*)in, (const bf16_t*)w, (bf16_t*)out, g);
+        } else {
+            ProfScope ps("conv3x3_direct<fp32,ci16>", flops, 0);
             DSP_LAUNCH(ps, conv3x3_direct_f32_kernel<1>, grid, dim3(kThreads), 0, st, (const float*)in, (const float*)w,
                        (float*)out, g);
-        else
-            DSP_LAUNCH(ps, conv3x3_direct_f32_kernel<2>, grid, dim3(kThreads), 0, st, (const float*)in, (const float*)w,
-                       (float*)out, g);
+        }
         DSP_HIP(hipGetLastError());
         return DSP_OK;
     }
+    // (partial rows are planned for aligned tensors)
+    DSP_REQUIRE(g.stats == nullptr || !direct_eligible<T>(g, nullptr, nullptr), DSP_EINVAL,
+                "conv forward with column sums: x, w and y must be 16-byte aligned");
     constexpr int KB = 128;  // bytes of k per LDS row of the large tiles: 64 bf16 / 32 floats
     // 16-byte gathers need channel runs of E elements and 16-byte aligned bases; the per-row tap masks
     // hold up to 64 taps (larger filters, and dilated gathers of more than 32 taps, take the generic path)
@@ -3864,7 +4008,8 @@ static GatherGeom forward_geom(const ConvShape& c, bool pair)
 int conv_forward_row_tiles(int dtype, const ConvShape& c, bool pair)
 {
     const GatherGeom g = forward_geom(c, pair);
-    if (dtype == DSP_FP32 && direct_eligible<float>(g, nullptr, nullptr)) return direct_grid(g);
+    if (dtype == DSP_FP32 && direct_eligible<float>(g, nullptr, nullptr)) return direct_grid<float>(g);
+    if (dtype == DSP_BF16 && direct_eligible<bf16_t>(g, nullptr, nullptr)) return direct_grid<bf16_t>(g);
     int bm;
     if (dtype == DSP_BF16) {
         const int id = select_gather_tile<bf16_t>(g, &bm);
@@ -3893,10 +4038,6 @@ int launch_conv_forward(int dtype, const ConvShape& c, const void* x, const void
         g.out1 = twin->y;
         g.stats1 = twin->column_sums;
     }
-    if (column_sums && dtype == DSP_FP32)
-        // the number of row tiles the caller sized column_sums for assumes aligned tensors
-        DSP_REQUIRE(direct_eligible<float>(g, nullptr, nullptr) == direct_eligible<float>(g, x, y), DSP_EINVAL,
-                    "conv forward with column sums: x and y must be 16-byte aligned");
     const double flops = 2.0 * conv_macs(c) * (twin ? 2 : 1);
     return dtype == DSP_BF16 ? dispatch_gather<bf16_t>(g, false, x, w, y, st, flops)
                              : dispatch_gather<float>(g, false, x, w, y, st, flops);

@@ -115,6 +115,29 @@ def test_direct_to_lds_tiles(shape):
     test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
 
 
+# The bf16 kernel that keeps the filters of 16- and 32-channel 3x3 layers in registers: fewer pixels than one group of 16, a
+# ragged last group, all pairs of channel counts, stride 2, no padding, several groups per wave.
+SMALL_3X3 = [
+    (1, 3, 3, 16, 16, 3, 3, 1, 1),
+    (1, 3, 3, 32, 32, 3, 3, 1, 0),
+    (2, 7, 9, 16, 32, 3, 3, 1, 1),
+    (2, 7, 9, 32, 16, 3, 3, 2, 1),
+    (5, 8, 6, 32, 32, 3, 3, 2, 0),
+    (41, 21, 23, 32, 32, 3, 3, 1, 1),
+    (37, 29, 31, 16, 32, 3, 3, 1, 2),
+]
+
+
+@pytest.mark.parametrize("shape", SMALL_3X3, ids=lambda s: "x".join(map(str, s)))
+def test_filters_in_registers_16_and_32_channels(shape):
+    D.dsp_profile_start(64)
+    try:
+        test_conv_forward_dgrad_wgrad(shape, D.DSP_BF16)
+    finally:
+        launched = {k["name"] for k in D.dsp_profile_stop()}
+    assert "conv3x3_direct<bf16,ci%d>" % shape[3] in launched, launched
+
+
 @pytest.mark.parametrize("dtype", [D.DSP_FP32, D.DSP_BF16], ids=["fp32", "bf16"])
 @pytest.mark.parametrize("co", [16, 32])
 def test_backward_data_whose_parity_class_is_a_small_3x3(co, dtype):
