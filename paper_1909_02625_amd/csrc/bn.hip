@@ -95,15 +95,12 @@ __device__ inline void reduce_wave(double (&s0)[VW], double (&s1)[VW], double (*
 // serves the others takes a barrier and 2 VW double additions in LDS per level, a third of the launch on small maps.  Together
 // with loads that stay packed until they are used (126 instead of 177 registers, four waves per SIMD instead of two or three),
 // backward sums with sign bytes: 131072 x 16 bf16 8.9 -> 5.5 us, 12544 x 256 8.2 -> 6.7, 200704 x 128 23.8 -> 18.4 (5.6 TB/s).
-// EXCHANGE (exchanges_lanes) is a template parameter: the code of the one form between the loop and the other's cost a launch of
-// a few microseconds 0.5 us of instruction fetches.
-inline bool exchanges_lanes(const RowLayout& L) { return L.cvb <= 64 && (L.cvb & (L.cvb - 1)) == 0; }
-template <int VW, bool EXCHANGE>
+template <int VW>
 __device__ inline void combine_row_lanes(double (&s0)[VW], double (&s1)[VW], double (&red)[VW][kThreads][2],
                                          bool active, int rlane, const RowLayout& L, double* __restrict__ part_row, int c0)
 {
     const int tid = threadIdx.x;
-    if constexpr (EXCHANGE) {  // (every thread has a row lane, and one workgroup column holds all channels)
+    if (L.cvb <= 64 && (L.cvb & (L.cvb - 1)) == 0) {  // (then every thread has a row lane, and one workgroup column holds all channels)
         const int C = L.cvb * VW;
         double(*sums)[2] = &red[0][0];
         double(*mine)[2] = sums + (tid >> 6) * C;
@@ -170,7 +167,7 @@ struct AddOut {
     const T* b1;   // second instance: the other operand and the sum
     T* out1;
 };
-template <typename T, int VW, int MODE, int RM, bool EXCHANGE>
+template <typename T, int VW, int MODE, int RM>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RM == 1 ? 3 : 4))) void bn_sums_kernel(const T* __restrict__ x, const T* __restrict__ dy,
                                                            const T* __restrict__ y, const float* __restrict__ mean,
                                                            const float* __restrict__ invstd, double* __restrict__ part,
@@ -255,7 +252,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RM == 
             }
         }
     }
-    combine_row_lanes<VW, EXCHANGE>(s0, s1, red, active, rlane, L, part + (int64_t)blockIdx.x * C * 2, c0);
+    combine_row_lanes<VW>(s0, s1, red, active, rlane, L, part + (int64_t)blockIdx.x * C * 2, c0);
 }
 
 // Merging the partials.  The partials of a conv epilogue can be thousands of rows (one per row tile), so a
@@ -828,7 +825,6 @@ __device__ inline void pool_cell_grad(const PoolCells& p, int n, int a, int b, i
 }
 
 // s0 = sum dz, s1 = sum dz * xhat over the cells of a workgroup (thread = channel vector tid % cv, cell lane tid / cv)
-template <bool EXCHANGE>
 __global__ __launch_bounds__(kThreads) void bn_pool_bwd_reduce_kernel(const bf16_t* __restrict__ x, PoolCells p,
                                                                       const float* __restrict__ mean,
                                                                       const float* __restrict__ invstd,
@@ -875,7 +871,7 @@ __global__ __launch_bounds__(kThreads) void bn_pool_bwd_reduce_kernel(const bf16
                     s1[i] += (double)(dz * ((xv[q][i] - mu[i]) * is[i]));
                 }
         }
-    combine_row_lanes<8, EXCHANGE>(s0, s1, red, active, clane, L, part + (int64_t)blockIdx.x * C * 2, c0);
+    combine_row_lanes<8>(s0, s1, red, active, clane, L, part + (int64_t)blockIdx.x * C * 2, c0);
 }
 
 // dx = [dx_prev +] c1*dz - c2*x + c0 for the four pixels of a cell; item i = (cell i / cv, channel vector i % cv)
@@ -984,7 +980,7 @@ int bn_forward_t(const void* x, const void* res, void* y, const float* gamma, co
         nblk = presummed;
     } else {
         ProfScope ps(sizeof(T) == 2 ? "bn_stats<bf16>" : "bn_stats<fp32>", tensor_bytes, 1);
-        DSP_LAUNCH(ps, (exchanges_lanes(L) ? bn_sums_kernel<T, VW, 0, 0, true> : bn_sums_kernel<T, VW, 0, 0, false>), grid, dim3(kThreads), 0, st, (const T*)x, (const T*)nullptr,
+        DSP_LAUNCH(ps, (bn_sums_kernel<T, VW, 0, 0>), grid, dim3(kThreads), 0, st, (const T*)x, (const T*)nullptr,
                    (const T*)nullptr, (const float*)nullptr, (const float*)nullptr, buf.partial, M, C, L, rows,
                    (const T*)(tw ? tw->x : nullptr), tw ? tw->buf.partial : nullptr, AddOut<T>{}, (const float*)nullptr);
     }
@@ -1043,7 +1039,7 @@ int bn_backward_t(const void* dy, const void* x, const void* y, void* dx, void* 
     const double tensor_bytes = (double)M * C * sizeof(T);
     {
         ProfScope ps(sizeof(T) == 2 ? "bn_bwd_reduce<bf16>" : "bn_bwd_reduce<fp32>", tensor_bytes * (RM == 1 ? 3 : 2) + (RM == 3 ? tensor_bytes / (VW * sizeof(T)) : 0.0), 1);
-        DSP_LAUNCH(ps, (exchanges_lanes(L) ? bn_sums_kernel<T, VW, 1, RM, true> : bn_sums_kernel<T, VW, 1, RM, false>), grid, dim3(kThreads), 0, st, (const T*)x, (const T*)dy,
+        DSP_LAUNCH(ps, (bn_sums_kernel<T, VW, 1, RM>), grid, dim3(kThreads), 0, st, (const T*)x, (const T*)dy,
                    (const T*)y, (const float*)buf.mean, (const float*)buf.invstd, buf.partial, M, C, L, rows,
                    (const T*)nullptr, (double*)nullptr, AddOut<T>{}, fcoef);
     }
@@ -1105,7 +1101,7 @@ int add_stats_t(const void* a, const void* b, void* y, int64_t M, int C, double*
     const unsigned ni = tw ? 2 : 1;
     const dim3 grid(nblk, ceil_div(L.cv, L.cvb), ni);
     ProfScope ps("add_fwd_stats", (double)M * C * sizeof(T) * 3.0 * ni, 1);
-    DSP_LAUNCH(ps, (exchanges_lanes(L) ? bn_sums_kernel<T, VW, 2, 0, true> : bn_sums_kernel<T, VW, 2, 0, false>), grid, dim3(kThreads), 0, st, (const T*)a, (const T*)b, (const T*)nullptr,
+    DSP_LAUNCH(ps, (bn_sums_kernel<T, VW, 2, 0>), grid, dim3(kThreads), 0, st, (const T*)a, (const T*)b, (const T*)nullptr,
                (const float*)nullptr, (const float*)nullptr, partial, M, C, L, rows, (const T*)(tw ? tw->a : nullptr),
                tw ? tw->partial : nullptr, (AddOut<T>{(T*)y, (const T*)(tw ? tw->b : nullptr), (T*)(tw ? tw->y : nullptr)}),
                (const float*)nullptr);
@@ -1232,7 +1228,7 @@ static int bn_pool_backward(const PoolGrad& pg, const void* x, void* dx, bool xa
     const double tensor_bytes = (double)M * C * 2.0, pool_bytes = (double)cells * C * 3.0;
     {
         ProfScope ps("bn_pool_bwd_reduce<bf16>", tensor_bytes + pool_bytes, 1);
-        DSP_LAUNCH(ps, (exchanges_lanes(L) ? bn_pool_bwd_reduce_kernel<true> : bn_pool_bwd_reduce_kernel<false>), dim3(nblk, ceil_div(L.cv, L.cvb)), dim3(kThreads), 0, st, (const bf16_t*)x, p,
+        DSP_LAUNCH(ps, bn_pool_bwd_reduce_kernel, dim3(nblk, ceil_div(L.cv, L.cvb)), dim3(kThreads), 0, st, (const bf16_t*)x, p,
                    (const float*)buf.mean, (const float*)buf.invstd, fcoef, buf.partial, (uint32_t)cells, C, L, cells_per_block);
     }
     {
