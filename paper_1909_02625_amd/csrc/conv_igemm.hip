@@ -32,7 +32,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) double f64x2;
 
 constexpr int kThreads = 256;
 
@@ -975,7 +975,8 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
 // Epilogue in registers: a lane holds, for output row lane % 32 of a block, runs of four channels at 8 q + 4 (lane / 32); two
 // v_permlane32_swap per pair of runs leave each lane one run of eight, stored as 16 bytes.  The stores count in vmcnt, in
 // order, so the waits of the next ST - 2 k tiles leave them outstanding.  Column sums: the block rows in registers, 32 rows by
-// a tree of lane exchanges, the waves through LDS, in double, behind the next barrier.
+// a tree of lane exchanges, the waves through LDS, behind the next barrier; in fp32 up to 16 rows, as in the kernel above (its 256
+// rows are dealt out to 16 threads a column), in double from there.
 // 256 x 28x28, 128 -> 128 3x3 83 -> 75 us; 512 images 152 -> 144; 256 x 7x7, 512 -> 512 61 -> 59.6; where there is one round of
 // tiles about as before (128 x 14x14, 1024 -> 256 1x1 19.7 -> 20.1); conv4_x 80.8 -> 79.3 ms for 32 steps.  What bounds it, with
 // parts of the work left out (512 x 28x28): MFMAs alone 63 us, loads alone 100, both 112, with the LDS reads 129, with the
@@ -984,32 +985,55 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
 // from it, tiles of 128 x 128 neither.
 template <typename TL>
 struct StreamLds {
-    static constexpr int SUMS = TL::WGM * TL::BN * 2 * (int)sizeof(float);
+    static constexpr int SUMS = TL::WGM * TL::BN * 2 * (int)sizeof(double);
     static constexpr int BYTES = TL::RING_BYTES + 2 * SUMS;
-    static_assert(TL::KG == 1 && !TL::GEN && BYTES <= 160 * 1024, "one contraction per workgroup");
+    static_assert(TL::KG == 1 && !TL::GEN && TL::TM == 2 && BYTES <= 160 * 1024, "one contraction per workgroup; sixteen rows per float sum");
 };
 struct StreamArgs {
     int tiles, items;  // output tiles of one problem, of the launch (instances x groups x tiles)
     int instances;
 };
 
-// Sum of COUNT values over the 32 lanes of equal lane / 32; lane l ends with the sum of value number `which`.
-template <int N, int MASK, int COUNT>
-__device__ inline void sum_lanes32(float (&a)[N], float (&b)[N], int lane, int& which)
+// Column sums over the 32 lanes of equal lane / 32.  Each lane brings COUNT values (powers of two: `which` counts up to the
+// number of the one it ends with); an exchange hands half of them to the lane across.
+template <int MASK>
+__device__ inline float lane_across(float v)
 {
-    if constexpr (MASK < 32) {
-        const bool up = (lane & MASK) != 0;
-        constexpr int HALF = COUNT > 1 ? COUNT / 2 : 1, PATTERN = (MASK << 10) | 0x1f;
+    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), (MASK << 10) | 0x1f));
+}
+template <int MASK>
+__device__ inline double lane_across(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_ds_swizzle((int)(uint32_t)b, (MASK << 10) | 0x1f);
+    const uint32_t hi = __builtin_amdgcn_ds_swizzle((int)(uint32_t)(b >> 32), (MASK << 10) | 0x1f);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int MASK, int COUNT, typename F, int N>
+__device__ inline void sum_lanes_step(F (&a)[N], F (&b)[N], int lane, int& which)
+{
+    const bool up = (lane & MASK) != 0;
+    constexpr int HALF = COUNT > 1 ? COUNT / 2 : 1;
 #pragma unroll
-        for (int i = 0; i < HALF; ++i) {
-            const float ka = COUNT > 1 && up ? a[i + HALF] : a[i], sa = COUNT > 1 && !up ? a[(i + HALF) % N] : a[i];
-            const float kb = COUNT > 1 && up ? b[i + HALF] : b[i], sb = COUNT > 1 && !up ? b[(i + HALF) % N] : b[i];
-            a[i] = ka + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(sa), PATTERN));
-            b[i] = kb + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(sb), PATTERN));
-        }
-        if (COUNT > 1 && up) which += HALF;
-        sum_lanes32<N, MASK * 2, HALF>(a, b, lane, which);
+    for (int i = 0; i < HALF; ++i) {
+        const F ka = COUNT > 1 && up ? a[i + HALF] : a[i], sa = COUNT > 1 && !up ? a[(i + HALF) % N] : a[i];
+        const F kb = COUNT > 1 && up ? b[i + HALF] : b[i], sb = COUNT > 1 && !up ? b[(i + HALF) % N] : b[i];
+        a[i] = ka + lane_across<MASK>(sa);
+        b[i] = kb + lane_across<MASK>(sb);
     }
+    if (COUNT > 1 && up) which += HALF;
+}
+// Sixteen values, each of two rows: a float holds the sum of at most 16 rows (eight lanes), the four sums of those are in double.
+__device__ inline void sum_lanes32(float (&a)[16], float (&b)[16], int lane, int& which, double& sa, double& sb)
+{
+    sum_lanes_step<1, 16>(a, b, lane, which);
+    sum_lanes_step<2, 8>(a, b, lane, which);
+    sum_lanes_step<4, 4>(a, b, lane, which);
+    double da[2] = {(double)a[0], (double)a[1]}, db[2] = {(double)b[0], (double)b[1]};
+    sum_lanes_step<8, 2>(da, db, lane, which);
+    sum_lanes_step<16, 1>(da, db, lane, which);
+    sa = da[0];
+    sb = db[0];
 }
 
 template <typename TL>
@@ -1162,10 +1186,10 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
     double* sums_dst = nullptr;
     auto flush_sums = [&]() __attribute__((always_inline)) {
         if (sums_tile >= 0 && tid < 2 * BN && (tid >> 1) < sums_cols) {
-            const float* sred = (const float*)(smem + TL::RING_BYTES + sums_half * StreamLds<TL>::SUMS);
+            const double* sred = (const double*)(smem + TL::RING_BYTES + sums_half * StreamLds<TL>::SUMS);
             double a = 0.0;
 #pragma unroll
-            for (int w = 0; w < TL::WGM; ++w) a += (double)sred[w * 2 * BN + tid];
+            for (int w = 0; w < TL::WGM; ++w) a += sred[w * 2 * BN + tid];
             sums_dst[((int64_t)sums_tile * g.Cos + sums_c0) * 2 + tid] = a;
         }
         sums_tile = -1;
@@ -1186,7 +1210,7 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
             row_off[i] = m < g.M ? (uint32_t)((int)out_row(g, m) * g.Cos + out_c0) * 2u : kOutOfRange;
         }
         sums_half ^= 1;
-        float* sred = (float*)(smem + TL::RING_BYTES + sums_half * StreamLds<TL>::SUMS) + wave_m * 2 * BN;
+        double* sred = (double*)(smem + TL::RING_BYTES + sums_half * StreamLds<TL>::SUMS) + wave_m * 2 * BN;
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int lcol = (wave_n * TN + j) * 32;
@@ -1233,9 +1257,10 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
             if (stats) {
                 // value number e of lane (row, fg) is column 8 (e / 4) + 4 fg + e % 4
                 int which = 0;
-                sum_lanes32<16, 1, 16>(s0, s1, lane, which);
+                double sa, sb;
+                sum_lanes32(s0, s1, lane, which, sa, sb);
                 const int col = lcol + 8 * (which >> 2) + 4 * fg + (which & 3);
-                if ((lane & 16) == 0) *(f32x2*)(sred + col * 2) = f32x2{s0[0], s1[0]};
+                if ((lane & 16) == 0) *(f64x2*)(sred + col * 2) = f64x2{sa, sb};
             }
         }
         if (stats) {

@@ -300,6 +300,42 @@ def test_parameters_read_by_several_threads(cin, width):
         D.dsp_block_destroy(block)
 
 
+def test_column_sums_of_few_rows_per_float():
+    """Statistics of columns whose mean is sixteen times their deviation, behind the convolution kernel that walks several output
+    tiles.  One row of every 64 holds 127.5 and the others 258: the squares of 16 rows add up exactly in fp32, those of 64 lose
+    a quarter, which the cancellation in E[y^2] - mean^2 makes 7.5e-6 of 1 / std.  dgamma = sum dz (y - mean) / std over the
+    rows with 127.5 (dz = 1 there, 0 elsewhere) is 1 / std up to a rounding of 1 / std, of y - mean and of their product, 2^-24
+    each, of mean (2^-23 of y - mean) and of the result."""
+    n, hw, c = 168, 28, 128
+    layers = [dict(op="conv", cin=c, cout=c, r=3, s=3, stride=1, pad=1, **{"in": -1}),
+              dict(op="bn", c=c, relu=False, res=None, **{"in": 0})]
+    w = np.zeros((c, c, 3, 3), np.float32)  # y = x
+    w[np.arange(c), np.arange(c), 1, 1] = 1.0
+    desc, keep = D.make_block_desc(layers, (n, c, hw, hw), D.DSP_BF16, 0, 1, 0, needs_input_grad=False)
+    block = D.dsp_block_init(desc, np.concatenate([w.ravel(), np.ones(c, np.float32), np.zeros(c, np.float32)]))
+    try:
+        m = n * hw * hw
+        special = (torch.arange(m, device="cuda")[:, None] - torch.arange(c, device="cuda")[None, :]) % 64 == 0
+        d_x = torch.where(special, 127.5, 258.0).to(torch.bfloat16)
+        d_grad = special.to(torch.bfloat16)
+        d_out = torch.empty_like(d_x)
+        torch.cuda.synchronize()
+        D.dsp_profile_start(64)
+        try:
+            D.dsp_block_forward(block, 0, d_x, d_out)
+            D.dsp_block_recompute_backward(block, 0, d_grad, None)
+            torch.cuda.synchronize()
+        finally:
+            launched = {k["name"] for k in D.dsp_profile_stop()}
+        assert "conv_dma_gemm<bf16,BM256,BN128,BK64,8x1 waves>" in launched, launched
+        dgamma = D.dsp_block_get_grads(block)[w.size:w.size + c].astype(np.float64)
+    finally:
+        D.dsp_block_destroy(block)
+    mean, sq = (63 * 258.0 + 127.5) / 64, (63 * 258.0**2 + 127.5**2) / 64
+    want = m / 64 * (127.5 - mean) / np.sqrt(sq - mean**2 + 1e-5)
+    assert np.abs(dgamma / want - 1.0).max() < 6 * 2.0**-24
+
+
 def _free_running(cfg, params, rng, dtype, ticks, p=None, m=None, rtol=1e-3):
     K = cfg["K"]
     p = cfg["p"] if p is None else p
