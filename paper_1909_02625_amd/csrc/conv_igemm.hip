@@ -3473,7 +3473,7 @@ int run_dma_stream(GatherGeom g, const void* in, const void* w, void* out, hipSt
     }
     static const KernelName name = [] {
         KernelName k;
-        snprintf(k.text, sizeof(k.text), "conv_dma_gemm<bf16,BM%d,BN%d,BK%d,%dx%d waves>", TL::BM, TL::BN, TL::BK, TL::NW, TL::KG);
+        snprintf(k.text, sizeof(k.text), "conv_dma_stream<bf16,BM%d,BN%d,BK%d,%d waves>", TL::BM, TL::BN, TL::BK, TL::NW);
         return k;
     }();
     {

@@ -327,7 +327,7 @@ def test_column_sums_of_few_rows_per_float():
             torch.cuda.synchronize()
         finally:
             launched = {k["name"] for k in D.dsp_profile_stop()}
-        assert "conv_dma_gemm<bf16,BM256,BN128,BK64,8x1 waves>" in launched, launched
+        assert "conv_dma_stream<bf16,BM256,BN128,BK64,8 waves>" in launched, launched
         dgamma = D.dsp_block_get_grads(block)[w.size:w.size + c].astype(np.float64)
     finally:
         D.dsp_block_destroy(block)
