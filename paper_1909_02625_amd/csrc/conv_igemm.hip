@@ -977,8 +977,8 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
 // order, so the waits of the next ST - 2 k tiles leave them outstanding.  Column sums: the block rows in registers, 32 rows by
 // a tree of lane exchanges, the waves through LDS, behind the next barrier; in fp32 up to 16 rows, as in the kernel above (its 256
 // rows are dealt out to 16 threads a column), in double from there.
-// 256 x 28x28, 128 -> 128 3x3 83 -> 75 us; 512 images 152 -> 144; 256 x 7x7, 512 -> 512 61 -> 59.6; where there is one round of
-// tiles about as before (128 x 14x14, 1024 -> 256 1x1 19.7 -> 20.1); conv4_x 80.8 -> 79.3 ms for 32 steps.  What bounds it, with
+// 256 x 28x28, 128 -> 128 3x3 83 -> 75 us; 512 images 152 -> 144; 256 x 7x7, 512 -> 512 61 -> 59.6 (single rounds: see streams());
+// conv4_x 80.8 -> 79.3 ms for 32 steps.  What bounds it, with
 // parts of the work left out (512 x 28x28): MFMAs alone 63 us, loads alone 100, both 112, with the LDS reads 129, with the
 // stores 148 -- the loads: a compute unit gets 50 to 60 bytes of them a nanosecond, rows of 64 bytes at most 64, rows of 128
 // at most 136 (loads alone, from L2).  The 256 x 256 tile (rows of 64 bytes in four stages, or of 128 in two) gained nothing
@@ -3452,6 +3452,19 @@ int run_dma(GatherGeom g, const void* in, const void* w, void* out, hipStream_t 
     return DSP_OK;
 }
 
+// The stream pays where it has loads to hide: several output tiles per workgroup, or one of more than nine k tiles of 64.  Times
+// with filters from memory, as a network finds them (input just written), one tile per workgroup -> stream:
+//   one round, K = 256 .. 576: nine layers 0.92-1.04x, mean 0.97 (K = 320 12.7 -> 13.8 us, 1x1 K = 576 18.7 -> 17.9); with the
+//   filters still in the caches from the launch before 0.85-1.0x
+//   one round, K = 640 and above: 1.03-1.43x (K = 768 22.4 -> 19.9, 1152 25.7 -> 22.6, 3456 61.2 -> 47.7); from the caches 0.87-1.07x
+//   two rounds 1.03-1.12x; from the caches 0.95-1.18x, three rounds and more 1.02-1.20x
+// conv4_x (196 tiles, K = 1024 and 2304) is 2.4 % slower with its single rounds off the stream.
+template <typename TL>
+bool streams(const GatherGeom& g)
+{
+    return tile_count(g, TL::BM, TL::BN) * (g.in1 ? 2 : 1) > kComputeUnits || g.Kdim > 9 * 64;
+}
+
 // Workgroups: as many rounds as one workgroup per compute unit needs, the items spread evenly over them -- what is left of the
 // chip stays free for other streams' kernels.
 template <typename TL>
@@ -3489,7 +3502,10 @@ int dispatch_dma(int id, const GatherGeom& g, const void* in, const void* w, voi
 {
     switch (id) {
     case kDmaId + 0: return run_dma<DmaTile<256, 256, 2, 4, 64, 4, 2>>(g, in, w, out, st, flops);
-    case kDmaId + 1: return run_dma_stream<DmaTile<256, 128, 4, 2, 128, 3, 2>>(g, in, w, out, st, flops);
+    case kDmaId + 1: {
+        typedef DmaTile<256, 128, 4, 2, 128, 3, 2> TL;
+        return streams<TL>(g) ? run_dma_stream<TL>(g, in, w, out, st, flops) : run_dma<TL>(g, in, w, out, st, flops);
+    }
     case kDmaId + 2: return run_dma<DmaTile<256, 128, 2, 2, 64, 3, 2>>(g, in, w, out, st, flops);
     case kDmaId + 3: return run_dma<DmaTile<128, 128, 2, 4, 64, 4, 4>>(g, in, w, out, st, flops);
     case kDmaId + 4: return run_dma<DmaTile<128, 128, 2, 4, 128, 4, 2>>(g, in, w, out, st, flops);

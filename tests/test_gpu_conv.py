@@ -182,7 +182,9 @@ def test_direct_to_lds_backward_weight(shape):
 # in columns).  The tiles are chosen by a model of their durations, so a change of that model may ask for other shapes here.
 EVERY_TILE = [
     ("conv_dma_gemm<bf16,BM256,BN256,BK32,8x1 waves>", (90, 35, 14, 64, 144, 1, 1, 1, 0)),
-    ("conv_dma_stream<bf16,BM256,BN128,BK64,8 waves>", (36, 37, 25, 256, 72, 1, 1, 1, 0)),
+    ("conv_dma_gemm<bf16,BM256,BN128,BK64,8x1 waves>", (36, 37, 25, 256, 72, 1, 1, 1, 0)),       # one round, four k tiles
+    ("conv_dma_stream<bf16,BM256,BN128,BK64,8 waves>", (36, 37, 25, 640, 72, 1, 1, 1, 0)),       # one round, ten
+    ("conv_dma_stream<bf16,BM256,BN128,BK64,8 waves>", (180, 30, 31, 448, 72, 1, 1, 1, 0)),      # three rounds, seven
     ("conv_dma_gemm<bf16,BM256,BN128,BK32,4x1 waves>", (108, 25, 37, 64, 80, 1, 1, 1, 0)),
     ("conv_dma_gemm<bf16,BM128,BN128,BK32,8x1 waves>", (18, 34, 27, 64, 72, 1, 1, 1, 0)),
     ("conv_dma_gemm<bf16,BM128,BN128,BK64,8x1 waves>", (27, 37, 17, 512, 72, 1, 1, 1, 0)),
