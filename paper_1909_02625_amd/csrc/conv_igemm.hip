@@ -1999,11 +1999,9 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_bf16_kernel(const bf1
         toff[t] = (uint32_t)((tr[t] * g.Wi + ts[t]) * CI + ch0) * 2u;
         if (tap_of(t) >= 9) tr[t] = 1 << 20;  // (never inside)
     }
-    double s0[CO][4], s1[CO][4];
+    double s0[CO * 4], s1[CO * 4];
 #pragma unroll
-    for (int c = 0; c < CO; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s0[c][e] = s1[c][e] = 0.0;
+    for (int e = 0; e < CO * 4; ++e) s0[e] = s1[e] = 0.0;
 
     // operands of pixel group grp; pixels past the end read zeros
     auto gather = [&](u32x4 (&x)[STEPS], int grp) {
@@ -2041,8 +2039,8 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_bf16_kernel(const bf1
                     Run4<bf16_t>::unpack(v, f);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        s0[c][e] += (double)f[e];
-                        s1[c][e] += (double)f[e] * (double)f[e];
+                        s0[4 * c + e] += (double)f[e];
+                        s1[4 * c + e] += (double)f[e] * (double)f[e];
                     }
                 }
             }
@@ -2067,20 +2065,23 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_bf16_kernel(const bf1
         }
     }
     if (stats) {
-#pragma unroll
-        for (int c = 0; c < CO; ++c)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-#pragma unroll
-                for (int off = 1; off < 16; off <<= 1) {
-                    s0[c][e] += __shfl_xor(s0[c][e], off, 64);
-                    s1[c][e] += __shfl_xor(s1[c][e], off, 64);
-                }
-                if (px == 0) {
-                    red[wave][c * 16 + 4 * kq + e][0] = s0[c][e];
-                    red[wave][c * 16 + 4 * kq + e][1] = s1[c][e];
-                }
-            }
+        // value number 4 c + e is channel 16 c + 4 kq + e; sixteen lanes share it
+        int which = 0;
+        if constexpr (CO == 2) {
+            sum_lanes_step<1, 8>(s0, s1, lane, which);
+            sum_lanes_step<2, 4>(s0, s1, lane, which);
+            sum_lanes_step<4, 2>(s0, s1, lane, which);
+        } else {
+            sum_lanes_step<1, 4>(s0, s1, lane, which);
+            sum_lanes_step<2, 2>(s0, s1, lane, which);
+            sum_lanes_step<4, 1>(s0, s1, lane, which);
+        }
+        sum_lanes_step<8, 1>(s0, s1, lane, which);
+        if ((px & (CO == 2 ? 8 : 12)) == 0) {
+            const int c = (which >> 2) * 16 + 4 * kq + (which & 3);
+            red[wave][c][0] = s0[0];
+            red[wave][c][1] = s1[0];
+        }
         __syncthreads();
         if (tid < CO * 32) {
             double a = 0.0;
