@@ -2003,8 +2003,8 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_bf16_kernel(const bf1
 #pragma unroll
     for (int e = 0; e < CO * 4; ++e) s0[e] = s1[e] = 0.0;
 
-    // operands of pixel group grp; pixels past the end read zeros
-    auto gather = [&](u32x4 (&x)[STEPS], int grp) {
+    // operands of pixel group grp (pixels past the end read zeros), and what an accumulating launch adds to
+    auto gather = [&](u32x4 (&x)[STEPS], u32x2 (&old)[CO], int grp) {
         const int m = grp * 16 + px;
         const bool live = m < g.M;
         const int tq = (int)fast_div((uint32_t)m, g.wo_mul, g.wo_sh), wo = m - tq * g.Wo;
@@ -2016,8 +2016,11 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_bf16_kernel(const bf1
             const bool ok = live && (unsigned)(th0 + tr[t]) < (unsigned)g.Hi && (unsigned)(tw0 + ts[t]) < (unsigned)g.Wi;
             x[t] = load16(rin, ok ? base + toff[t] : kOutOfRange);
         }
+        if (g.accum && live)
+#pragma unroll
+            for (int c = 0; c < CO; ++c) old[c] = *(const u32x2*)(out + (size_t)m * (CO * 16) + c * 16 + 4 * kq);
     };
-    auto finish = [&](const u32x4 (&x)[STEPS], int grp) {
+    auto finish = [&](const u32x4 (&x)[STEPS], const u32x2 (&old)[CO], int grp) {
         const int m = grp * 16 + px;
 #pragma unroll
         for (int c = 0; c < CO; ++c) {
@@ -2028,7 +2031,7 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_bf16_kernel(const bf1
             if (m < g.M) {
                 if (g.accum) {
                     float o[4];
-                    Run4<bf16_t>::unpack(*(const u32x2*)dst, o);
+                    Run4<bf16_t>::unpack(old[c], o);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) acc[e] += o[e];
                 }
@@ -2051,15 +2054,16 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_bf16_kernel(const bf1
     const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
     int grp = tile * WAVES + wave;
     u32x4 xr[DEPTH][STEPS];
+    u32x2 old[DEPTH][CO];
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d)
-        if (grp + d * stride_g < groups) gather(xr[d], grp + d * stride_g);  // (wave-uniform conditions)
+        if (grp + d * stride_g < groups) gather(xr[d], old[d], grp + d * stride_g);  // (wave-uniform conditions)
     while (grp < groups) {
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) {
             if (grp < groups) {
-                finish(xr[d], grp);
-                if (grp + DEPTH * stride_g < groups) gather(xr[d], grp + DEPTH * stride_g);
+                finish(xr[d], old[d], grp);
+                if (grp + DEPTH * stride_g < groups) gather(xr[d], old[d], grp + DEPTH * stride_g);
             }
             grp += stride_g;
         }
