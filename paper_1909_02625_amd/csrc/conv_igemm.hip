@@ -1963,9 +1963,12 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_f32_kernel(const floa
 // lane with 4 consecutive output channels of one pixel: one 8-byte store.  A wave walks groups of 16 pixels with DEPTH - 1
 // groups of loads in flight.  The column sums for a following batch norm are taken of the values as stored, in double, one
 // partial row per workgroup -- the 64-row tiles left 2048 rows to merge at M = 131072.
-// Bound by the latency of its loads, with one wave per SIMD.  Against the register-staged tiles: 128 x 32x32, 16 -> 16 7.6 -> 6.2
-// us, 128 x 16x16, 32 -> 32 6.1 -> 5.1, 256 x 56x56, 32 -> 32 45.6 -> 41.0, 16 x 16x16, 32 -> 32 5.3 -> 4.7; resnet56 with
-// them 1.21 -> 1.13 ms a tick (four streams; 128 and 192 workgroups the same, 384 1.21, 512 1.23).
+// The sixteen lanes of a channel meet in a tree that halves what a lane holds; an accumulating launch fetches the old values with
+// the operands (behind the sums they took 20 us of 62 at 800 k pixels, 32 -> 32).
+// Bound by the latency of its loads, with one wave per SIMD.  Against the register-staged tiles, forward alone: 128 x 32x32, 16 -> 16
+// 7.0 -> 5.7 us, 16 -> 32 8.4 -> 7.1, 32 -> 16 9.3 -> 8.1, 32 -> 32 10.8 -> 9.8; 256 x 56x56, 32 -> 32 40.3 -> 40.0; forward beside a
+// recompute with column sums and their merge: 128 x 32x32, 16 -> 16 20.1 -> 15.0, 128 x 16x16, 32 -> 32 14.8 -> 14.6, 128 x 56x56, 16 -> 32 45.0 ->
+// 27.4; resnet56 1.21 -> 1.12 ms a tick (four streams; 128 and 192 workgroups the same as 256, 384 1.21, 512 1.23).
 template <int CI, int CO>
 __global__ __launch_bounds__(kThreads) void conv3x3_direct_bf16_kernel(const bf16_t* __restrict__ in_,
                                                                        const bf16_t* __restrict__ wgt,
@@ -3279,12 +3282,20 @@ inline int64_t tile_count(const GatherGeom& g, int bm, int bn)
 }
 
 // The register-resident-filter kernels: 3x3, no dilation, consecutive output rows, 16-byte aligned tensors; fp32 with 16
-// gathered channels and 16 or 32 output channels (the kernel also handles 32 gathered channels, but there the per-wave filter
-// load outweighs the saved LDS traffic and the tiled kernel is faster), bf16 with 16 or 32 on both sides.
+// gathered channels and 16 or 32 output channels (with 32 gathered channels the per-wave filter load outweighs the saved LDS
+// traffic and the tiled kernel is faster), bf16 with 16 or 32 on both sides.
+// bf16, tiles -> filters in registers, 2 k to 1.6 M pixels: 16 gathered channels 0.97-1.4x (stride 1 and 2), 32 at stride 1
+// 1.01-1.3x, accumulating launches 1.04-1.47x, launches with column sums 0.93-1.8x.  What stays with the tiles:
+//   32 channels at stride 2 on middling maps, where a wave walks three or four groups of strided pixels with two in flight:
+//   65 k pixels, 32 -> 16 6.5 us there and 7.3 here, 32 -> 32 7.7 and 8.4; with column sums 8 k pixels, 32 -> 32 11.3 and 13.2 (32 k
+//   pixels, 32 -> 16 5.4 and 4.5; 98 k, 32 -> 32 12.6 and 11.0, 32 -> 16 9.5 and 9.7)
+//   plain launches 32 -> 32 of more than a million pixels (1.6 M: 81.0 us there, 90.0 here; accumulating 100.7 and 96.8, with column sums
+//   189 and 140; 0.8 M: 40.3 and 40.0)
 template <typename T>
 bool direct_eligible(const GatherGeom& g, const void* in, const void* out, const void* w = nullptr)
 {
     const bool ci = g.Ci == 16 || (sizeof(T) == 2 && g.Ci == 32);
+    if (sizeof(T) == 2 && g.ostride == 2 && g.Ci == 32 && g.M > (g.Co == 32 ? 4096 : 32768) && g.M < 98304) return false;
     return g.groups == 1 && g.R == 3 && g.S == 3 && g.idil == 1 && g.oh_mul == 0 && ci && (g.Co == 16 || g.Co == 32) &&
            ((uintptr_t)in % 16) == 0 && ((uintptr_t)out % 16) == 0 && (sizeof(T) == 4 || ((uintptr_t)w % 16) == 0);
 }
@@ -3578,7 +3589,8 @@ template <typename T>
 int dispatch_gather(GatherGeom g, bool accum, const void* in, const void* w, void* out, hipStream_t st, double flops)
 {
     constexpr int E = 16 / (int)sizeof(T);
-    if (direct_eligible<T>(g, in, out, w)) {
+    const bool tiles_ahead = sizeof(T) == 2 && g.Ci == 32 && g.Co == 32 && g.M > 1 << 20 && !accum && !g.stats;
+    if (direct_eligible<T>(g, in, out, w) && !tiles_ahead) {
         g.accum = accum ? 1 : 0;
         const dim3 grid(direct_grid<T>(g), g.in1 ? 2 : 1);
         if constexpr (sizeof(T) == 2) {

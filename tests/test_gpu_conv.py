@@ -138,6 +138,49 @@ def test_filters_in_registers_16_and_32_channels(shape):
     assert "conv3x3_direct<bf16,ci%d>" % shape[3] in launched, launched
 
 
+# ... and the edges of what it takes: (gathered channels, output channels, stride, output rows and columns, accumulating, taken)
+SMALL_3X3_EDGES = [
+    (32, 32, 2, 128, 32, False, True), (32, 32, 2, 129, 32, False, False),
+    (32, 16, 2, 1024, 32, False, True), (32, 16, 2, 1025, 32, False, False),
+    (32, 16, 2, 3071, 32, False, False), (32, 16, 2, 3072, 32, False, True),
+    (32, 32, 2, 3071, 32, False, False), (32, 32, 2, 3072, 32, False, True),
+    (16, 32, 2, 2048, 32, False, True),
+    (32, 32, 1, 1024, 1024, False, True), (32, 32, 1, 1025, 1024, False, False),
+    (32, 32, 1, 1025, 1024, True, True), (32, 16, 1, 1025, 1024, False, True),
+]
+
+
+@pytest.mark.parametrize("ci, co, stride, rows, cols, accumulate, taken", SMALL_3X3_EDGES)
+def test_filters_in_registers_where_the_tiles_take_over(ci, co, stride, rows, cols, accumulate, taken):
+    """An accumulating launch is backward-data (of a co -> ci layer), the others are forward; every element against fp64."""
+    h, w = stride * rows, stride * cols
+    x = torch.randn((1, h, w, ci), device="cuda").bfloat16()
+    f = (torch.randn((co, 3, 3, ci), device="cuda") / (3 * ci ** 0.5)).bfloat16()
+    y = torch.ones((1, rows, cols, co), device="cuda", dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    D.dsp_profile_start(16)
+    try:
+        if accumulate:
+            D.dsp_conv_backward_data(D.DSP_BF16, x, f, y, 1, rows, cols, co, ci, 3, 3, 1, 1, accumulate=True)
+        else:
+            D.dsp_conv_forward(D.DSP_BF16, x, f, y, 1, h, w, ci, co, 3, 3, stride, 1)
+        torch.cuda.synchronize()
+    finally:
+        launched = {k["name"] for k in D.dsp_profile_stop()}
+    assert ("conv3x3_direct<bf16,ci%d>" % ci in launched) == taken, launched
+    xp = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1))
+    ref = torch.full((rows * cols, co), float(accumulate), device="cuda", dtype=torch.float64)
+    mag = ref.clone()
+    for r in range(3):
+        for s in range(3):
+            a = xp[:, r:r + stride * (rows - 1) + 1:stride, s:s + stride * (cols - 1) + 1:stride].reshape(-1, ci)
+            b = f[:, r, s].double().t().contiguous()
+            ref += a @ b
+            mag += a.abs() @ b.abs()
+    # rounding to bf16, and 9 ci + 1 additions in fp32
+    assert ((y.double().view(-1, co) - ref).abs() <= 2.0**-8 * ref.abs() + (9 * ci + 2) * 2.0**-24 * mag).all()
+
+
 @pytest.mark.parametrize("dtype", [D.DSP_FP32, D.DSP_BF16], ids=["fp32", "bf16"])
 @pytest.mark.parametrize("co", [16, 32])
 def test_backward_data_whose_parity_class_is_a_small_3x3(co, dtype):
