@@ -100,7 +100,8 @@ __device__ inline void combine_row_lanes(double (&s0)[VW], double (&s1)[VW], dou
                                          bool active, int rlane, const RowLayout& L, double* __restrict__ part_row, int c0)
 {
     const int tid = threadIdx.x;
-    if (L.cvb <= 64 && (L.cvb & (L.cvb - 1)) == 0) {  // (then every thread has a row lane, and one workgroup column holds all channels)
+    // (then every thread has a row lane, and one workgroup column holds all channels; 8 channels and more come as vectors)
+    if (L.cvb <= (VW == 1 ? 4 : 64) && (L.cvb & (L.cvb - 1)) == 0) {
         const int C = L.cvb * VW;
         double(*sums)[2] = &red[0][0];
         double(*mine)[2] = sums + (tid >> 6) * C;
@@ -108,10 +109,13 @@ __device__ inline void combine_row_lanes(double (&s0)[VW], double (&s1)[VW], dou
         case 1: reduce_wave<VW, 1>(s0, s1, mine); break;
         case 2: reduce_wave<VW, 2>(s0, s1, mine); break;
         case 4: reduce_wave<VW, 4>(s0, s1, mine); break;
-        case 8: reduce_wave<VW, 8>(s0, s1, mine); break;
-        case 16: reduce_wave<VW, 16>(s0, s1, mine); break;
-        case 32: reduce_wave<VW, 32>(s0, s1, mine); break;
-        default: reduce_wave<VW, 64>(s0, s1, mine); break;
+        default:
+            if constexpr (VW > 1) {
+                if (L.cvb == 8) reduce_wave<VW, 8>(s0, s1, mine);
+                else if (L.cvb == 16) reduce_wave<VW, 16>(s0, s1, mine);
+                else if (L.cvb == 32) reduce_wave<VW, 32>(s0, s1, mine);
+                else reduce_wave<VW, 64>(s0, s1, mine);
+            }
         }
         __syncthreads();
         for (int i = tid; i < 2 * C; i += kThreads) {

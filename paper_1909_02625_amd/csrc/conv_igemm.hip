@@ -1816,16 +1816,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
-// ---- fp32 3x3 convolutions with 16 or 32 channels on both sides ----------------------------------
-// With so few channels the whole filter bank of 16 output channels fits in registers (9 * Ci / 16
-// 16-byte runs per lane), so no operand needs LDS: the MFMA computes y^T, D[co][pixel] with
+// ---- fp32 3x3 convolutions of 16 channels with 16 or 32 output channels --------------------------
+// With so few channels the whole filter bank of 16 output channels fits in registers (nine 16-byte
+// runs per lane), so no operand needs LDS: the MFMA computes y^T, D[co][pixel] with
 // A = filters (row co = lane % 16, k-run lane / 16) held for the whole kernel and B = the gathered
-// pixels, one coalesced 16-byte run per lane, tap and 16 channels (16 consecutive pixels = 1 KB per
-// wave load).  Lane (pixel p, quarter q) uses element e of its run in MFMA e, which pairs channel
+// pixels, one coalesced 16-byte run per lane and tap (16 consecutive pixels = 1 KB per wave load).  Lane (pixel p, quarter q) uses element e of its run in MFMA e, which pairs channel
 // 4q + e on both operands.  The result leaves each lane with 4 consecutive output channels of one
 // pixel: one 16-byte store.  A wave owns one group of 16 output channels and walks groups of 16
 // pixels; the column sums for a following batch norm are accumulated on the way.
-template <int CI16>
 __global__ __launch_bounds__(kThreads) void conv3x3_direct_f32_kernel(const float* __restrict__ in_,
                                                                       const float* __restrict__ wgt,
                                                                       float* __restrict__ out_, GatherGeom g)
@@ -1840,29 +1838,25 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_f32_kernel(const floa
     const int cg = wave % cgs, pw = wave / cgs, PW = 4 / cgs;
     const int groups = (g.M + 15) >> 4;
 
-    f32x4 wreg[TAPS][CI16];
+    f32x4 wreg[TAPS];
     {
         const float* wrow = wgt + (size_t)(cg * 16 + px) * g.Kdim + 4 * kq;
         if (((uintptr_t)wgt & 15) == 0) {
 #pragma unroll
-            for (int t = 0; t < TAPS; ++t)
-#pragma unroll
-                for (int c = 0; c < CI16; ++c) wreg[t][c] = *(const f32x4*)(wrow + t * g.Ci + c * 16);
+            for (int t = 0; t < TAPS; ++t) wreg[t] = *(const f32x4*)(wrow + t * 16);
         } else {
 #pragma unroll
-            for (int t = 0; t < TAPS; ++t)
-#pragma unroll
-                for (int c = 0; c < CI16; ++c) {
-                    const float* p = wrow + t * g.Ci + c * 16;
-                    wreg[t][c] = f32x4{p[0], p[1], p[2], p[3]};
-                }
+            for (int t = 0; t < TAPS; ++t) {
+                const float* p = wrow + t * 16;
+                wreg[t] = f32x4{p[0], p[1], p[2], p[3]};
+            }
         }
     }
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(in, (uint32_t)g.N * g.Hi * g.Wi * g.Ci * 4u);
     float s0[4] = {0.f, 0.f, 0.f, 0.f}, s1[4] = {0.f, 0.f, 0.f, 0.f};
 
     // 16-byte runs of pixel group grp, all taps; a group past the end reads zeros
-    auto gather = [&](f32x4 (&xin)[TAPS][CI16], int grp) {
+    auto gather = [&](f32x4 (&xin)[TAPS], int grp) {
         const int m = grp * 16 + px;
         const bool live = grp < groups && m < g.M;
         const int tq = (int)fast_div((uint32_t)m, g.wo_mul, g.wo_sh), wo = m - tq * g.Wo;
@@ -1876,21 +1870,16 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_f32_kernel(const floa
             for (int s2 = 0; s2 < 3; ++s2) {
                 const bool ok = hok && tw0 + s2 >= 0 && tw0 + s2 < g.Wi;
                 const uint32_t off = base + (uint32_t)((r * g.Wi + s2) * g.Ci) * 4u;
-#pragma unroll
-                for (int c = 0; c < CI16; ++c)
-                    xin[r * 3 + s2][c] = __builtin_bit_cast(f32x4, load16(rin, ok ? off + c * 64u : kOutOfRange));
+                xin[r * 3 + s2] = __builtin_bit_cast(f32x4, load16(rin, ok ? off : kOutOfRange));
             }
         }
     };
-    auto finish = [&](const f32x4 (&xin)[TAPS][CI16], int grp) {
+    auto finish = [&](const f32x4 (&xin)[TAPS], int grp) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < TAPS; ++t)
 #pragma unroll
-            for (int c = 0; c < CI16; ++c)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wreg[t][c][e], xin[t][c][e], acc, 0, 0, 0);
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wreg[t][e], xin[t][e], acc, 0, 0, 0);
         const int m = grp * 16 + px;
         if (m < g.M) {
             float* dst = out + (size_t)m * g.Co + cg * 16 + 4 * kq;
@@ -1908,9 +1897,9 @@ __global__ __launch_bounds__(kThreads) void conv3x3_direct_f32_kernel(const floa
     };
 
     // DEPTH register sets: the pixels of the next DEPTH - 1 groups are in flight while one is multiplied
-    constexpr int DEPTH = CI16 == 1 ? 4 : 2;
+    constexpr int DEPTH = 4;
     const int stride_g = gridDim.x * PW;
-    f32x4 xr[DEPTH][TAPS][CI16];
+    f32x4 xr[DEPTH][TAPS];
     const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
     int grp = tile * PW + pw;
 #pragma unroll
@@ -3600,7 +3589,7 @@ int dispatch_gather(GatherGeom g, bool accum, const void* in, const void* w, voi
             DSP_LAUNCH(ps, kern, grid, dim3(kThreads), 0, st, (const bf16_t*)in, (const bf16_t*)w, (bf16_t*)out, g);
         } else {
             ProfScope ps("conv3x3_direct<fp32,ci16>", flops, 0);
-            DSP_LAUNCH(ps, conv3x3_direct_f32_kernel<1>, grid, dim3(kThreads), 0, st, (const float*)in, (const float*)w,
+            DSP_LAUNCH(ps, conv3x3_direct_f32_kernel, grid, dim3(kThreads), 0, st, (const float*)in, (const float*)w,
                        (float*)out, g);
         }
         DSP_HIP(hipGetLastError());
