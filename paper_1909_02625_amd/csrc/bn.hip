@@ -93,8 +93,10 @@ __device__ inline void reduce_wave(double (&s0)[VW], double (&s1)[VW], double (*
 // vector at once) and writes the workgroup's partial row part_row[c][2].  Where a wave holds whole rows (a power of two of
 // channel vectors, at most 64) its lanes exchange their sums and only the four waves meet in LDS; the tree through LDS that
 // serves the others takes a barrier and 2 VW double additions in LDS per level, a third of the launch on small maps.  Together
-// with loads that stay packed until they are used (126 instead of 177 registers, four waves per SIMD instead of two or three),
-// backward sums with sign bytes: 131072 x 16 bf16 8.9 -> 5.5 us, 12544 x 256 8.2 -> 6.7, 200704 x 128 23.8 -> 18.4 (5.6 TB/s).
+// with loads that stay packed until they are used (registers, eight bf16 channels: ReLU from sign bytes 126 instead of 171, from x
+// 117 instead of 153, four waves per SIMD instead of two or three; from y 140 instead of 177, three waves), backward sums with
+// sign bytes: 131072 x 16 bf16 8.9 -> 5.5 us, 12544 x 256 8.2 -> 6.7, 200704 x 128 23.8 -> 18.4 (5.6 TB/s); from x 7.5 -> 5.0,
+// 7.9 -> 7.2, 21.8 -> 17.6.
 template <int VW>
 __device__ inline void combine_row_lanes(double (&s0)[VW], double (&s1)[VW], double (&red)[VW][kThreads][2],
                                          bool active, int rlane, const RowLayout& L, double* __restrict__ part_row, int c0)
@@ -215,8 +217,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RM == 
     const int64_t r_end = r_begin + rows_per_block < M ? r_begin + rows_per_block : M;
     if (active) {
         // U rows per trip with all their loads issued before the first add: the loop is bound by load
-        // latency, not by bandwidth, unless several rows are in flight per thread
-        constexpr int U = 4;
+        // latency, not by bandwidth, unless several rows are in flight per thread (three where the ReLU is decided from x in
+        // bf16: beside the constants of eight channels a fourth spills, 131072 x 16 5.5 -> 5.0 us, 30000 x 40 7.5 -> 6.7)
+        constexpr int U = RM == 2 && VW == 8 ? 3 : 4;
         for (int64_t r = r_begin + rlane; r < r_end; r += (int64_t)U * L.rl) {
             Raw xr[U], gr[U], yr[U];
             uint32_t bits[U];

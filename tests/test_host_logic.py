@@ -254,3 +254,16 @@ def test_traffic_of_a_kernel_whose_name_holds_spaces(tmp_path, monkeypatch):
     assert [bench.hbm_traffic("w", "bf16", n) for n in names] == [11.0, 22.0, 33.0]
     assert bench.hbm_traffic("w", "bf16", "conv_dma_gemm<bf16,BM256,BN128,BK64,8x1") is None
     assert bench.hbm_traffic("v", "bf16", "mean_kernel") is None
+
+
+def test_batch_norm_kernels_hold_their_values_in_registers():
+    """The summing kernels ask for a number of waves per SIMD; none pays for it with scratch memory (the compiler's own report)."""
+    import subprocess
+    from paper_1909_02625_amd import build
+    r = subprocess.run([build.HIPCC] + build.FLAGS + ['-DDSP_BUILD_ID="x"', "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage",
+                                                      "-c", os.path.join(build.CSRC, "bn.hip"), "-o", os.devnull],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    kernels = re.findall(r"Function Name: (\S+).*?ScratchSize \[bytes/lane\]: (\d+)", r.stderr, re.S)
+    assert sum("bn_sums_kernel" in k for k, _ in kernels) > 10
+    assert [(k, s) for k, s in kernels if int(s)] == []
