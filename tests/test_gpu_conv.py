@@ -199,6 +199,71 @@ def test_several_output_tiles_per_workgroup():
     assert "conv_dma_stream<bf16,BM256,BN128,BK64,8 waves>" in launched, launched
 
 
+# The stream over output tiles where a workgroup walks several: (shape of the layer, groups, backward-data).  389 tiles and a ragged
+# column count; three column tiles, the last of 8 channels; the four parity classes of a stride-2 layer on an odd map, 555-647
+# tiles each, whose output rows lie two pixels apart; filters larger than the input (column tiles walked first); groups.
+STREAMED = [
+    ((127, 28, 28, 104, 128, 3, 3, 1, 1), 1, True),
+    ((68, 23, 21, 264, 128, 3, 3, 1, 1), 1, True),
+    ((910, 27, 25, 72, 512, 3, 3, 2, 1), 1, True),
+    ((13, 16, 16, 1024, 4992, 1, 1, 1, 0), 1, False),
+    ((161, 16, 16, 256, 288, 3, 3, 1, 1), 4, False),
+]
+
+
+@pytest.mark.parametrize("shape, groups, kind", [(s, g, k) for s, g, b in STREAMED for k in (("plain", "accumulating") if b else ("forward",))],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_streamed_tiles(shape, groups, kind):
+    """Every element against fp64: the rounding to bf16 and an addition in fp32 per product."""
+    backward, accumulate = kind != "forward", kind == "accumulating"
+    N, H, W, Ci, Co, R, S, st, pd = shape
+    ho, wo = (H + 2 * pd - R) // st + 1, (W + 2 * pd - S) // st + 1
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(R * Ci + Co)
+    cg, og = Ci // groups, Co // groups
+    a = torch.randn((N, ho, wo, Co) if backward else (N, H, W, Ci), generator=gen, device="cuda").bfloat16()
+    w = (torch.randn((Co, R, S, cg), generator=gen, device="cuda") / (R * S * (og if backward else cg)) ** 0.5).bfloat16()
+    out = torch.randn((N, H, W, Ci) if backward else (N, ho, wo, Co), generator=gen, device="cuda").bfloat16()
+    old = out.double() if accumulate else torch.zeros_like(out, dtype=torch.float64)
+    d_w = torch.from_numpy(dgrad_filter_copy(w.float().cpu().numpy().transpose(0, 3, 1, 2), st, pd, groups)).to("cuda", torch.bfloat16) if backward else w
+    torch.cuda.synchronize()
+    D.dsp_profile_start(16)
+    try:
+        if backward:
+            D.dsp_grouped_conv_backward_data(D.DSP_BF16, a, d_w, out, *shape, groups, accumulate=accumulate)
+        else:
+            D.dsp_grouped_conv_forward(D.DSP_BF16, a, d_w, out, *shape, groups)
+        torch.cuda.synchronize()
+    finally:
+        launched = {k["name"]: k["launches"] for k in D.dsp_profile_stop()}
+    assert launched == {"conv_dma_stream<bf16,BM256,BN128,BK64,8 waves>": st * st}, launched
+    # the reference: one product per tap (and group), added up at the pixels of x it reads
+    pad = torch.nn.functional.pad
+    ref, mag = old.clone(), old.abs()
+    if backward:
+        ref, mag = pad(ref, (0, 0, pd, pd, pd, pd)), pad(mag, (0, 0, pd, pd, pd, pd))
+    src = a.double() if backward else pad(a.double(), (0, 0, pd, pd, pd, pd))
+    wd = w.double()
+    for r in range(R):
+        for s in range(S):
+            rows, cols = slice(r, r + st * (ho - 1) + 1, st), slice(s, s + st * (wo - 1) + 1, st)
+            for i in range(groups):
+                f = wd[i * og:(i + 1) * og, r, s]
+                if backward:
+                    t = src.reshape(-1, Co)
+                    ref[:, rows, cols] += (t @ f).view(N, ho, wo, Ci)
+                    mag[:, rows, cols] += (t.abs() @ f.abs()).view(N, ho, wo, Ci)
+                else:
+                    t, o = src[:, rows, cols, i * cg:(i + 1) * cg].reshape(-1, cg), slice(i * og, (i + 1) * og)
+                    f = f.t().contiguous()
+                    ref[..., o] += (t @ f).view(N, ho, wo, og)
+                    mag[..., o] += (t.abs() @ f.abs()).view(N, ho, wo, og)
+    if backward:
+        ref, mag = ref[:, pd:pd + H, pd:pd + W], mag[:, pd:pd + H, pd:pd + W]
+    k = R * S * (og if backward else cg)
+    assert ((out.double() - ref).abs() <= 2.0**-8 * ref.abs() + (k + 2) * 2.0**-24 * mag).all()
+
+
 # The direct-to-LDS backward-weight tiles where they can go wrong: channels and columns that fill no tile (8 of 64, 136 of
 # 128 + 128), fewer rows than one LDS stage and than the stages in flight, a step of 64 pixels that passes several images
 # (3 x 3 maps), one that stays inside a row (a row of 70), rows dropped by the stride at an odd edge, and eight slices of the

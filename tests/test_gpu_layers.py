@@ -119,31 +119,36 @@ def test_batch_norm_sums(shape, dtype):
         test_batch_norm_forward_and_backward(shape, dtype, relu, res)
 
 
-# (N, C, H, W), does the fp32 apply kernel merge the partial sums itself (up to 2048 partials, 1.5 MB)
+# (N, C, H, W), does the apply kernel merge the partial sums itself in fp32, in bf16 (up to 2048 partials, 1.5 MB)
 MERGE_SHAPES = [
-    ((1, 16, 1, 3), True),       # fewer rows than a workgroup holds
-    ((64, 4, 16, 16), True),     # a quarter of a channel group
-    ((7, 40, 9, 11), True),      # groups that do not divide the channels
-    ((2, 520, 6, 6), True),      # many groups, the last one short
-    ((3, 17, 20, 20), True),     # element-wise path
-    ((24, 16, 32, 32), True),    # 1.5 MB in fp32
-    ((1, 16, 157, 157), False),  # just above
-    ((16, 64, 256, 1), True),    # 64 partial rows of 32 channels
-    ((17, 64, 241, 1), False),   # 65
+    ((1, 16, 1, 3), True, True),        # fewer rows than a workgroup holds
+    ((64, 4, 16, 16), True, True),      # a quarter of a channel group
+    ((7, 40, 9, 11), True, True),       # groups that do not divide the channels
+    ((2, 520, 6, 6), True, True),       # many groups, the last one short
+    ((3, 17, 20, 20), True, True),      # element-wise path
+    ((24, 16, 32, 32), True, True),     # 1.5 MB in fp32
+    ((1, 16, 157, 157), False, True),   # just above
+    ((48, 16, 32, 32), False, True),    # 1.5 MB in bf16
+    ((1, 16, 192, 257), False, False),  # just above
+    ((16, 64, 256, 1), True, True),     # 64 partial rows of 32 channels in fp32, 32 of 64 in bf16
+    ((17, 64, 241, 1), False, False),   # one more
 ]
 
 
 @pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
-@pytest.mark.parametrize("shape,merged", MERGE_SHAPES, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else "")
-def test_batch_norm_that_merges_its_partial_sums(shape, merged, dtype):
+@pytest.mark.parametrize("shape,merged_fp32,merged_bf16", MERGE_SHAPES, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else "")
+def test_batch_norm_that_merges_its_partial_sums(shape, merged_fp32, merged_bf16, dtype):
     """The apply kernels that form the statistics of their own channels, at the edges of their range."""
     D.dsp_profile_start(64)
-    for relu, res in ((True, False), (True, True), (False, False)):
-        test_batch_norm_forward_and_backward(shape, dtype, relu, res)
-    names = [k["name"] for k in D.dsp_profile_stop()]
-    if dtype == D.DSP_FP32:
-        assert ("bn_merge_apply_relu<fp32>" in names and "bn_bwd_merge_apply<fp32>" in names) == merged
-        assert ("bn_fwd_finalize" in names or "bn_bwd_finalize" in names) == (not merged)
+    try:
+        for relu, res in ((True, False), (True, True), (False, False)):
+            test_batch_norm_forward_and_backward(shape, dtype, relu, res)
+    finally:
+        names = {k["name"] for k in D.dsp_profile_stop()}
+    merged, t = (merged_fp32, "fp32") if dtype == D.DSP_FP32 else (merged_bf16, "bf16")
+    assert {"bn_merge_apply_relu<%s>" % t, "bn_bwd_merge_apply<%s>" % t} <= names if merged else \
+        {"bn_fwd_finalize", "bn_bwd_finalize"} <= names
+    assert not names & ({"bn_fwd_finalize", "bn_bwd_finalize"} if merged else {"bn_merge_apply_relu<%s>" % t, "bn_bwd_merge_apply<%s>" % t})
 
 
 @pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
