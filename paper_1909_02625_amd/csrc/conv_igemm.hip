@@ -1820,10 +1820,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 // With so few channels the whole filter bank of 16 output channels fits in registers (nine 16-byte
 // runs per lane), so no operand needs LDS: the MFMA computes y^T, D[co][pixel] with
 // A = filters (row co = lane % 16, k-run lane / 16) held for the whole kernel and B = the gathered
-// pixels, one coalesced 16-byte run per lane and tap (16 consecutive pixels = 1 KB per wave load).  Lane (pixel p, quarter q) uses element e of its run in MFMA e, which pairs channel
-// 4q + e on both operands.  The result leaves each lane with 4 consecutive output channels of one
-// pixel: one 16-byte store.  A wave owns one group of 16 output channels and walks groups of 16
-// pixels; the column sums for a following batch norm are accumulated on the way.
+// pixels, one coalesced 16-byte run per lane and tap (16 consecutive pixels = 1 KB per wave load).
+// Lane (pixel p, quarter q) uses element e of its run in MFMA e, which pairs channel 4q + e on both
+// operands.  The result leaves each lane with 4 consecutive output channels of one pixel: one
+// 16-byte store.  A wave owns one group of 16 output channels and walks groups of 16 pixels; the
+// column sums for a following batch norm are accumulated on the way.
 __global__ __launch_bounds__(kThreads) void conv3x3_direct_f32_kernel(const float* __restrict__ in_,
                                                                       const float* __restrict__ wgt,
                                                                       float* __restrict__ out_, GatherGeom g)
@@ -3304,15 +3305,17 @@ int direct_grid(const GatherGeom& g)
 // compute units, a tile costs t0 + k64 * t where per_cu of them share the compute unit and t0_one + k64 * t_one where the
 // last round leaves it alone there, and a launch costs t_launch.  The constants are fits to measured durations (227 layers for
 // CI64, their input just written by another kernel, and 150 for GEN: 1x1 and 3x3, stride 1 and 2, M = 200 .. 670 k rows, Co =
-// 16 .. 1024, K = 16 .. 9216).  Over the 120 layers of profiles/direct_to_lds_tile_durations.txt, which holds every tile's
-// duration, the tile the table picks is 0.8 % (CI64) and 1.5 % (GEN) slower than the best one, geometric mean (worst 1.32x).
+// 16 .. 1024, K = 16 .. 9216).  The second row of CI64 was fitted to that tile without the stream over output tiles, which leaves
+// its choice as good: over the layers of profiles/direct_to_lds_tile_durations.txt, which holds every tile's duration, the tile
+// the table picks is slower than the best one by 0.9 % (CI64, 60 layers), 1.3 % (40 layers where that row is the lowest or within
+// 20 % of it; its rms there is 10 %) and 1.5 % (GEN, 60 layers), geometric mean (worst 1.32x).
 // Durations against the register-staged tiles: 1.39x (CI64) and, for K >= 512, 1.35x (GEN) faster over random layers;
 // 256 x 14x14, 256 -> 256 3x3: 79 -> 57 us (1.04 PFLOP/s); 64 x 14x14, 256 -> 256 3x3: 31 -> 20 us; 128 x 4x4, 512 -> 512 3x3:
 // 35 -> 17 us; 19 x 16x16, 1024 -> 256 1x1: 13.4 -> 9.2 us.
-// What bounds them: no unit is full.  Over the layers of ResNet-18 (batch 256) the matrix pipes work 53 % (256x256) and 38 %
-// (256x128) of the time, LDS reads take 22-23 % of the cycles with 4-5 % of them in conflict, and the waves wait for memory 43
-// and 26 % of theirs; over those of a ResNet-50 stage at batch 64, one round of tiles or less, the pipes work 26-34 %: a
-// launch of one tile per compute unit loads, multiplies and stores one after the other.
+// What bounds them: no unit is full.  Over the layers of ResNet-18 (batch 256) the matrix pipes work 55 % (256x256) and 46 %
+// (256x128, streamed; 38 % without) of the time, LDS reads take 24 % of the cycles with 4 and 1 % of them in conflict, and the
+// waves wait for memory 42 and 33 % of theirs; over those of a ResNet-50 stage at batch 64, one round of tiles or less, the pipes
+// work 27-35 %, 41 % streamed: a launch of one tile per compute unit loads, multiplies and stores one after the other.
 constexpr int kComputeUnits = 256;
 struct DmaCost {
     int bm, bn, per_cu;
