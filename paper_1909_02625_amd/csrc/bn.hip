@@ -157,6 +157,27 @@ __device__ inline void combine_row_lanes(double (&s0)[VW], double (&s1)[VW], dou
     }
 }
 
+// How tensors whose apply kernels merge the partial sums themselves are dealt out (see "finalize inside the apply kernels").
+constexpr int kMergeEntries = 2048;  // partial rows x channels of a group
+constexpr int64_t kMergeTensorBytes = (int64_t)3 << 19;
+// With kWideChannels and more the groups alone make enough workgroups, and the sums come in few rows (bn_group_sums_kernel):
+constexpr int kWideChannels = 128;
+constexpr int kWideConvEntries = 3072;       // partial rows x channels of a group where a convolution left them
+constexpr int64_t kWideTensorBytes = (int64_t)32 << 20;   // a quarter of it where a group is less than 128 bytes of a row
+constexpr int kWideRunBytes = 96 << 10;      // of a tensor, per workgroup that sums
+constexpr int kBnThreads = 512;
+struct BnLayout {
+    int cg, groups;              // channels per group, groups
+    int rows_per_wg, row_blocks;
+};
+__device__ inline int bn_work_item(const BnLayout& L, int* g0)
+{
+    const unsigned b = blockIdx.x, nb = gridDim.x, q = nb / 8, r = nb % 8, xcd = b % 8;
+    const unsigned item = xcd * q + (xcd < r ? xcd : r) + b / 8;
+    *g0 = (int)(item % (unsigned)L.groups) * L.cg;
+    return (int)(item / (unsigned)L.groups);
+}
+
 // ---- per-channel sums ---------------------------------------------------------------------------
 // MODE 0: s0 = sum x, s1 = sum x^2.
 // MODE 1: dz = dy * [y > 0] (if RM != 0); s0 = sum dz, s1 = sum dz * (x - mean) * invstd.  RM = 1 reads the stored y;
@@ -173,6 +194,76 @@ struct AddOut {
     const T* b1;   // second instance: the other operand and the sum
     T* out1;
 };
+template <int VW>
+struct BnSumCoef {
+    float mu[VW], is[VW], fsc[VW], fsh[VW];
+};
+template <int VW, int MODE, int RM>
+__device__ inline void load_sum_coef(BnSumCoef<VW>& k, const float* __restrict__ mean, const float* __restrict__ invstd,
+                                     const float* __restrict__ fcoef, int C, int c0)
+{
+#pragma unroll
+    for (int i = 0; i < VW; ++i) {
+        if (MODE == 1) {
+            k.mu[i] = mean[c0 + i];
+            k.is[i] = invstd[c0 + i];
+        }
+        if (MODE == 1 && RM == 2) {
+            k.fsc[i] = fcoef[c0 + i];
+            k.fsh[i] = fcoef[C + c0 + i];
+        }
+    }
+}
+// Adds the rows r, r + rl, .. below r_end of channel vector cvi (channels c0 ..) of cv to s0 and s1.
+template <typename T, int VW, int MODE, int RM>
+__device__ inline void add_rows(const T* __restrict__ x, const T* __restrict__ dy, const T* __restrict__ y, T* __restrict__ out,
+                                const BnSumCoef<VW>& k, int64_t r, int64_t r_end, int rl, int C, int c0, int cv, int cvi,
+                                double (&s0)[VW], double (&s1)[VW])
+{
+    typedef typename VecIO<T, VW>::Raw Raw;
+    // U rows per trip with all their loads issued before the first add: the loop is bound by load
+    // latency, not by bandwidth, unless several rows are in flight per thread (three where the ReLU is decided from x in
+    // bf16: beside the constants of eight channels a fourth spills, 131072 x 16 5.5 -> 5.0 us, 30000 x 40 7.5 -> 6.7)
+    constexpr int U = RM == 2 && VW == 8 ? 3 : 4;
+    for (; r < r_end; r += (int64_t)U * rl) {
+        Raw xr[U], gr[U], yr[U];
+        uint32_t bits[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t ru = r + (int64_t)u * rl;
+            if (ru < r_end) {
+                xr[u] = VecIO<T, VW>::raw(x + ru * C + c0);
+                if (MODE >= 1) gr[u] = VecIO<T, VW>::raw(dy + ru * C + c0);
+                if (MODE == 1 && RM == 1) yr[u] = VecIO<T, VW>::raw(y + ru * C + c0);
+                if (MODE == 1 && RM == 3) bits[u] = ((const uint8_t*)y)[ru * cv + cvi];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (r + (int64_t)u * rl >= r_end) break;
+            float xv[VW], gv[VW], yv[VW];
+            VecIO<T, VW>::unpack(xr[u], xv);
+            if (MODE >= 1) VecIO<T, VW>::unpack(gr[u], gv);
+            if (MODE == 1 && RM == 1) VecIO<T, VW>::unpack(yr[u], yv);
+#pragma unroll
+            for (int i = 0; i < VW; ++i) {
+                if (MODE == 2) xv[i] = to_float<T>(from_float<T>(xv[i] + gv[i]));  // the value as stored
+                if (MODE == 0 || MODE == 2) {
+                    s0[i] += (double)xv[i];
+                    s1[i] += (double)xv[i] * (double)xv[i];
+                } else {
+                    const bool on = RM == 0 ? true
+                                    : RM == 1 ? yv[i] > 0.f
+                                    : RM == 2 ? bn_value<T>(xv[i], k.fsc[i], k.fsh[i]) > 0.f : ((bits[u] >> i) & 1u) != 0;
+                    const float dz = on ? gv[i] : 0.f;
+                    s0[i] += (double)dz;
+                    s1[i] += (double)(dz * ((xv[i] - k.mu[i]) * k.is[i]));
+                }
+            }
+            if (MODE == 2) VecIO<T, VW>::store(out + (r + (int64_t)u * rl) * C + c0, xv);
+        }
+    }
+}
 template <typename T, int VW, int MODE, int RM>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RM == 1 ? 3 : 4))) void bn_sums_kernel(const T* __restrict__ x, const T* __restrict__ dy,
                                                            const T* __restrict__ y, const float* __restrict__ mean,
@@ -182,7 +273,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RM == 
                                                            AddOut<T> add, const float* __restrict__ fcoef)
 {
     // blockIdx.z = 1: the second instance of a twin launch (other tensor, same shape)
-    typedef typename VecIO<T, VW>::Raw Raw;
     T* __restrict__ out = add.out;
     if (blockIdx.z) {
         x = x1;
@@ -201,77 +291,68 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RM == 
     double s0[VW], s1[VW];
 #pragma unroll
     for (int i = 0; i < VW; ++i) s0[i] = s1[i] = 0.0;
-    float mu[VW], is[VW], fsc[VW], fsh[VW];
-    if (MODE == 1 && active) {
-#pragma unroll
-        for (int i = 0; i < VW; ++i) {
-            mu[i] = mean[c0 + i];
-            is[i] = invstd[c0 + i];
-            if (RM == 2) {
-                fsc[i] = fcoef[c0 + i];
-                fsh[i] = fcoef[C + c0 + i];
-            }
-        }
-    }
+    BnSumCoef<VW> k;
+    if (active) load_sum_coef<VW, MODE, RM>(k, mean, invstd, fcoef, C, c0);
     const int64_t r_begin = (int64_t)blockIdx.x * rows_per_block;
     const int64_t r_end = r_begin + rows_per_block < M ? r_begin + rows_per_block : M;
-    if (active) {
-        // U rows per trip with all their loads issued before the first add: the loop is bound by load
-        // latency, not by bandwidth, unless several rows are in flight per thread (three where the ReLU is decided from x in
-        // bf16: beside the constants of eight channels a fourth spills, 131072 x 16 5.5 -> 5.0 us, 30000 x 40 7.5 -> 6.7)
-        constexpr int U = RM == 2 && VW == 8 ? 3 : 4;
-        for (int64_t r = r_begin + rlane; r < r_end; r += (int64_t)U * L.rl) {
-            Raw xr[U], gr[U], yr[U];
-            uint32_t bits[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t ru = r + (int64_t)u * L.rl;
-                if (ru < r_end) {
-                    xr[u] = VecIO<T, VW>::raw(x + ru * C + c0);
-                    if (MODE >= 1) gr[u] = VecIO<T, VW>::raw(dy + ru * C + c0);
-                    if (MODE == 1 && RM == 1) yr[u] = VecIO<T, VW>::raw(y + ru * C + c0);
-                    if (MODE == 1 && RM == 3) bits[u] = ((const uint8_t*)y)[ru * L.cv + cvi];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (r + (int64_t)u * L.rl >= r_end) break;
-                float xv[VW], gv[VW], yv[VW];
-                VecIO<T, VW>::unpack(xr[u], xv);
-                if (MODE >= 1) VecIO<T, VW>::unpack(gr[u], gv);
-                if (MODE == 1 && RM == 1) VecIO<T, VW>::unpack(yr[u], yv);
-#pragma unroll
-                for (int i = 0; i < VW; ++i) {
-                    if (MODE == 2) xv[i] = to_float<T>(from_float<T>(xv[i] + gv[i]));  // the value as stored
-                    if (MODE == 0 || MODE == 2) {
-                        s0[i] += (double)xv[i];
-                        s1[i] += (double)xv[i] * (double)xv[i];
-                    } else {
-                        const bool on = RM == 0 ? true
-                                        : RM == 1 ? yv[i] > 0.f
-                                        : RM == 2 ? bn_value<T>(xv[i], fsc[i], fsh[i]) > 0.f : ((bits[u] >> i) & 1u) != 0;
-                        const float dz = on ? gv[i] : 0.f;
-                        s0[i] += (double)dz;
-                        s1[i] += (double)(dz * ((xv[i] - mu[i]) * is[i]));
-                    }
-                }
-                if (MODE == 2) VecIO<T, VW>::store(out + (r + (int64_t)u * L.rl) * C + c0, xv);
-            }
-        }
-    }
+    if (active) add_rows<T, VW, MODE, RM>(x, dy, y, out, k, r_begin + rlane, r_end, L.rl, C, c0, L.cv, cvi, s0, s1);
     combine_row_lanes<VW>(s0, s1, red, active, rlane, L, part + (int64_t)blockIdx.x * C * 2, c0);
+}
+
+// The same sums with few partial rows, for tensors whose apply kernels merge them: a workgroup takes a group of L.cg channels over a
+// run of rows (the work items of those kernels), so that what each of their workgroups reads back, rows x channels of a
+// group, stays at kMergeEntries while the groups still fill the chip.
+template <typename T, int VW, int MODE, int RM>
+__global__ __launch_bounds__(kBnThreads) __attribute__((amdgpu_waves_per_eu(RM == 1 ? 3 : 4))) void bn_group_sums_kernel(
+    const T* __restrict__ x, const T* __restrict__ dy, const T* __restrict__ y, const float* __restrict__ mean,
+    const float* __restrict__ invstd, double* __restrict__ part, int64_t M, int C, BnLayout L, const T* __restrict__ x1,
+    double* __restrict__ part1, const float* __restrict__ fcoef)
+{
+    if (blockIdx.y) {  // the second instance of a twin launch
+        x = x1;
+        part = part1;
+    }
+    constexpr int NW = kBnThreads / 64;
+    __shared__ double sums[NW][64][2];
+    int g0;
+    const int rb = bn_work_item(L, &g0);
+    const int tid = threadIdx.x, vpr = L.cg / VW, rpp = kBnThreads / vpr, c0 = g0 + (tid % vpr) * VW;
+    const bool active = c0 < C;  // (channels come in whole vectors)
+    double s0[VW], s1[VW];
+#pragma unroll
+    for (int i = 0; i < VW; ++i) s0[i] = s1[i] = 0.0;
+    BnSumCoef<VW> k;
+    if (active) {
+        load_sum_coef<VW, MODE, RM>(k, mean, invstd, fcoef, C, c0);
+        const int64_t r_begin = (int64_t)rb * L.rows_per_wg, r_end = r_begin + L.rows_per_wg < M ? r_begin + L.rows_per_wg : M;
+        add_rows<T, VW, MODE, RM>(x, dy, y, (T*)nullptr, k, r_begin + tid / vpr, r_end, rpp, C, c0, C / VW, c0 / VW, s0, s1);
+    }
+    double(*mine)[2] = sums[tid >> 6];
+    if (L.cg == 64) reduce_wave<VW, 64 / VW>(s0, s1, mine);
+    else if (L.cg == 32) reduce_wave<VW, 32 / VW>(s0, s1, mine);
+    else reduce_wave<VW, 16 / VW>(s0, s1, mine);
+    __syncthreads();
+    if (tid < 2 * L.cg && g0 + (tid >> 1) < C) {
+        double a = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) a += sums[w][tid >> 1][tid & 1];
+        part[((int64_t)rb * C + g0) * 2 + tid] = a;
+    }
 }
 
 // Merging the partials.  The partials of a conv epilogue can be thousands of rows (one per row tile), so a
 // workgroup of kMergeLanes x 4 threads takes 4 channels and reads whole 64-byte row segments, up to 8 loads
-// in flight per thread and added in row order; then a fixed tree over the row lanes.  Returns the two sums
-// of channel blockIdx.x * 4 + (threadIdx.x & 3) to the threads of row lane 0.
+// in flight per thread and added in row order; then a fixed tree over the row lanes: the sums cross LDS behind one barrier,
+// the first wave adds the lanes 32 and 16 apart as it reads them and the others by exchanges.  Returns the two sums
+// of channel blockIdx.x * 4 + (threadIdx.x & 3) to the threads of row lane 0; the waves but the first return nothing.
+// What bounds these launches is the chain load -> tree -> coefficients -> store, each load a miss to memory behind a launch
+// that wrote from other dies, so nothing in it may wait for a second load: the channel's parameters are fetched with the
+// partials.
 constexpr int kMergeLanes = 64;
 typedef __attribute__((ext_vector_type(2))) double f64x2;
-__device__ inline void merge_partials(const double* __restrict__ part, int nblk, int C, double (&red)[kMergeLanes][4][2],
-                                      double* sa, double* sb)
+__device__ inline void merge_partials(const double* __restrict__ part, int nblk, int C, f64x2 (&red)[kMergeLanes * 4], double* sa, double* sb)
 {
-    const int cq = threadIdx.x & 3, r = threadIdx.x >> 2;
+    const int tid = threadIdx.x, cq = tid & 3, r = tid >> 2;
     const int c = blockIdx.x * 4 + cq;
     double a = 0.0, b = 0.0;
     if (c < C)
@@ -288,18 +369,17 @@ __device__ inline void merge_partials(const double* __restrict__ part, int nblk,
                 b += v[u][1];
             }
         }
-    red[r][cq][0] = a;
-    red[r][cq][1] = b;
+    red[tid] = f64x2{a, b};
     __syncthreads();
-    for (int w = kMergeLanes / 2; w > 0; w >>= 1) {
-        if (r < w) {
-            red[r][cq][0] += red[r + w][cq][0];
-            red[r][cq][1] += red[r + w][cq][1];
-        }
-        __syncthreads();
+    if (tid >= 64) return;
+    f64x2 t = (red[tid] + red[tid + 128]) + (red[tid + 64] + red[tid + 192]);
+#pragma unroll
+    for (int w = 32; w >= 4; w >>= 1) {
+        t[0] += __shfl_xor(t[0], w, 64);
+        t[1] += __shfl_xor(t[1], w, 64);
     }
-    *sa = red[0][cq][0];
-    *sb = red[0][cq][1];
+    *sa = t[0];
+    *sb = t[1];
 }
 
 // Forward: mean, invstd, coef = {scale, shift}.
@@ -313,7 +393,7 @@ __device__ inline void bn_forward_coef(double a, double b, double inv_M, float e
     const double mu = a * inv_M;
     double var = b * inv_M - mu * mu;
     if (var < 0.0) var = 0.0;
-    const double is = 1.0 / sqrt(var + (double)eps);
+    const double is = rsqrt(var + (double)eps);
     const double sc = (double)gamma * is;
     *scale = (float)sc;
     *shift = (float)((double)beta - mu * sc);
@@ -329,13 +409,15 @@ __global__ __launch_bounds__(kMergeLanes * 4) void bn_fwd_finalize_kernel(BnStat
                                                                           const float* __restrict__ gamma,
                                                                           const float* __restrict__ beta)
 {
-    __shared__ double red[kMergeLanes][4][2];
+    __shared__ f64x2 red[kMergeLanes * 4];
     const BnStatOut o = blockIdx.y ? o1 : o0;
+    const int c = blockIdx.x * 4 + (threadIdx.x & 3);
+    const bool mine = threadIdx.x < 4 && c < C;
+    const float ga = mine ? gamma[c] : 0.f, be = mine ? beta[c] : 0.f;
     double a, b;
     merge_partials(o.part, nblk, C, red, &a, &b);
-    const int c = blockIdx.x * 4 + (threadIdx.x & 3);
     float scale, shift;
-    if ((threadIdx.x >> 2) == 0 && c < C) bn_forward_coef(a, b, inv_M, eps, gamma[c], beta[c], o, c, C, true, &scale, &shift);
+    if (mine) bn_forward_coef(a, b, inv_M, eps, ga, be, o, c, C, true, &scale, &shift);
 }
 
 // Backward: dgamma, dbeta and dx = c1*dz - c2*x + c0 with
@@ -345,14 +427,21 @@ struct BnGradOut {
     const float *gamma, *mean, *invstd;
     float *dgamma, *dbeta, *coef;
 };
-__device__ inline void bn_backward_coef(double a, double b, double inv_M, const BnGradOut& o, int c, bool store, float* k1, float* k2,
-                                        float* k0)
+struct BnChannel {
+    float gamma, mean, invstd;
+};
+__device__ inline BnChannel bn_channel(const BnGradOut& o, bool mine, int c)
 {
-    const double c1 = (double)o.gamma[c] * (double)o.invstd[c];
-    const double c2 = c1 * (double)o.invstd[c] * b * inv_M;
+    return mine ? BnChannel{o.gamma[c], o.mean[c], o.invstd[c]} : BnChannel{};
+}
+__device__ inline void bn_backward_coef(double a, double b, double inv_M, const BnGradOut& o, const BnChannel& p, int c, bool store,
+                                        float* k1, float* k2, float* k0)
+{
+    const double c1 = (double)p.gamma * (double)p.invstd;
+    const double c2 = c1 * (double)p.invstd * b * inv_M;
     *k1 = (float)c1;
     *k2 = (float)c2;
-    *k0 = (float)(c2 * (double)o.mean[c] - c1 * a * inv_M);
+    *k0 = (float)(c2 * (double)p.mean - c1 * a * inv_M);
     if (store) {
         o.dbeta[c] = (float)a;
         o.dgamma[c] = (float)b;
@@ -360,11 +449,13 @@ __device__ inline void bn_backward_coef(double a, double b, double inv_M, const 
 }
 __global__ __launch_bounds__(kMergeLanes * 4) void bn_bwd_finalize_kernel(BnGradOut o, int nblk, int C, double inv_M)
 {
-    __shared__ double red[kMergeLanes][4][2];
+    __shared__ f64x2 red[kMergeLanes * 4];
+    const int c = blockIdx.x * 4 + (threadIdx.x & 3);
+    const bool mine = threadIdx.x < 4 && c < C;
+    const BnChannel p = bn_channel(o, mine, c);
     double a, b;
     merge_partials(o.part, nblk, C, red, &a, &b);
-    const int c = blockIdx.x * 4 + (threadIdx.x & 3);
-    if ((threadIdx.x >> 2) == 0 && c < C) bn_backward_coef(a, b, inv_M, o, c, true, o.coef + c, o.coef + C + c, o.coef + 2 * C + c);
+    if (mine) bn_backward_coef(a, b, inv_M, o, p, c, true, o.coef + c, o.coef + C + c, o.coef + 2 * C + c);
 }
 
 // y = [relu](scale*x + shift [+ res]); blockIdx.y selects the instance of a twin launch
@@ -454,29 +545,24 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(const T* __restr
 // while it merges.  Its first row block also leaves the statistics.  Consecutive work items (the groups of one run of rows,
 // which share cache lines and partial rows) go to one XCD.  The sums are taken in merge_partials' order (64 row lanes, then a
 // tree), so which of the two forms a shape takes does not show in the results.
-// Bound by latency.  Forward and backward with their sums, six launches against four: 2664 x 72 fp32 27.8 -> 20.9 us, 2048 x 16
+// Bound by latency: the partials and the first rows come from memory, the coefficients depend on the former and the stores on both.
+// Two rows in flight a thread and 256 workgroups: with four rows the registers leave one workgroup per compute unit, with 512
+// workgroups the partials are read twice as often (resnet20 1.5 %, resnet56 0.5 % slower).
+// Up to 127 channels, forward and backward with their sums, six launches against four: 2664 x 72 fp32 27.8 -> 20.9 us, 2048 x 16
 // fp32 27.7 -> 21.1.  The line lies where the gain ends inside a network, where other streams' kernels fill the chip during
 // the extra launch anyway while every workgroup's merge reads L2: with merging up to 8192 partials (rows x channels of a group)
-// and 32 MB resnet20 was 8 % slower and conv4_x 4.5 %, up to 4096 and 2 MB resnet20 still 1 %, a 2048 x 512 bf16 layer 3 %.
-constexpr int kMergeEntries = 2048;  // partial rows x channels of a group
-constexpr int64_t kMergeTensorBytes = (int64_t)3 << 19;
-constexpr int kBnThreads = 512;
-struct BnLayout {
-    int cg, groups;              // channels per group, groups
-    int rows_per_wg, row_blocks;
-};
-__device__ inline int bn_work_item(const BnLayout& L, int* g0)
-{
-    const unsigned b = blockIdx.x, nb = gridDim.x, q = nb / 8, r = nb % 8, xcd = b % 8;
-    const unsigned item = xcd * q + (xcd < r ? xcd : r) + b / 8;
-    *g0 = (int)(item % (unsigned)L.groups) * L.cg;
-    return (int)(item / (unsigned)L.groups);
-}
-
+// and 32 MB resnet20 was 8 % slower and conv4_x 4.5 %, up to 4096 and 2 MB resnet20 still 1 %.
+// From 128 channels on the sums are dealt out by channel groups and leave at most 2048 partials.  Forward / backward with sign
+// bytes, sums included: 12544 x 256 bf16 12.7 -> 10.3 / 14.7 -> 12.8 us, 4864 x 1024 bf16 18.8 -> 12.1 / 21.5 -> 15.4, 11956 x 256 fp32
+// 15.1 -> 11.9 / 18.6 -> 14.4; 107 calls of 128 to 2048 channels 1.16x, those near the far lines 1.00-1.07x; conv4_x driven by
+// separate calls 1856 -> 1774 us a step.  Groups of 64 bytes lose above 8 MB (36285 x 200 bf16, from y: 25.4 -> 27.9).  A convolution's rows are
+// merged up to 3072 partials: 38 rows of conv4_x at batch 19 (2432) gain 4 %, 256 rows x 16 channels (4096) of
+// resnet56 lose 0.5 %.
 // Sums of channel g0 + tid % CG to the threads of row group 0 (tid < CG).  Thread = (channel, row group rg of RG): it holds the
-// row lanes rg, rg + RG, .. of the 64; the lanes 32, 16, .. RG apart meet in its registers, the others in LDS.
+// row lanes rg, rg + RG, .. of the 64; the lanes 32, 16, .. RG apart meet in its registers, the others cross LDS behind one
+// barrier and meet in the first wave, eight of them as they are read, the rest by exchanges.
 template <int CG>
-__device__ inline void merge_group(const double* __restrict__ part, int nblk, int C, int g0, double (&red)[kBnThreads][2], double* sa,
+__device__ inline void merge_group(const double* __restrict__ part, int nblk, int C, int g0, f64x2 (&red)[kBnThreads], double* sa,
                                    double* sb)
 {
     constexpr int RG = kBnThreads / CG, NL = kMergeLanes / RG;
@@ -505,20 +591,22 @@ __device__ inline void merge_group(const double* __restrict__ part, int nblk, in
             a[j] += a[j + w];
             b[j] += b[j + w];
         }
-    red[tid][0] = a[0];
-    red[tid][1] = b[0];
+    red[tid] = f64x2{a[0], b[0]};
     __syncthreads();
-    for (int w = RG / 2; w > 0; w >>= 1) {
-        if (rg < w) {
-            red[tid][0] += red[tid + w * CG][0];
-            red[tid][1] += red[tid + w * CG][1];
-        }
-        __syncthreads();
+    if (tid >= 64) return;
+    // (lane tid reads the row groups tid / CG + (64 / CG) j of its channel)
+    const f64x2 s04 = red[tid] + red[tid + 256], s15 = red[tid + 64] + red[tid + 320], s26 = red[tid + 128] + red[tid + 384],
+                s37 = red[tid + 192] + red[tid + 448];
+    f64x2 t = (s04 + s26) + (s15 + s37);
+#pragma unroll
+    for (int w = 32; w >= CG; w >>= 1) {
+        t[0] += __shfl_xor(t[0], w, 64);
+        t[1] += __shfl_xor(t[1], w, 64);
     }
-    *sa = red[tid][0];
-    *sb = red[tid][1];
+    *sa = t[0];
+    *sb = t[1];
 }
-__device__ inline void merge_channels(const BnLayout& L, const double* part, int nblk, int C, int g0, double (&red)[kBnThreads][2],
+__device__ inline void merge_channels(const BnLayout& L, const double* part, int nblk, int C, int g0, f64x2 (&red)[kBnThreads],
                                       double* sa, double* sb)
 {
     if (L.cg == 64) merge_group<64>(part, nblk, C, g0, red, sa, sb);
@@ -532,7 +620,7 @@ __global__ __launch_bounds__(kBnThreads) void bn_fwd_merge_apply_kernel(BnApplyI
                                                                   const float* __restrict__ gamma, const float* __restrict__ beta)
 {
     typedef typename VecIO<T, VW>::Raw Raw;
-    __shared__ double red[kBnThreads][2];
+    __shared__ f64x2 red[kBnThreads];
     __shared__ float coef[2][64];
     const BnApplyIo io = blockIdx.y ? io1 : io0;
     const BnStatOut o = blockIdx.y ? o1 : o0;
@@ -545,7 +633,7 @@ __global__ __launch_bounds__(kBnThreads) void bn_fwd_merge_apply_kernel(BnApplyI
     const int cl = (tid % vpr) * VW, c0 = g0 + cl;
     const bool active = c0 < C;  // (channels come in whole vectors)
     const int64_t r_end = (int64_t)(rb + 1) * L.rows_per_wg < M ? (int64_t)(rb + 1) * L.rows_per_wg : M;
-    constexpr int U = 4;
+    constexpr int U = 2;
     int64_t r = (int64_t)rb * L.rows_per_wg + tid / vpr;
     Raw xr[U], rr[U];
     auto load = [&]() {
@@ -557,11 +645,12 @@ __global__ __launch_bounds__(kBnThreads) void bn_fwd_merge_apply_kernel(BnApplyI
             if (HAS_RES) rr[u] = VecIO<T, VW>::raw(res + ru * C + c0);
         }
     };
+    const bool mine = tid < L.cg && g0 + tid < C;
+    const float ga = mine ? gamma[g0 + tid] : 0.f, be = mine ? beta[g0 + tid] : 0.f;
     load();  // on their way while the partials are merged
     double a, b;
     merge_channels(L, o.part, nblk, C, g0, red, &a, &b);
-    if (tid < L.cg && g0 + tid < C)
-        bn_forward_coef(a, b, inv_M, eps, gamma[g0 + tid], beta[g0 + tid], o, g0 + tid, C, rb == 0, &coef[0][tid], &coef[1][tid]);
+    if (mine) bn_forward_coef(a, b, inv_M, eps, ga, be, o, g0 + tid, C, rb == 0, &coef[0][tid], &coef[1][tid]);
     __syncthreads();
     float sc[VW], sh[VW];
 #pragma unroll
@@ -606,7 +695,7 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_merge_apply_kernel(const T*
                                                                   int C, double inv_M, const float* __restrict__ fcoef)
 {
     typedef typename VecIO<T, VW>::Raw Raw;
-    __shared__ double red[kBnThreads][2];
+    __shared__ f64x2 red[kBnThreads];
     __shared__ float coef[3][64];
     int g0;
     const int rb = bn_work_item(L, &g0);
@@ -614,7 +703,7 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_merge_apply_kernel(const T*
     const int cl = (tid % vpr) * VW, c0 = g0 + cl;
     const bool active = c0 < C;
     const int64_t r_end = (int64_t)(rb + 1) * L.rows_per_wg < M ? (int64_t)(rb + 1) * L.rows_per_wg : M;
-    constexpr int U = 4;
+    constexpr int U = 2;
     int64_t r = (int64_t)rb * L.rows_per_wg + tid / vpr;
     Raw gr[U], xr[U], yr[U], pr[U], rr[U];
     uint32_t bits[U];
@@ -631,22 +720,25 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_merge_apply_kernel(const T*
             if (HAS_RES && RES_ACC) rr[u] = VecIO<T, VW>::raw(dres + ru * C + c0);
         }
     };
+    const bool mine = tid < L.cg && g0 + tid < C;
+    const BnChannel p = bn_channel(o, mine, g0 + tid);
+    float c1[VW], c2[VW], c3[VW], fsc[VW], fsh[VW];
+    if (RM == 2)
+#pragma unroll
+        for (int k = 0; k < VW; ++k) {
+            fsc[k] = active ? fcoef[c0 + k] : 0.f;
+            fsh[k] = active ? fcoef[C + c0 + k] : 0.f;
+        }
     load();
     double a, b;
     merge_channels(L, o.part, nblk, C, g0, red, &a, &b);
-    if (tid < L.cg && g0 + tid < C)
-        bn_backward_coef(a, b, inv_M, o, g0 + tid, rb == 0, &coef[0][tid], &coef[1][tid], &coef[2][tid]);
+    if (mine) bn_backward_coef(a, b, inv_M, o, p, g0 + tid, rb == 0, &coef[0][tid], &coef[1][tid], &coef[2][tid]);
     __syncthreads();
-    float c1[VW], c2[VW], c3[VW], fsc[VW], fsh[VW];
 #pragma unroll
     for (int k = 0; k < VW; ++k) {
         c1[k] = active ? coef[0][cl + k] : 0.f;
         c2[k] = active ? coef[1][cl + k] : 0.f;
         c3[k] = active ? coef[2][cl + k] : 0.f;
-        if (RM == 2) {
-            fsc[k] = active ? fcoef[c0 + k] : 0.f;
-            fsh[k] = active ? fcoef[C + c0 + k] : 0.f;
-        }
     }
     while (r < r_end) {
 #pragma unroll
@@ -936,19 +1028,34 @@ BnLayout bn_layout(int64_t M, int C, int VW, int64_t blocks)
     L.row_blocks = ceil_div(M, L.rows_per_wg);
     return L;
 }
-// Up to 512 workgroups over all groups and instances, fewer where a thread would get less than two vectors.
+// Up to 256 workgroups over all groups and instances, fewer where a thread would get less than two vectors.
 BnLayout merge_layout(int64_t M, int C, int VW, int instances)
 {
     const int cg = bn_channel_group(C, VW), groups = ceil_div(C, cg);
     const int64_t rpp = kBnThreads / (cg / VW);
-    int64_t blocks = (512 + groups * instances - 1) / (groups * instances);
+    int64_t blocks = (256 + groups * instances - 1) / (groups * instances);
     const int64_t most = (M + 2 * rpp - 1) / (2 * rpp);
     if (blocks > most) blocks = most;
     return bn_layout(M, C, VW, blocks < 1 ? 1 : blocks);
 }
+inline int64_t wide_tensor_bytes(int cg, int esz) { return cg * esz >= 128 ? kWideTensorBytes : kWideTensorBytes / 4; }
 inline bool merges(int64_t M, int C, int VW, int esz, int nblk)
 {
-    return M * C * esz <= kMergeTensorBytes && (int64_t)nblk * bn_channel_group(C, VW) <= kMergeEntries;
+    const int cg = bn_channel_group(C, VW);
+    const bool wide = C >= kWideChannels;
+    return M * C * esz <= (wide ? wide_tensor_bytes(cg, esz) : kMergeTensorBytes) &&
+           (int64_t)nblk * cg <= (wide ? kWideConvEntries : kMergeEntries);
+}
+// Work items of bn_group_sums_kernel: at most kMergeEntries / cg runs of rows, two rows a thread or more; false where the tensor has
+// too few channels or is too large for so few.
+bool group_sums_layout(int64_t M, int C, int VW, int esz, BnLayout* L)
+{
+    const int cg = bn_channel_group(C, VW), rpp = kBnThreads / (cg / VW);
+    int64_t runs = kMergeEntries / cg;
+    const int64_t most = (M + 2 * rpp - 1) / (2 * rpp);
+    if (runs > most) runs = most;
+    *L = bn_layout(M, C, VW, runs);
+    return C >= kWideChannels && M * C * esz <= wide_tensor_bytes(cg, esz) && (int64_t)L->rows_per_wg * cg * esz <= kWideRunBytes;
 }
 
 int plan_rows(int64_t M, const RowLayout& L, int* nblk)
@@ -983,8 +1090,15 @@ int bn_forward_t(const void* x, const void* res, void* y, const float* gamma, co
     const unsigned ni = tw ? 2 : 1;
     const dim3 grid(nblk, ceil_div(L.cv, L.cvb), ni);
     const double tensor_bytes = (double)M * C * sizeof(T) * ni;
+    BnLayout gl;
     if (presummed > 0) {
         nblk = presummed;
+    } else if (!stats_only && group_sums_layout(M, C, VW, sizeof(T), &gl)) {
+        nblk = gl.row_blocks;
+        ProfScope ps(sizeof(T) == 2 ? "bn_stats<bf16>" : "bn_stats<fp32>", tensor_bytes, 1);
+        DSP_LAUNCH(ps, (bn_group_sums_kernel<T, VW, 0, 0>), dim3((unsigned)(gl.groups * gl.row_blocks), ni), dim3(kBnThreads), 0, st,
+                   (const T*)x, (const T*)nullptr, (const T*)nullptr, (const float*)nullptr, (const float*)nullptr, buf.partial, M, C,
+                   gl, (const T*)(tw ? tw->x : nullptr), tw ? tw->buf.partial : nullptr, (const float*)nullptr);
     } else {
         ProfScope ps(sizeof(T) == 2 ? "bn_stats<bf16>" : "bn_stats<fp32>", tensor_bytes, 1);
         DSP_LAUNCH(ps, (bn_sums_kernel<T, VW, 0, 0>), grid, dim3(kThreads), 0, st, (const T*)x, (const T*)nullptr,
@@ -1044,9 +1158,17 @@ int bn_backward_t(const void* dy, const void* x, const void* y, void* dx, void* 
     const int rows = plan_rows(M, L, &nblk);
     const dim3 grid(nblk, ceil_div(L.cv, L.cvb));
     const double tensor_bytes = (double)M * C * sizeof(T);
+    BnLayout gl;
+    const bool grouped = group_sums_layout(M, C, VW, sizeof(T), &gl);
+    if (grouped) nblk = gl.row_blocks;
     {
         ProfScope ps(sizeof(T) == 2 ? "bn_bwd_reduce<bf16>" : "bn_bwd_reduce<fp32>", tensor_bytes * (RM == 1 ? 3 : 2) + (RM == 3 ? tensor_bytes / (VW * sizeof(T)) : 0.0), 1);
-        DSP_LAUNCH(ps, (bn_sums_kernel<T, VW, 1, RM>), grid, dim3(kThreads), 0, st, (const T*)x, (const T*)dy,
+        if (grouped)
+            DSP_LAUNCH(ps, (bn_group_sums_kernel<T, VW, 1, RM>), dim3((unsigned)(gl.groups * gl.row_blocks)), dim3(kBnThreads), 0, st,
+                       (const T*)x, (const T*)dy, (const T*)y, (const float*)buf.mean, (const float*)buf.invstd, buf.partial, M, C, gl,
+                       (const T*)nullptr, (double*)nullptr, fcoef);
+        else
+            DSP_LAUNCH(ps, (bn_sums_kernel<T, VW, 1, RM>), grid, dim3(kThreads), 0, st, (const T*)x, (const T*)dy,
                    (const T*)y, (const float*)buf.mean, (const float*)buf.invstd, buf.partial, M, C, L, rows,
                    (const T*)nullptr, (double*)nullptr, AddOut<T>{}, fcoef);
     }

@@ -151,6 +151,27 @@ def test_batch_norm_that_merges_its_partial_sums(shape, merged_fp32, merged_bf16
     assert not names & ({"bn_fwd_finalize", "bn_bwd_finalize"} if merged else {"bn_merge_apply_relu<%s>" % t, "bn_bwd_merge_apply<%s>" % t})
 
 
+# 128 channels and more: sums by channel groups, merged by the apply kernels
+WIDE_SHAPES = [
+    ((1, 128, 1, 1), True, True),       # one row
+    ((3, 129, 5, 7), True, True),       # element-wise path, one channel in the last group
+    ((5, 136, 31, 33), True, True),     # groups that do not divide the channels
+    ((2, 1032, 9, 9), True, True),      # many groups, the last one short
+    ((64, 256, 32, 12), True, True),    # the longest runs in bf16 (96 KB of a group)
+    ((3, 256, 8193, 1), True, False),   # a few rows more
+    ((8, 200, 75, 61), True, False),    # 64-byte groups in bf16, 14 MB
+    ((2, 160, 131, 201), False, False), # above 32 MB in fp32, longer runs in bf16
+]
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+@pytest.mark.parametrize("shape,merged_fp32,merged_bf16", WIDE_SHAPES, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else "")
+def test_batch_norm_sums_by_channel_groups(shape, merged_fp32, merged_bf16, dtype):
+    test_batch_norm_that_merges_its_partial_sums(shape, merged_fp32, merged_bf16, dtype)
+    if shape[1] % 8 == 0:
+        test_batch_norm_relu_decided_from_sign_bytes(shape, dtype, True)
+
+
 @pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
 @pytest.mark.parametrize("shape", [(3, 24, 7, 5), (4, 16, 32, 32), (2, 2048, 3, 3), (32, 64, 56, 56)], ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("res", [True, False], ids=["res", "nores"])
