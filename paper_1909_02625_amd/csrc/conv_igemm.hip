@@ -20,6 +20,7 @@
 
 #include <atomic>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -230,6 +231,26 @@ struct GatherGeom {
     double* stats1;
 };
 
+// The four parity classes of a stride-2 backward-data as one launch (blockIdx.y): what differs between them.
+struct ClassGeom {
+    int Ho, Wo, R, S, pad_h, pad_w, M, Kdim, s_inv, oh_off, ow_off;
+    uint32_t wo_mul, wo_sh, ho_mul, ho_sh;
+    uint32_t w_off;  // first element of the class's filters
+};
+struct ClassSet {
+    GatherGeom g;
+    ClassGeom cls[4];
+};
+__device__ inline GatherGeom class_geom(const ClassSet& c, int q)
+{
+    GatherGeom g = c.g;
+    const ClassGeom& k = c.cls[q];
+    g.Ho = k.Ho; g.Wo = k.Wo; g.R = k.R; g.S = k.S; g.pad_h = k.pad_h; g.pad_w = k.pad_w; g.M = k.M; g.Kdim = k.Kdim; g.s_inv = k.s_inv;
+    g.oh_off = k.oh_off; g.ow_off = k.ow_off;
+    g.wo_mul = k.wo_mul; g.wo_sh = k.wo_sh; g.ho_mul = k.ho_mul; g.ho_sh = k.ho_sh;
+    return g;
+}
+
 // 16-byte loads through a buffer descriptor: the hardware returns zeros for any offset at or past
 // `bytes`, so padding taps, rows past the end of the tensor and the k tail need no branch and no
 // zero fill -- the lane just presents an out-of-range offset.
@@ -271,28 +292,27 @@ __device__ inline unsigned xcd_tile(unsigned b, unsigned nb)
     return xcd * q + (xcd < r ? xcd : r) + idx;
 }
 
+// (in, out, stats: of the instance at hand; block, blocks: of the launch's tiles; group, groups: of a grouped convolution)
 template <typename TL, bool VEC, bool DIL>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::MIN_WAVES))) void conv_gather_gemm_kernel(const typename TL::T* __restrict__ in_,
-                                                                    const typename TL::T* __restrict__ wgt,
-                                                                    typename TL::T* __restrict__ out_, GatherGeom g)
+__device__ __forceinline__ void gather_gemm_tile(const typename TL::T* __restrict__ in, const typename TL::T* __restrict__ wgt,
+                                                 typename TL::T* __restrict__ out, double* stats, const GatherGeom& g, unsigned block,
+                                                 unsigned blocks, int group, int groups)
 {
     typedef typename TL::T T;
     constexpr int E = TL::E, CPR = TL::CPR, ROWS_PER_PASS = kThreads / CPR;
     constexpr uint32_t SZ = sizeof(T);
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const T* __restrict__ in = blockIdx.y ? (const T*)g.in1 : in_;
-    T* __restrict__ out = blockIdx.y ? (T*)g.out1 : out_;
-    double* stats = blockIdx.y ? g.stats1 : g.stats;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wave_m = wave / TL::WGN, wave_n = wave % TL::WGN;
     // consecutive workgroups share the same rows of `in` and sweep the output channels
     const int tiles_n = (g.Co + TL::BN - 1) / TL::BN;
-    const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
+    const unsigned tile = xcd_tile(block, blocks);
     const int m0 = (tile / tiles_n) * TL::BM, n0 = (tile % tiles_n) * TL::BN;
     // grouped convolution: this workgroup's group reads channels [in_c0, in_c0 + Ci) of rows Cis wide and writes
     // channels [out_c0, out_c0 + Co) of rows Cos wide, with the filters of output channels out_c0 ..
-    const int in_c0 = blockIdx.z * g.Ci, out_c0 = blockIdx.z * g.Co;
+    const int in_c0 = group * g.Ci, out_c0 = group * g.Co;
+    if (m0 >= g.M) return;  // (a class with fewer tiles than the launch has for each)
 
     const int kc = tid % CPR;    // which 16-byte run of the k tile this thread moves
     const int row0 = tid / CPR;  // first tile row it moves; further rows are +ROWS_PER_PASS apart
@@ -342,7 +362,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::MI
         b_off[i] = (row < TL::BN && co < g.Co) ? (uint32_t)((out_c0 + co) * g.Kdim) * SZ : kOutOfRange;
     }
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(in, (uint32_t)g.N * g.Hi * g.Wi * g.Cis * SZ);
-    const __amdgpu_buffer_rsrc_t rw = make_rsrc(wgt, (uint32_t)gridDim.z * g.Co * g.Kdim * SZ);
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(wgt, (uint32_t)groups * g.Co * g.Kdim * SZ);
 
     // k position of this thread's run in k tile kt: element kk = kt*BK + kc*E = (kr*S + ks)*Ci + kci
     const T zero = from_float<T>(0.f);
@@ -581,6 +601,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::MI
     }
 }
 
+template <typename TL, bool VEC, bool DIL>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::MIN_WAVES))) void conv_gather_gemm_kernel(
+    const typename TL::T* __restrict__ in, const typename TL::T* __restrict__ wgt, typename TL::T* __restrict__ out, GatherGeom g)
+{
+    typedef typename TL::T T;
+    gather_gemm_tile<TL, VEC, DIL>(blockIdx.y ? (const T*)g.in1 : in, wgt, blockIdx.y ? (T*)g.out1 : out, blockIdx.y ? g.stats1 : g.stats, g,
+                                   blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
+}
+template <typename TL>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::MIN_WAVES))) void conv_gather_classes_kernel(
+    const typename TL::T* __restrict__ in, const typename TL::T* __restrict__ wgt, typename TL::T* __restrict__ out, ClassSet c)
+{
+    const GatherGeom g = class_geom(c, blockIdx.y);
+    gather_gemm_tile<TL, true, false>(in, wgt + c.cls[blockIdx.y].w_off, out, nullptr, g, blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
+}
+
 // ---- bf16 gather-GEMM fed by direct global -> LDS loads ---------------------------------------------
 // For bf16 layers whose gathered channel count (of one group) is a multiple of a k tile (64 or 32 elements, so that a k
 // tile lies inside one filter tap) the operands need no detour through registers: `buffer_load ... lds` moves 16 bytes
@@ -650,28 +686,26 @@ __device__ inline void dma16_at(__amdgpu_buffer_rsrc_t r, char* lds_wave_base, u
 }
 
 template <typename TL>
-__global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL::WAVES, TL::WAVES))) void conv_dma_gemm_kernel(
-    const bf16_t* __restrict__ in_, const bf16_t* __restrict__ wgt, bf16_t* __restrict__ out_, GatherGeom g)
+__device__ __forceinline__ void dma_gemm_tile(const bf16_t* __restrict__ in, const bf16_t* __restrict__ wgt, bf16_t* __restrict__ out,
+                                              double* stats, const GatherGeom& g, unsigned block, unsigned blocks, int group, int groups)
 {
     typedef bf16_t T;
     constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN, NKS = TL::NKS, ST = TL::STAGES;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const T* __restrict__ in = blockIdx.y ? (const T*)g.in1 : in_;
-    T* __restrict__ out = blockIdx.y ? (T*)g.out1 : out_;
-    double* stats = blockIdx.y ? g.stats1 : g.stats;
 
     const int tid = threadIdx.x, lane = tid & 63, wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = TL::KG == 1 ? wave_id : wave_id % TL::NW, kgrp = TL::KG == 1 ? 0 : wave_id / TL::NW;
     const int wave_m = wave / TL::WGN, wave_n = wave % TL::WGN;
     const int tiles_n = (g.Co + BN - 1) / BN;
-    const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
+    const unsigned tile = xcd_tile(block, blocks);
     // consecutive tiles (which meet in one XCD's L2) sweep the output channels of the same input rows, or, where the
     // filters are the larger operand, the rows of the same output channels
-    const unsigned tiles_m = gridDim.x / tiles_n;
+    const unsigned tiles_m = (unsigned)((g.M + BM - 1) / BM);
+    if (tile >= tiles_m * tiles_n) return;  // (a class with fewer tiles than the launch has for each)
     const unsigned tile_m = g.n_major ? tile % tiles_m : tile / tiles_n, tile_n = g.n_major ? tile / tiles_m : tile % tiles_n;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     char* const ring = smem + kgrp * TL::RING_BYTES;
-    const int in_c0 = blockIdx.z * g.Ci, out_c0 = blockIdx.z * g.Co;  // grouped convolution: as in the kernel above
+    const int in_c0 = group * g.Ci, out_c0 = group * g.Co;  // grouped convolution: as in the kernel above
 
     // loader state: this lane owns position (lane % CPR) of row (lane / CPR) of each 1 KB row group its wave loads.  Row
     // group i of the wave is instruction wave * LOADS + i of the k tile: input rows first, then filter rows.
@@ -708,7 +742,7 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
             if (!TL::GEN) l_base[i] += (uint32_t)(lpos ^ TL::swz(row)) * 16u;
         }
     }
-    const uint32_t in_bytes = (uint32_t)g.N * g.Hi * g.Wi * g.Cis * 2u, w_bytes = (uint32_t)gridDim.z * g.Co * g.Kdim * 2u;
+    const uint32_t in_bytes = (uint32_t)g.N * g.Hi * g.Wi * g.Cis * 2u, w_bytes = (uint32_t)groups * g.Co * g.Kdim * 2u;
     const bool wave_in = wave * TL::LOADS < TL::A_INST;
     const __amdgpu_buffer_rsrc_t rwave = make_rsrc(wave_in ? (const void*)in : (const void*)wgt, wave_in ? in_bytes : w_bytes);
     const __amdgpu_buffer_rsrc_t rw = make_rsrc(wgt, w_bytes);
@@ -964,6 +998,21 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
             dst[1] = b;
         }
     }
+}
+
+template <typename TL>
+__global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL::WAVES, TL::WAVES))) void conv_dma_gemm_kernel(
+    const bf16_t* __restrict__ in, const bf16_t* __restrict__ wgt, bf16_t* __restrict__ out, GatherGeom g)
+{
+    dma_gemm_tile<TL>(blockIdx.y ? (const bf16_t*)g.in1 : in, wgt, blockIdx.y ? (bf16_t*)g.out1 : out, blockIdx.y ? g.stats1 : g.stats, g,
+                      blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
+}
+template <typename TL>
+__global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL::WAVES, TL::WAVES))) void conv_dma_classes_kernel(
+    const bf16_t* __restrict__ in, const bf16_t* __restrict__ wgt, bf16_t* __restrict__ out, ClassSet c)
+{
+    const GatherGeom g = class_geom(c, blockIdx.y);
+    dma_gemm_tile<TL>(in, wgt + c.cls[blockIdx.y].w_off, out, nullptr, g, blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
 }
 
 // ---- the same contraction as one stream of k tiles over several output tiles (256 x 128 tile) -----------------------
@@ -3234,6 +3283,33 @@ const char* tile_name()
     return name.text;
 }
 
+// The register-staged tile of an id of select_gather_tile
+template <typename TL>
+struct TileTag {
+    typedef TL Type;
+};
+template <typename T, typename F>
+int with_gather_tile(int id, int kdim, F f)
+{
+    constexpr int KB = 128;  // bytes of k per LDS row of the large tiles: 64 bf16 / 32 floats
+    switch (id) {
+    case 0: return f(TileTag<Tile<T, 16, 4, 1, 4, 1, 64, 2>>());
+    case 1: return f(TileTag<Tile<T, 16, 4, 1, 1, 1, 64, 2>>());
+    case 2: return f(TileTag<Tile<T, 32, 4, 1, 2, 1, 64, 2>>());
+    case 3: return f(TileTag<Tile<T, 32, 4, 1, 1, 1, 128, 2>>());
+    case 4:
+        // short contractions (1x1 filters over few channels) of bf16: 32-deep k steps and three workgroups per
+        // compute unit; the two-tile prologue is half as long and the epilogues of more workgroups overlap
+        if (sizeof(T) == 2 && kdim <= 512) return f(TileTag<Tile<T, 32, 2, 2, 2, 2, 64, 2>>());
+        return f(TileTag<Tile<T, 32, 2, 2, 2, 2, KB, 2>>());
+    case 5: return f(TileTag<Tile<T, 32, 2, 2, 2, 1, KB, 2>>());
+    case 6: return f(TileTag<Tile<T, 32, 2, 2, 1, 1, KB, 2>>());
+    case 7: return f(TileTag<Tile<T, 16, 4, 1, 1, 2, 128, 2>>());
+    case 10: return f(TileTag<Tile<T, 32, 4, 1, 2, 2, 64, 2>>());
+    default: return f(TileTag<Tile<T, 16, 2, 2, 1, 1, 256, 2>>());
+    }
+}
+
 template <typename TL, bool VEC, bool DIL>
 int run_gather(const GatherGeom& g, const void* in, const void* w, void* out, hipStream_t st, double flops)
 {
@@ -3434,6 +3510,17 @@ int select_gather_tile(const GatherGeom& g, int* bm)
 }
 
 template <typename TL>
+const char* dma_tile_name()
+{
+    static const KernelName name = [] {
+        KernelName k;
+        snprintf(k.text, sizeof(k.text), "conv_dma_gemm<bf16,BM%d,BN%d,BK%d,%dx%d waves%s>", TL::BM, TL::BN, TL::BK, TL::NW, TL::KG,
+                 TL::GEN ? ",any Ci" : "");
+        return k;
+    }();
+    return name.text;
+}
+template <typename TL>
 int run_dma(GatherGeom g, const void* in, const void* w, void* out, hipStream_t st, double flops)
 {
     const int64_t tiles = (int64_t)ceil_div(g.M, TL::BM) * ceil_div(g.Co, TL::BN);
@@ -3445,14 +3532,8 @@ int run_dma(GatherGeom g, const void* in, const void* w, void* out, hipStream_t 
         DSP_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
         attr_done = true;
     }
-    static const KernelName name = [] {
-        KernelName k;
-        snprintf(k.text, sizeof(k.text), "conv_dma_gemm<bf16,BM%d,BN%d,BK%d,%dx%d waves%s>", TL::BM, TL::BN, TL::BK, TL::NW, TL::KG,
-                 TL::GEN ? ",any Ci" : "");
-        return k;
-    }();
     {
-        ProfScope ps(name.text, flops, 0);
+        ProfScope ps(dma_tile_name<TL>(), flops, 0);
         DSP_LAUNCH(ps, kern, dim3((unsigned)tiles, g.in1 ? 2 : 1, (unsigned)g.groups), dim3(TL::THREADS), TL::LDS_BYTES, st,
                    (const bf16_t*)in, (const bf16_t*)w, (bf16_t*)out, g);
     }
@@ -3506,32 +3587,41 @@ int run_dma_stream(GatherGeom g, const void* in, const void* w, void* out, hipSt
     return DSP_OK;
 }
 
-int dispatch_dma(int id, const GatherGeom& g, const void* in, const void* w, void* out, hipStream_t st, double flops)
+// The direct-to-LDS tile of an id of select_dma_tile
+typedef DmaTile<256, 128, 4, 2, 128, 3, 2> StreamTile;
+template <typename F>
+int with_dma_tile(int id, F f)
 {
     switch (id) {
-    case kDmaId + 0: return run_dma<DmaTile<256, 256, 2, 4, 64, 4, 2>>(g, in, w, out, st, flops);
-    case kDmaId + 1: {
-        typedef DmaTile<256, 128, 4, 2, 128, 3, 2> TL;
-        return streams<TL>(g) ? run_dma_stream<TL>(g, in, w, out, st, flops) : run_dma<TL>(g, in, w, out, st, flops);
+    case kDmaId + 0: return f(TileTag<DmaTile<256, 256, 2, 4, 64, 4, 2>>());
+    case kDmaId + 1: return f(TileTag<StreamTile>());
+    case kDmaId + 2: return f(TileTag<DmaTile<256, 128, 2, 2, 64, 3, 2>>());
+    case kDmaId + 3: return f(TileTag<DmaTile<128, 128, 2, 4, 64, 4, 4>>());
+    case kDmaId + 4: return f(TileTag<DmaTile<128, 128, 2, 4, 128, 4, 2>>());
+    case kDmaId + 5: return f(TileTag<DmaTile<128, 64, 2, 2, 128, 3, 2>>());
+    case kDmaId + 6: return f(TileTag<DmaTile<128, 64, 4, 1, 64, 4, 3>>());
+    case kDmaId + 7: return f(TileTag<DmaTile<256, 64, 4, 1, 64, 4, 2>>());
+    case kDmaId + 8: return f(TileTag<DmaTile<64, 64, 2, 2, 128, 4, 2>>());
+    case kDmaId + 9: return f(TileTag<DmaTile<64, 64, 2, 2, 128, 4, 2, 2>>());
+    case kDmaId + 10: return f(TileTag<DmaTile<32, 32, 1, 1, 64, 4, 2, 8>>());
+    case kDmaGenId + 0: return f(TileTag<DmaTile<256, 256, 2, 4, 64, 4, 2, 1, true>>());
+    case kDmaGenId + 1: return f(TileTag<DmaTile<256, 128, 2, 2, 64, 3, 2, 1, true>>());
+    case kDmaGenId + 2: return f(TileTag<DmaTile<128, 128, 2, 4, 64, 4, 4, 1, true>>());
+    case kDmaGenId + 3: return f(TileTag<DmaTile<64, 64, 2, 2, 64, 4, 4, 1, true>>());
+    case kDmaGenId + 4: return f(TileTag<DmaTile<64, 64, 2, 2, 64, 4, 2, 2, true>>());
+    case kDmaGenId + 5: return f(TileTag<DmaTile<32, 32, 1, 1, 64, 4, 2, 8, true>>());
+    case kDmaGenId + 6: return f(TileTag<DmaTile<128, 32, 2, 1, 64, 4, 2, 2, true>>());
+    default: return f(TileTag<DmaTile<64, 32, 2, 1, 64, 4, 2, 2, true>>());
     }
-    case kDmaId + 2: return run_dma<DmaTile<256, 128, 2, 2, 64, 3, 2>>(g, in, w, out, st, flops);
-    case kDmaId + 3: return run_dma<DmaTile<128, 128, 2, 4, 64, 4, 4>>(g, in, w, out, st, flops);
-    case kDmaId + 4: return run_dma<DmaTile<128, 128, 2, 4, 128, 4, 2>>(g, in, w, out, st, flops);
-    case kDmaId + 5: return run_dma<DmaTile<128, 64, 2, 2, 128, 3, 2>>(g, in, w, out, st, flops);
-    case kDmaId + 6: return run_dma<DmaTile<128, 64, 4, 1, 64, 4, 3>>(g, in, w, out, st, flops);
-    case kDmaId + 7: return run_dma<DmaTile<256, 64, 4, 1, 64, 4, 2>>(g, in, w, out, st, flops);
-    case kDmaId + 8: return run_dma<DmaTile<64, 64, 2, 2, 128, 4, 2>>(g, in, w, out, st, flops);
-    case kDmaId + 9: return run_dma<DmaTile<64, 64, 2, 2, 128, 4, 2, 2>>(g, in, w, out, st, flops);
-    case kDmaId + 10: return run_dma<DmaTile<32, 32, 1, 1, 64, 4, 2, 8>>(g, in, w, out, st, flops);
-    case kDmaGenId + 0: return run_dma<DmaTile<256, 256, 2, 4, 64, 4, 2, 1, true>>(g, in, w, out, st, flops);
-    case kDmaGenId + 1: return run_dma<DmaTile<256, 128, 2, 2, 64, 3, 2, 1, true>>(g, in, w, out, st, flops);
-    case kDmaGenId + 2: return run_dma<DmaTile<128, 128, 2, 4, 64, 4, 4, 1, true>>(g, in, w, out, st, flops);
-    case kDmaGenId + 3: return run_dma<DmaTile<64, 64, 2, 2, 64, 4, 4, 1, true>>(g, in, w, out, st, flops);
-    case kDmaGenId + 4: return run_dma<DmaTile<64, 64, 2, 2, 64, 4, 2, 2, true>>(g, in, w, out, st, flops);
-    case kDmaGenId + 5: return run_dma<DmaTile<32, 32, 1, 1, 64, 4, 2, 8, true>>(g, in, w, out, st, flops);
-    case kDmaGenId + 6: return run_dma<DmaTile<128, 32, 2, 1, 64, 4, 2, 2, true>>(g, in, w, out, st, flops);
-    default: return run_dma<DmaTile<64, 32, 2, 1, 64, 4, 2, 2, true>>(g, in, w, out, st, flops);
-    }
+}
+int dispatch_dma(int id, const GatherGeom& g, const void* in, const void* w, void* out, hipStream_t st, double flops)
+{
+    return with_dma_tile(id, [&](auto t) -> int {
+        typedef typename decltype(t)::Type TL;
+        if constexpr (std::is_same<TL, StreamTile>::value)
+            if (streams<TL>(g)) return run_dma_stream<TL>(g, in, w, out, st, flops);
+        return run_dma<TL>(g, in, w, out, st, flops);
+    });
 }
 
 int run_c64(const GatherGeom& g, const void* in, const void* w, void* out, hipStream_t st, double flops)
@@ -3601,7 +3691,6 @@ int dispatch_gather(GatherGeom g, bool accum, const void* in, const void* w, voi
     // (partial rows are planned for aligned tensors)
     DSP_REQUIRE(g.stats == nullptr || !direct_eligible<T>(g, nullptr, nullptr), DSP_EINVAL,
                 "conv forward with column sums: x, w and y must be 16-byte aligned");
-    constexpr int KB = 128;  // bytes of k per LDS row of the large tiles: 64 bf16 / 32 floats
     // 16-byte gathers need channel runs of E elements and 16-byte aligned bases; the per-row tap masks
     // hold up to 64 taps (larger filters, and dilated gathers of more than 32 taps, take the generic path)
     const bool vec = (g.Ci % E) == 0 && ((uintptr_t)in % 16) == 0 && ((uintptr_t)w % 16) == 0 &&
@@ -3636,22 +3725,61 @@ int dispatch_gather(GatherGeom g, bool accum, const void* in, const void* w, voi
         else if (tile_count(g, 64, 64) >= kEnoughTiles) id = 6;
         else id = 8;
     }
-    switch (id) {
-    case 0: return run_gather_v<Tile<T, 16, 4, 1, 4, 1, 64, 2>>(g, vec, in, w, out, st, flops);
-    case 1: return run_gather_v<Tile<T, 16, 4, 1, 1, 1, 64, 2>>(g, vec, in, w, out, st, flops);
-    case 2: return run_gather_v<Tile<T, 32, 4, 1, 2, 1, 64, 2>>(g, vec, in, w, out, st, flops);
-    case 3: return run_gather_v<Tile<T, 32, 4, 1, 1, 1, 128, 2>>(g, vec, in, w, out, st, flops);
-    case 4:
-        // short contractions (1x1 filters over few channels) of bf16: 32-deep k steps and three workgroups per
-        // compute unit; the two-tile prologue is half as long and the epilogues of more workgroups overlap
-        if (sizeof(T) == 2 && g.Kdim <= 512) return run_gather_v<Tile<T, 32, 2, 2, 2, 2, 64, 2>>(g, vec, in, w, out, st, flops);
-        return run_gather_v<Tile<T, 32, 2, 2, 2, 2, KB, 2>>(g, vec, in, w, out, st, flops);
-    case 5: return run_gather_v<Tile<T, 32, 2, 2, 2, 1, KB, 2>>(g, vec, in, w, out, st, flops);
-    case 6: return run_gather_v<Tile<T, 32, 2, 2, 1, 1, KB, 2>>(g, vec, in, w, out, st, flops);
-    case 7: return run_gather_v<Tile<T, 16, 4, 1, 1, 2, 128, 2>>(g, vec, in, w, out, st, flops);
-    case 10: return run_gather_v<Tile<T, 32, 4, 1, 2, 2, 64, 2>>(g, vec, in, w, out, st, flops);
-    default: return run_gather_v<Tile<T, 16, 2, 2, 1, 1, 256, 2>>(g, vec, in, w, out, st, flops);
+    return with_gather_tile<T>(id, g.Kdim, [&](auto t) { return run_gather_v<typename decltype(t)::Type>(g, vec, in, w, out, st, flops); });
+}
+
+// n parity classes of a stride-2 backward-data in one launch: a grid row each, as many tiles as the largest has.
+template <typename K>
+int run_classes(K kern, const char* name, const ClassSet& c, int n, int bm, int bn, int threads, int lds, const void* in, const void* w,
+                void* out, hipStream_t st, double flops)
+{
+    int64_t tiles = 0;
+    for (int q = 0; q < n; ++q) {
+        const int64_t t = (int64_t)ceil_div(c.cls[q].M, bm) * ceil_div(c.g.Co, bn);
+        if (t > tiles) tiles = t;
     }
+    DSP_REQUIRE(tiles > 0 && tiles < (1ll << 31), DSP_EINVAL, "conv: bad tile count");
+    {
+        ProfScope ps(name, flops, 0);
+        kern(ps, dim3((unsigned)tiles, (unsigned)n, (unsigned)c.g.groups), dim3(threads), lds, st, in, w, out, c);
+    }
+    DSP_HIP(hipGetLastError());
+    return DSP_OK;
+}
+// all: the classes as one problem, for the choice of a tile
+template <typename T>
+int dispatch_classes(ClassSet& c, int n, GatherGeom all, const void* in, const void* w, void* out, hipStream_t st, double flops)
+{
+    int bm;
+    const int id = select_gather_tile<T>(all, &bm);
+    if constexpr (sizeof(T) == 2)
+        if (id >= kDmaId) {
+            c.g.n_major = (int64_t)all.Co * all.Kdim > (int64_t)all.N * all.Hi * all.Wi * all.Ci;
+            return with_dma_tile(id, [&](auto t) -> int {
+                typedef typename decltype(t)::Type TL;
+                static std::atomic<bool> attr_done{false};
+                if (!attr_done) {
+                    DSP_HIP(hipFuncSetAttribute((const void*)conv_dma_classes_kernel<TL>, hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
+                    attr_done = true;
+                }
+                auto launch = [](ProfScope& ps, dim3 grid, dim3 block, int lds, hipStream_t s, const void* i, const void* f, void* o, const ClassSet& k) {
+                    DSP_LAUNCH(ps, conv_dma_classes_kernel<TL>, grid, block, lds, s, (const bf16_t*)i, (const bf16_t*)f, (bf16_t*)o, k);
+                };
+                return run_classes(launch, dma_tile_name<TL>(), c, n, TL::BM, TL::BN, TL::THREADS, TL::LDS_BYTES, in, w, out, st, flops);
+            });
+        }
+    return with_gather_tile<T>(id, all.Kdim, [&](auto t) -> int {
+        typedef typename decltype(t)::Type TL;
+        static std::atomic<bool> attr_done{false};
+        if (!attr_done && TL::LDS_BYTES > 48 * 1024) {
+            DSP_HIP(hipFuncSetAttribute((const void*)conv_gather_classes_kernel<TL>, hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES));
+            attr_done = true;
+        }
+        auto launch = [](ProfScope& ps, dim3 grid, dim3 block, int lds, hipStream_t s, const void* i, const void* f, void* o, const ClassSet& k) {
+            DSP_LAUNCH(ps, conv_gather_classes_kernel<TL>, grid, block, lds, s, (const T*)i, (const T*)f, (T*)o, k);
+        };
+        return run_classes(launch, tile_name<TL, true, false>(), c, n, TL::BM, TL::BN, kThreads, TL::LDS_BYTES, in, w, out, st, flops);
+    });
 }
 
 template <typename TL, bool VEC>
@@ -4131,26 +4259,72 @@ int launch_conv_backward_data(int dtype, const ConvShape& c, const void* dy, con
                                  : dispatch_gather<float>(g, accumulate, dy, wt, dx, st, flops);
     }
     // stride 2: one dense problem per parity class of the input pixel (hi % 2, wi % 2); together they perform exactly
-    // the multiply-accumulates of the definition (none on the zeros between the strided gradient's pixels)
+    // the multiply-accumulates of the definition (none on the zeros between the strided gradient's pixels).  All classes go in one
+    // launch, a grid row each, the longest contraction first: as four launches in a row each but the first waits for the last
+    // workgroup of the one before, and classes of a quarter of the map fill the chip only together.  90 layers, four launches
+    // -> one: 1.56x (fp32 1.48, bf16 1.65); 37 x 23x17, 40 -> 72 fp32 21.6 -> 9.7 us, 256 x 56x56, 64 -> 128 bf16 98.5 -> 70.1,
+    // 256 x 14x14, 256 -> 512 bf16 52.6 -> 49.5.  A single class (1x1, accumulating) and tensors that are not read in whole 16-byte
+    // runs take the plain launches, and so do classes that each are more than two rounds of streamed tiles, whose loads run on from
+    // tile to tile (910 x 27x25, 72 -> 512: 246.6 us as four, 246.4 as one; 512 x 28x28, 128 -> 256, two rounds each: 106.5 and 90.5).
     DgradClass cls[4];
     dgrad_classes(c, cls);
-    double taps = 0;
-    for (const DgradClass& k : cls) taps += (double)k.Rc * k.Sc * k.Hc * k.Wc;
+    const size_t esz = dtype_size(dtype);
+    const int E = 16 / (int)esz;
+    GatherGeom gq[4];
+    double macs[4], taps = 0;  // of a class; of all
+    int order[4], n = 0;       // the classes that have work, the largest first
     for (int q = 0; q < 4; ++q) {
         const DgradClass& k = cls[q];
-        if (k.Hc == 0 || k.Wc == 0) continue;
+        macs[q] = (double)k.Rc * k.Sc * k.Hc * k.Wc;
+        taps += macs[q];
         const bool empty = k.Rc == 0 || k.Sc == 0;  // no tap reaches these pixels: their gradient is zero
-        if (empty && accumulate) continue;
-        GatherGeom g = make_geom(c.N, c.Ho, c.Wo, Cog, k.Hc, k.Wc, Cig, empty ? 1 : k.Rc, empty ? 1 : k.Sc, -k.off_h,
-                                 -k.off_w, 1, 1);
+        if (k.Hc == 0 || k.Wc == 0 || (empty && accumulate)) continue;
+        GatherGeom& g = gq[q];
+        g = make_geom(c.N, c.Ho, c.Wo, Cog, k.Hc, k.Wc, Cig, empty ? 1 : k.Rc, empty ? 1 : k.Sc, -k.off_h, -k.off_w, 1, 1);
         set_groups(g, G, c.Cout, c.Cin);
         if (empty) g.Kdim = 0;
         g.oh_mul = 2; g.ow_mul = 2; g.oh_off = q >> 1; g.ow_off = q & 1; g.OH = c.H; g.OW = c.W;
-        const size_t esz = dtype_size(dtype);
-        const void* wq = (const char*)wt + k.wt_off * esz;
-        const double fq = taps > 0 ? flops * ((double)k.Rc * k.Sc * k.Hc * k.Wc / taps) : 0.0;
-        DSP_TRY(dtype == DSP_BF16 ? dispatch_gather<bf16_t>(g, accumulate, dy, wq, dx, st, fq)
-                                  : dispatch_gather<float>(g, accumulate, dy, wq, dx, st, fq));
+        int at = n++;
+        for (; at > 0 && macs[order[at - 1]] < macs[q]; --at) order[at] = order[at - 1];
+        order[at] = q;
+    }
+    const bool vec = Cog % E == 0 && Cig % E == 0 && (uintptr_t)dy % 16 == 0 && (uintptr_t)wt % 16 == 0 && (uintptr_t)dx % 16 == 0 &&
+                     c.R * c.S <= 64;
+    bool long_streams = dtype == DSP_BF16;
+    for (int i = 0; i < n && long_streams; ++i)
+        long_streams = select_dma_tile<bf16_t>(gq[order[i]]) == kDmaId + 1 &&
+                       tile_count(gq[order[i]], StreamTile::BM, StreamTile::BN) > 2 * kComputeUnits;
+    if (n > 1 && vec && !long_streams) {
+        ClassSet cs{};
+        cs.g = gq[order[0]];
+        cs.g.accum = accumulate ? 1 : 0;
+        cs.g.out_vec = 1;
+        double work = 0;
+        for (int i = 0; i < n; ++i) {
+            const GatherGeom& g = gq[order[i]];
+            ClassGeom& k = cs.cls[i];
+            k.Ho = g.Ho; k.Wo = g.Wo; k.R = g.R; k.S = g.S; k.pad_h = g.pad_h; k.pad_w = g.pad_w; k.M = g.M; k.Kdim = g.Kdim; k.s_inv = g.s_inv;
+            k.oh_off = g.oh_off; k.ow_off = g.ow_off;
+            k.wo_mul = g.wo_mul; k.wo_sh = g.wo_sh; k.ho_mul = g.ho_mul; k.ho_sh = g.ho_sh;
+            k.w_off = (uint32_t)cls[order[i]].wt_off;
+            work += (double)g.M * g.Kdim;
+        }
+        // The tile: in bf16 that of the largest class with the rows that make up the work of all.  In fp32 that of the largest class as it
+        // is: the register-staged tiles are bound by their chain of k steps, which that class has the longest of (169 x 9x9, 224 -> 992:
+        // 205 us with the tile for all rows, 176 with its own).
+        GatherGeom all = cs.g;
+        if (dtype == DSP_BF16 && all.Kdim > 0) all.M = (int)(work / all.Kdim);
+        return dtype == DSP_BF16 ? dispatch_classes<bf16_t>(cs, n, all, dy, wt, dx, st, flops)
+                                 : dispatch_classes<float>(cs, n, all, dy, wt, dx, st, flops);
+    }
+    for (int q = 0; q < 4; ++q) {
+        bool has = false;
+        for (int i = 0; i < n; ++i) has = has || order[i] == q;
+        if (!has) continue;
+        const void* wq = (const char*)wt + cls[q].wt_off * esz;
+        const double fq = taps > 0 ? flops * (macs[q] / taps) : 0.0;
+        DSP_TRY(dtype == DSP_BF16 ? dispatch_gather<bf16_t>(gq[q], accumulate, dy, wq, dx, st, fq)
+                                  : dispatch_gather<float>(gq[q], accumulate, dy, wq, dx, st, fq));
     }
     return DSP_OK;
 }

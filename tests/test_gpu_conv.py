@@ -189,6 +189,38 @@ def test_backward_data_whose_parity_class_is_a_small_3x3(co, dtype):
     test_conv_forward_dgrad_wgrad((3, 13, 14, 16, co, 5, 5, 2, 2), dtype)
 
 
+# Stride-2 backward-data as one launch over the parity classes: (shape, launches).  Maps of one row or column (two classes exist), a 7x7
+# filter (classes of up to 16 taps), filters larger than the input, several ragged tiles per class, classes that no tap reaches,
+# eight wave groups of which the last have no k tile; one class (a 1x1 map), and channels that are no whole 16-byte runs.
+PARITY_CLASSES = [
+    ((5, 1, 9, 16, 24, 3, 3, 2, 1), 1), ((3, 9, 1, 24, 16, 3, 3, 2, 1), 1), ((2, 15, 13, 8, 16, 7, 7, 2, 3), 1),
+    ((1, 3, 3, 264, 320, 3, 3, 2, 1), 1), ((40, 23, 21, 64, 136, 3, 3, 2, 1), 1), ((6, 33, 31, 264, 72, 1, 1, 2, 0), 1),
+    ((2, 7, 5, 40, 64, 3, 3, 2, 1), 1), ((3, 1, 1, 16, 16, 3, 3, 2, 1), 1), ((3, 8, 7, 12, 18, 3, 3, 2, 1), 4),
+]
+
+
+@pytest.mark.parametrize("dtype", [D.DSP_FP32, D.DSP_BF16], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("shape, launches", PARITY_CLASSES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_parity_classes_in_one_launch(shape, launches, dtype):
+    test_conv_forward_dgrad_wgrad(shape, dtype)
+    N, H, W, Ci, Co, R, S, st, pd = shape
+    td = torch.bfloat16 if dtype == D.DSP_BF16 else torch.float32
+    ho, wo = (H + 2 * pd - R) // st + 1, (W + 2 * pd - S) // st + 1
+    dy, wt = torch.randn(N * ho * wo * Co + 1, device="cuda").to(td), torch.randn(Ci * R * S * Co, device="cuda").to(td)
+    dx, dx1 = (torch.full((N * H * W * Ci,), float("nan"), device="cuda", dtype=td) for _ in range(2))
+    D.dsp_profile_start(16)
+    try:
+        D.dsp_conv_backward_data(dtype, dy[:-1], wt, dx, *shape)
+        torch.cuda.synchronize()
+    finally:
+        got = sum(k["launches"] for k in D.dsp_profile_stop())
+    assert got == launches
+    dy[1:] = dy[:-1].clone()  # the same on tensors that are not 16-byte aligned: class by class, element-wise gathers
+    D.dsp_conv_backward_data(dtype, dy[1:], wt, dx1, *shape)
+    torch.cuda.synchronize()
+    assert rel_err(dx1.double().cpu().numpy(), dx.double().cpu().numpy()) < _tol(dtype)
+
+
 def test_several_output_tiles_per_workgroup():
     """389 tiles of 256 x 128 for 256 compute units, the last row tile and the channels ragged."""
     D.dsp_profile_start(64)
