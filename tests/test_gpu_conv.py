@@ -408,6 +408,55 @@ def test_filter_row_that_fills_the_tap_mask(shape, dtype):
     test_conv_forward_dgrad_wgrad(shape, dtype)
 
 
+# Backward-weight with one 16 x 16 block of channels per workgroup: (N, H, W, Cin, Cout, stride), taken in fp32, in bf16.  One pixel; one column;
+# several images a tile, the last tile short; tiles of part of an image, the last one short; strided odd and even maps; the widest
+# row; the most blocks in either type and one more.
+NARROW = [
+    ((1, 1, 1, 16, 16, 1), True, True), ((3, 5, 1, 32, 16, 1), True, True), ((29, 7, 9, 16, 32, 1), True, True),
+    ((5, 43, 31, 16, 16, 1), True, True), ((4, 29, 30, 32, 16, 2), True, True), ((3, 34, 37, 16, 48, 2), True, True),
+    ((1, 9, 128, 16, 16, 1), True, True), ((2, 9, 129, 16, 16, 1), False, False), ((9, 12, 11, 64, 32, 1), True, True),
+    ((9, 12, 11, 64, 64, 1), False, True), ((64, 17, 16, 64, 64, 1), False, False), ((2, 9, 9, 16, 24, 1), False, False),
+]
+
+
+@pytest.mark.parametrize("dtype", [D.DSP_FP32, D.DSP_BF16], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("shape, fp32, bf16", NARROW, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
+def test_backward_weight_by_channel_blocks(shape, fp32, bf16, dtype):
+    N, H, W, Ci, Co, st = shape
+    td = torch.bfloat16 if dtype == D.DSP_BF16 else torch.float32
+    ho, wo = (H - 1) // st + 1, (W - 1) // st + 1
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H * W)
+    x, dy = torch.randn((N, H, W, Ci), generator=gen, device="cuda").to(td), torch.randn((N, ho, wo, Co), generator=gen, device="cuda").to(td)
+    full = (N, H, W, Ci, Co, 3, 3, st, 1)
+    ws_bytes = D.dsp_conv_workspace_bytes(*full)
+    ws = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device="cuda")
+    for infinite in (False, True):
+        if infinite:  # in the corners of the map: it reaches the taps that read them and no others
+            x[0, 0, W - 1, 3] = x[0, H - 1, 0, 5] = float("inf")
+        dw = torch.full((Co, 3, 3, Ci), float("nan"), device="cuda")
+        D.dsp_profile_start(16)
+        try:
+            D.dsp_conv_backward_weight(dtype, x, dy, dw, *full, ws, ws_bytes)
+            torch.cuda.synchronize()
+        finally:
+            names = {k["name"] for k in D.dsp_profile_stop()}
+        assert any(n.startswith("conv_wgrad_narrow") for n in names) == (fp32 if dtype == D.DSP_FP32 else bf16), names
+        xp, d = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1)), dy.double().reshape(-1, Co)
+        ref, mag = torch.empty((Co, 3, 3, Ci), device="cuda", dtype=torch.float64), torch.empty((Co, 3, 3, Ci), device="cuda", dtype=torch.float64)
+        for r in range(3):
+            for s in range(3):
+                a = xp[:, r:r + st * (ho - 1) + 1:st, s:s + st * (wo - 1) + 1:st].reshape(-1, Ci)
+                finite = torch.where(a.isinf(), torch.zeros_like(a), a)
+                ref[:, r, s], mag[:, r, s] = d.t().contiguous() @ finite, d.abs().t().contiguous() @ finite.abs()
+                ref[:, r, s][:, a.isinf().any(0)] = float("inf")
+        hit = ref.isinf()
+        assert torch.equal(~dw.isfinite(), hit)
+        if not infinite or H * W > 1:
+            # an fp32 addition per pixel (products of bf16 values are exact, of fp32 ones rounded once)
+            assert ((dw.double() - ref).abs() <= (N * ho * wo + 1) * 2.0**-24 * mag)[~hit].all()
+
+
 # (N, H, W, Cin, Cout, R, S, stride, pad, groups)
 GROUPED = [
     (3, 9, 9, 32, 48, 3, 3, 1, 1, 4),       # 8 -> 12 channels per group: bf16 rows of the output are no whole 16-byte runs
