@@ -3445,7 +3445,12 @@ int with_gather_tile(int id, int kdim, F f)
         // compute unit; the two-tile prologue is half as long and the epilogues of more workgroups overlap
         if (sizeof(T) == 2 && kdim <= 512) return f(TileTag<Tile<T, 32, 2, 2, 2, 2, 64, 2>>());
         return f(TileTag<Tile<T, 32, 2, 2, 2, 2, KB, 2>>());
-    case 5: return f(TileTag<Tile<T, 32, 2, 2, 2, 1, KB, 2>>());
+    case 5:
+        // fp32 contractions of at most 64: k steps of 16 floats; of 32 half is beyond a contraction of 16, and two more workgroups fit a
+        // compute unit, which is what these launches, bound by their stores, lack (128 x 32x32, 16 -> 64 1x1 17.2 -> 12.1 us, 64 MB at
+        // 5.1 TB/s being 8.2; 128 x 16x16, 64 -> 128 12.8 -> 12.1; resnet164 8882 -> 8587 us a tick; up to 320 no further gain)
+        if (sizeof(T) == 4 && kdim <= 64) return f(TileTag<Tile<T, 32, 2, 2, 2, 1, 64, 2>>());
+        return f(TileTag<Tile<T, 32, 2, 2, 2, 1, KB, 2>>());
     case 6: return f(TileTag<Tile<T, 32, 2, 2, 1, 1, KB, 2>>());
     case 7: return f(TileTag<Tile<T, 16, 4, 1, 1, 2, 128, 2>>());
     case 10: return f(TileTag<Tile<T, 32, 4, 1, 2, 2, 64, 2>>());

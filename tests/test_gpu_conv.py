@@ -408,6 +408,21 @@ def test_filter_row_that_fills_the_tap_mask(shape, dtype):
     test_conv_forward_dgrad_wgrad(shape, dtype)
 
 
+# fp32, 128 x 64 tiles with k steps of 16 and, above a contraction of 64, of 32; ragged rows, channels and contractions.
+SHORT_CONTRACTIONS = [((49, 32, 33, 16, 64, 1, 1, 1, 0), 16), ((51, 32, 33, 64, 40, 1, 1, 1, 0), 16), ((50, 33, 32, 4, 60, 3, 3, 1, 1), 16),
+                      ((51, 32, 33, 68, 40, 1, 1, 1, 0), 32)]
+
+
+@pytest.mark.parametrize("shape, bk", SHORT_CONTRACTIONS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_short_contractions_fp32(shape, bk):
+    D.dsp_profile_start(64)
+    try:
+        test_conv_forward_dgrad_wgrad(shape, D.DSP_FP32)
+    finally:
+        names = {k["name"] for k in D.dsp_profile_stop()}
+    assert "conv_gather_gemm<fp32,mfma32,BM128,BN64,BK%d,vec>" % bk in names, names
+
+
 # Backward-weight with one 16 x 16 block of channels per workgroup: (N, H, W, Cin, Cout, stride), taken in fp32, in bf16.  One pixel; one column;
 # several images a tile, the last tile short; tiles of part of an image, the last one short; strided odd and even maps; the widest
 # row; the most blocks in either type and one more.
