@@ -3030,23 +3030,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     }
 }
 
-// ---- backward-weight of narrow layers: one 16 x 16 block of channels per workgroup, pixels staged once for all taps ----------
-// A 3x3 filter of 16 to 64 channels makes a GEMM output so small that tiles of it are mostly padding (16 x 144 on the 64x64 tile)
+// ---- bf16 backward-weight of narrow layers: one 16 x 16 block of channels per workgroup, pixels staged once for all taps ------
+// A 3x3 filter of 16 or 32 channels makes a GEMM output so small that tiles of it are mostly padding (16 x 144 on the 64x64 tile)
 // and every tap gathers its own copy of the pixels.  Here a workgroup owns 16 output channels x 16 input channels x ALL taps: the
-// rows of x that a run of output pixels touches, and their dy, go into LDS once as they lie in memory (16 channels a slot), and
-// the operand of tap (r, s) is read at a constant distance from the operand of tap (0, 0).  Its eight waves take every eighth k
+// rows of x that a run of output pixels touches, and their dy, go into LDS once as they lie in memory (16 channels, 32 bytes, a slot),
+// and the operand of tap (r, s) is read at a constant distance from the operand of tap (0, 0).  Its eight waves take every eighth k
 // step and are summed through LDS in wave order; the workgroups of a slice (its blocks of channels) meet in one L2.
-//   slot (row i, column j) of an image's patch holds input pixel (first row + i, j - pad); a row has W + pad slots, so that the column
+//   slot (row i, column j) of an image's patch holds input pixel (first row + i, j - 1); a row has W + 1 slots, so that the column
 //   right of an image row is the zero column left of the next.  A table gives the slot of an output pixel's first tap; pixels
 //   past the tile read a zone of zeros behind the patch (never another pixel times a zero of dy: infinities stay where they are).
-//   fp32: lane (pixel % 4, channel) of a 16x16x4 step, plain LDS reads.  bf16: the transpose read, lane group g of a 16x16x32 step holds the
-//   pixels 4 g .. 4 g + 3 and 16 + 4 g .. of its 32.
+//   Operands come by transpose reads; lane group g of a 16x16x32 step holds the pixels 4 g .. 4 g + 3 and 16 + 4 g .. of its 32.
 // Bound by latency: the pixels arrive in one go before the first step and the sums of the waves follow the last; loading the next
-// tile under the steps of this one, in halves of the LDS, was no faster (resnet20 1.5 % slower, resnet56 1 %).  1x1 filters, which use a
-// staged pixel once, are 3-20 % slower here than on the tiles.
-// With the summing launch, tiles (16 -> 16 fp32: filters streamed from memory) -> here: 128 x 32x32, 16 -> 16 bf16 15.6 -> 9.9 us, fp32 19.5 ->
-// 15.6; 128 x 16x16, 32 -> 32 bf16 11.6 -> 10.2, fp32 23.5 -> 15.9; 200 x 40x40, 16 -> 16 bf16 25.7 -> 12.6.  resnet56 bf16 1115 -> 1029 us a tick,
-// resnet20 fp32 857 -> 834, resnet164 fp32 9001 -> 8876.
+// tile under the steps of this one, in halves of the LDS, was 1 % slower in resnet56.  1x1 filters, which use a staged pixel once, are
+// 3-20 % slower here than on the tiles.
+// With the summing launch, tiles -> here: 128 x 32x32, 16 -> 16 15.6 -> 9.9 us; 128 x 16x16, 32 -> 32 11.6 -> 10.2; 200 x 40x40, 16 -> 16 25.7 ->
+// 12.6.  resnet56 1117 -> 1025 us a tick (launch hand-over of the pipeline included, 1 %).
 struct NarrowArgs {
     int pitch, prows;            // slots of a patch row, rows of an image's patch
     int rows, imgs, row_tiles;   // output rows and images of a tile (one of them is 1 or all), tiles of an image
@@ -3057,33 +3055,25 @@ struct NarrowArgs {
     int dy_off, tab_off;         // bytes
     uint32_t pitch_mul, pitch_sh, prows_mul, prows_sh;
 };
-constexpr int kNarrowThreads = 512;
-template <typename T>
-struct NarrowSlot {
-    static constexpr int BYTES = 16 * (int)sizeof(T), CHUNKS = BYTES / 16;
-    static constexpr int STEP = sizeof(T) == 2 ? 32 : 4;  // pixels of a k step
-};
+constexpr int kNarrowThreads = 512, kNarrowSlot = 32, kNarrowStep = 32;  // bytes of a slot, pixels of a k step
 
-template <typename T>
-__global__ __launch_bounds__(kNarrowThreads) __attribute__((amdgpu_waves_per_eu(4))) void conv_wgrad_narrow_kernel(
-    const T* __restrict__ x, const T* __restrict__ dy, float* __restrict__ part, WgradGeom g, NarrowArgs a)
+__global__ __launch_bounds__(kNarrowThreads) __attribute__((amdgpu_waves_per_eu(4))) void conv_wgrad_narrow_bf16_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy, float* __restrict__ part, WgradGeom g, NarrowArgs a)
 {
-    typedef NarrowSlot<T> SL;
-    constexpr int R = 3, S = 3, TAPS = R * S, NW = kNarrowThreads / 64, SB = SL::BYTES;
-    constexpr uint32_t SZ = sizeof(T);
+    constexpr int R = 3, S = 3, TAPS = R * S, NW = kNarrowThreads / 64, SB = kNarrowSlot, CHUNKS = SB / 16;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned lin = xcd_tile(blockIdx.x, gridDim.x);
     const int slice = (int)(lin / (unsigned)a.pairs), pair = (int)(lin - (unsigned)slice * a.pairs);
     const int co_b = pair / a.ci_blocks, ci0 = (pair - co_b * a.ci_blocks) * 16, co0 = co_b * 16;
-    const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, (uint32_t)g.N * g.H * g.W * g.Ci * SZ);
-    const __amdgpu_buffer_rsrc_t rdy = make_rsrc(dy, (uint32_t)g.M * g.Co * SZ);
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, (uint32_t)g.N * g.H * g.W * g.Ci * 2u);
+    const __amdgpu_buffer_rsrc_t rdy = make_rsrc(dy, (uint32_t)g.M * g.Co * 2u);
 
     int* const tab = (int*)(smem + a.tab_off);
-    for (int p = tid; p < a.steps * SL::STEP; p += kNarrowThreads) {
+    for (int p = tid; p < a.steps * kNarrowStep; p += kNarrowThreads) {
         const int t = (int)fast_div((uint32_t)p, g.wo_mul, g.wo_sh), j = p - t * g.Wo;
         const int img = a.imgs > 1 ? (int)fast_div((uint32_t)t, g.ho_mul, g.ho_sh) : 0, i = t - img * g.Ho;
-        tab[p] = ((img * a.prows + i * g.stride) * a.pitch + j * g.stride) * SB;
+        tab[p] = ((img * a.prows + i) * a.pitch + j) * SB;
     }
 
     f32x4 acc[TAPS];
@@ -3095,64 +3085,38 @@ __global__ __launch_bounds__(kNarrowThreads) __attribute__((amdgpu_waves_per_eu(
         const int tn = t / a.row_tiles, n0 = tn * a.imgs, r0 = (t - tn * a.row_tiles) * a.rows;
         const int pix = a.imgs > 1 ? min(a.imgs, g.N - n0) * g.Ho * g.Wo : min(a.rows, g.Ho - r0) * g.Wo;
         __syncthreads();
-        for (int c0 = wave * 64; c0 < a.x_slots * SL::CHUNKS; c0 += kNarrowThreads) {
-            const int c = c0 + lane, slot = c / SL::CHUNKS;
-            const int pr = (int)fast_div((uint32_t)slot, a.pitch_mul, a.pitch_sh), col = slot - pr * a.pitch - g.pad;
+        for (int c0 = wave * 64; c0 < a.x_slots * CHUNKS; c0 += kNarrowThreads) {
+            const int c = c0 + lane, slot = c / CHUNKS;
+            const int pr = (int)fast_div((uint32_t)slot, a.pitch_mul, a.pitch_sh), col = slot - pr * a.pitch - 1;
             const int img = a.imgs > 1 ? (int)fast_div((uint32_t)pr, a.prows_mul, a.prows_sh) : 0;
-            const int row = r0 * g.stride - g.pad + pr - img * a.prows;
+            const int row = r0 - 1 + pr - img * a.prows;
             const bool ok = slot < a.zero && n0 + img < g.N && row >= 0 && row < g.H && col >= 0 && col < g.W;
-            const uint32_t off = ((uint32_t)((n0 + img) * g.H + row) * g.W + col) * g.Ci * SZ + ci0 * SZ + (c % SL::CHUNKS) * 16;
+            const uint32_t off = ((uint32_t)((n0 + img) * g.H + row) * g.W + col) * g.Ci * 2u + ci0 * 2 + (c % CHUNKS) * 16;
             dma16(rx, smem + c0 * 16, ok ? off : kOutOfRange);
         }
-        const uint32_t dy0 = ((uint32_t)(n0 * g.Ho + r0) * g.Wo * g.Co + co0) * SZ;
-        for (int c0 = wave * 64; c0 < a.steps * SL::STEP * SL::CHUNKS; c0 += kNarrowThreads) {
-            const int c = c0 + lane, slot = c / SL::CHUNKS;
-            dma16(rdy, smem + a.dy_off + c0 * 16, slot < pix ? dy0 + (uint32_t)slot * g.Co * SZ + (c % SL::CHUNKS) * 16 : kOutOfRange);
+        const uint32_t dy0 = ((uint32_t)(n0 * g.Ho + r0) * g.Wo * g.Co + co0) * 2u;
+        for (int c0 = wave * 64; c0 < a.steps * kNarrowStep * CHUNKS; c0 += kNarrowThreads) {
+            const int c = c0 + lane, slot = c / CHUNKS;
+            dma16(rdy, smem + a.dy_off + c0 * 16, slot < pix ? dy0 + (uint32_t)slot * g.Co * 2u + (c % CHUNKS) * 16 : kOutOfRange);
         }
         __syncthreads();  // (waits for the loads too)
         auto entry = [&](int p) __attribute__((always_inline)) { return p < pix ? tab[p] : a.zero * SB; };
-        if constexpr (sizeof(T) == 4) {
-            const char *const xl = smem + (lane & 15) * 4, *const dl = smem + a.dy_off + (lane & 15) * 4;
-            int p = wave * SL::STEP + (lane >> 4);
-            const int p_end = a.steps * SL::STEP;
-            float da = 0.f, xb[TAPS] = {};
-            auto fetch = [&](float& d, float (&b)[TAPS]) __attribute__((always_inline)) {
-                d = *(const float*)(dl + p * SB);
-                const char* q = xl + entry(p);
+        const char *const xl = smem + (lane & 3) * 8, *const dl = smem + a.dy_off + (lane & 3) * 8;
+        for (int ks = wave; ks < a.steps; ks += NW) {
+            const int p0 = ks * kNarrowStep + (lane >> 2), p1 = p0 + 16;
+            const u32x2 d0 = lds_read_tr16(dl + p0 * SB), d1 = lds_read_tr16(dl + p1 * SB);
+            const char *const q0 = xl + entry(p0), *const q1 = xl + entry(p1);
+            const u32x4 d = {d0[0], d0[1], d1[0], d1[1]};
+            u32x4 b[TAPS];
 #pragma unroll
-                for (int r = 0; r < R; ++r)
+            for (int r = 0; r < R; ++r)
 #pragma unroll
-                    for (int s = 0; s < S; ++s) b[r * S + s] = *(const float*)(q + r * row_b + s * SB);
-                p += NW * SL::STEP;
-            };
-            if (p < p_end) fetch(da, xb);
-            for (int ks = wave; ks < a.steps; ks += NW) {
-                float dn = 0.f, xn[TAPS] = {};
-                if (ks + NW < a.steps) fetch(dn, xn);  // the operands of the next step, under this step's products
+                for (int s = 0; s < S; ++s) {
+                    const u32x2 b0 = lds_read_tr16(q0 + r * row_b + s * SB), b1 = lds_read_tr16(q1 + r * row_b + s * SB);
+                    b[r * S + s] = u32x4{b0[0], b0[1], b1[0], b1[1]};
+                }
 #pragma unroll
-                for (int k = 0; k < TAPS; ++k) acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(da, xb[k], acc[k], 0, 0, 0);
-                da = dn;
-#pragma unroll
-                for (int k = 0; k < TAPS; ++k) xb[k] = xn[k];
-            }
-        } else {
-            const char *const xl = smem + (lane & 3) * 8, *const dl = smem + a.dy_off + (lane & 3) * 8;
-            for (int ks = wave; ks < a.steps; ks += NW) {
-                const int p0 = ks * SL::STEP + (lane >> 2), p1 = p0 + 16;
-                const u32x2 d0 = lds_read_tr16(dl + p0 * SB), d1 = lds_read_tr16(dl + p1 * SB);
-                const char *const q0 = xl + entry(p0), *const q1 = xl + entry(p1);
-                const u32x4 d = {d0[0], d0[1], d1[0], d1[1]};
-                u32x4 b[TAPS];
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int s = 0; s < S; ++s) {
-                        const u32x2 b0 = lds_read_tr16(q0 + r * row_b + s * SB), b1 = lds_read_tr16(q1 + r * row_b + s * SB);
-                        b[r * S + s] = u32x4{b0[0], b0[1], b1[0], b1[1]};
-                    }
-#pragma unroll
-                for (int k = 0; k < TAPS; ++k) Mma<T, 16>::run(d, b[k], acc[k]);
-            }
+            for (int k = 0; k < TAPS; ++k) Mma<bf16_t, 16>::run(d, b[k], acc[k]);
         }
     }
     __syncthreads();
@@ -4151,53 +4115,56 @@ int wgrad_c16_splits(const ConvShape& c, int* m_per_split)
     return ceil_div(M, per);
 }
 
-// Narrow layers: 3x3 / pad 1, both channel counts multiples of 16.  Every block of 16 input channels stages dy and every block of 16
-// output channels stages x again, so the line lies at eight blocks of 16 x 16 (fp32 32 -> 64 1.01x, 64 -> 64 0.90-0.96x; bf16 48 -> 64 at 38 k pixels
-// 0.98x, 64 -> 64 at 131 k 0.64x), in bf16 at sixteen where the pixels are few (64 -> 64 at 8 k 1.07x).  Rows of more than 128 pixels do not fit.
+// Narrow layers: bf16, 3x3 / stride 1 / pad 1, 16 or 32 channels on both sides, rows that fit LDS.  Every block of 16 input channels stages
+// dy and every block of 16 output channels stages x again, and from 48 channels on the tiles have less padding: 186 x 51x49, 32 -> 48
+// 35.6 us there and 44.3 here, 213 x 45x47, 16 -> 64 24.3 and 33.4, 128 x 8x8, 64 -> 64 10.9 and 10.7.  At stride 2, where a quarter as many
+// products share the staging, 10.3 and 11.8 (142 x 22x22, 16 -> 48).
 constexpr int kNarrowLds = 79 * 1024;
 bool wgrad_narrow_eligible(int dtype, const ConvShape& c)
 {
-    if (conv_groups(c) != 1 || c.Cin % 16 != 0 || c.Cout % 16 != 0 || c.R != 3 || c.S != 3 || c.pad != 1 || c.W > 128) return false;
-    const int64_t pairs = (int64_t)(c.Cin / 16) * (c.Cout / 16), M = (int64_t)c.N * c.Ho * c.Wo;
-    return (c.stride == 1 || c.stride == 2) && (pairs <= 8 || (dtype == DSP_BF16 && pairs <= 16 && M * pairs <= 1 << 18)) &&
-           !wgrad_c64_eligible(dtype, c) && (int64_t)c.N * c.H * c.W < 1 << 30;
+    return dtype == DSP_BF16 && conv_groups(c) == 1 && (c.Cin == 16 || c.Cin == 32) && (c.Cout == 16 || c.Cout == 32) && c.R == 3 &&
+           c.S == 3 && c.pad == 1 && c.stride == 1 && c.W <= 128 && (int64_t)c.N * c.H * c.W < 1 << 30;
 }
 // The largest tile that fits LDS twice per compute unit and leaves the slices a tile each: a workgroup per compute unit over all
-// blocks, a slice of 512 pixels or more (below that the summing launch costs more than the workgroups gain), `most` slices at most.
-NarrowArgs wgrad_narrow_plan(int dtype, const ConvShape& c, int most, int* slices, int* lds)
+// blocks, a slice of kNarrowSlice pixels or more (60 layers 1.17x with 128, 1.14x with 256, 1.11x with 512), and no more slices
+// than the workspace of the other kernels holds.
+constexpr int kNarrowSlice = 128;
+NarrowArgs wgrad_narrow_plan(const ConvShape& c, int* slices, int* lds)
 {
-    const int sb = 16 * (int)dtype_size(dtype), step = dtype == DSP_BF16 ? 32 : 4;
+    int per;
+    const int s32 = wgrad_c16_eligible(DSP_FP32, c) ? wgrad_c16_splits(c, &per) : wgrad_plan(DSP_FP32, c).staged_splits;
+    const int s16 = wgrad_plan(DSP_BF16, c).staged_splits, most = s32 > s16 ? s32 : s16;
     NarrowArgs a{};
-    a.pitch = c.W + c.pad;
+    a.pitch = c.W + 1;
     a.ci_blocks = c.Cin / 16;
     a.pairs = a.ci_blocks * (c.Cout / 16);
-    int want = kComputeUnits / a.pairs;
-    const int64_t M = (int64_t)c.N * c.Ho * c.Wo;
-    if (want > M / 512) want = (int)(M / 512);
+    const int64_t M = (int64_t)c.N * c.H * c.W;
+    int64_t want = kComputeUnits / a.pairs;
+    if (want > M / kNarrowSlice) want = M / kNarrowSlice;
     if (want > most) want = most;
     if (want < 1) want = 1;
     auto fit = [&](int rows, int imgs) {
         a.rows = rows;
         a.imgs = imgs;
-        a.prows = (rows - 1) * c.stride + c.R;
-        a.steps = ceil_div((int64_t)imgs * rows * c.Wo, step);
+        a.prows = rows + 2;
+        a.steps = ceil_div((int64_t)imgs * rows * c.W, kNarrowStep);
         a.zero = imgs * a.prows * a.pitch;
-        a.x_slots = ceil_div((int64_t)(a.zero + (c.R - 1) * a.pitch + c.S) * sb, 1024) * 1024 / sb;
-        a.dy_off = a.x_slots * sb;
-        a.tab_off = a.dy_off + ceil_div((int64_t)a.steps * step * sb, 1024) * 1024;
-        a.row_tiles = ceil_div(c.Ho, rows);
+        a.x_slots = ceil_div((int64_t)(a.zero + 2 * a.pitch + 3) * kNarrowSlot, 1024) * 1024 / kNarrowSlot;
+        a.dy_off = a.x_slots * kNarrowSlot;
+        a.tab_off = a.dy_off + ceil_div((int64_t)a.steps * kNarrowStep * kNarrowSlot, 1024) * 1024;
+        a.row_tiles = ceil_div(c.H, rows);
         a.tiles = ceil_div(c.N, imgs) * a.row_tiles;
-        const int red = 8 * c.R * c.S * 1024, bytes = a.tab_off + a.steps * step * 4;
+        const int red = 8 * 9 * 1024, bytes = a.tab_off + a.steps * kNarrowStep * 4;
         *lds = bytes > red ? bytes : red;
         return bytes <= kNarrowLds;
     };
     int parts = 1;  // tiles of an image
-    while (!fit(ceil_div(c.Ho, parts), 1) && ceil_div(c.Ho, parts) > 1) ++parts;
-    while (a.tiles < want && a.rows > 1 && a.rows * c.Wo > 256) fit(ceil_div(c.Ho, ++parts), 1);
-    if (a.rows == c.Ho) {
+    while (!fit(ceil_div(c.H, parts), 1) && ceil_div(c.H, parts) > 1) ++parts;
+    while (a.tiles < want && a.rows > 1 && a.rows * c.W > 256) fit(ceil_div(c.H, ++parts), 1);
+    if (a.rows == c.H) {
         int imgs = 1;
-        while (ceil_div(c.N, imgs + 1) >= want && (imgs + 1) * c.Ho * c.Wo <= 512 && fit(c.Ho, imgs + 1)) ++imgs;
-        fit(c.Ho, imgs);
+        while (ceil_div(c.N, imgs + 1) >= want && (imgs + 1) * c.H * c.W <= 512 && fit(c.H, imgs + 1)) ++imgs;
+        fit(c.H, imgs);
     }
     a.per = ceil_div(a.tiles, want);
     *slices = ceil_div(a.tiles, a.per);
@@ -4205,34 +4172,25 @@ NarrowArgs wgrad_narrow_plan(int dtype, const ConvShape& c, int most, int* slice
     fast_div_constants((uint32_t)a.prows, &a.prows_mul, &a.prows_sh);
     return a;
 }
-// The most slices whose partials fit the workspace of the other kernels.
-int wgrad_narrow_most(const ConvShape& c)
-{
-    int per;
-    const int a = wgrad_c16_eligible(DSP_FP32, c) ? wgrad_c16_splits(c, &per) : wgrad_plan(DSP_FP32, c).staged_splits;
-    const int b = wgrad_plan(DSP_BF16, c).staged_splits;
-    return a > b ? a : b;
-}
-int wgrad_narrow_slices(int dtype, const ConvShape& c)
+int wgrad_narrow_slices(const ConvShape& c)
 {
     int slices, lds;
-    (void)wgrad_narrow_plan(dtype, c, wgrad_narrow_most(c), &slices, &lds);
+    (void)wgrad_narrow_plan(c, &slices, &lds);
     return slices;
 }
 
-template <typename T>
 int run_wgrad_narrow(const ConvShape& c, const WgradGeom& g, const void* x, const void* dy, float* dst, hipStream_t st, double flops)
 {
     int slices, lds;
-    const NarrowArgs a = wgrad_narrow_plan(sizeof(T) == 2 ? DSP_BF16 : DSP_FP32, c, wgrad_narrow_most(c), &slices, &lds);
-    auto kern = conv_wgrad_narrow_kernel<T>;
+    const NarrowArgs a = wgrad_narrow_plan(c, &slices, &lds);
     static std::atomic<bool> attr_done{false};
     if (!attr_done) {
-        DSP_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kNarrowLds));
+        DSP_HIP(hipFuncSetAttribute((const void*)conv_wgrad_narrow_bf16_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kNarrowLds));
         attr_done = true;
     }
-    ProfScope ps(sizeof(T) == 2 ? "conv_wgrad_narrow<bf16,16x16>" : "conv_wgrad_narrow<fp32,16x16>", flops, 0);
-    DSP_LAUNCH(ps, kern, dim3((unsigned)(slices * a.pairs)), dim3(kNarrowThreads), lds, st, (const T*)x, (const T*)dy, dst, g, a);
+    ProfScope ps("conv_wgrad_narrow<bf16,16x16>", flops, 0);
+    DSP_LAUNCH(ps, conv_wgrad_narrow_bf16_kernel, dim3((unsigned)(slices * a.pairs)), dim3(kNarrowThreads), lds, st, (const bf16_t*)x,
+               (const bf16_t*)dy, dst, g, a);
     return DSP_OK;
 }
 
@@ -4261,7 +4219,7 @@ int dispatch_wgrad(const ConvShape& c, const void* x, const void* dy, float* dw,
     // (a caller that sums the slices later has been told how many there are)
     const bool staged = !vec && !defer_reduce;
     int c64_per = 0;
-    const int splits = narrow ? wgrad_narrow_slices(dtype, c)
+    const int splits = narrow ? wgrad_narrow_slices(c)
                        : c64 ? wgrad_c64_slices(c, &c64_per)
                            : stem ? wgrad_stem_slices(c, &c64_per)
                                   : c16 ? wgrad_c16_splits(c, &g.m_per_split) : staged ? pl.staged_splits : pl.splits;
@@ -4276,7 +4234,7 @@ int dispatch_wgrad(const ConvShape& c, const void* x, const void* dy, float* dw,
     }
     int rc;
     if (narrow) {
-        rc = run_wgrad_narrow<T>(c, g, x, dy, dst, st, flops);
+        rc = run_wgrad_narrow(c, g, x, dy, dst, st, flops);
     } else if (c64) {
         // (the slice count is fixed by the shape; tensors that are not 16-byte aligned cannot use this kernel)
         DSP_REQUIRE(vec, DSP_EINVAL, "conv backward-weight: x and dy of this layer shape must be 16-byte aligned");
@@ -4594,7 +4552,7 @@ int conv_backward_weight_slices(int dtype, const ConvShape& c)
 {
     // aligned 16-byte tensors assumed (the slicing does not depend on the alignment)
     int per;
-    if (wgrad_narrow_eligible(dtype, c)) return wgrad_narrow_slices(dtype, c);
+    if (wgrad_narrow_eligible(dtype, c)) return wgrad_narrow_slices(c);
     if (wgrad_c64_eligible(dtype, c)) return wgrad_c64_slices(c, nullptr);
     if (wgrad_stem_eligible(dtype, c)) return wgrad_stem_slices(c, nullptr);
     if (wgrad_c16_eligible(dtype, c)) return wgrad_c16_splits(c, &per);
