@@ -869,6 +869,19 @@ static int probe_after_tick(dsp_pipeline* pl, int64_t tau)
     return DSP_OK;
 }
 
+// Whether `bytes` bytes at `ptr` lie within one allocation of device memory.
+static bool device_range(const void* ptr, size_t bytes)
+{
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)ptr) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const size_t at = (size_t)((const char*)ptr - (const char*)base);
+    return at <= size && bytes <= size - at;
+}
+
 // The data source: the mini-batch into block 0's ring slot and the labels into the label ring.
 static int copy_mini_batch(dsp_pipeline* pl, int64_t tau, const void* d_batch, const int32_t* d_labels, hipStream_t user, bool graph_tick)
 {
@@ -922,9 +935,13 @@ int dsp_pipeline_step(dsp_pipeline* pl, const void* d_batch, const int32_t* d_la
     const int phase = graph_tick ? (int)(tau % pl->period) : 0;
 
     const bool eager = !pl->serial && !graph_tick;
-    const bool threads = eager && start_workers(pl, tau);
+    // The threads start early only for a mini-batch that the copies cannot refuse: a step that fails on its input must leave every
+    // block where it was, so that the caller can repeat it.
+    const bool early = eager && device_range(d_batch, pl->in_bytes) && (!d_labels || device_range(d_labels, (size_t)pl->N * 4));
+    bool threads = early && start_workers(pl, tau);
     const int rc_in = copy_mini_batch(pl, tau, d_batch, d_labels, user, graph_tick);
-    if (!eager) DSP_TRY(rc_in);
+    if (!early) DSP_TRY(rc_in);
+    if (eager && !early) threads = start_workers(pl, tau);
 
     if (pl->serial) {
         // ordinary backpropagation: forward up the chain, backward down the chain, one stream (a delayed block

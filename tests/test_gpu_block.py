@@ -474,6 +474,38 @@ def test_pipeline_equals_manual_fifo_schedule_bit_for_bit(name, dtype, ticks, kw
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("name,ticks,kw", [
+    ("tiny2", 12, {}),
+    ("resnet20", 12, {"batch": 4, "hw": 8, "p": (0, 0, 0), "m": (2, 1, 0)}),   # forward-locked
+])
+def test_mini_batches_of_either_memory_give_the_same_bits(name, ticks, kw):
+    """The launch threads start before the mini-batch is copied only where it and the labels lie in device memory: from pinned
+    host memory, in turn with device memory, every loss and parameter is the one of device memory alone."""
+    cfg, params, rng = _setup(name, **kw)
+    batches = [make_batch(rng, cfg["input"], cfg["classes"]) for _ in range(ticks)]
+    out = []
+    for pinned in (False, True):
+        blocks = build_gpu_blocks(cfg, params, D.DSP_FP32)
+        pl = D.dsp_pipeline_init(blocks, cfg["p"], cfg["m"], cfg["lr"], cfg["beta"], cfg["wd"], ticks)
+        try:
+            kept = []
+            for i, (x, y) in enumerate(batches):
+                dx, dy = to_dev(x, D.DSP_FP32), torch.from_numpy(y).cuda()
+                if pinned and i % 3:
+                    dx = torch.empty(dx.shape, dtype=dx.dtype, pin_memory=True).copy_(dx)
+                if pinned and i % 3 == 2:
+                    dy = torch.empty(dy.shape, dtype=dy.dtype, pin_memory=True).copy_(dy)
+                torch.cuda.synchronize()
+                kept.append((dx, dy))
+                D.dsp_pipeline_step(pl, dx, dy)
+            out.append([D.dsp_pipeline_losses(pl)] + [D.dsp_block_get_params(b) for b in blocks])
+        finally:
+            D.dsp_pipeline_destroy(pl)
+            destroy_blocks(blocks)
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("name,dtype,ticks,kw,spare,graphs", [
     ("tiny2", D.DSP_FP32, 30, {}, 1, False),
     ("resnet20", D.DSP_FP32, 30, {"batch": 8, "hw": 16}, 3, False),
