@@ -178,6 +178,7 @@ struct dsp_block {
     void* wgrad_ws = nullptr;  // per-slice partial weight gradients, one region per conv layer
     size_t wgrad_ws_bytes = 0;
     WgradReduceSet* wgrad_set = nullptr;  // sums all regions in one launch at the end of the backward sweep
+    WgradReduceSet* wgrad_set_odd = nullptr;  // the same for a d_grad_out off the 16-byte addresses, where that makes other slices
     double* bn_partial = nullptr;
     float* bn_coef = nullptr;
     size_t bn_partial_elems = 0;
@@ -215,6 +216,13 @@ static const void* weights_for_forward(const dsp_block* b, const Layer& L)
 static const void* weights_for_dgrad(const dsp_block* b, const Layer& L)
 {
     return b->dtype == DSP_BF16 ? (const void*)((const bf16_t*)b->wt + L.wt_off) : (const void*)((const float*)b->wt + L.wt_off);
+}
+
+// The tensor in whose gradient buffer the gradient of tensor t lies (out_idx: the caller's).
+static int grad_owner(const dsp_block* b, int t)
+{
+    while (t != b->out_idx && b->grad_alias[t] >= 0) t = b->grad_alias[t];
+    return t;
 }
 
 static int build_graph(dsp_block* b)
@@ -562,15 +570,21 @@ static int build_graph(dsp_block* b)
     b->wgrad_ws_bytes = ws;
     DSP_TRY(dev_alloc(b, &b->wgrad_ws, ws, &b->ws_bytes));
     {
-        std::vector<WgradReduceItem> items;
-        for (Layer& L : b->layers) {
+        std::vector<WgradReduceItem> items, odd;  // (the block's own buffers are aligned; the caller's gradient need not be)
+        bool differ = false;
+        for (int i = 0; i < d.n_layers; ++i) {
+            const Layer& L = b->layers[i];
             if (L.d.op != DSP_OP_CONV) continue;
             float* dw = L.cin_pad ? L.dw_pad : b->g + L.p0;
             items.push_back(WgradReduceItem{(const float*)((char*)b->wgrad_ws + L.wg_off), dw,
                                             (size_t)L.cs.Cout * L.cs.R * L.cs.S * (L.cs.Cin / conv_groups(L.cs)),
-                                            conv_backward_weight_slices(b->dtype, L.cs)});
+                                            conv_backward_weight_slices(b->dtype, L.cs, true)});
+            odd.push_back(items.back());
+            if (grad_owner(b, i) == b->out_idx) odd.back().slices = conv_backward_weight_slices(b->dtype, L.cs, false);
+            differ = differ || odd.back().slices != items.back().slices;
         }
         DSP_TRY(wgrad_reduce_set_create(items.data(), (int)items.size(), &b->wgrad_set));
+        if (differ) DSP_TRY(wgrad_reduce_set_create(odd.data(), (int)odd.size(), &b->wgrad_set_odd));
     }
     size_t partial_elems = (size_t)bn_max_partial_blocks() * max_c;
     for (int i = 0; i + 1 < d.n_layers; ++i) {
@@ -838,8 +852,7 @@ static int run_backward(dsp_block* b, const void* in, const void* gout, void* gi
         const Tensor& s = L.d.in0 < 0 ? b->input : b->T[L.d.in0];
         const void* src = L.d.in0 < 0 ? in : b->T[L.d.in0].act;
         auto dy_of = [&](int layer) -> const void* {  // the buffer that holds the gradient of a layer's output
-            int t = layer;
-            while (t != b->out_idx && b->grad_alias[t] >= 0) t = b->grad_alias[t];
+            const int t = grad_owner(b, layer);
             return (t == b->out_idx) ? gout : b->T[t].grad;
         };
         const void* dy = dy_of(i);
@@ -862,11 +875,7 @@ static int run_backward(dsp_block* b, const void* in, const void* gout, void* gi
             void* dres = L.in1_grad ? grad_of(L.d.in1) : nullptr;
             DSP_REQUIRE(L.in0_grad, DSP_EINVAL, "bn directly on the data input is not supported");
             const void* dx_add = nullptr;
-            if (L.dx_add_from >= 0) {
-                int t = L.dx_add_from;
-                while (t != b->out_idx && b->grad_alias[t] >= 0) t = b->grad_alias[t];
-                dx_add = (t == b->out_idx) ? gout : b->T[t].grad;
-            }
+            if (L.dx_add_from >= 0) dx_add = dy_of(L.dx_add_from);
             PoolGrad pg{};
             if (L.pool_bwd) {  // dy is the backward of the pool behind this layer, formed inside the kernels
                 const Layer& Pl = b->layers[i + 1];
@@ -910,7 +919,7 @@ static int run_backward(dsp_block* b, const void* in, const void* gout, void* gi
             break;
         }
     }
-    DSP_TRY(wgrad_reduce_set_launch(b->wgrad_set, st));
+    DSP_TRY(wgrad_reduce_set_launch(b->wgrad_set_odd && (uintptr_t)gout % 16 != 0 ? b->wgrad_set_odd : b->wgrad_set, st));
     for (Layer& L : b->layers)
         if (L.d.op == DSP_OP_CONV && L.cin_pad)
             DSP_TRY(launch_gather_f32(L.dw_pad, b->tmap + L.p0, (int32_t)L.wt_off, b->g + L.p0,
@@ -972,6 +981,7 @@ int dsp_block_destroy(dsp_block* b)
     (void)hipDeviceSynchronize();
     for (void* p : b->allocs) (void)hipFree(p);
     wgrad_reduce_set_destroy(b->wgrad_set);
+    wgrad_reduce_set_destroy(b->wgrad_set_odd);
     relayout_block_gone();
     delete b->fwd_lane;
     delete b;

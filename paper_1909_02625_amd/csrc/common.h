@@ -186,10 +186,11 @@ int launch_conv_backward_data(int dtype, const ConvShape& c, const void* dy, con
                               bool accumulate, hipStream_t st);
 // dw[Cout][R][S][Cin] (float) = sum over (n, ho, wo) of dy * x;  ws holds the split partials.
 // defer_reduce: write the per-slice partial sums to ws only; the caller sums them later (for all its layers
-// at once, wgrad_reduce_set_*).  conv_backward_weight_slices = number of slices (1: dw is written directly).
+// at once, wgrad_reduce_set_*).  conv_backward_weight_slices = number of slices (1: dw is written directly); aligned: both
+// tensors lie on 16-byte addresses.
 int launch_conv_backward_weight(int dtype, const ConvShape& c, const void* x, const void* dy, float* dw, void* ws,
                                 size_t ws_bytes, hipStream_t st, bool defer_reduce = false);
-int conv_backward_weight_slices(int dtype, const ConvShape& c);
+int conv_backward_weight_slices(int dtype, const ConvShape& c, bool aligned);
 struct WgradReduceItem {
     const float* partials;  // [slices][n]
     float* dw;              // [n]

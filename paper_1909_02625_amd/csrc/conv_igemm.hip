@@ -4216,7 +4216,7 @@ int dispatch_wgrad(const ConvShape& c, const void* x, const void* dy, float* dw,
     const bool stem = wgrad_stem_eligible(dtype, c);
     const bool narrow = wgrad_narrow_eligible(dtype, c) && ((uintptr_t)x % 16) == 0 && ((uintptr_t)dy % 16) == 0;
     const bool vec = (g.Ci % E) == 0 && (g.Co % E) == 0 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)dy % 16) == 0;
-    // (a caller that sums the slices later has been told how many there are)
+    // (a caller that sums the slices later has been told how many there are: conv_backward_weight_slices)
     const bool staged = !vec && !defer_reduce;
     int c64_per = 0;
     const int splits = narrow ? wgrad_narrow_slices(c)
@@ -4548,11 +4548,10 @@ int launch_conv_backward_weight(int dtype, const ConvShape& c, const void* x, co
                              : dispatch_wgrad<float>(c, x, dy, dw, ws, ws_bytes, st, flops, defer_reduce);
 }
 
-int conv_backward_weight_slices(int dtype, const ConvShape& c)
+int conv_backward_weight_slices(int dtype, const ConvShape& c, bool aligned)
 {
-    // aligned 16-byte tensors assumed (the slicing does not depend on the alignment)
     int per;
-    if (wgrad_narrow_eligible(dtype, c)) return wgrad_narrow_slices(c);
+    if (aligned && wgrad_narrow_eligible(dtype, c)) return wgrad_narrow_slices(c);
     if (wgrad_c64_eligible(dtype, c)) return wgrad_c64_slices(c, nullptr);
     if (wgrad_stem_eligible(dtype, c)) return wgrad_stem_slices(c, nullptr);
     if (wgrad_c16_eligible(dtype, c)) return wgrad_c16_splits(c, &per);

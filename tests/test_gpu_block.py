@@ -336,6 +336,55 @@ def test_column_sums_of_few_rows_per_float():
     assert np.abs(dgamma / want - 1.0).max() < 6 * 2.0**-24
 
 
+# (N, H, W, channels, the block ends in the sum of its input and the convolution): bf16 3x3 layers whose backward-weight kernel leaves
+# more slices of partial sums than the one for unaligned tensors, fewer, and one where that one leaves several
+@pytest.mark.parametrize("n, h, w, c, add", [(128, 32, 32, 16, False), (128, 16, 16, 32, False), (8, 32, 32, 16, False), (3, 14, 15, 16, False),
+                                            (8, 32, 32, 16, True), (16, 16, 16, 32, True)])
+def test_error_gradient_off_the_16_byte_addresses(n, h, w, c, add):
+    """The error gradient a caller hands in may lie anywhere: with the same values two bytes further the filters' gradient is
+    the same up to the order of its fp32 sums (two sums of the M exact products each, so 2 M 2^-24 of the sum of magnitudes) also
+    where an aligned call and one with a gradient of larger values came before."""
+    layers = [dict(op="conv", cin=c, cout=c, r=3, s=3, stride=1, pad=1, **{"in": -1}), dict(op="bn", c=c, relu=True, res=None, **{"in": 0}),
+              dict(op="conv", cin=c, cout=c, r=3, s=3, stride=1, pad=1, **{"in": 1})]
+    if add:
+        layers.append(dict(op="add", res=0, **{"in": 2}))
+    rng = np.random.default_rng(c)
+    desc, keep = D.make_block_desc(layers, (n, c, h, w), D.DSP_BF16, 0, 1, 0, needs_input_grad=False)
+    block = D.dsp_block_init(desc, flatten_params(layers, make_params(layers, rng)))
+    try:
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(n)
+        x = torch.randn((n, h, w, c), generator=gen, device="cuda").to(torch.bfloat16)
+        m = n * h * w
+        room = torch.randn(m * c + 8, generator=gen, device="cuda").to(torch.bfloat16)
+        out, got, names = torch.empty_like(x), [], []
+        for t, (off, scale) in enumerate([(0, 64.0), (0, 1.0), (1, 1.0), (0, 64.0), (1, 1.0)]):
+            g = torch.zeros_like(room)
+            g[off:off + m * c] = room[:m * c] * scale
+            D.dsp_block_forward(block, t, x, out)
+            D.dsp_profile_start(64)
+            try:
+                D.dsp_block_recompute_backward(block, t, g[off:], None)
+                torch.cuda.synchronize()
+            finally:
+                names.append({k["name"] for k in D.dsp_profile_stop()})
+            got.append(D.dsp_block_get_grads(block).astype(np.float64))
+            D.dsp_param_update(block, 0.0, 0.0)
+        assert "conv_wgrad_narrow<bf16,16x16>" in names[1]
+        act = D.dsp_block_get_activation(block, 1, m * c * 2)  # what the last convolution reads
+    finally:
+        D.dsp_block_destroy(block)
+    a = torch.from_numpy(act).view(torch.bfloat16).cuda().double().abs().reshape(n, h, w, c)
+    a, d = torch.nn.functional.pad(a, (0, 0, 1, 1, 1, 1)), room[:m * c].double().abs().reshape(m, c)
+    mag = torch.stack([d.t().contiguous() @ a[:, r:r + h, s:s + w].reshape(m, c) for r in range(3) for s in range(3)], -1)  # [cout][cin][tap]
+    bound = 2 * m * 2.0**-24 * mag.cpu().numpy().ravel()
+    last = c * c * 9  # the last layer with parameters is the convolution whose dy this is
+    for other in (got[2], got[4]):
+        assert (np.abs(other - got[1])[-last:] <= bound).all()
+    # every other gradient: through one bf16 map whose roundings another order of sums may move
+    assert rel_err(got[2], got[1]) < TOL[D.DSP_BF16] and np.array_equal(got[2], got[4])
+
+
 def _free_running(cfg, params, rng, dtype, ticks, p=None, m=None, rtol=1e-3):
     K = cfg["K"]
     p = cfg["p"] if p is None else p
