@@ -37,10 +37,12 @@ int block_load_params_device(dsp_block* b, const float* d_src, hipStream_t st);
 // ---- error plumbing ---------------------------------------------------------------------------
 void set_error(const char* fmt, ...);
 
+// (The runtime keeps the error of a refused call until it is asked for: left there, the next launch's check would report it.)
 #define DSP_HIP(call)                                                                      \
     do {                                                                                   \
         hipError_t e__ = (call);                                                           \
         if (e__ != hipSuccess) {                                                           \
+            (void)hipGetLastError();                                                       \
             ::dsp::set_error("%s failed: %s (%s:%d)", #call, hipGetErrorString(e__), __FILE__, __LINE__); \
             return DSP_EHIP;                                                               \
         }                                                                                  \
