@@ -882,12 +882,12 @@ static bool device_range(const void* ptr, size_t bytes)
     return at <= size && bytes <= size - at;
 }
 
-// The data source: the mini-batch into block 0's ring slot and the labels into the label ring.
+// The data source: the mini-batch, which stands behind in_ready of the caller's stream, into block 0's ring slot and the labels into
+// the label ring.
 static int copy_mini_batch(dsp_pipeline* pl, int64_t tau, const void* d_batch, const int32_t* d_labels, hipStream_t user, bool graph_tick)
 {
     const int K = pl->K, R = pl->ev_depth, prev = (int)((tau + R - 1) % R);
     hipStream_t s0 = pl->streams[0];
-    DSP_HIP(hipEventRecord(pl->in_ready, user));
     DSP_HIP(hipStreamWaitEvent(s0, pl->in_ready, 0));
     if (tau > 0 && !pl->serial) {
         // block 0's slot for this tick is free (its own earlier ticks ran on this stream); a graph tick
@@ -935,8 +935,10 @@ int dsp_pipeline_step(dsp_pipeline* pl, const void* d_batch, const int32_t* d_la
     const int phase = graph_tick ? (int)(tau % pl->period) : 0;
 
     const bool eager = !pl->serial && !graph_tick;
-    // The threads start early only for a mini-batch that the copies cannot refuse: a step that fails on its input must leave every
-    // block where it was, so that the caller can repeat it.
+    // A step that is refused for what the caller handed in must leave every block where it was, so that the caller can repeat it: the
+    // threads start only once the caller's stream has taken an event, and early only for a mini-batch that the copies cannot
+    // refuse.  What is left then are the pipeline's own streams and events.
+    DSP_HIP(hipEventRecord(pl->in_ready, user));
     const bool early = eager && device_range(d_batch, pl->in_bytes) && (!d_labels || device_range(d_labels, (size_t)pl->N * 4));
     bool threads = early && start_workers(pl, tau);
     const int rc_in = copy_mini_batch(pl, tau, d_batch, d_labels, user, graph_tick);

@@ -25,7 +25,7 @@ def runtime(tmp_path_factory):
     return lib
 
 
-@pytest.mark.parametrize("fault", ["batch", "labels"])
+@pytest.mark.parametrize("fault", ["batch", "labels", "stream"])
 @pytest.mark.parametrize("schedule", SCHEDULES)
 def test_a_refused_step_can_be_repeated(runtime, schedule, fault):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), runtime, schedule, fault], capture_output=True, text=True,
@@ -52,7 +52,7 @@ def _run(rt, D, cfg, params, schedule, fault):
     for t in range(TICKS):
         if fault and t == REFUSED_AT:
             was = state()
-            bad = {"batch": (strange, y.value, 0), "labels": (x.value, strange, 0)}[fault]
+            bad = {"batch": (strange, y.value, 0), "labels": (x.value, strange, 0), "stream": (x.value, y.value, 0x7)}[fault]
             for _ in range(2):
                 with pytest.raises(D.DSPError) as e:
                     D.dsp_pipeline_step(pl, bad[0], bad[1], stream=bad[2])
