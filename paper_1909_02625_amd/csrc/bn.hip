@@ -1093,7 +1093,7 @@ int bn_forward_t(const void* x, const void* res, void* y, const float* gamma, co
     BnLayout gl;
     if (presummed > 0) {
         nblk = presummed;
-    } else if (!stats_only && group_sums_layout(M, C, VW, sizeof(T), &gl)) {
+    } else if (group_sums_layout(M, C, VW, sizeof(T), &gl)) {  // (of every form: the bits of the statistics do not depend on it)
         nblk = gl.row_blocks;
         ProfScope ps(sizeof(T) == 2 ? "bn_stats<bf16>" : "bn_stats<fp32>", tensor_bytes, 1);
         DSP_LAUNCH(ps, (bn_group_sums_kernel<T, VW, 0, 0>), dim3((unsigned)(gl.groups * gl.row_blocks), ni), dim3(kBnThreads), 0, st,

@@ -241,8 +241,8 @@ bool bn_relu_maxpool_supported(int dtype, int C, int k);
 int launch_bn_relu_maxpool_forward(int dtype, const void* x, const float* coef, void* y, uint8_t* argmax, int N, int H, int W,
                                    int C, int k, int stride, int pad, hipStream_t st);
 // y = a + b over [M][C] (as launch_add_forward) and, in the same pass, the per-block column sums {sum y, sum y^2}
-// of the stored values in partial[add_stats_blocks()][C][2]: exactly what launch_bn_forward(y, ...) would compute
-// first, so the batch norm that reads y is called with presummed = add_stats_blocks().  twin: a second instance.
+// of the stored values in partial[add_stats_blocks()][C][2], which launch_bn_forward(y, ...) takes in place of its own first pass
+// with presummed = add_stats_blocks() (the same sums; from 128 channels on in other runs of rows).  twin: a second instance.
 struct AddStatsTwin {
     const void* a;
     const void* b;

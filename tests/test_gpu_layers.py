@@ -332,6 +332,26 @@ def test_bn_relu_maxpool_in_one_pass_and_relu_decided_from_x(shape):
                                            N, H, W, C, k, st, pd, ws, ws_bytes)
 
 
+@pytest.mark.parametrize("shape", [(3, 128, 31, 31), (2, 136, 40, 52), (9, 256, 31, 40), (3, 64, 30, 30)], ids=lambda s: "x".join(map(str, s)))
+def test_pooled_form_takes_its_sums_in_the_order_of_the_stored_one(shape):
+    """Columns whose 64-bit sums depend on the order of the additions (beside 2^57 and its negative in a channel's first and last row
+    every 1 in between is lost or kept): both forms leave the same statistics, bit for bit."""
+    N, C, H, W = shape
+    M, dtype, ws_bytes = N * H * W, D.DSP_BF16, D.dsp_bn_workspace_bytes(C)
+    x = torch.ones((M, C), device="cuda", dtype=torch.bfloat16)
+    x[0], x[M - 1] = 2.0**57, -2.0**57
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+    gamma, beta, y = torch.ones(C, device="cuda"), torch.zeros(C, device="cuda"), torch.empty_like(x)
+    mean, invstd, mean2, invstd2 = (torch.empty(C, device="cuda") for _ in range(4))
+    D.dsp_bn_forward(dtype, x, None, y, gamma, beta, EPS, M, C, True, mean, invstd, ws, ws_bytes)
+    pool = torch.empty((N, (H - 1) // 2 + 1, (W - 1) // 2 + 1, C), device="cuda", dtype=torch.bfloat16)
+    taps, coef = torch.empty(pool.shape, device="cuda", dtype=torch.uint8), torch.empty(2 * C, device="cuda")
+    D.dsp_bn_relu_maxpool_forward(dtype, x, gamma, beta, EPS, N, H, W, C, 3, 2, 1, pool, taps, mean2, invstd2, coef, ws, ws_bytes)
+    torch.cuda.synchronize()
+    assert torch.equal(mean, mean2) and torch.equal(invstd, invstd2)
+    assert ((mean - (M - 2) / M).abs() > 1e-6).all()  # (the order does show)
+
+
 def test_bn_relu_maxpool_rejects_what_it_does_not_cover():
     x = torch.zeros(4096, device="cuda")
     ws = torch.empty(D.dsp_bn_workspace_bytes(8), dtype=torch.uint8, device="cuda")
