@@ -160,10 +160,10 @@ __device__ inline void combine_row_lanes(double (&s0)[VW], double (&s1)[VW], dou
 // How tensors whose apply kernels merge the partial sums themselves are dealt out (see "finalize inside the apply kernels").
 constexpr int kMergeEntries = 2048;  // partial rows x channels of a group
 constexpr int64_t kMergeTensorBytes = (int64_t)3 << 19;
-// With kWideChannels and more the groups alone make enough workgroups, and the sums come in few rows (bn_group_sums_kernel):
+// With kWideChannels and more the sums come by channel groups and in few rows (bn_group_sums_kernel):
 constexpr int kWideChannels = 128;
 constexpr int kWideConvEntries = 3072;       // partial rows x channels of a group where a convolution left them
-constexpr int64_t kWideTensorBytes = (int64_t)32 << 20;   // a quarter of it where a group is less than 128 bytes of a row
+constexpr int kWideBackwardWgs = 96;         // workgroups of the largest such backward sums, at least
 constexpr int kWideRunBytes = 96 << 10;      // of a tensor, per workgroup that sums
 constexpr int kBnThreads = 512;
 struct BnLayout {
@@ -301,7 +301,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RM == 
 
 // The same sums with few partial rows, for tensors whose apply kernels merge them: a workgroup takes a group of L.cg channels over a
 // run of rows (the work items of those kernels), so that what each of their workgroups reads back, rows x channels of a
-// group, stays at kMergeEntries while the groups still fill the chip.
+// group, stays at kMergeEntries.  That is kMergeEntries / cg runs, so at most 32 x C / 64 workgroups of 64 channels, 64 at C = 128 and 256
+// from C = 512 on in bf16, and 64 x C / 32 in fp32; a run of kWideRunBytes ends it at 48 KB x C of a tensor (6 MB at C = 128 in bf16).
 template <typename T, int VW, int MODE, int RM>
 __global__ __launch_bounds__(kBnThreads) __attribute__((amdgpu_waves_per_eu(RM == 1 ? 3 : 4))) void bn_group_sums_kernel(
     const T* __restrict__ x, const T* __restrict__ dy, const T* __restrict__ y, const float* __restrict__ mean,
@@ -554,10 +555,19 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(const T* __restr
 // and 32 MB resnet20 was 8 % slower and conv4_x 4.5 %, up to 4096 and 2 MB resnet20 still 1 %.
 // From 128 channels on the sums are dealt out by channel groups and leave at most 2048 partials.  Forward / backward with sign
 // bytes, sums included: 12544 x 256 bf16 12.7 -> 10.3 / 14.7 -> 12.8 us, 4864 x 1024 bf16 18.8 -> 12.1 / 21.5 -> 15.4, 11956 x 256 fp32
-// 15.1 -> 11.9 / 18.6 -> 14.4; 107 calls of 128 to 2048 channels 1.16x, those near the far lines 1.00-1.07x; conv4_x driven by
-// separate calls 1856 -> 1774 us a step.  Groups of 64 bytes lose above 8 MB (36285 x 200 bf16, from y: 25.4 -> 27.9).  A convolution's rows are
-// merged up to 3072 partials: 38 rows of conv4_x at batch 19 (2432) gain 4 %, 256 rows x 16 channels (4096) of
-// resnet56 lose 0.5 %.
+// 15.1 -> 11.9 / 18.6 -> 14.4; conv4_x driven by separate calls 1856 -> 1774 us a step.  The far lines are where 10000 calls of 128 to
+// 2048 channels and up to 32 MB, timed in graphs against three launches, stop gaining (whole groups of 128 bytes / a ragged last group / an
+// odd number of channels); the backward ones serve every form of the ReLU, which all have to take their sums in one order:
+//   forward   8-12 MB 1.48 / 1.25 / 1.18, 16-20 MB 1.13 / 1.07 / 0.98, 28-32 MB 1.06 / 1.02 / 0.94; lines at 32, 16 and 12 MB.  Beyond 20 MB
+//             a residual in fp32 leaves 0.95-1.07 (7163 x 768 22.5 -> 23.4 us), without one 1.01-1.19.
+//   backward  8-12 MB 1.27 / 1.19 / 1.06, 12-16 MB 1.14 / 1.12 / 0.98, 16-20 MB 1.06 / 1.01 / 0.93, 24-28 MB 0.98 / 0.92 / 0.85: x and dy, which both
+//             launches read, are 32 MB at 16, what the L2s of the dies hold together; lines at 16, 12 and 8 MB.  From x alone the gain ends
+//             later (16-20 MB 1.11), from y with a residual earlier (12697 x 576 bf16, 14 MB, 27.2 -> 28.9 us).  Powers of two gain
+//             up to the end (24-32 MB 1.03-1.08 in fp32, 1.05-1.24 in bf16; why, no counter was asked).
+// Groups of 64 bytes end at 8 MB, backward with a ragged last one at 6 (bf16, 18912 x 200, from y with a residual: 18.3 -> 20.8 us at 7.2 MB,
+// 1.1x at 6.2).  The backward sums of two groups, 64 workgroups, lose at any size (16384 x 128 bf16 from x 11.1 -> 13.1 us, from sign
+// bytes 11.0 -> 11.7), three gain (1.05-1.2x; at 16384 rows from x 0.97).
+// A convolution's rows are merged up to 3072 partials.
 // Sums of channel g0 + tid % CG to the threads of row group 0 (tid < CG).  Thread = (channel, row group rg of RG): it holds the
 // row lanes rg, rg + RG, .. of the 64; the lanes 32, 16, .. RG apart meet in its registers, the others cross LDS behind one
 // barrier and meet in the first wave, eight of them as they are read, the rest by exchanges.
@@ -1038,24 +1048,35 @@ BnLayout merge_layout(int64_t M, int C, int VW, int instances)
     if (blocks > most) blocks = most;
     return bn_layout(M, C, VW, blocks < 1 ? 1 : blocks);
 }
-inline int64_t wide_tensor_bytes(int cg, int esz) { return cg * esz >= 128 ? kWideTensorBytes : kWideTensorBytes / 4; }
-inline bool merges(int64_t M, int C, int VW, int esz, int nblk)
+// The largest tensor whose sums are taken by channel groups or, behind a convolution, merged by the apply kernel (the lines: see
+// "finalize inside the apply kernels").
+int64_t wide_tensor_bytes(int C, int VW, int cg, int esz, bool backward)
+{
+    constexpr int64_t MB = 1 << 20;
+    const bool whole = C % cg == 0;  // no group shares a cache line with the next
+    if (cg * esz < 128) return (whole || !backward ? 8 : 6) * MB * (cg * esz) / 64;
+    if (!backward) return (whole ? 32 : VW > 1 ? 16 : 12) * MB;
+    return ((C & (C - 1)) == 0 ? 32 : whole ? 16 : VW > 1 ? 12 : 8) * MB;
+}
+// wide: the partials are those of bn_group_sums_kernel or of a convolution.
+inline bool merges(int64_t M, int C, int VW, int esz, int nblk, bool wide, bool backward)
 {
     const int cg = bn_channel_group(C, VW);
-    const bool wide = C >= kWideChannels;
-    return M * C * esz <= (wide ? wide_tensor_bytes(cg, esz) : kMergeTensorBytes) &&
+    wide = wide && C >= kWideChannels;
+    return M * C * esz <= (wide ? wide_tensor_bytes(C, VW, cg, esz, backward) : kMergeTensorBytes) &&
            (int64_t)nblk * cg <= (wide ? kWideConvEntries : kMergeEntries);
 }
 // Work items of bn_group_sums_kernel: at most kMergeEntries / cg runs of rows, two rows a thread or more; false where the tensor has
 // too few channels or is too large for so few.
-bool group_sums_layout(int64_t M, int C, int VW, int esz, BnLayout* L)
+bool group_sums_layout(int64_t M, int C, int VW, int esz, bool backward, BnLayout* L)
 {
     const int cg = bn_channel_group(C, VW), rpp = kBnThreads / (cg / VW);
     int64_t runs = kMergeEntries / cg;
     const int64_t most = (M + 2 * rpp - 1) / (2 * rpp);
     if (runs > most) runs = most;
     *L = bn_layout(M, C, VW, runs);
-    return C >= kWideChannels && M * C * esz <= wide_tensor_bytes(cg, esz) && (int64_t)L->rows_per_wg * cg * esz <= kWideRunBytes;
+    if (backward && L->groups * (kMergeEntries / cg) < kWideBackwardWgs) return false;
+    return C >= kWideChannels && M * C * esz <= wide_tensor_bytes(C, VW, cg, esz, backward) && (int64_t)L->rows_per_wg * cg * esz <= kWideRunBytes;
 }
 
 int plan_rows(int64_t M, const RowLayout& L, int* nblk)
@@ -1093,7 +1114,7 @@ int bn_forward_t(const void* x, const void* res, void* y, const float* gamma, co
     BnLayout gl;
     if (presummed > 0) {
         nblk = presummed;
-    } else if (group_sums_layout(M, C, VW, sizeof(T), &gl)) {  // (of every form: the bits of the statistics do not depend on it)
+    } else if (group_sums_layout(M, C, VW, sizeof(T), false, &gl)) {  // (of every form: the bits of the statistics do not depend on it)
         nblk = gl.row_blocks;
         ProfScope ps(sizeof(T) == 2 ? "bn_stats<bf16>" : "bn_stats<fp32>", tensor_bytes, 1);
         DSP_LAUNCH(ps, (bn_group_sums_kernel<T, VW, 0, 0>), dim3((unsigned)(gl.groups * gl.row_blocks), ni), dim3(kBnThreads), 0, st,
@@ -1109,7 +1130,7 @@ int bn_forward_t(const void* x, const void* res, void* y, const float* gamma, co
     const BnStatOut o1 = tw ? BnStatOut{tw->buf.partial, tw->buf.mean, tw->buf.invstd, tw->buf.coef} : o0;
     const BnApplyIo io0{x, res, y, buf.coef, relu_bits};
     const BnApplyIo io1 = tw ? BnApplyIo{tw->x, tw->res, tw->y, tw->buf.coef, tw->relu_bits} : io0;
-    if (!stats_only && merges(M, C, VW, sizeof(T), nblk)) {
+    if (!stats_only && merges(M, C, VW, sizeof(T), nblk, true, false)) {
         const BnLayout ml = merge_layout(M, C, VW, (int)ni);
         ProfScope ps(sizeof(T) == 2 ? "bn_merge_apply_relu<bf16>" : "bn_merge_apply_relu<fp32>", tensor_bytes * (res ? 3 : 2), 1);
 #define BN_APPLY(R, H)                                                                                                             \
@@ -1159,7 +1180,7 @@ int bn_backward_t(const void* dy, const void* x, const void* y, void* dx, void* 
     const dim3 grid(nblk, ceil_div(L.cv, L.cvb));
     const double tensor_bytes = (double)M * C * sizeof(T);
     BnLayout gl;
-    const bool grouped = group_sums_layout(M, C, VW, sizeof(T), &gl);
+    const bool grouped = group_sums_layout(M, C, VW, sizeof(T), true, &gl);
     if (grouped) nblk = gl.row_blocks;
     {
         ProfScope ps(sizeof(T) == 2 ? "bn_bwd_reduce<bf16>" : "bn_bwd_reduce<fp32>", tensor_bytes * (RM == 1 ? 3 : 2) + (RM == 3 ? tensor_bytes / (VW * sizeof(T)) : 0.0), 1);
@@ -1177,7 +1198,7 @@ int bn_backward_t(const void* dy, const void* x, const void* y, void* dx, void* 
     // writes dx (and dres)
     const double apply_bytes = tensor_bytes * (2 + (RM == 1 ? 1 : 0) + 1 + (xacc ? 1 : 0) + (dres ? 1 + (racc ? 1 : 0) : 0)) +
                                (RM == 3 ? tensor_bytes / (VW * sizeof(T)) : 0.0);
-    if (merges(M, C, VW, sizeof(T), nblk)) {
+    if (merges(M, C, VW, sizeof(T), nblk, grouped, true)) {
         const BnLayout ml = merge_layout(M, C, VW, 1);
         ProfScope ps(sizeof(T) == 2 ? "bn_bwd_merge_apply<bf16>" : "bn_bwd_merge_apply<fp32>", apply_bytes, 1);
 #define BN_BAPPLY(H, RA, XA)                                                                                               \

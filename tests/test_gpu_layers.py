@@ -138,7 +138,8 @@ MERGE_SHAPES = [
 @pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
 @pytest.mark.parametrize("shape,merged_fp32,merged_bf16", MERGE_SHAPES, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else "")
 def test_batch_norm_that_merges_its_partial_sums(shape, merged_fp32, merged_bf16, dtype):
-    """The apply kernels that form the statistics of their own channels, at the edges of their range."""
+    """The apply kernels that form the statistics of their own channels, at the edges of their range (one flag, or one each for
+    forward and backward)."""
     D.dsp_profile_start(64)
     try:
         for relu, res in ((True, False), (True, True), (False, False)):
@@ -146,9 +147,10 @@ def test_batch_norm_that_merges_its_partial_sums(shape, merged_fp32, merged_bf16
     finally:
         names = {k["name"] for k in D.dsp_profile_stop()}
     merged, t = (merged_fp32, "fp32") if dtype == D.DSP_FP32 else (merged_bf16, "bf16")
-    assert {"bn_merge_apply_relu<%s>" % t, "bn_bwd_merge_apply<%s>" % t} <= names if merged else \
-        {"bn_fwd_finalize", "bn_bwd_finalize"} <= names
-    assert not names & ({"bn_fwd_finalize", "bn_bwd_finalize"} if merged else {"bn_merge_apply_relu<%s>" % t, "bn_bwd_merge_apply<%s>" % t})
+    forward, backward = merged if isinstance(merged, tuple) else (merged, merged)
+    for own, finalize, merge in ((forward, "bn_fwd_finalize", "bn_merge_apply_relu<%s>" % t),
+                                 (backward, "bn_bwd_finalize", "bn_bwd_merge_apply<%s>" % t)):
+        assert (merge if own else finalize) in names and (finalize if own else merge) not in names
 
 
 # 128 channels and more: sums by channel groups, merged by the apply kernels
@@ -159,8 +161,12 @@ WIDE_SHAPES = [
     ((2, 1032, 9, 9), True, True),      # many groups, the last one short
     ((64, 256, 32, 12), True, True),    # the longest runs in bf16 (96 KB of a group)
     ((3, 256, 8193, 1), True, False),   # a few rows more
-    ((8, 200, 75, 61), True, False),    # 64-byte groups in bf16, 14 MB
+    ((8, 200, 75, 61), False, False),   # rows of no whole lines, 29 MB; 64-byte groups in bf16, 14 MB
     ((2, 160, 131, 201), False, False), # above 32 MB in fp32, longer runs in bf16
+    ((4, 128, 32, 32), True, (True, False)),              # two groups in bf16: the backward sums of 64 workgroups
+    ((16, 320, 41, 21), (True, False), True),             # 16.8 MB in fp32
+    ((12, 200, 35, 41), (True, False), (True, False)),    # rows of no whole lines, 13.1 MB; 64-byte groups in bf16, 6.6 MB
+    ((5, 201, 51, 44), (True, False), (True, True)),      # element-wise path, 8.6 MB; 64-byte groups in bf16, 4.3 MB
 ]
 
 
