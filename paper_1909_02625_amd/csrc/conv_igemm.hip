@@ -4118,12 +4118,16 @@ int wgrad_c16_splits(const ConvShape& c, int* m_per_split)
 // Narrow layers: bf16, 3x3 / stride 1 / pad 1, 16 or 32 channels on both sides, rows that fit LDS.  Every block of 16 input channels stages
 // dy and every block of 16 output channels stages x again, and from 48 channels on the tiles have less padding: 186 x 51x49, 32 -> 48
 // 35.6 us there and 44.3 here, 213 x 45x47, 16 -> 64 24.3 and 33.4, 128 x 8x8, 64 -> 64 10.9 and 10.7.  At stride 2, where a quarter as many
-// products share the staging, 10.3 and 11.8 (142 x 22x22, 16 -> 48).
+// products share the staging, 10.3 and 11.8 (142 x 22x22, 16 -> 48).  Up to 512 pixels the tiles need one slice and no summing launch:
+// 160 layers in graphs, 0.76-1.01x up to there (3 x 10x9, 32 -> 16 5.1 us there and 6.2 here), 1.03-2.5x from 550 on (2 x 42x41, 16 -> 16 8.1
+// and 6.7; 46 x 92x91 29.9 and 13.0).
 constexpr int kNarrowLds = 79 * 1024;
+constexpr int kNarrowPixels = 512;
 bool wgrad_narrow_eligible(int dtype, const ConvShape& c)
 {
     return dtype == DSP_BF16 && conv_groups(c) == 1 && (c.Cin == 16 || c.Cin == 32) && (c.Cout == 16 || c.Cout == 32) && c.R == 3 &&
-           c.S == 3 && c.pad == 1 && c.stride == 1 && c.W <= 128 && (int64_t)c.N * c.H * c.W < 1 << 30;
+           c.S == 3 && c.pad == 1 && c.stride == 1 && c.W <= 128 && (int64_t)c.N * c.H * c.W > kNarrowPixels &&
+           (int64_t)c.N * c.H * c.W < 1 << 30;
 }
 // The largest tile that fits LDS twice per compute unit and leaves the slices a tile each: a workgroup per compute unit over all
 // blocks, a slice of kNarrowSlice pixels or more (60 layers 1.17x with 128, 1.14x with 256, 1.11x with 512), and no more slices

@@ -425,9 +425,10 @@ def test_short_contractions_fp32(shape, bk):
 
 # bf16 backward-weight with one 16 x 16 block of channels per workgroup: (N, H, W, Cin, Cout, stride), taken.  One pixel; one column; several
 # images a tile, the last tile short; tiles of part of an image, the last one short; the widest row and the next; more channels, channels
-# that make no block, a stride.
+# that make no block, a stride; the fewest pixels and one less.
 NARROW = [
-    ((1, 1, 1, 16, 16, 1), True), ((3, 5, 1, 32, 16, 1), True), ((29, 7, 9, 16, 32, 1), True), ((5, 43, 31, 16, 16, 1), True),
+    ((520, 1, 1, 16, 16, 1), True), ((103, 5, 1, 32, 16, 1), True), ((3, 9, 19, 32, 16, 1), True), ((2, 16, 16, 16, 16, 1), False),
+    ((29, 7, 9, 16, 32, 1), True), ((5, 43, 31, 16, 16, 1), True),
     ((1, 9, 128, 16, 16, 1), True), ((2, 9, 129, 16, 16, 1), False), ((9, 12, 11, 32, 32, 1), True), ((9, 12, 11, 48, 16, 1), False),
     ((2, 9, 9, 16, 24, 1), False), ((4, 29, 30, 32, 16, 2), False),
 ]
