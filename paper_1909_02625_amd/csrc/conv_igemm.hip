@@ -292,8 +292,10 @@ __device__ inline unsigned xcd_tile(unsigned b, unsigned nb)
     return xcd * q + (xcd < r ? xcd : r) + idx;
 }
 
-// (in, out, stats: of the instance at hand; block, blocks: of the launch's tiles; group, groups: of a grouped convolution)
-template <typename TL, bool VEC, bool DIL>
+// (in, out, stats: of the instance at hand; block, blocks: of the launch's tiles; group, groups: of a grouped convolution.  PART: the launch
+// may have more tiles than the problem.  Only then is there a way out at the top: behind one the arguments are fetched late, in two goes,
+// which cost the 64 x 16 fp32 tile 1 % over 48 layers and the 64 x 64 bf16 one 3 % over six.)
+template <typename TL, bool VEC, bool DIL, bool PART>
 __device__ __forceinline__ void gather_gemm_tile(const typename TL::T* __restrict__ in, const typename TL::T* __restrict__ wgt,
                                                  typename TL::T* __restrict__ out, double* stats, const GatherGeom& g, unsigned block,
                                                  unsigned blocks, int group, int groups)
@@ -312,7 +314,7 @@ __device__ __forceinline__ void gather_gemm_tile(const typename TL::T* __restric
     // grouped convolution: this workgroup's group reads channels [in_c0, in_c0 + Ci) of rows Cis wide and writes
     // channels [out_c0, out_c0 + Co) of rows Cos wide, with the filters of output channels out_c0 ..
     const int in_c0 = group * g.Ci, out_c0 = group * g.Co;
-    if (m0 >= g.M) return;  // (a class with fewer tiles than the launch has for each)
+    if (PART && m0 >= g.M) return;  // (a class with fewer tiles than the launch has for each)
 
     const int kc = tid % CPR;    // which 16-byte run of the k tile this thread moves
     const int row0 = tid / CPR;  // first tile row it moves; further rows are +ROWS_PER_PASS apart
@@ -606,7 +608,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::MI
     const typename TL::T* __restrict__ in, const typename TL::T* __restrict__ wgt, typename TL::T* __restrict__ out, GatherGeom g)
 {
     typedef typename TL::T T;
-    gather_gemm_tile<TL, VEC, DIL>(blockIdx.y ? (const T*)g.in1 : in, wgt, blockIdx.y ? (T*)g.out1 : out, blockIdx.y ? g.stats1 : g.stats, g,
+    gather_gemm_tile<TL, VEC, DIL, false>(blockIdx.y ? (const T*)g.in1 : in, wgt, blockIdx.y ? (T*)g.out1 : out, blockIdx.y ? g.stats1 : g.stats, g,
                                    blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
 }
 template <typename TL>
@@ -614,7 +616,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TL::MI
     const typename TL::T* __restrict__ in, const typename TL::T* __restrict__ wgt, typename TL::T* __restrict__ out, ClassSet c)
 {
     const GatherGeom g = class_geom(c, blockIdx.y);
-    gather_gemm_tile<TL, true, false>(in, wgt + c.cls[blockIdx.y].w_off, out, nullptr, g, blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
+    gather_gemm_tile<TL, true, false, true>(in, wgt + c.cls[blockIdx.y].w_off, out, nullptr, g, blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
 }
 
 // ---- bf16 gather-GEMM fed by direct global -> LDS loads ---------------------------------------------
@@ -685,7 +687,7 @@ __device__ inline void dma16_at(__amdgpu_buffer_rsrc_t r, char* lds_wave_base, u
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)lds_wave_base, 16, (int)byte_off, soff, 0, 0);
 }
 
-template <typename TL>
+template <typename TL, bool PART>
 __device__ __forceinline__ void dma_gemm_tile(const bf16_t* __restrict__ in, const bf16_t* __restrict__ wgt, bf16_t* __restrict__ out,
                                               double* stats, const GatherGeom& g, unsigned block, unsigned blocks, int group, int groups)
 {
@@ -700,8 +702,8 @@ __device__ __forceinline__ void dma_gemm_tile(const bf16_t* __restrict__ in, con
     const unsigned tile = xcd_tile(block, blocks);
     // consecutive tiles (which meet in one XCD's L2) sweep the output channels of the same input rows, or, where the
     // filters are the larger operand, the rows of the same output channels
-    const unsigned tiles_m = (unsigned)((g.M + BM - 1) / BM);
-    if (tile >= tiles_m * tiles_n) return;  // (a class with fewer tiles than the launch has for each)
+    const unsigned tiles_m = PART ? (unsigned)((g.M + BM - 1) / BM) : blocks / tiles_n;
+    if (PART && tile >= tiles_m * tiles_n) return;  // (a class with fewer tiles than the launch has for each)
     const unsigned tile_m = g.n_major ? tile % tiles_m : tile / tiles_n, tile_n = g.n_major ? tile / tiles_m : tile % tiles_n;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     char* const ring = smem + kgrp * TL::RING_BYTES;
@@ -1004,7 +1006,7 @@ template <typename TL>
 __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL::WAVES, TL::WAVES))) void conv_dma_gemm_kernel(
     const bf16_t* __restrict__ in, const bf16_t* __restrict__ wgt, bf16_t* __restrict__ out, GatherGeom g)
 {
-    dma_gemm_tile<TL>(blockIdx.y ? (const bf16_t*)g.in1 : in, wgt, blockIdx.y ? (bf16_t*)g.out1 : out, blockIdx.y ? g.stats1 : g.stats, g,
+    dma_gemm_tile<TL, false>(blockIdx.y ? (const bf16_t*)g.in1 : in, wgt, blockIdx.y ? (bf16_t*)g.out1 : out, blockIdx.y ? g.stats1 : g.stats, g,
                       blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
 }
 template <typename TL>
@@ -1012,7 +1014,7 @@ __global__ __launch_bounds__(TL::THREADS) __attribute__((amdgpu_waves_per_eu(TL:
     const bf16_t* __restrict__ in, const bf16_t* __restrict__ wgt, bf16_t* __restrict__ out, ClassSet c)
 {
     const GatherGeom g = class_geom(c, blockIdx.y);
-    dma_gemm_tile<TL>(in, wgt + c.cls[blockIdx.y].w_off, out, nullptr, g, blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
+    dma_gemm_tile<TL, true>(in, wgt + c.cls[blockIdx.y].w_off, out, nullptr, g, blockIdx.x, gridDim.x, blockIdx.z, gridDim.z);
 }
 
 // ---- the same contraction as one stream of k tiles over several output tiles (256 x 128 tile) -----------------------
