@@ -347,8 +347,9 @@ __global__ __launch_bounds__(kBnThreads) __attribute__((amdgpu_waves_per_eu(RM =
 // the first wave adds the lanes 32 and 16 apart as it reads them and the others by exchanges.  Returns the two sums
 // of channel blockIdx.x * 4 + (threadIdx.x & 3) to the threads of row lane 0; the waves but the first return nothing.
 // What bounds these launches is the chain load -> tree -> coefficients -> store, each load a miss to memory behind a launch
-// that wrote from other dies, so nothing in it may wait for a second load: the channel's parameters are fetched with the
-// partials.
+// that wrote from other dies; the channel's parameters are fetched with the partials.  (One barrier instead of six and that
+// early fetch gain nothing measurable in the finalize launches, 0.999-1.003x over seven networks and layers; they have the form of
+// merge_group below, where the merge stands in front of every workgroup's rows.)
 constexpr int kMergeLanes = 64;
 typedef __attribute__((ext_vector_type(2))) double f64x2;
 __device__ inline void merge_partials(const double* __restrict__ part, int nblk, int C, f64x2 (&red)[kMergeLanes * 4], double* sa, double* sb)
@@ -394,7 +395,7 @@ __device__ inline void bn_forward_coef(double a, double b, double inv_M, float e
     const double mu = a * inv_M;
     double var = b * inv_M - mu * mu;
     if (var < 0.0) var = 0.0;
-    const double is = rsqrt(var + (double)eps);
+    const double is = rsqrt(var + (double)eps);  // (1 / sqrt is a chain twice as long; the statistics of 120 calls kept their bits)
     const double sc = (double)gamma * is;
     *scale = (float)sc;
     *shift = (float)((double)beta - mu * sc);
@@ -567,7 +568,10 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(const T* __restr
 // Groups of 64 bytes end at 8 MB, backward with a ragged last one at 6 (bf16, 18912 x 200, from y with a residual: 18.3 -> 20.8 us at 7.2 MB,
 // 1.1x at 6.2).  The backward sums of two groups, 64 workgroups, lose at any size (16384 x 128 bf16 from x 11.1 -> 13.1 us, from sign
 // bytes 11.0 -> 11.7), three gain (1.05-1.2x; at 16384 rows from x 0.97).
-// A convolution's rows are merged up to 3072 partials.
+// A convolution's rows are merged up to 3072 partials.  Alone, a batch norm behind a 1x1 convolution gains beyond that as well (128 to 2048
+// channels, 3072-4096 partials 1.08x in bf16 and 1.13x in fp32, 6144-8192 1.07 and 1.11, 8192-12288 1.04 and 1.05), but inside conv4_x at
+// batch 64, whose convolutions leave 49 rows x 64 channels (3136), the step is 2 % slower with them merged (32 steps 77.0
+// -> 78.7 ms, up to 4096 or 8192 alike); at batch 19 the 38 rows (2432) gain 4 %, resnet18 and resnext29 do not move.
 // Sums of channel g0 + tid % CG to the threads of row group 0 (tid < CG).  Thread = (channel, row group rg of RG): it holds the
 // row lanes rg, rg + RG, .. of the 64; the lanes 32, 16, .. RG apart meet in its registers, the others cross LDS behind one
 // barrier and meet in the first wave, eight of them as they are read, the rest by exchanges.

@@ -869,8 +869,8 @@ static int probe_after_tick(dsp_pipeline* pl, int64_t tau)
     return DSP_OK;
 }
 
-// Whether `bytes` bytes at `ptr` lie within one allocation of device memory.
-static bool device_range(const void* ptr, size_t bytes)
+// Whether `bytes` bytes at `ptr` lie within one allocation that the runtime knows (device memory, pinned host memory).
+static bool allocated_range(const void* ptr, size_t bytes)
 {
     hipDeviceptr_t base = nullptr;
     size_t size = 0;
@@ -939,7 +939,7 @@ int dsp_pipeline_step(dsp_pipeline* pl, const void* d_batch, const int32_t* d_la
     // threads start only once the caller's stream has taken an event, and early only for a mini-batch that the copies cannot
     // refuse.  What is left then are the pipeline's own streams and events.
     DSP_HIP(hipEventRecord(pl->in_ready, user));
-    const bool early = eager && device_range(d_batch, pl->in_bytes) && (!d_labels || device_range(d_labels, (size_t)pl->N * 4));
+    const bool early = eager && allocated_range(d_batch, pl->in_bytes) && (!d_labels || allocated_range(d_labels, (size_t)pl->N * 4));
     bool threads = early && start_workers(pl, tau);
     const int rc_in = copy_mini_batch(pl, tau, d_batch, d_labels, user, graph_tick);
     if (!early) DSP_TRY(rc_in);

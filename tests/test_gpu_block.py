@@ -528,8 +528,8 @@ def test_pipeline_equals_manual_fifo_schedule_bit_for_bit(name, dtype, ticks, kw
     ("resnet20", 12, {"batch": 4, "hw": 8, "p": (0, 0, 0), "m": (2, 1, 0)}),   # forward-locked
 ])
 def test_mini_batches_of_either_memory_give_the_same_bits(name, ticks, kw):
-    """The launch threads start before the mini-batch is copied only where it and the labels lie in device memory: from pinned
-    host memory, in turn with device memory, every loss and parameter is the one of device memory alone."""
+    """From pinned host memory, in turn with device memory, every loss and parameter is the one of device memory alone.  (Which
+    mini-batches the launch threads start ahead of, and what a refused one leaves behind: test_refused_steps.py.)"""
     cfg, params, rng = _setup(name, **kw)
     batches = [make_batch(rng, cfg["input"], cfg["classes"]) for _ in range(ticks)]
     out = []
