@@ -71,8 +71,9 @@ constexpr int kMaxGraphs = 128;
 // host time each, so issuing the K chains from K threads keeps the launch rate off the critical path.
 // A job is handed over, and its end awaited, by a flag that the waiting side watches for kSpin before it goes to sleep: waking a
 // sleeper costs as long as several launches, and the next tick of a small network follows within that time.  (tiny2, a dozen launches
-// a block, medians of 16 ticks over five processes: 1817 us before, 1664 with this, the start of the threads before the mini-batch is
-// copied and one wait and one event less a tick; 1790-1890 without this, 1823 without the early start.  resnet20 1.02x, resnet56 1.01x.)
+// a block: with this, the start of the threads before the mini-batch is copied and one wait and one event less a tick 1.02-1.23x in five
+// comparisons whose sides repeat within 3-17 %, 16 ticks 1.60-1.83 ms against 1.86-2.01; medians over five processes without this 1.79-1.89,
+// without the early start 1.82.  resnet20 1.026x, resnet56 1.01x.)
 constexpr std::chrono::microseconds kSpin{50};
 struct Worker {
     std::thread th;
