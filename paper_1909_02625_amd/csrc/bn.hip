@@ -556,7 +556,7 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(const T* __restr
 // and 32 MB resnet20 was 8 % slower and conv4_x 4.5 %, up to 4096 and 2 MB resnet20 still 1 %.
 // From 128 channels on the sums are dealt out by channel groups and leave at most 2048 partials.  Forward / backward with sign
 // bytes, sums included: 12544 x 256 bf16 12.7 -> 10.3 / 14.7 -> 12.8 us, 4864 x 1024 bf16 18.8 -> 12.1 / 21.5 -> 15.4, 11956 x 256 fp32
-// 15.1 -> 11.9 / 18.6 -> 14.4; conv4_x driven by separate calls 1856 -> 1774 us a step.  The far lines are where 10000 calls of 128 to
+// 15.1 -> 11.9 / 18.6 -> 14.4; conv4_x driven by separate calls 1856 -> 1774 us a step.  The far lines are where 11500 calls of 128 to
 // 2048 channels and up to 32 MB, timed in graphs against three launches, stop gaining (whole groups of 128 bytes / a ragged last group / an
 // odd number of channels); the backward ones serve every form of the ReLU, which all have to take their sums in one order:
 //   forward   8-12 MB 1.48 / 1.25 / 1.18, 16-20 MB 1.13 / 1.07 / 0.98, 28-32 MB 1.06 / 1.02 / 0.94; lines at 32, 16 and 12 MB.  Beyond 20 MB
